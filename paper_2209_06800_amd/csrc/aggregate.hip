@@ -24,7 +24,7 @@ template <bool BF16>
 __global__ __launch_bounds__(kBlock) void fixup_kernel(const SplitRow *split_rows, int32_t n_split, int32_t dim, const float *scratch,
                                                        int64_t scratch_ld, const void *x_local, int64_t ld_x,
                                                        const float *dinv_own, int32_t gcn, float self_w, void *out_v, int32_t out_bf16,
-                                                       int64_t ld_out, int32_t out_vec_ok, int32_t phase, const float *bias, int32_t relu,
+                                                       int64_t ld_out, int32_t phase, const float *bias, int32_t relu,
                                                        int32_t no_self)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -53,39 +53,48 @@ __global__ __launch_bounds__(kBlock) void fixup_kernel(const SplitRow *split_row
         const float total[4] = {sum.x, sum.y, sum.z, sum.w};
         float *o = static_cast<float *>(out_v) + static_cast<int64_t>(sr.row) * ld_out + k;
         uint16_t *ob = static_cast<uint16_t *>(out_v) + static_cast<int64_t>(sr.row) * ld_out + k;
-        float r[4];
+        const bool whole = k + 3 < dim;
+        float r[4], xv[4] = {0.f, 0.f, 0.f, 0.f};
+        if (!no_self) {
+            const int64_t at = static_cast<int64_t>(sr.row) * ld_x + k;
+            if constexpr (BF16) {
+                const uint16_t *x = static_cast<const uint16_t *>(x_local) + at;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (k + e < dim) xv[e] = __uint_as_float(static_cast<uint32_t>(x[e]) << 16);
+            } else {
+                const float *x = static_cast<const float *>(x_local) + at;
+                if (whole) {
+                    const float4 q = load_loose<float4>(x);
+                    xv[0] = q.x; xv[1] = q.y; xv[2] = q.z; xv[3] = q.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (k + e < dim) xv[e] = x[e];
+                }
+            }
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             r[e] = 0.f;
             if (k + e < dim) {
-                float xv = 0.f;
-                if (no_self) {
-                } else if constexpr (BF16)
-                    xv = __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t *>(x_local)[static_cast<int64_t>(sr.row) * ld_x + k + e]) << 16);
-                else
-                    xv = static_cast<const float *>(x_local)[static_cast<int64_t>(sr.row) * ld_x + k + e];
-                r[e] = phase == 2 ? o[e] + dv * total[e] : dv * (total[e] + ws * xv);
+                r[e] = phase == 2 ? o[e] + dv * total[e] : dv * (total[e] + ws * xv[e]);
                 if (phase != 1) {
                     if (bias) r[e] += bias[k + e];
                     if (relu) r[e] = fmaxf(r[e], 0.f);
                 }
             }
         }
-        if (out_bf16) {
-            if (out_vec_ok && k + 3 < dim) {
-                *reinterpret_cast<uint2 *>(ob) = make_uint2(f32_to_bf16_bits(r[0]) | (f32_to_bf16_bits(r[1]) << 16),
-                                                            f32_to_bf16_bits(r[2]) | (f32_to_bf16_bits(r[3]) << 16));
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (k + e < dim) ob[e] = static_cast<uint16_t>(f32_to_bf16_bits(r[e]));
-            }
-        } else if (out_vec_ok && k + 3 < dim) {
-            *reinterpret_cast<float4 *>(o) = make_float4(r[0], r[1], r[2], r[3]);
+        if (whole) {
+            if (out_bf16) store_vec_bf16<4>(ob, r);
+            else store_vec<4>(o, r);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (k + e < dim) o[e] = r[e];
+                if (k + e < dim) {
+                    if (out_bf16) ob[e] = static_cast<uint16_t>(f32_to_bf16_bits(r[e]));
+                    else o[e] = r[e];
+                }
         }
     }
 }
@@ -214,18 +223,26 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     const size_t esz = bf16 ? 2 : 4;
     const void *xh = x_halo ? x_halo : x_local;   // never dereferenced when there is no halo
 
-    // Widest vector the layout allows: it must keep every row start aligned, and the row must hold a
-    // whole number of vectors -- counting the padding between dim and ld_x, which is read (its
-    // values only reach output columns that do not exist) and never written.
+    // 16 bytes per lane whatever the layout.  Where the padding between dim and ld_x completes the last
+    // vector (and rows and bases are aligned) the padding is read; its values only reach output columns
+    // that do not exist.  Elsewhere -- a plain contiguous tensor of an odd width -- the last vector is
+    // moved back to end with the row, so that nothing past the table is read, and stores only the columns
+    // that are its own.  Such loads and stores are aligned to an element only, which global memory takes at
+    // full width (260 k-node R-MAT, half share, 75 contiguous fp32 columns: 226 us element by element, 167 us).
+    // Rows shorter than a vector go element by element.
     if (out_dim <= 0) out_dim = dim;
-    int vec = 1;
-    const int cand[3] = {bf16 ? 8 : 4, 2, 1};
-    for (int c : cand) {
-        const size_t bytes = c * esz;
-        const int64_t padded = (static_cast<int64_t>(dim) + c - 1) / c * c;
-        if (padded <= ld_x && ld_x % c == 0 && aligned(x_local, bytes) && aligned(xh, bytes)) { vec = c; dim = static_cast<int32_t>(padded); break; }
+    int vec = bf16 ? 8 : 4;
+    int32_t last_col;
+    {
+        const int64_t padded = (static_cast<int64_t>(dim) + vec - 1) / vec * vec;
+        if (padded <= ld_x && ld_x % vec == 0 && aligned(x_local, 16) && aligned(xh, 16)) {
+            dim = static_cast<int32_t>(padded);
+        } else if (dim < vec) {
+            vec = 1;
+        }
+        last_col = dim - vec;
     }
-    const int nvec = dim / vec;
+    const int nvec = (dim + vec - 1) / vec;
     // Column slabs: when one XCD's share of the table rows does not fit its L2 at full width, the
     // launch walks the feature dimension slab by slab (grid.y), all work items of slab 0 first,
     // so that what stays in L2 between two uses of a table row is a slab of it, not the whole
@@ -258,7 +275,7 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     if (slab_vecs > 64 * 4) slab_vecs = 64 * 4;
     const int n_slabs = (nvec + slab_vecs - 1) / slab_vecs;
     if (n_slabs > 65535) return fail(MGG_ERR_UNSUPPORTED, "dim %d too wide (at most %d)", dim, 65535 * 64 * 4 * vec);
-    int lpr = 4;
+    int lpr = vec == 1 && bf16 ? 8 : 4;            // (rows shorter than a vector have one kernel per element type)
     while (lpr < slab_vecs && lpr < 64) lpr <<= 1;
     const int ch = (slab_vecs + 63) / 64;
 
@@ -289,6 +306,7 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     a.out = out; a.scratch = scratch;
     a.ld_x = ld_x; a.ld_out = ld_out; a.scratch_ld = scratch_ld;
     a.nvec = nvec;
+    a.last_col = last_col;
     a.slab_vecs = slab_vecs;
     a.n_items = static_cast<int32_t>(p->items.size());
     const int wpb = p->wpb;
@@ -318,16 +336,9 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     a.out_dim = out_dim;
     a.relu = act == MGG_ACT_RELU;
     a.out_bf16 = out_dtype == MGG_BF16;
-    if (a.out_bf16) {           // one store of 2 * vec bytes per vector
-        a.out_vec_ok = (ld_out % vec == 0) && aligned(out, static_cast<size_t>(vec) * 2);
-    } else {                    // 16-byte stores at most (two per 8-element vector)
-        const size_t out_bytes = (vec >= 4 ? 4 : vec) * sizeof(float);
-        a.out_vec_ok = (ld_out % (vec >= 4 ? 4 : vec) == 0) && aligned(out, out_bytes);
-    }
-
     // one launch for both neighbour lists (the default), or -- as the ablation of interleaving --
     // the local lists first and the remote lists in a second launch that adds to the result
-    const bool two_phases = p->opt_split_phases != 0 && !p->halo_gid.empty() && !a.out_bf16;   // phase 2 reads `out` back
+    const bool two_phases = p->opt_split_phases != 0 && !p->halo_gid.empty() && out_dtype != MGG_BF16;   // phase 2 reads `out` back
     for (int phase = two_phases ? 1 : 0; phase <= (two_phases ? 2 : 0); ++phase) {
         a.phase = phase;
         const int64_t short_waves = (short_groups + a.short_per_wave - 1) / a.short_per_wave;
@@ -344,13 +355,12 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
         const int32_t n_split = static_cast<int32_t>(p->split_rows.size());
         if (n_split > 0) {
             const dim3 fgrid(static_cast<unsigned>((n_split + kWavesPerBlock - 1) / kWavesPerBlock));
-            const int32_t fix_vec_ok = (ld_out % 4 == 0) && aligned(out, a.out_bf16 ? 8 : 16);
             if (bf16)
                 hipLaunchKernelGGL(fixup_kernel<true>, fgrid, dim3(kBlock), 0, stream, p->d.split_rows, n_split, out_dim, scratch,
-                                   scratch_ld, x_local, ld_x, p->d.dinv_own, gcn ? 1 : 0, a.self_w, out, a.out_bf16, ld_out, fix_vec_ok, a.phase, bias, a.relu, a.no_self);
+                                   scratch_ld, x_local, ld_x, p->d.dinv_own, gcn ? 1 : 0, a.self_w, out, a.out_bf16, ld_out, a.phase, bias, a.relu, a.no_self);
             else
                 hipLaunchKernelGGL(fixup_kernel<false>, fgrid, dim3(kBlock), 0, stream, p->d.split_rows, n_split, out_dim, scratch,
-                                   scratch_ld, x_local, ld_x, p->d.dinv_own, gcn ? 1 : 0, a.self_w, out, a.out_bf16, ld_out, fix_vec_ok, a.phase, bias, a.relu, a.no_self);
+                                   scratch_ld, x_local, ld_x, p->d.dinv_own, gcn ? 1 : 0, a.self_w, out, a.out_bf16, ld_out, a.phase, bias, a.relu, a.no_self);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return hip_fail(e, "fix-up kernel launch");
         }

@@ -1,4 +1,4 @@
-// Aggregation kernels for bf16 tables (16-, 4- and 2-byte vectors per lane), fp32 accumulation.
+// Aggregation kernels for bf16 tables (16 bytes per lane; element by element below that width), fp32 accumulation.
 #include "aggregate_kernels.h"
 
 namespace mgg {
@@ -6,8 +6,7 @@ namespace mgg {
 hipError_t launch_aggregate_bf16(const AggArgs &a, bool gcn, int vec, dim3 grid, int wpb, hipStream_t stream, int lpr, int ch, bool lds)
 {
     if (vec == 8) return dispatch_shape<true, 8>(a, gcn, grid, wpb, stream, lpr, ch, lds);
-    if (vec == 2) return dispatch_shape<true, 2>(a, gcn, grid, wpb, stream, lpr, ch, lds);
-    return dispatch_shape<true, 1>(a, gcn, grid, wpb, stream, lpr, ch, lds);
+    return launch_cfg<Cfg<true, 1, 8, 1>>(a, gcn, grid, wpb, stream, lds);      // rows shorter than a vector
 }
 
 }  // namespace mgg

@@ -57,7 +57,8 @@ struct AggArgs {
     float self_w;            // GIN: 1 + eps
     int32_t out_bf16;
     int32_t no_self;         // bags: the owned row has no embedding of its own, x_local is only a table
-    int32_t out_vec_ok;      // out rows allow VEC-wide stores
+    int32_t last_col;        // first column of the last vector: (nvec - 1) * VEC, or less when that vector is moved back to end
+                             // with the row (it then gathers some columns of its neighbour and drops them)
     int32_t out_dim;         // columns of `out` that exist (<= nvec * VEC; the rest of the last vector is padding of the tables)
     int32_t phase;           // 0: local and remote lists in one launch; 1: local lists (+ self term) only;
                              // 2: remote lists only, added to what phase 1 left in out
@@ -68,11 +69,21 @@ struct AggArgs {
 // ---- element access ---------------------------------------------------------------------
 template <bool BF16, int VEC> struct Raw;
 template <> struct Raw<false, 4> { using type = float4; };
-template <> struct Raw<false, 2> { using type = float2; };
 template <> struct Raw<false, 1> { using type = float; };
 template <> struct Raw<true, 8> { using type = uint4; };
-template <> struct Raw<true, 2> { using type = uint32_t; };
 template <> struct Raw<true, 1> { using type = uint16_t; };
+
+// Loads and stores of a vector that is only as aligned as its elements (global memory takes 16-byte
+// accesses at any element boundary; the code only must not promise more).
+template <class T, int ALIGN = 4>
+__device__ __forceinline__ T load_loose(const void *p)
+{
+    T v;
+    __builtin_memcpy(&v, __builtin_assume_aligned(p, ALIGN), sizeof v);
+    return v;
+}
+template <class T, int ALIGN = 4>
+__device__ __forceinline__ void store_loose(void *p, const T &v) { __builtin_memcpy(__builtin_assume_aligned(p, ALIGN), &v, sizeof v); }
 
 __device__ __forceinline__ float bf16_lo(uint32_t d) { return __uint_as_float(d << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t d) { return __uint_as_float(d & 0xffff0000u); }
@@ -82,34 +93,25 @@ __device__ __forceinline__ void unpack(const typename Raw<BF16, VEC>::type &r, f
 {
     if constexpr (!BF16) {
         if constexpr (VEC == 4) { f[0] = r.x; f[1] = r.y; f[2] = r.z; f[3] = r.w; }
-        else if constexpr (VEC == 2) { f[0] = r.x; f[1] = r.y; }
         else { f[0] = r; }
     } else {
         if constexpr (VEC == 8) {
             f[0] = bf16_lo(r.x); f[1] = bf16_hi(r.x); f[2] = bf16_lo(r.y); f[3] = bf16_hi(r.y);
             f[4] = bf16_lo(r.z); f[5] = bf16_hi(r.z); f[6] = bf16_lo(r.w); f[7] = bf16_hi(r.w);
-        } else if constexpr (VEC == 2) { f[0] = bf16_lo(r); f[1] = bf16_hi(r); }
-        else { f[0] = __uint_as_float(static_cast<uint32_t>(r) << 16); }
+        } else { f[0] = __uint_as_float(static_cast<uint32_t>(r) << 16); }
     }
 }
 
 template <int VEC>
-__device__ __forceinline__ void store_vec(float *dst, const float (&v)[VEC], bool vec_ok)
+__device__ __forceinline__ void store_vec(float *dst, const float (&v)[VEC])
 {
-    if (vec_ok) {
-        if constexpr (VEC == 8) {
-            reinterpret_cast<float4 *>(dst)[0] = make_float4(v[0], v[1], v[2], v[3]);
-            reinterpret_cast<float4 *>(dst)[1] = make_float4(v[4], v[5], v[6], v[7]);
-        } else if constexpr (VEC == 4) {
-            *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-        } else if constexpr (VEC == 2) {
-            *reinterpret_cast<float2 *>(dst) = make_float2(v[0], v[1]);
-        } else {
-            dst[0] = v[0];
-        }
+    if constexpr (VEC == 8) {
+        store_loose<float4>(dst, make_float4(v[0], v[1], v[2], v[3]));
+        store_loose<float4>(dst + 4, make_float4(v[4], v[5], v[6], v[7]));
+    } else if constexpr (VEC == 4) {
+        store_loose<float4>(dst, make_float4(v[0], v[1], v[2], v[3]));
     } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) dst[e] = v[e];
+        dst[0] = v[0];
     }
 }
 
@@ -120,20 +122,18 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
     return u >> 16;
 }
 
-// bf16 output: the same VEC values, rounded, as one 2*VEC-byte store when the layout allows
+// bf16 output: the same VEC values, rounded, as one 2*VEC-byte store
 template <int VEC>
-__device__ __forceinline__ void store_vec_bf16(uint16_t *dst, const float (&v)[VEC], bool vec_ok)
+__device__ __forceinline__ void store_vec_bf16(uint16_t *dst, const float (&v)[VEC])
 {
-    if (vec_ok && VEC >= 2) {
-        uint32_t pk[VEC >= 2 ? VEC / 2 : 1];
+    if constexpr (VEC >= 2) {
+        uint32_t pk[VEC / 2];
 #pragma unroll
         for (int e = 0; e < VEC / 2; ++e) pk[e] = f32_to_bf16_bits(v[2 * e]) | (f32_to_bf16_bits(v[2 * e + 1]) << 16);
-        if constexpr (VEC == 8) *reinterpret_cast<uint4 *>(dst) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-        else if constexpr (VEC == 4) *reinterpret_cast<uint2 *>(dst) = make_uint2(pk[0], pk[1]);
-        else if constexpr (VEC == 2) *reinterpret_cast<uint32_t *>(dst) = pk[0];
+        if constexpr (VEC == 8) store_loose<uint4, 2>(dst, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+        else store_loose<uint2, 2>(dst, make_uint2(pk[0], pk[1]));
     } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) dst[e] = static_cast<uint16_t>(f32_to_bf16_bits(v[e]));
+        dst[0] = static_cast<uint16_t>(f32_to_bf16_bits(v[0]));
     }
 }
 
@@ -187,14 +187,14 @@ struct Lanes {
     int sub;                    // which neighbour row of a load instruction
     int lis;                    // first vector of the row this lane owns
     int vend;                   // end of the column slab (in vectors)
-    uint32_t col_off[K::CH];
+    uint32_t col_off[K::CH];    // byte offset of each chunk in a table row
     __device__ __forceinline__ void init(const AggArgs &a, int lane)
     {
         sub = lane / K::LPR;
         lis = lane % K::LPR + static_cast<int>(blockIdx.y) * a.slab_vecs;
         vend = min(a.nvec, (static_cast<int>(blockIdx.y) + 1) * a.slab_vecs);
 #pragma unroll
-        for (int c = 0; c < K::CH; ++c) col_off[c] = static_cast<uint32_t>(min(c * K::LPR + lis, vend - 1)) * K::VEC_BYTES;
+        for (int c = 0; c < K::CH; ++c) col_off[c] = static_cast<uint32_t>(min(min(c * K::LPR + lis, vend - 1) * K::VEC, a.last_col)) * static_cast<uint32_t>(sizeof(typename K::elem));
     }
 };
 
@@ -209,13 +209,14 @@ __device__ __forceinline__ uint32_t lane_read(uint32_t v, int j)
 template <class K, bool WIDE>
 __device__ __forceinline__ typename K::raw load_row_chunk(const char *table, uint32_t off_lo, uint32_t off_hi, uint32_t col)
 {
+    constexpr int AL = sizeof(typename K::elem);
     if constexpr (WIDE) {
         const uint64_t off = (static_cast<uint64_t>(off_hi) << 32 | off_lo) + col;
-        return *reinterpret_cast<const typename K::raw *>(table + off);
+        return load_loose<typename K::raw, AL>(table + off);
     } else if constexpr (K::NPW == 1) {
-        return *reinterpret_cast<const typename K::raw *>((table + off_lo) + col);   // the row's address is wave-uniform
+        return load_loose<typename K::raw, AL>((table + off_lo) + col);   // the row's address is wave-uniform
     } else {
-        return *reinterpret_cast<const typename K::raw *>(table + (off_lo + col));   // 32-bit offset from a uniform base
+        return load_loose<typename K::raw, AL>(table + (off_lo + col));   // 32-bit offset from a uniform base
     }
 }
 
@@ -307,8 +308,8 @@ __device__ __forceinline__ void row_offset(int idx, uint64_t ldb, uint32_t &lo, 
 
 // Final value of an owned row from its neighbour sum: adds the self term and the row factor.
 template <class K>
-__device__ __forceinline__ void write_final(const AggArgs &a, bool gcn, const Acc<K> &acc, const typename K::raw (&xs)[K::CH], int32_t row, int lis,
-                                            int vend)
+__device__ __forceinline__ void write_final(const AggArgs &a, bool gcn, const Acc<K> &acc, const typename K::raw (&xs)[K::CH], int32_t row,
+                                            const Lanes<K> &ln)
 {
     float *o = static_cast<float *>(a.out) + static_cast<int64_t>(row) * a.ld_out;             // fp32 output
     uint16_t *ob = static_cast<uint16_t *>(a.out) + static_cast<int64_t>(row) * a.ld_out;     // bf16 output
@@ -316,8 +317,9 @@ __device__ __forceinline__ void write_final(const AggArgs &a, bool gcn, const Ac
     const float ws = gcn ? dv : a.self_w;     // GCN: dv * (sum + dv * x_v) = sum_u x_u/sqrt(du dv) + x_v/dv^2
 #pragma unroll
     for (int c = 0; c < K::CH; ++c) {
-        const int vi = c * K::LPR + lis;
-        if (vi < vend) {
+        const int vi = c * K::LPR + ln.lis;
+        if (vi < ln.vend) {
+            const int col0 = static_cast<int>(ln.col_off[c] / sizeof(typename K::elem)), own0 = vi * K::VEC;   // own0 > col0: moved back
             float xv[K::VEC], r[K::VEC];
             if (a.no_self || a.phase == 2) {
 #pragma unroll
@@ -327,7 +329,7 @@ __device__ __forceinline__ void write_final(const AggArgs &a, bool gcn, const Ac
             }
             if (a.phase == 2) {                 // second of two launches: add to the first one's result
 #pragma unroll
-                for (int e = 0; e < K::VEC; ++e) r[e] = (vi * K::VEC + e < a.out_dim ? o[vi * K::VEC + e] : 0.f) + dv * acc.v[c][e];
+                for (int e = 0; e < K::VEC; ++e) r[e] = (col0 + e >= own0 && col0 + e < a.out_dim ? o[col0 + e] : 0.f) + dv * acc.v[c][e];
             } else {
 #pragma unroll
                 for (int e = 0; e < K::VEC; ++e) r[e] = dv * (acc.v[c][e] + ws * xv[e]);
@@ -336,41 +338,46 @@ __device__ __forceinline__ void write_final(const AggArgs &a, bool gcn, const Ac
                 if (a.bias) {
 #pragma unroll
                     for (int e = 0; e < K::VEC; ++e)
-                        if (vi * K::VEC + e < a.out_dim) r[e] += a.bias[vi * K::VEC + e];
+                        if (col0 + e < a.out_dim) r[e] += a.bias[col0 + e];
                 }
                 if (a.relu) {
 #pragma unroll
                     for (int e = 0; e < K::VEC; ++e) r[e] = fmaxf(r[e], 0.f);
                 }
             }
-            const int col0 = vi * K::VEC;
-            if (a.out_bf16) {                   // (never combined with phase 2, which reads `out` back)
-                if (col0 + K::VEC <= a.out_dim) {
-                    store_vec_bf16<K::VEC>(ob + col0, r, a.out_vec_ok);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < K::VEC; ++e)
-                        if (col0 + e < a.out_dim) ob[col0 + e] = static_cast<uint16_t>(f32_to_bf16_bits(r[e]));
-                }
-            } else if (col0 + K::VEC <= a.out_dim) {
-                store_vec<K::VEC>(o + col0, r, a.out_vec_ok);
-            } else {                            // last vector reaches into the padding: store what exists
+            // a last vector that reaches into the padding stores what exists, one that was moved back what is its own
+            const bool whole = col0 == own0 && col0 + K::VEC <= a.out_dim;
+            if (whole) {
+                if (a.out_bf16) store_vec_bf16<K::VEC>(ob + col0, r);     // (never combined with phase 2, which reads `out` back)
+                else store_vec<K::VEC>(o + col0, r);
+            } else {
 #pragma unroll
                 for (int e = 0; e < K::VEC; ++e)
-                    if (col0 + e < a.out_dim) o[col0 + e] = r[e];
+                    if (col0 + e >= own0 && col0 + e < a.out_dim) {
+                        if (a.out_bf16) ob[col0 + e] = static_cast<uint16_t>(f32_to_bf16_bits(r[e]));
+                        else o[col0 + e] = r[e];
+                    }
             }
         }
     }
 }
 
 template <class K>
-__device__ __forceinline__ void write_partial(const AggArgs &a, const Acc<K> &acc, int32_t slot, int lis, int vend)
+__device__ __forceinline__ void write_partial(const AggArgs &a, const Acc<K> &acc, int32_t slot, const Lanes<K> &ln)
 {
     float *o = a.scratch + static_cast<int64_t>(slot) * a.scratch_ld;
 #pragma unroll
     for (int c = 0; c < K::CH; ++c) {
-        const int vi = c * K::LPR + lis;
-        if (vi < vend) store_vec<K::VEC>(o + static_cast<int64_t>(vi) * K::VEC, acc.v[c], true);
+        const int vi = c * K::LPR + ln.lis;
+        if (vi >= ln.vend) continue;
+        const int col0 = static_cast<int>(ln.col_off[c] / sizeof(typename K::elem)), own0 = vi * K::VEC;
+        if (col0 == own0) {                     // (scratch rows hold whole vectors)
+            store_vec<K::VEC>(o + col0, acc.v[c]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < K::VEC; ++e)
+                if (col0 + e >= own0) o[col0 + e] = acc.v[c][e];
+        }
     }
 }
 
@@ -455,7 +462,7 @@ __device__ __forceinline__ void load_self_row(const AggArgs &a, int32_t row, con
 {
     const char *base = static_cast<const char *>(a.x_local) + static_cast<int64_t>(row) * a.ld_x * static_cast<int64_t>(sizeof(typename K::elem));
 #pragma unroll
-    for (int c = 0; c < K::CH; ++c) xs[c] = *reinterpret_cast<const typename K::raw *>(base + ln.col_off[c]);
+    for (int c = 0; c < K::CH; ++c) xs[c] = load_loose<typename K::raw, sizeof(typename K::elem)>(base + ln.col_off[c]);
 }
 
 template <class K, bool GCN, bool WIDE>
@@ -564,8 +571,8 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
                         for (int e = 0; e < K::VEC; ++e) acc.v[c][e] += __shfl_xor(acc.v[c][e], off);
                 if (ln.sub == 0) {
-                    if (it.slot < 0) write_final<K>(a, GCN, acc, xs, it.row, ln.lis, ln.vend);
-                    else write_partial<K>(a, acc, it.slot, ln.lis, ln.vend);
+                    if (it.slot < 0) write_final<K>(a, GCN, acc, xs, it.row, ln);
+                    else write_partial<K>(a, acc, it.slot, ln);
                 }
             } else {
                 ids_ready = false;
@@ -666,7 +673,7 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
                     }
                 }
             }
-            if (have) write_final<K>(a, GCN, acc, xs, row, ln.lis, ln.vend);
+            if (have) write_final<K>(a, GCN, acc, xs, row, ln);
             sd_cur = sd_nxt; sd_nxt = sd_nn;
             fi_l = ni_l; fw_l = nw_l; fi_r = ni_r; fw_r = nw_r;
         }

@@ -172,6 +172,35 @@ def test_padded_rows_and_unaligned_base(ld_pad, misalign):
     check_aggregate(row_ptr, col, 2, 0, bounds, xb, "gin", ld_pad=ld_pad, misalign=misalign, what="bf16 padded")
 
 
+@pytest.mark.parametrize("dim,bf16,slab", [(4, False, 0), (5, False, 0), (63, False, 64), (65, False, 128), (255, False, 0), (257, False, 256), (1029, False, 1),
+                                           (8, True, 0), (9, True, 0), (127, True, 64), (129, True, 128), (515, True, 0)])
+def test_rows_at_any_element_boundary(dim, bf16, slab):
+    """Plain contiguous rows of any width, bases one element off a 16-byte boundary, the table's last row ending with its
+    buffer: 16-byte loads whose last vector ends with the row; the columns around the output stay as they were."""
+    row_ptr, col, rng = small_rmat(scale=10, draws=20000, seed=4000 + dim)
+    n = row_ptr.size - 1
+    x = rng.standard_normal((n, dim)).astype(np.float32)
+    if bf16:
+        x = inputs.to_bf16_bits(x)
+    bounds = inputs.equal_node_bounds(n, 2)
+    for build in (dict(), dict(xcd_min_deg=20, dist=1)):
+        check_aggregate(row_ptr, col, 2, 0, bounds, x, "gcn", misalign=1, build=build, options={"col_slab_bytes": slab}, what=f"dim {dim} gcn")
+        part = binding.mgg_build_partition(row_ptr, col, 2, 1, bounds, **build)
+        part.set_option("col_slab_bytes", slab)
+        xl, xh = to_dev(x[bounds[1]:]), to_dev(x[part.export()["halo_gid"]])
+        plain = binding.mgg_aggregate(part, "gin", xl, xh, eps=0.5)
+        buf = torch.full((int(part.info.n_own), dim + 3), -7.0, dtype=torch.float32, device=DEV)
+        binding.mgg_aggregate(part, "gin", xl, xh, eps=0.5, out=buf[:, 1:dim + 1])
+        part.set_option("split_phases", 1)
+        two = binding.mgg_aggregate(part, "gin", xl, xh, eps=0.5)
+        torch.cuda.synchronize()
+        assert torch.equal(buf[:, 1:dim + 1], plain) and torch.all(buf[:, :1] == -7.0) and torch.all(buf[:, dim + 1:] == -7.0)
+        # the same fp32 sums in another order: n terms of up to max|x|, n u apart
+        terms = int(part.info.nnz_local + part.info.nnz_remote) * 4.0 * 2.0 ** -24
+        assert float((two - plain).abs().max()) <= terms
+        part.destroy()
+
+
 def test_tables_beyond_4gb_take_64_bit_row_offsets():
     """Row offsets inside a table are 32-bit unless a table reaches beyond 4 GB; rows spaced 2.1 MB apart
     put a 2048-row table there (work items, short rows and the self term all use the wide path)."""
