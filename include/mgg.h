@@ -385,9 +385,10 @@ mgg_status_t mgg_tune_aggregate(int64_t num_nodes, const int64_t *row_ptr, const
  *   "items_per_wave"   0 = automatic (default), or 1..64: work items a wavefront takes one after
  *                      the other, the next one's ids and descriptor requested while it gathers
  *   "short_per_wave"   the same for the groups of short rows a wavefront takes
- *   "update_stream" 0/1 (process-wide only) the Update kernels added for streaming efficiency (whole-line
- *                      kernels, the one-kernel MLP, two W slabs in LDS) are used where they apply
- *                      (default 1; 0 = the plain register-resident and slab kernels everywhere)
+ *   "update_stream" 0/1 (process-wide only) the Update kernels for bf16 weights that were added for streaming
+ *                      efficiency (whole-line kernels, the one-kernel MLP) are used where they apply
+ *                      (default 1; 0 = the plain register-resident and slab kernels everywhere);
+ *                      fp32 weights take the same kernels either way
  * Unknown key or bad value -> MGG_ERR_INVALID_ARG. */
 mgg_status_t mgg_set_option(const char *key, int32_t value);
 mgg_status_t mgg_get_option(const char *key, int32_t *value);

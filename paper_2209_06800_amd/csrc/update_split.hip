@@ -1,0 +1,574 @@
+// Dense Update with fp32 weights for gfx950 (section 1: Update is a fully-connected layer; section 7:
+// X W with ReLU): out = act(A . W + bias), fp32 in and out, on the bf16 matrix instruction.
+//
+// v_mfma_f32_32x32x2_f32 runs at 1/16 of the bf16 rate (about 157 TFLOP/s), which bounded every fp32 shape
+// wider than about 64 x 64.  An fp32 number is the exact sum of three bf16 numbers (24 = 8 + 8 + 8 bits of
+// significand; each part is rounded to nearest, so the next one is at most 2^-8 of it and of either sign), and
+// a product of two bf16 numbers is exact in fp32.  a w = (a1 + a2 + a3)(w1 + w2 + w3) is summed from its
+// six largest terms, small ones first; the three that are left out are below 2^-24 |a w| together and of
+// random sign.  Six bf16 MFMAs cost 6/16 of the fp32 one, and 16 terms enter the accumulator per rounding
+// instead of 2.
+//
+// The split is exact while no part overflows or becomes denormal.  Per 32-row tile the kernel looks at the
+// largest magnitude of each row of A and of each column of W: if one is non-zero and below 2^-50, or
+// 2^127 and more (infinities included; a NaN needs no help, it stays one through the split), the tile is
+// computed again with the fp32 instruction from global memory -- slow, exact about infinities, and not
+// met by data of ordinary scale.
+//
+// What bounds it: HBM for narrow outputs, the matrix pipe and the operand traffic through LDS for wide ones (602 -> 256:
+// the pipe is busy 0.5 of the time at the 1.95 GHz the chip holds, of which 0.11 is the last, partly filled round of tiles).
+// Measured against the fp32-instruction kernels this file replaces (us before -> after, one MI355X; fp32 rows end to end
+// unless a leading dimension is given), and the 2-norm error against float64, which is lower at every shape tried:
+//   232,965 x 602 (ld 608) -> 256    718 -> 448     4.4e-7 -> 3.8e-7
+//   120,011 x 602 -> 256             428 -> 216     4.4e-7 -> 3.8e-7
+//   400,000 x 250 -> 250             968 -> 354     2.8e-7 -> 2.4e-7
+//   306,128 x 100 -> 256             231 -> 153     1.8e-7 -> 1.5e-7
+//   1,771,062 x 256 -> 47            688 -> 482     2.9e-7 -> 2.4e-7
+//   300,000 x 128 -> 128             156 ->  90     2.0e-7 -> 1.6e-7
+//   100,000 x 75 -> 33                41 ->  20     1.6e-7 -> 1.4e-7
+//   262,144 x 64 -> 64                38 ->  31     1.5e-7 -> 1.1e-7
+//   2,000 x 602 -> 256               117 ->  31     4.4e-7 -> 3.7e-7
+//   400,000 x 32 -> 16                20 ->  21     1.0e-7 -> 0.7e-7     (HBM; the narrowest gain nothing)
+//
+// Layout.  Eight wavefronts; a wavefront owns 32 rows x NT*32 columns.  A slab of 32 k values is read with 8
+// lanes per row (one whole 128-byte line per row and instruction, at any alignment: 16-byte loads need only
+// element alignment, and a vector that would pass the end of a ragged row is moved back to end with it), staged raw in a
+// per-wavefront LDS buffer, read back in operand layout and split there: every element of A is split once.
+// W is split while it is staged: three planes of 16-byte pieces [k / 8][column], so that operand reads and
+// staging writes are conflict-free and W needs no alignment.
+//   - RESIDENT: all of W in LDS, split once per workgroup; wavefronts walk over their tiles without a barrier;
+//   - otherwise two slabs of W in LDS: the next one is loaded into registers, split between the MFMAs of the
+//     current one and written to the other buffer; one barrier per slab.
+#include <utility>
+
+#include "update_common.h"
+
+namespace mgg {
+
+namespace {
+
+using namespace upd;
+
+constexpr int kSWaves = 8, kSThreads = kWave * kSWaves;
+constexpr int kLda = 36;                                    // row of the per-wavefront buffer, in floats
+constexpr int kWaveBytes = 32 * kLda * 4;
+constexpr int kLdsMax = 160 * 1024 - 1024;                  // (colmax: 1 KB)
+constexpr int w_slab_bytes(int nc) { return 3 * 4 * nc * 16; }
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+union Frag { uint32_t u[4]; uint4 q; bf16x8 v; };
+
+extern __shared__ __attribute__((aligned(16))) unsigned char lds_split[];
+
+__device__ __forceinline__ void wave_sync_lds()
+{
+    // LDS traffic of one wavefront is executed in order; this only keeps the compiler from reordering it
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ uint32_t cvt_pk(float lo, float hi)
+{
+    const f32x2 f = {lo, hi};
+    union { bf16x2 b; uint32_t u; } r;
+    r.b = __builtin_convertvector(f, bf16x2);              // round to nearest even
+    return r.u;
+}
+
+// eight fp32 values -> three bf16 operands whose sum they are
+__device__ __forceinline__ void split8(const float (&f)[8], Frag (&o)[3])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float lo = f[2 * e], hi = f[2 * e + 1];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            const uint32_t pk = cvt_pk(lo, hi);
+            o[s].u[e] = pk;
+            if (s < 2) { lo -= __uint_as_float(pk << 16); hi -= __uint_as_float(pk & 0xffff0000u); }
+        }
+    }
+}
+
+__device__ __forceinline__ bool out_of_range(float m) { return m != 0.f && !(m >= 0x1p-50f && m < 0x1p127f); }
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_loose __attribute__((aligned(4)));       // in memory, at any element
+struct RawA { f32x4 v[4]; };
+
+// f(integral_constant 0), f(1), ... f(N - 1): steps whose number decides at compile time what they hold
+template <class F, int... X>
+__device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, X...>) { (f(std::integral_constant<int, X>{}), ...); }
+
+// 32 rows x 32 k values: instruction j takes rows 8 j + lane / 8.  Rows past the end are clamped to the last
+// one (never stored).  A vector that would reach past the row ends with it instead: slab position 4 c + e then holds
+// k = min(k0 + 4 c, d_in - 4) + e, and W is laid out to match (w_row).  m0 is wave-uniform: an address is a
+// scalar base and a 32-bit offset per lane (the host checks the leading dimensions for it).
+__device__ __forceinline__ void load_a(const UpdArgs &p, int64_t m0, int k0, int lane, RawA &r)
+{
+    const int64_t last = (p.n_rows - 1) / 32 * 32;
+    m0 = m0 < last ? m0 : last;
+    const int rows = static_cast<int>(p.n_rows - m0 < 32 ? p.n_rows - m0 : 32);
+    const char *base = reinterpret_cast<const char *>(static_cast<const float *>(p.a) + m0 * p.ld_a);
+    const uint32_t col = static_cast<uint32_t>(min(k0 + (lane & 7) * 4, p.d_in - 4));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t off = (static_cast<uint32_t>(min(j * 8 + (lane >> 3), rows - 1)) * static_cast<uint32_t>(p.ld_a) + col) * 4u;
+        r.v[j] = *reinterpret_cast<const f32x4_loose *>(base + off);
+    }
+}
+
+__device__ __forceinline__ void stage_a(const RawA &r, int lane, float *abuf)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *reinterpret_cast<f32x4 *>(abuf + (j * 8 + (lane >> 3)) * kLda + (lane & 7) * 4) = r.v[j];
+}
+
+// The row of W that meets slab position pos (counted from the first slab; pos & 3 = e in load_a).  Where load_a moved
+// a vector back its first elements were met before: `again`, and their weight is zero.  (Zero times an infinity of A: the
+// tile goes through exact_tile then.)
+__device__ __forceinline__ int w_row(int pos, int d_in, bool &again)
+{
+    const int first = pos & ~3, k = min(first, d_in - 4) + (pos & 3);
+    again = k < first;
+    return k;
+}
+
+// One unit of W: 8 consecutive slab positions of one column.  Unit id0 + lane (id0 wave-uniform, a multiple of 64) is
+// (position / 8, column) = (id / NC, id % NC).  Columns past the edge read the last one and are never stored.
+template <int NC>
+__device__ __forceinline__ int unit_pos(int id0, int lane) { return NC >= kWave ? id0 / NC * 8 : (id0 + lane) / NC * 8; }      // (scalar if NC >= 64)
+
+template <int NC>
+__device__ __forceinline__ void load_w_unit(const UpdArgs &p, int k0, int id0, int n0, int lane, float (&f)[8])
+{
+    const int n = min(n0 + (NC >= kWave ? id0 % NC + lane : lane % NC), p.d_out - 1);
+    const int pos = k0 + unit_pos<NC>(id0, lane);
+    const char *base = static_cast<const char *>(p.w);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        bool again;
+        const uint32_t k = static_cast<uint32_t>(w_row(pos + e, p.d_in, again)), row = k * static_cast<uint32_t>(p.d_out) * 4u;   // (host: W below 2 GB)
+        if constexpr (NC >= kWave) f[e] = *reinterpret_cast<const float *>(base + row + static_cast<uint32_t>(n) * 4u);
+        else f[e] = *reinterpret_cast<const float *>(base + (row + static_cast<uint32_t>(n) * 4u));
+    }
+}
+
+// plane s of unit (kg, n) of a slab -> w[s][kg][n]
+template <int NC>
+__device__ __forceinline__ void store_w_unit(const UpdArgs &p, int k0, int id0, int lane, float (&f)[8], uint4 *w, uint32_t *colmax)
+{
+    const int id = id0 + lane, pos = k0 + unit_pos<NC>(id0, lane);
+    float m = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        bool again;
+        (void)w_row(pos + e, p.d_in, again);
+        f[e] = again ? 0.f : f[e];
+        m = fmaxf(m, fabsf(f[e]));
+    }
+    Frag o[3];
+    split8(f, o);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) w[s * 4 * NC + id % (4 * NC)] = o[s].q;
+    atomicMax(&colmax[id % NC], __float_as_uint(m));
+}
+
+// The A operands of a slab as the loop carries them: the first half (k 0..7 and 16..23 of the slab) split, the second raw.
+struct SlabA {
+    Frag a0[3];
+    float raw1[8];
+    float amax;              // largest magnitude of this lane's 16 values
+};
+
+__device__ __forceinline__ void read_raw(const float *abuf, int lane, int c, float (&f)[8])
+{
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const float4 x = *reinterpret_cast<const float4 *>(abuf + (lane & 31) * kLda + 16 * (lane >> 5) + 8 * c + 4 * q);
+        f[4 * q] = x.x; f[4 * q + 1] = x.y; f[4 * q + 2] = x.z; f[4 * q + 3] = x.w;
+    }
+}
+
+// Products of one K slab: acc += A slab * W slab, in 2 NT steps of six MFMAs.  The W operands of a step are read from LDS
+// one step ahead; between(x), called after step x, holds everything else the wavefront has to do, spread over the steps,
+// so that the matrix pipe is not left idle while a wavefront waits, converts or stores (the fences keep the compiler
+// from gathering it at the end).  In it, the next slab replaces `sa`: its raw half is used up by step NT - 1.
+template <int NT, class Between>
+__device__ __forceinline__ void multiply_slab(f32x16 (&acc)[NT], SlabA &sa, const uint4 *w, int lane, Between between)
+{
+    constexpr int NC = NT * 32, S = 2 * NT;
+    const uint4 *wl = w + 2 * (lane >> 5) * NC + (lane & 31);
+    Frag b[2][3], a0[3], a1[3];
+    auto load_b = [&](int x) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) b[x & 1][s].q = wl[s * 4 * NC + x / NT * NC + x % NT * 32];
+    };
+#pragma unroll
+    for (int s = 0; s < 3; ++s) a0[s] = sa.a0[s];
+    load_b(0);
+    static_for([&](auto step) __attribute__((always_inline)) {
+        constexpr int x = step;
+        if constexpr (x + 1 < S) load_b(x + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (x == NT - 1) split8(sa.raw1, a1);
+        constexpr int wi[6] = {2, 0, 1, 1, 0, 0}, ai[6] = {0, 2, 1, 0, 1, 0};          // small terms first
+#pragma unroll
+        for (int y = 0; y < 6; ++y)
+            acc[x % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[x & 1][wi[y]].v, x < NT ? a0[ai[y]].v : a1[ai[y]].v, acc[x % NT], 0, 0, 0);
+        between(step);
+        __builtin_amdgcn_sched_barrier(0);
+    }, std::make_integer_sequence<int, S>{});
+}
+
+// The part of `between` that brings the next slab of A from registers through LDS into operands.  The slab after that is
+// requested right behind the last piece of W: a wavefront waits for its loads in order, and those of A come from HBM.
+template <int NT, int x, class Next>
+__device__ __forceinline__ void next_a(RawA &q, int lane, float *abuf, SlabA &sa, float (&raw0)[8], Next &&issue)
+{
+    constexpr int S = 2 * NT, X0 = S * 6 / 16, X1 = S > 4 ? S - 2 : S / 2;
+    if constexpr (x == X0) {
+        wave_sync_lds();
+        stage_a(q, lane, abuf);
+        wave_sync_lds();
+        issue();
+    }
+    if constexpr (x == X1) {
+        read_raw(abuf, lane, 0, raw0);
+        read_raw(abuf, lane, 1, sa.raw1);
+    }
+    if constexpr (x == S - 1) {
+        sa.amax = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sa.amax = fmaxf(fmaxf(sa.amax, fabsf(raw0[e])), fabsf(sa.raw1[e]));
+        split8(raw0, sa.a0);
+        wave_sync_lds();                                    // the buffer is free for the epilogue
+    }
+}
+
+// the same at once, for the first slab
+__device__ __forceinline__ void first_a(RawA &q, int lane, float *abuf, SlabA &sa)
+{
+    float raw0[8];
+    stage_a(q, lane, abuf);
+    wave_sync_lds();
+    read_raw(abuf, lane, 0, raw0);
+    read_raw(abuf, lane, 1, sa.raw1);
+    sa.amax = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sa.amax = fmaxf(fmaxf(sa.amax, fabsf(raw0[e])), fabsf(sa.raw1[e]));
+    split8(raw0, sa.a0);
+    wave_sync_lds();
+}
+
+// acc holds the transposed 32x32 tiles (register r of lane (m, h): row m, column 8*(r/4) + 4*h + r%4); each goes
+// through the wavefront's LDS buffer and leaves with 8 lanes per row, a whole line per row where rows are aligned.
+template <int NT>
+__device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc)[NT], float *cbuf, int64_t m0, int n0, int lane)
+{
+    const int m = lane & 31, h = lane >> 5, c = (lane & 7) * 4;
+    const int rows = static_cast<int>(p.n_rows - m0 < 32 ? p.n_rows - m0 : 32);
+    const int esz = p.out_bf16 ? 2 : 4;
+    char *base = static_cast<char *>(p.out) + (m0 * p.ld_out + n0) * esz;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if (n0 + t * 32 >= p.d_out) break;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<float4 *>(cbuf + m * kLda + 8 * q + 4 * h) = make_float4(acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]);
+        wave_sync_lds();
+        const int col = n0 + t * 32 + c;
+        float b[4] = {0.f, 0.f, 0.f, 0.f};
+        if (p.bias) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (col + e < p.d_out) b[e] = p.bias[col + e];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = j * 8 + (lane >> 3);
+            const float4 x = *reinterpret_cast<const float4 *>(cbuf + r * kLda + c);
+            float v[4] = {x.x + b[0], x.y + b[1], x.z + b[2], x.w + b[3]};
+            if (p.relu) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+            }
+            if (r >= rows || col >= p.d_out) continue;
+            char *at = base + (static_cast<uint32_t>(r) * static_cast<uint32_t>(p.ld_out) + static_cast<uint32_t>(t * 32 + c)) * static_cast<uint32_t>(esz);
+            if (p.out_bf16) {
+                uint16_t *o = reinterpret_cast<uint16_t *>(at);
+                if (col + 4 <= p.d_out) {
+                    const uint32_t pk[2] = {f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16), f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16)};
+                    __builtin_memcpy(__builtin_assume_aligned(o, 2), pk, 8);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < p.d_out) o[e] = static_cast<uint16_t>(f32_to_bf16_bits(v[e]));
+                }
+            } else {
+                float *o = reinterpret_cast<float *>(at);
+                if (col + 4 <= p.d_out) {
+                    __builtin_memcpy(__builtin_assume_aligned(o, 4), v, 16);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < p.d_out) o[e] = v[e];
+                }
+            }
+        }
+        wave_sync_lds();
+    }
+}
+
+// The tile once more with the fp32 instruction, operands straight from global memory (any magnitude), 32 columns at a
+// time over what store_lines has written (the same lanes write the same places, so the order is theirs).
+__device__ __forceinline__ void exact_tile(const UpdArgs &p, float *cbuf, int64_t m0, int n0, int n_end, int lane)
+{
+    const int i = lane & 31, h = lane >> 5;
+    if (m0 >= p.n_rows) return;                              // a wavefront of the last row tile that has no rows
+    const int rows = static_cast<int>(p.n_rows - m0 < 32 ? p.n_rows - m0 : 32);
+    const char *A = reinterpret_cast<const char *>(static_cast<const float *>(p.a) + m0 * p.ld_a), *W = static_cast<const char *>(p.w);
+    const uint32_t aoff = (static_cast<uint32_t>(min(i, rows - 1)) * static_cast<uint32_t>(p.ld_a) + static_cast<uint32_t>(h)) * 4u;
+#pragma unroll 1
+    for (; n0 < n_end && n0 < p.d_out; n0 += 32) {
+        f32x16 acc[1];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
+        const uint32_t woff = (static_cast<uint32_t>(h) * static_cast<uint32_t>(p.d_out) + static_cast<uint32_t>(min(n0 + i, p.d_out - 1))) * 4u;
+#pragma unroll 1
+        for (int k0 = 0; k0 < p.d_in; k0 += 2) {
+            const bool in = k0 + h < p.d_in;
+            const float af = in ? *reinterpret_cast<const float *>(A + static_cast<int64_t>(k0) * 4 + aoff) : 0.f;
+            const float wf = in ? *reinterpret_cast<const float *>(W + static_cast<int64_t>(k0) * p.d_out * 4 + woff) : 0.f;
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf, af, acc[0], 0, 0, 0);
+        }
+        store_lines<1>(p, acc, cbuf, m0, n0, lane);
+    }
+}
+
+template <int NC>
+__device__ __forceinline__ bool columns_out_of_range(const uint32_t *colmax, int lane)
+{
+    bool bad = false;
+    for (int n = lane; n < NC; n += kWave) bad |= out_of_range(__uint_as_float(colmax[n]));
+    return __ballot(bad) != 0;
+}
+
+// What only depends on the arguments and the lane would be computed ahead of all loops and held in registers that
+// the accumulators need; the epilogue works on a copy the compiler cannot see through.
+__device__ __forceinline__ UpdArgs opaque(UpdArgs p)
+{
+    asm volatile("" : "+s"(p.out), "+s"(p.bias), "+s"(p.d_out), "+s"(p.w), "+s"(p.a), "+s"(p.ld_out), "+s"(p.ld_a));
+    return p;
+}
+
+__device__ __forceinline__ int opaque(int lane)
+{
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// wavefronts per SIMD the registers are cut for: 2 where the accumulators alone take 128, else two workgroups per CU
+#define MGG_SPLIT_WAVES(NT) ((NT) >= 4 ? 2 : 4)
+
+template <int NT>
+__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(MGG_SPLIT_WAVES(NT), MGG_SPLIT_WAVES(NT))))
+void update_split_resident_kernel(const UpdArgs p)
+{
+    constexpr int NC = NT * 32, SLAB = w_slab_bytes(NC) / 16;
+    __shared__ uint32_t colmax[NC];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int n0 = static_cast<int>(blockIdx.y) * NC;
+    const int n_slabs = (p.d_in + 31) / 32;
+    uint4 *w = reinterpret_cast<uint4 *>(lds_split);
+    float *abuf = reinterpret_cast<float *>(lds_split + n_slabs * w_slab_bytes(NC) + wave * kWaveBytes);
+
+    // tiles are dealt out workgroup by workgroup, so that a small call still spreads over the chip
+    const int64_t n_tiles = (p.n_rows + 31) / 32, stride = static_cast<int64_t>(gridDim.x) * kSWaves;
+    int64_t tile = static_cast<int64_t>(wave) * gridDim.x + blockIdx.x;
+    RawA q[2];
+    int64_t itile = tile;                                    // issue cursor: the slab requested next
+    int is = 0;
+    auto issue = [&](RawA &r) __attribute__((always_inline)) {
+        load_a(p, itile * 32, is * 32, lane, r);             // (past the last tile: rows are clamped)
+        if (++is == n_slabs) { is = 0; itile += stride; }
+    };
+    issue(q[0]);
+    issue(q[1]);
+    for (int n = threadIdx.x; n < NC; n += kSThreads) colmax[n] = 0u;
+    __syncthreads();
+    {
+        const int units = n_slabs * 4 * NC;
+        constexpr int B = 2;
+        for (int base = wave * kWave; base < units; base += B * kSThreads) {
+            float f[B][8];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                load_w_unit<NC>(p, 0, base + b * kSThreads, n0, lane, f[b]);      // (past the end: the last row again, not kept)
+            }
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int id0 = base + b * kSThreads;                             // (units is a multiple of a wavefront)
+                if (id0 < units) store_w_unit<NC>(p, 0, id0, lane, f[b], w + id0 / (4 * NC) * SLAB, colmax);
+            }
+        }
+    }
+    __syncthreads();
+    const bool bad_w = columns_out_of_range<NC>(colmax, lane);
+
+    if (tile >= n_tiles) return;
+    SlabA sa;
+    first_a(q[0], lane, abuf, sa);
+    q[0] = q[1];
+    issue(q[1]);
+    do {
+        f32x16 acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+        float amax = 0.f;
+        int s = 0;
+#pragma unroll 1
+        do {
+            amax = fmaxf(amax, sa.amax);
+            float raw0[8];
+            multiply_slab<NT>(acc, sa, w + s * SLAB, lane, [&](auto step) __attribute__((always_inline)) {
+                next_a<NT, decltype(step)::value>(q[0], lane, abuf, sa, raw0, [&]() __attribute__((always_inline)) { q[0] = q[1]; issue(q[1]); });
+            });
+        } while (++s < n_slabs);
+        amax = fmaxf(amax, __shfl_xor(amax, 32));
+        const bool again = bad_w || __ballot(out_of_range(amax));
+        store_lines<NT>(opaque(p), acc, abuf, tile * 32, n0, opaque(lane));
+        if (again) exact_tile(opaque(p), abuf, tile * 32, n0, n0 + NC, opaque(lane));
+        tile += stride;
+    } while (tile < n_tiles);
+}
+
+template <int NT>
+__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
+{
+    constexpr int NC = NT * 32, SLAB = w_slab_bytes(NC) / 16;
+    constexpr int UNITS = (4 * NC + kSThreads - 1) / kSThreads;          // of a slab, per thread
+    __shared__ uint32_t colmax[NC];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int n0 = static_cast<int>(blockIdx.y) * NC;
+    const int n_slabs = (p.d_in + 31) / 32;
+    uint4 *w = reinterpret_cast<uint4 *>(lds_split);                     // two slabs
+    float *abuf = reinterpret_cast<float *>(lds_split + 2 * w_slab_bytes(NC) + wave * kWaveBytes);
+    // (narrow slabs have fewer units than threads: some are staged twice, with the same values)
+    auto unit0 = [&](int u) { return (u * kSThreads + wave * kWave) % (4 * NC); };
+    auto load_w = [&](int ks, int u, float (&f)[8]) { load_w_unit<NC>(p, ks * 32, unit0(u), n0, lane, f); };
+    auto store_w = [&](int buf, int ks, int u, float (&f)[8]) { store_w_unit<NC>(p, ks * 32, unit0(u), lane, f, w + buf * SLAB, colmax); };
+
+    int64_t tile = blockIdx.x;                                           // the host launches at most n_tiles workgroups
+    auto first_row = [&](int64_t t) { return (t * kSWaves + wave) * 32; };
+    RawA q;
+    SlabA sa;
+    load_a(p, first_row(tile), 0, lane, q);
+    {
+        float wf[UNITS][8];
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) load_w(0, u, wf[u]);
+        for (int n = threadIdx.x; n < NC; n += kSThreads) colmax[n] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) store_w(0, 0, u, wf[u]);
+    }
+    first_a(q, lane, abuf, sa);
+    // issue cursor of A: the slab after the one in `sa` (after the last tile: rows are clamped, and never used)
+    int64_t itile = tile;
+    int is = 0;
+    auto issue = [&]() __attribute__((always_inline)) {
+        if (++is == n_slabs) { is = 0; itile += gridDim.x; }
+        load_a(p, first_row(itile), is * 32, lane, q);
+    };
+    issue();
+    __syncthreads();
+    int cur = 0;
+#pragma unroll 1
+    for (;;) {
+        f32x16 acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+        float amax = 0.f;
+        const int64_t ntile = tile + gridDim.x;
+        int ks = 0;
+#pragma unroll 1
+        do {
+            amax = fmaxf(amax, sa.amax);
+            const int nks = ks + 1 == n_slabs ? 0 : ks + 1;            // the slab after this one
+            float raw0[8], wf[8];
+            multiply_slab<NT>(acc, sa, w + cur * SLAB, lane, [&](auto step) __attribute__((always_inline)) {
+                // W: one unit after the other through the same registers, five sixteenths of the slab in flight each
+                constexpr int S = 2 * NT, x = step;
+#pragma unroll
+                for (int u = 0; u < UNITS; ++u) {
+                    if (x == u * 6 * S / 16) load_w(nks, u, wf);
+                    if (x == (u * 6 + 5) * S / 16) store_w(cur ^ 1, nks, u, wf);       // the other buffer: nobody reads it before the barrier
+                }
+                next_a<NT, x>(q, lane, abuf, sa, raw0, issue);
+            });
+            __syncthreads();
+            cur ^= 1;
+        } while (++ks < n_slabs);
+        amax = fmaxf(amax, __shfl_xor(amax, 32));
+        const bool again = columns_out_of_range<NC>(colmax, lane) || __ballot(out_of_range(amax));
+        store_lines<NT>(opaque(p), acc, abuf, first_row(tile), n0, opaque(lane));
+        if (again) exact_tile(opaque(p), abuf, first_row(tile), n0, n0 + NC, opaque(lane));
+        if (ntile >= n_tiles) break;
+        tile = ntile;
+    }
+}
+
+template <int NT>
+hipError_t launch_resident(const UpdArgs &p, int cus, hipStream_t s)
+{
+    const size_t lds = static_cast<size_t>((p.d_in + 31) / 32) * w_slab_bytes(NT * 32) + kSWaves * kWaveBytes;
+    const int gy = (p.d_out + NT * 32 - 1) / (NT * 32);
+    const int64_t n_tiles = (p.n_rows + 31) / 32;
+    const int64_t slots = static_cast<int64_t>(cus) * (NT < 4 && 2 * (lds + 1024) <= 160 * 1024 ? 2 : 1);
+    const dim3 grid(static_cast<unsigned>(n_tiles < slots ? n_tiles : slots), static_cast<unsigned>(gy));
+    if (lds > 48 * 1024)                                     // beyond what a launch may take unasked
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_resident_kernel<NT>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    hipLaunchKernelGGL((update_split_resident_kernel<NT>), grid, dim3(kSThreads), lds, s, p);
+    return hipGetLastError();
+}
+
+template <int NT>
+hipError_t launch_slab(const UpdArgs &p, int cus, hipStream_t s)
+{
+    constexpr int lds = 2 * w_slab_bytes(NT * 32) + kSWaves * kWaveBytes;
+    const int gy = (p.d_out + NT * 32 - 1) / (NT * 32);
+    const int64_t n_tiles = (p.n_rows + 32 * kSWaves - 1) / (32 * kSWaves);
+    const dim3 grid(static_cast<unsigned>(n_tiles < cus ? n_tiles : cus), static_cast<unsigned>(gy));
+    if (lds > 48 * 1024)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_slab_kernel<NT>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    hipLaunchKernelGGL((update_split_slab_kernel<NT>), grid, dim3(kSThreads), lds, s, p, n_tiles);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, hipError_t *err)
+{
+    // a row shorter than a 16-byte vector, or 32-bit offsets inside W or a 32-row tile of A or out that could overflow
+    if (p.d_in < 4 || p.d_out > (1 << 20) || p.ld_a > (1 << 24) || p.ld_out > (1 << 24) || static_cast<int64_t>(p.d_in) * p.d_out > (1 << 29)) return false;
+    const int64_t n_slabs = (p.d_in + 31) / 32;
+    auto resident = [&](int nt) { return n_slabs * w_slab_bytes(nt * 32) + kSWaves * kWaveBytes <= kLdsMax; };
+    // As many columns per wavefront as there are (up to 256), so that A is read and split once.  Few rows: narrower
+    // column blocks side by side until the workgroups cover the chip (the rows are re-read out of the caches).
+    int nt = p.d_out > 128 ? 8 : p.d_out > 64 ? 4 : p.d_out > 32 ? 2 : 1;
+    auto groups = [&](int t) { return (resident(t) ? (p.n_rows + 31) / 32 : (p.n_rows + 255) / 256) * ((p.d_out + 32 * t - 1) / (32 * t)); };
+    while (nt > 1 && groups(nt) < cus) nt /= 2;
+    if (resident(nt)) *err = nt == 8 ? launch_resident<8>(p, cus, stream) : nt == 4 ? launch_resident<4>(p, cus, stream) : nt == 2 ? launch_resident<2>(p, cus, stream) : launch_resident<1>(p, cus, stream);
+    else *err = nt == 8 ? launch_slab<8>(p, cus, stream) : nt == 4 ? launch_slab<4>(p, cus, stream) : nt == 2 ? launch_slab<2>(p, cus, stream) : launch_slab<1>(p, cus, stream);
+    return true;
+}
+
+}  // namespace mgg

@@ -1,6 +1,6 @@
 // Dense Update for gfx950, whole-line variant (section 1: Update is a fully-connected layer;
-// section 7: X W with ReLU, GIN's MLP) for the shapes that are bound by HBM: a tall A, a weight
-// matrix small enough to stay in LDS.
+// section 7: X W with ReLU, GIN's MLP) for the shapes that are bound by HBM: a tall A, a bf16 weight
+// matrix small enough to stay in LDS (fp32 weights: update_split.hip).
 //
 // What the memory system rewards, measured with copy kernels of the same tile shape: every global
 // instruction should consume whole 128-byte lines (a tile copy with 2 lanes per row moves 2.7 TB/s,
@@ -31,9 +31,6 @@ using namespace upd;
 // cost registers or spills and are slower than these.
 #ifndef MGG_SD_B16      // bf16 A (16 registers a slab); fp32 A on the bf16 path takes half as many
 #define MGG_SD_B16 2
-#endif
-#ifndef MGG_SD_F32      // fp32 path (16 registers a slab)
-#define MGG_SD_F32 2
 #endif
 
 extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
@@ -235,90 +232,6 @@ void update_bf16_stream_kernel(const UpdArgs p)
     while (tile < n_tiles) do_tile();   // memory operations on entry and on its back edge
 }
 
-// ---- fp32 weights: v_mfma_f32_32x32x2_f32, K slabs of 32 ----------------------------------------
-// Slab: 128 bytes per row, 8 lanes per row, 8 rows per instruction; staged as fp32 [32][36].
-struct RawF { float4 v[4]; };
-
-__device__ __forceinline__ void load_slab_f32(const UpdArgs &p, int64_t t, int is, int lane, RawF &r)
-{
-    const int sub = lane / 8, chunk = lane % 8;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        int64_t row = t * 32 + j * 8 + sub;
-        row = row < p.n_rows ? row : p.n_rows - 1;
-        r.v[j] = *reinterpret_cast<const float4 *>(static_cast<const float *>(p.a) + row * p.ld_a + is * 32 + chunk * 4);
-    }
-}
-
-template <int NT, int NS, int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MGG_UPD_STREAM_WAVES(NT), MGG_UPD_STREAM_WAVES(NT))))
-void update_f32_stream_kernel(const UpdArgs p)
-{
-    constexpr int BK = 32, NC = NT * 32, LDA = BK + 4;
-    constexpr int W_BYTES = NS * BK * NC * 4;
-    constexpr int WAVE_BYTES = wave_lds_bytes<NT, false>(32 * LDA * 4);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i = lane & 31, h = lane >> 5;
-    float *w_lds = reinterpret_cast<float *>(lds_all);
-    float *abuf = reinterpret_cast<float *>(lds_all + W_BYTES + wave * WAVE_BYTES);
-    fill_w_f32<NC>(w_lds, static_cast<const float *>(p.w), 0, NS * BK, 0, p);
-    __syncthreads();
-
-    const int64_t n_tiles = (p.n_rows + 31) / 32, stride = static_cast<int64_t>(gridDim.x) * kWaves;
-    int64_t tile = static_cast<int64_t>(blockIdx.x) * kWaves + wave;
-    if (tile >= n_tiles) return;
-    int64_t itile = tile;
-    int is = 0;
-    RawF q[D];
-    auto issue = [&]() {
-        RawF r;
-        load_slab_f32(p, itile, is, lane, r);
-        if (++is == NS) { is = 0; itile += stride; }
-        return r;
-    };
-#pragma unroll
-    for (int d = 0; d < D; ++d) q[d] = issue();
-
-    auto do_tile = [&]() {
-        f32x16 acc[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            {
-                const int sub = lane / 8, chunk = lane % 8;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) *reinterpret_cast<float4 *>(abuf + (j * 8 + sub) * LDA + chunk * 4) = q[0].v[j];
-            }
-#pragma unroll
-            for (int d = 0; d + 1 < D; ++d) q[d] = q[d + 1];
-            q[D - 1] = issue();
-            wave_sync_lds();
-            // lane (i, h) takes k = 16h .. 16h + 15 of the slab, MFMA number c contracts {c, 16 + c}
-            float af[16];
-#pragma unroll
-            for (int c4 = 0; c4 < 4; ++c4) {
-                const float4 x = *reinterpret_cast<const float4 *>(abuf + i * LDA + 16 * h + 4 * c4);
-                af[4 * c4] = x.x; af[4 * c4 + 1] = x.y; af[4 * c4 + 2] = x.z; af[4 * c4 + 3] = x.w;
-            }
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                const float *wrow = w_lds + (s * BK + 16 * h + c) * NC + i;
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wrow[t * 32], af[c], acc[t], 0, 0, 0);
-            }
-            wave_sync_lds();
-        }
-        store_tile_lines<NT, false>(p, acc, abuf, tile * 32, lane);
-        tile += stride;
-    };
-    do_tile();
-    while (tile < n_tiles) do_tile();
-}
-
 // ---- two linears in one kernel (GIN's MLP, section 7) ------------------------------------------
 // out = act2(act1(A W1 + b1) W2 + b2) with bf16 weights, A the aggregation result (fp32 or bf16), a hidden
 // width of at most 128.  The hidden tile never leaves the registers: the accumulators of the first
@@ -489,21 +402,6 @@ hipError_t launch_bf16(const UpdArgs &p, bool a_bf16, int cus, hipStream_t s)
     return a_bf16 ? go(update_bf16_stream_kernel<NT, NS, true, false, MGG_SD_B16>, wb) : go(update_bf16_stream_kernel<NT, NS, false, false, MGG_SD_B16 / 2>, wb);
 }
 
-template <int NT, int NS>
-hipError_t launch_f32(const UpdArgs &p, int cus, hipStream_t s)
-{
-    constexpr int W_BYTES = NS * 32 * NT * 32 * 4;
-    const int wave_bytes = wave_lds_bytes<NT, false>(32 * 36 * 4);
-    const size_t lds = static_cast<size_t>(W_BYTES) + kWaves * static_cast<size_t>(wave_bytes);
-    int per_cu = static_cast<int>((160 * 1024) / (lds + 512));
-    const int cap = MGG_UPD_STREAM_WAVES(NT);
-    per_cu = per_cu < 1 ? 1 : (per_cu > cap ? cap : per_cu);
-    const int64_t want = ((p.n_rows + 31) / 32 + kWaves - 1) / kWaves;
-    const int blocks = static_cast<int>(want < static_cast<int64_t>(cus) * per_cu ? want : static_cast<int64_t>(cus) * per_cu);
-    hipLaunchKernelGGL((update_f32_stream_kernel<NT, NS, MGG_SD_F32>), dim3(blocks), dim3(kThreads), lds, s, p);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 bool launch_mlp_stream(int64_t n_rows, mgg_dtype_t a_dtype, const void *a, int64_t ld_a, int32_t d_in, const void *w1, const float *b1,
@@ -530,40 +428,23 @@ bool launch_mlp_stream(int64_t n_rows, mgg_dtype_t a_dtype, const void *a, int64
 
 bool launch_update_stream(const upd::UpdArgs &p, bool w_bf16, bool a_bf16, int cus, hipStream_t stream, hipError_t *err)
 {
-    // covered: rows of A that allow 16-byte loads, d_in a whole number of K slabs (1, 2 or 4 of 64 for
-    // bf16 weights; 1, 2, 4 or 8 of 32 for fp32 weights), 33..128 output columns
-    if (!p.a_vec_ok || p.d_out <= 32 || p.d_out > 128) return false;
+    // covered: bf16 weights, rows of A that allow 16-byte loads, d_in a whole number of K slabs (1, 2 or 4 of 64),
+    // 33..128 output columns
+    if (!w_bf16 || !p.a_vec_ok || p.d_out <= 32 || p.d_out > 128) return false;
     const int nt = p.d_out > 64 ? 4 : 2;
     *err = hipSuccess;
-    if (w_bf16) {
-        if (p.d_in % 64) return false;
-        const int ns = p.d_in / 64;
-        if (nt == 2) {
-            if (ns == 1) *err = launch_bf16<2, 1>(p, a_bf16, cus, stream);
-            else if (ns == 2) *err = launch_bf16<2, 2>(p, a_bf16, cus, stream);
-            else if (ns == 4) *err = launch_bf16<2, 4>(p, a_bf16, cus, stream);
-            else return false;
-        } else {
-            if (ns == 1) *err = launch_bf16<4, 1>(p, a_bf16, cus, stream);
-            else if (ns == 2) *err = launch_bf16<4, 2>(p, a_bf16, cus, stream);
-            else if (ns == 4) *err = launch_bf16<4, 4>(p, a_bf16, cus, stream);
-            else return false;
-        }
-        return true;
-    }
-    if (a_bf16 || p.d_in % 32) return false;
-    const int ns = p.d_in / 32;
+    if (p.d_in % 64) return false;
+    const int ns = p.d_in / 64;
     if (nt == 2) {
-        if (ns == 1) *err = launch_f32<2, 1>(p, cus, stream);
-        else if (ns == 2) *err = launch_f32<2, 2>(p, cus, stream);
-        else if (ns == 4) *err = launch_f32<2, 4>(p, cus, stream);
-        else if (ns == 8) *err = launch_f32<2, 8>(p, cus, stream);
+        if (ns == 1) *err = launch_bf16<2, 1>(p, a_bf16, cus, stream);
+        else if (ns == 2) *err = launch_bf16<2, 2>(p, a_bf16, cus, stream);
+        else if (ns == 4) *err = launch_bf16<2, 4>(p, a_bf16, cus, stream);
         else return false;
     } else {
-        if (ns == 1) *err = launch_f32<4, 1>(p, cus, stream);
-        else if (ns == 2) *err = launch_f32<4, 2>(p, cus, stream);
-        else if (ns == 4) *err = launch_f32<4, 4>(p, cus, stream);
-        else return false;          // 8 slabs of a 128-column matrix do not fit LDS next to the buffers
+        if (ns == 1) *err = launch_bf16<4, 1>(p, a_bf16, cus, stream);
+        else if (ns == 2) *err = launch_bf16<4, 2>(p, a_bf16, cus, stream);
+        else if (ns == 4) *err = launch_bf16<4, 4>(p, a_bf16, cus, stream);
+        else return false;
     }
     return true;
 }

@@ -1,0 +1,76 @@
+"""Update with fp32 weights on the bf16 matrix instruction: tile edges, ragged and unaligned operands, both kernel
+forms, and magnitudes the split into bf16 parts does not cover."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2209_06800_amd import binding
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def place(x, ld, shift):
+    """A copy of x with leading dimension ld whose first element lies `shift` elements past a 16-byte boundary."""
+    n, d = x.shape
+    buf = torch.full((n * ld + shift,), float("nan"), device=DEV)
+    v = buf[shift:].as_strided((n, d), (ld, 1))
+    v.copy_(x)
+    return v
+
+
+def reference(a, w, b):
+    """float64 result, and a forward-error bound: d_in products and additions, each within 2^-24 of its partial sum, the
+    sums bounded by |a| @ |w| -- the bound of a plain fp32 dot product, with a factor 2 for the bias and the last rounding."""
+    a, w = a.double().cpu(), w.double().cpu()
+    b = b.double().cpu()
+    return a @ w + b, 2.0 * (a.shape[1] + 2) * 2.0 ** -24 * (a.abs() @ w.abs() + b.abs())
+
+
+@pytest.mark.parametrize("n,d_in,d_out,ld,shift", [
+    (1, 4, 1, 4, 0), (31, 5, 3, 5, 1), (33, 16, 16, 16, 0), (64, 31, 33, 31, 3), (257, 33, 32, 33, 1), (1000, 75, 47, 75, 2),
+    (4097, 100, 256, 100, 0), (300, 256, 65, 256, 0), (2049, 602, 256, 608, 0), (513, 602, 255, 602, 1), (70000, 64, 64, 64, 0),
+    (70001, 100, 200, 103, 1), (70003, 257, 129, 257, 0), (9000, 320, 64, 320, 0), (9000, 321, 64, 321, 0), (66000, 161, 128, 161, 0),
+    (200, 1000, 300, 1000, 0), (70000, 40, 256, 40, 0)])
+def test_update_split_shapes(n, d_in, d_out, ld, shift):
+    g = torch.Generator(device=DEV).manual_seed(n + 7 * d_in + d_out)
+    a = place(torch.randn(n, d_in, device=DEV, generator=g), ld, shift)
+    w = place(torch.randn(d_in, d_out, device=DEV, generator=g) * 0.1, d_out, shift)
+    b = torch.randn(d_out, device=DEV, generator=g)
+    ref, bound = reference(a, w, b)
+    for out_dtype in (torch.float32, torch.bfloat16):
+        buf = torch.full((n + 1, d_out + 3), float("nan"), dtype=out_dtype, device=DEV)
+        binding.mgg_update(a, w, b, "none", out=buf[:n, :d_out])
+        assert torch.isnan(buf[:, d_out:]).all() and torch.isnan(buf[n:]).all()       # nothing past the edges
+        err = (buf[:n, :d_out].double().cpu() - ref).abs()
+        extra = 0 if out_dtype == torch.float32 else 2.0 ** -8 * ref.abs()             # half a unit in the last place of bf16
+        assert (err <= bound + extra).all(), (err - bound).max()
+
+
+@pytest.mark.parametrize("d_in,d_out", [(64, 64), (602, 256)])
+@pytest.mark.parametrize("where", ["a", "w"])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38, 1e-30, 1e-37, 0.0])
+def test_update_split_magnitudes(d_in, d_out, where, value):
+    """One row of A, or one column of W, of extreme magnitude: infinities stay infinities of the right sign, NaN stays in
+    its row or column, tiny and huge operands keep fp32 accuracy."""
+    n = 333
+    g = torch.Generator(device=DEV).manual_seed(d_in)
+    a = torch.rand(n, d_in, device=DEV, generator=g) + 0.5
+    w = torch.rand(d_in, d_out, device=DEV, generator=g) + 0.5
+    if where == "a":
+        if abs(value) < 1:
+            a[40] *= value
+        else:
+            a[40, 3] = value
+    elif abs(value) < 1:
+        w[:, 5] *= value
+    else:
+        w[3, 5] = value
+    if value == 3.4e38:                        # keeps the products inside fp32
+        a, w = (a, w * 0.25) if where == "a" else (a * 0.25, w)
+    out = binding.mgg_update(a, w, None, "none").double().cpu()
+    ref, bound = reference(a, w, torch.zeros(d_out, device=DEV))
+    fin = torch.isfinite(ref)
+    assert torch.equal(torch.isnan(ref), torch.isnan(out))
+    assert torch.equal(ref[torch.isinf(ref)], out[torch.isinf(ref)])
+    assert ((out - ref).abs()[fin] <= bound[fin] + d_in * 2.0 ** -126).all()          # (results below the normal range may be flushed)
