@@ -425,17 +425,18 @@ mgg_status_t launch_row_softmax(int64_t n_rows, int32_t d, mgg_dtype_t dtype, vo
 
 static mgg_status_t launch_update_gemm(int64_t n_rows, mgg_dtype_t a_dtype, const void *a, int64_t ld_a, int32_t d_in,
                                        mgg_dtype_t w_dtype, const void *w, const float *bias, int32_t d_out, mgg_act_t act,
-                                       mgg_dtype_t out_dtype, void *out, int64_t ld_out, hipStream_t stream);
+                                       mgg_dtype_t out_dtype, void *out, int64_t ld_out, hipStream_t stream, bool *softmax);
 
 mgg_status_t launch_update(int64_t n_rows, mgg_dtype_t a_dtype, const void *a, int64_t ld_a, int32_t d_in,
                            mgg_dtype_t w_dtype, const void *w, const float *bias, int32_t d_out, mgg_act_t act,
                            mgg_dtype_t out_dtype, void *out, int64_t ld_out, hipStream_t stream)
 {
-    // softmax couples the columns of a row: the product is written first, the rows are normalised in place
-    const bool softmax = act == MGG_ACT_SOFTMAX;
+    // softmax couples the columns of a row: the product is written first and the rows are normalised in place, unless the
+    // product's kernel holds whole rows and has done it
+    bool softmax = act == MGG_ACT_SOFTMAX;
     if (softmax && d_out > 8 * kWave) return fail(MGG_ERR_UNSUPPORTED, "softmax over %d columns (at most %d)", d_out, 8 * kWave);
     mgg_status_t s = launch_update_gemm(n_rows, a_dtype, a, ld_a, d_in, w_dtype, w, bias, d_out, softmax ? MGG_ACT_NONE : act,
-                                        out_dtype, out, ld_out, stream);
+                                        out_dtype, out, ld_out, stream, &softmax);
     if (s != MGG_OK || !softmax) return s;
     return launch_row_softmax(n_rows, d_out, out_dtype, out, ld_out, stream);
 }
@@ -465,7 +466,7 @@ mgg_status_t launch_update_mlp(int64_t n_rows, mgg_dtype_t a_dtype, const void *
 
 static mgg_status_t launch_update_gemm(int64_t n_rows, mgg_dtype_t a_dtype, const void *a, int64_t ld_a, int32_t d_in,
                                        mgg_dtype_t w_dtype, const void *w, const float *bias, int32_t d_out, mgg_act_t act,
-                                       mgg_dtype_t out_dtype, void *out, int64_t ld_out, hipStream_t stream)
+                                       mgg_dtype_t out_dtype, void *out, int64_t ld_out, hipStream_t stream, bool *softmax)
 {
     if (n_rows == 0) return MGG_OK;
     const bool w_bf16 = w_dtype == MGG_BF16, a_bf16 = a_dtype == MGG_BF16;
@@ -489,7 +490,7 @@ static mgg_status_t launch_update_gemm(int64_t n_rows, mgg_dtype_t a_dtype, cons
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (!w_bf16) {
         hipError_t e = hipSuccess;
-        if (launch_update_split(p, cus, stream, &e)) {
+        if (launch_update_split(p, cus, stream, softmax, &e)) {
             if (e != hipSuccess) return hip_fail(e, "update kernel launch");
             return MGG_OK;
         }

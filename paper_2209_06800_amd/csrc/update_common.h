@@ -209,8 +209,8 @@ __device__ __forceinline__ void fill_w_bf16_t(uint16_t *lds, int ldw, const uint
 bool launch_update_stream(const upd::UpdArgs &p, bool w_bf16, bool a_bf16, int cus, hipStream_t stream, hipError_t *err);
 
 // fp32 weights on the bf16 matrix instruction (update_split.hip); returns false when the shape is not
-// covered (d_in < 4) and nothing was launched.
-bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, hipError_t *err);
+// covered (d_in < 4) and nothing was launched.  *softmax: a row softmax is wanted; cleared if the kernel does it.
+bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, bool *softmax, hipError_t *err);
 
 // Two linears with bf16 weights in one kernel, hidden tile kept in registers (update_stream.hip);
 // returns false when the shape is not covered and nothing was launched.

@@ -265,7 +265,8 @@ __device__ __forceinline__ void first_a(RawA &q, int lane, float *abuf, SlabA &s
 
 // acc holds the transposed 32x32 tiles (register r of lane (m, h): row m, column 8*(r/4) + 4*h + r%4); each goes
 // through the wavefront's LDS buffer and leaves with 8 lanes per row, a whole line per row where rows are aligned.
-template <int NT>
+// PLAIN: as it is, without bias and ReLU.
+template <int NT, bool PLAIN>
 __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc)[NT], float *cbuf, int64_t m0, int n0, int lane)
 {
     const int m = lane & 31, h = lane >> 5, c = (lane & 7) * 4;
@@ -281,7 +282,7 @@ __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc
         wave_sync_lds();
         const int col = n0 + t * 32 + c;
         float b[4] = {0.f, 0.f, 0.f, 0.f};
-        if (p.bias) {
+        if (!PLAIN && p.bias) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (col + e < p.d_out) b[e] = p.bias[col + e];
@@ -291,7 +292,7 @@ __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc
             const int r = j * 8 + (lane >> 3);
             const float4 x = *reinterpret_cast<const float4 *>(cbuf + r * kLda + c);
             float v[4] = {x.x + b[0], x.y + b[1], x.z + b[2], x.w + b[3]};
-            if (p.relu) {
+            if (!PLAIN && p.relu) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
             }
@@ -322,8 +323,47 @@ __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc
     }
 }
 
-// The tile once more with the fp32 instruction, operands straight from global memory (any magnitude), 32 columns at a
+// Row softmax on the accumulators (bias first), for outputs whose whole row one wavefront holds: row m lies in lanes m and
+// m + 32, so maximum and sum need one exchange.  Saves the pass that would read and write every row again
+// (row_softmax_kernel: 7 us of a 65 us two-layer GCN on 30 k nodes).
+template <int NT>
+__device__ __forceinline__ void softmax_rows(const UpdArgs &p, f32x16 (&acc)[NT], int lane)
+{
+    const int h = lane >> 5;
+    float m = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int col = t * 32 + 8 * (r / 4) + 4 * h + r % 4;
+            if (col < p.d_out) {
+                if (p.bias) acc[t][r] += p.bias[col];
+            } else {
+                acc[t][r] = -INFINITY;
+            }
+            m = fmaxf(m, acc[t][r]);
+        }
+    m = fmaxf(m, __shfl_xor(m, 32));
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int col = t * 32 + 8 * (r / 4) + 4 * h + r % 4;
+            acc[t][r] = col < p.d_out ? expf(acc[t][r] - m) : 0.f;
+            sum += acc[t][r];
+        }
+    sum += __shfl_xor(sum, 32);
+    const float inv = 1.f / sum;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] *= inv;
+}
+
+// The tile once more with the fp32 instruction, operands straight from global memory (any magnitude), NT*32 columns at a
 // time over what store_lines has written (the same lanes write the same places, so the order is theirs).
+template <int NT, bool SOFTMAX>
 __device__ __forceinline__ void exact_tile(const UpdArgs &p, float *cbuf, int64_t m0, int n0, int n_end, int lane)
 {
     const int i = lane & 31, h = lane >> 5;
@@ -332,19 +372,27 @@ __device__ __forceinline__ void exact_tile(const UpdArgs &p, float *cbuf, int64_
     const char *A = reinterpret_cast<const char *>(static_cast<const float *>(p.a) + m0 * p.ld_a), *W = static_cast<const char *>(p.w);
     const uint32_t aoff = (static_cast<uint32_t>(min(i, rows - 1)) * static_cast<uint32_t>(p.ld_a) + static_cast<uint32_t>(h)) * 4u;
 #pragma unroll 1
-    for (; n0 < n_end && n0 < p.d_out; n0 += 32) {
-        f32x16 acc[1];
+    for (; n0 < n_end && n0 < p.d_out; n0 += NT * 32) {
+        f32x16 acc[NT];
+        uint32_t woff[NT];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
-        const uint32_t woff = (static_cast<uint32_t>(h) * static_cast<uint32_t>(p.d_out) + static_cast<uint32_t>(min(n0 + i, p.d_out - 1))) * 4u;
+        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+            woff[t] = (static_cast<uint32_t>(h) * static_cast<uint32_t>(p.d_out) + static_cast<uint32_t>(min(n0 + t * 32 + i, p.d_out - 1))) * 4u;
+        }
 #pragma unroll 1
         for (int k0 = 0; k0 < p.d_in; k0 += 2) {
             const bool in = k0 + h < p.d_in;
             const float af = in ? *reinterpret_cast<const float *>(A + static_cast<int64_t>(k0) * 4 + aoff) : 0.f;
-            const float wf = in ? *reinterpret_cast<const float *>(W + static_cast<int64_t>(k0) * p.d_out * 4 + woff) : 0.f;
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf, af, acc[0], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const float wf = in ? *reinterpret_cast<const float *>(W + static_cast<int64_t>(k0) * p.d_out * 4 + woff[t]) : 0.f;
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf, af, acc[t], 0, 0, 0);
+            }
         }
-        store_lines<1>(p, acc, cbuf, m0, n0, lane);
+        if constexpr (SOFTMAX) softmax_rows<NT>(p, acc, lane);
+        store_lines<NT, SOFTMAX>(p, acc, cbuf, m0, n0, lane);
     }
 }
 
@@ -373,7 +421,7 @@ __device__ __forceinline__ int opaque(int lane)
 // wavefronts per SIMD the registers are cut for: 2 where the accumulators alone take 128, else two workgroups per CU
 #define MGG_SPLIT_WAVES(NT) ((NT) >= 4 ? 2 : 4)
 
-template <int NT>
+template <int NT, bool SOFTMAX>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(MGG_SPLIT_WAVES(NT), MGG_SPLIT_WAVES(NT))))
 void update_split_resident_kernel(const UpdArgs p)
 {
@@ -441,8 +489,9 @@ void update_split_resident_kernel(const UpdArgs p)
         } while (++s < n_slabs);
         amax = fmaxf(amax, __shfl_xor(amax, 32));
         const bool again = bad_w || __ballot(out_of_range(amax));
-        store_lines<NT>(opaque(p), acc, abuf, tile * 32, n0, opaque(lane));
-        if (again) exact_tile(opaque(p), abuf, tile * 32, n0, n0 + NC, opaque(lane));
+        if constexpr (SOFTMAX) softmax_rows<NT>(opaque(p), acc, opaque(lane));
+        store_lines<NT, SOFTMAX>(opaque(p), acc, abuf, tile * 32, n0, opaque(lane));
+        if (again) exact_tile<SOFTMAX ? NT : 1, SOFTMAX>(opaque(p), abuf, tile * 32, n0, n0 + NC, opaque(lane));
         tile += stride;
     } while (tile < n_tiles);
 }
@@ -519,14 +568,14 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
         } while (++ks < n_slabs);
         amax = fmaxf(amax, __shfl_xor(amax, 32));
         const bool again = columns_out_of_range<NC>(colmax, lane) || __ballot(out_of_range(amax));
-        store_lines<NT>(opaque(p), acc, abuf, first_row(tile), n0, opaque(lane));
-        if (again) exact_tile(opaque(p), abuf, first_row(tile), n0, n0 + NC, opaque(lane));
+        store_lines<NT, false>(opaque(p), acc, abuf, first_row(tile), n0, opaque(lane));
+        if (again) exact_tile<1, false>(opaque(p), abuf, first_row(tile), n0, n0 + NC, opaque(lane));
         if (ntile >= n_tiles) break;
         tile = ntile;
     }
 }
 
-template <int NT>
+template <int NT, bool SOFTMAX>
 hipError_t launch_resident(const UpdArgs &p, int cus, hipStream_t s)
 {
     const size_t lds = static_cast<size_t>((p.d_in + 31) / 32) * w_slab_bytes(NT * 32) + kSWaves * kWaveBytes;
@@ -535,8 +584,8 @@ hipError_t launch_resident(const UpdArgs &p, int cus, hipStream_t s)
     const int64_t slots = static_cast<int64_t>(cus) * (NT < 4 && 2 * (lds + 1024) <= 160 * 1024 ? 2 : 1);
     const dim3 grid(static_cast<unsigned>(n_tiles < slots ? n_tiles : slots), static_cast<unsigned>(gy));
     if (lds > 48 * 1024)                                     // beyond what a launch may take unasked
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_resident_kernel<NT>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    hipLaunchKernelGGL((update_split_resident_kernel<NT>), grid, dim3(kSThreads), lds, s, p);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_resident_kernel<NT, SOFTMAX>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    hipLaunchKernelGGL((update_split_resident_kernel<NT, SOFTMAX>), grid, dim3(kSThreads), lds, s, p);
     return hipGetLastError();
 }
 
@@ -555,7 +604,7 @@ hipError_t launch_slab(const UpdArgs &p, int cus, hipStream_t s)
 
 }  // namespace
 
-bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, hipError_t *err)
+bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, bool *softmax, hipError_t *err)
 {
     // a row shorter than a 16-byte vector, or 32-bit offsets inside W or a 32-row tile of A or out that could overflow
     if (p.d_in < 4 || p.d_out > (1 << 20) || p.ld_a > (1 << 24) || p.ld_out > (1 << 24) || static_cast<int64_t>(p.d_in) * p.d_out > (1 << 29)) return false;
@@ -566,7 +615,15 @@ bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, hip
     int nt = p.d_out > 128 ? 8 : p.d_out > 64 ? 4 : p.d_out > 32 ? 2 : 1;
     auto groups = [&](int t) { return (resident(t) ? (p.n_rows + 31) / 32 : (p.n_rows + 255) / 256) * ((p.d_out + 32 * t - 1) / (32 * t)); };
     while (nt > 1 && groups(nt) < cus) nt /= 2;
-    if (resident(nt)) *err = nt == 8 ? launch_resident<8>(p, cus, stream) : nt == 4 ? launch_resident<4>(p, cus, stream) : nt == 2 ? launch_resident<2>(p, cus, stream) : launch_resident<1>(p, cus, stream);
+    // softmax in the epilogue where a wavefront holds whole rows in few registers; elsewhere it stays the caller's second pass
+    const bool fused = *softmax && nt <= 2 && p.d_out <= nt * 32 && resident(nt);
+    if (fused) {
+        *err = nt == 2 ? launch_resident<2, true>(p, cus, stream) : launch_resident<1, true>(p, cus, stream);
+        *softmax = false;
+    } else if (resident(nt)) {
+        *err = nt == 8 ? launch_resident<8, false>(p, cus, stream) : nt == 4 ? launch_resident<4, false>(p, cus, stream)
+             : nt == 2 ? launch_resident<2, false>(p, cus, stream) : launch_resident<1, false>(p, cus, stream);
+    }
     else *err = nt == 8 ? launch_slab<8>(p, cus, stream) : nt == 4 ? launch_slab<4>(p, cus, stream) : nt == 2 ? launch_slab<2>(p, cus, stream) : launch_slab<1>(p, cus, stream);
     return true;
 }

@@ -74,3 +74,24 @@ def test_update_split_magnitudes(d_in, d_out, where, value):
     assert torch.equal(torch.isnan(ref), torch.isnan(out))
     assert torch.equal(ref[torch.isinf(ref)], out[torch.isinf(ref)])
     assert ((out - ref).abs()[fin] <= bound[fin] + d_in * 2.0 ** -126).all()          # (results below the normal range may be flushed)
+
+
+@pytest.mark.parametrize("n,d_in,d_out,tiny", [(1, 4, 1, False), (9001, 16, 7, False), (9001, 100, 32, True), (20011, 64, 33, False),
+                                               (20011, 64, 64, True), (20011, 64, 65, False), (20011, 352, 64, False)])
+def test_update_split_softmax(n, d_in, d_out, tiny):
+    """Softmax on the accumulators (up to 64 columns, W resident), in the tiles that are computed again too, and around the
+    sizes where it stays a second pass.  A softmax moves by at most half the change of its logits; 1e-6 for expf, the sum
+    and the division."""
+    g = torch.Generator(device=DEV).manual_seed(d_out)
+    a = torch.randn(n, d_in, device=DEV, generator=g)
+    w = torch.randn(d_in, d_out, device=DEV, generator=g) * 0.3
+    b = torch.randn(d_out, device=DEV, generator=g)
+    if tiny:
+        a[n // 2] *= 1e-30
+    logits, bound = reference(a, w, b)
+    ref = torch.softmax(logits, 1)
+    buf = torch.full((n + 1, d_out + 3), float("nan"), device=DEV)
+    binding.mgg_update(a, w, b, "softmax", out=buf[:n, :d_out])
+    assert torch.isnan(buf[:, d_out:]).all() and torch.isnan(buf[n:]).all()
+    err = (buf[:n, :d_out].double().cpu() - ref).abs()
+    assert (err <= 1e-6 + bound.amax(1, keepdim=True) * ref).all(), err.max()
