@@ -100,7 +100,8 @@ def lib():
                               "(there is no fallback path)")
         # torch first: it ships its own HIP runtime under the same soname, and the stream
         # handles and device pointers handed to the library must belong to that runtime
-        import torch  # noqa: F401
+        import torch
+        _DTYPE_CODE.update({torch.float32: F32, torch.bfloat16: BF16})
         L = C.CDLL(LIB_PATH)
         L.mgg_last_error.restype = C.c_char_p
         L.mgg_version.restype = C.c_char_p
@@ -174,13 +175,19 @@ def _np_ptr(a: Optional[np.ndarray]):
 
 
 # ------------------------------------------------------------------------------- torch glue
+# Marshalling is what the smallest calls spend their time on (a layer of a 4 k-node graph: two launches of a few
+# microseconds each), so these avoid ctypes objects and torch's stream wrapper where a plain int does.
+_DTYPE_CODE = {}                # torch dtype -> mgg_dtype_t, filled when the library is loaded
+
+
 def _torch_dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported tensor dtype {t.dtype}")
+    code = _DTYPE_CODE.get(t.dtype)
+    if code is None:
+        lib()
+        code = _DTYPE_CODE.get(t.dtype)
+        if code is None:
+            raise TypeError(f"unsupported tensor dtype {t.dtype}")
+    return code
 
 
 def _dev_ptr(t):
@@ -188,19 +195,21 @@ def _dev_ptr(t):
         return None
     if not t.is_cuda:
         raise TypeError("device tensor expected")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _ld(t) -> int:
     if t.dim() != 2 or t.stride(1) != 1:
         raise ValueError("row-major 2-D tensor with unit column stride expected")
-    return int(t.stride(0)) if t.shape[0] > 1 else max(int(t.stride(0)), int(t.shape[1]))
+    ld = t.stride(0)
+    return ld if t.shape[0] > 1 else max(ld, t.shape[1])
 
 
 def _stream(stream=None):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is None:
+        import torch
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())     # current_stream().cuda_stream
+    return stream.cuda_stream
 
 
 # ------------------------------------------------------------------------------- partition
@@ -212,6 +221,8 @@ class Partition:
         self.info = PartitionInfo()
         _check(lib().mgg_partition_info(self._h, C.byref(self.info)))
         self._reserved = int(self.info.reserved_dim)
+        # what every call checks its tensors against, as plain values
+        self._n_own, self._n_halo, self._n_local, self._bags = self.info.n_own, self.info.num_halo, self.info.n_local_rows, bool(self.info.is_bags)
 
     @property
     def handle(self):
@@ -336,32 +347,33 @@ def mgg_get_option(key: str) -> int:
 def _check_tables(part: Partition, x_local, x_halo, out, dim: int, bags: bool = False):
     """The C ABI takes bare pointers and one leading dimension for both tables; what it cannot see is
     checked here: both tables of one dtype, device and row stride, and every buffer long enough."""
-    i = part.info
-    if bool(i.is_bags) != bags:
+    if part._bags != bags:
         return                      # the wrong kind of partition for this call: the library says so
-    n_local = int(i.n_local_rows) if bags else int(i.n_own)
+    n_own, n_halo = part._n_own, part._n_halo
+    n_local = part._n_local if bags else n_own
     ref = x_local if x_local is not None else x_halo
     if ref is None:
-        if n_local or int(i.num_halo):
+        if n_local or n_halo:
             raise ValueError("no embedding table given")
         return
     if x_local is not None and x_halo is not None:
         if x_halo.dtype != x_local.dtype or x_halo.device != x_local.device:
             raise ValueError(f"x_halo is {x_halo.dtype} on {x_halo.device}, x_local is {x_local.dtype} on {x_local.device}")
-        if int(x_halo.shape[0]) > 0 and int(x_local.shape[0]) > 0 and _ld(x_halo) != _ld(x_local):
+        if x_halo.shape[0] > 0 and x_local.shape[0] > 0 and _ld(x_halo) != _ld(x_local):
             raise ValueError(f"x_halo has row stride {_ld(x_halo)}, x_local {_ld(x_local)}: the library takes one ld_x for both tables")
-    for name, t, rows in (("x_local", x_local, n_local), ("x_halo", x_halo, int(i.num_halo))):
+    for name, t, rows in (("x_local", x_local, n_local), ("x_halo", x_halo, n_halo)):
         if t is None:
             continue
-        if t.dim() != 2 or int(t.shape[1]) < dim:
-            raise ValueError(f"{name} must be 2-D with at least {dim} columns, got {tuple(t.shape)}")
-        if int(t.shape[0]) < rows:
-            raise ValueError(f"{name} has {int(t.shape[0])} rows, the partition needs {rows}")
-    if x_halo is None and int(i.num_halo) > 0 and not bags:
-        raise ValueError(f"x_halo is missing: the partition has {int(i.num_halo)} halo rows")
+        shape = t.shape
+        if len(shape) != 2 or shape[1] < dim:
+            raise ValueError(f"{name} must be 2-D with at least {dim} columns, got {tuple(shape)}")
+        if shape[0] < rows:
+            raise ValueError(f"{name} has {shape[0]} rows, the partition needs {rows}")
+    if x_halo is None and n_halo > 0 and not bags:
+        raise ValueError(f"x_halo is missing: the partition has {n_halo} halo rows")
     if out is not None:
-        if out.dim() != 2 or int(out.shape[0]) < int(i.n_own) or int(out.shape[1]) < dim:
-            raise ValueError(f"out must hold at least {int(i.n_own)} x {dim}, got {tuple(out.shape)}")
+        if out.dim() != 2 or out.shape[0] < n_own or out.shape[1] < dim:
+            raise ValueError(f"out must hold at least {n_own} x {dim}, got {tuple(out.shape)}")
         if out.device != ref.device:
             raise ValueError("out lives on another device than the tables")
 
@@ -462,14 +474,16 @@ def _layer_desc(mode, eps, weights, biases, acts, order="agg_first"):
     d.mode = _MODE[mode]
     d.eps = eps
     d.n_linear = len(weights)
-    d.dims[0] = int(weights[0].shape[0])
+    dims, w_ptr, b_ptr, act = d.dims, d.w, d.bias, d.act
+    dims[0] = weights[0].shape[0]
     for i, w in enumerate(weights):
         if not w.is_contiguous():
             raise ValueError("weights must be contiguous")
-        d.dims[i + 1] = int(w.shape[1])
-        d.w[i] = w.data_ptr()
-        d.bias[i] = None if biases is None or biases[i] is None else biases[i].data_ptr()
-        d.act[i] = _ACT[acts[i]]
+        dims[i + 1] = w.shape[1]
+        w_ptr[i] = w.data_ptr()
+        if biases is not None and biases[i] is not None:
+            b_ptr[i] = biases[i].data_ptr()
+        act[i] = _ACT[acts[i]]
     d.w_dtype = _torch_dtype_code(weights[0])
     return d
 
@@ -488,15 +502,14 @@ def mgg_layer_forward(part: Partition, mode: str, x_local, x_halo, weights, acts
     if len(weights) not in (1, 2):
         raise MggError(ERR_INVALID_ARG, "a layer has 1 or 2 linears")
     d = _layer_desc(mode, eps, weights, biases, acts, order)
-    need = int(lib().mgg_layer_workspace_bytes(part.handle, C.byref(d)))
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x_local.device)
+    if workspace is None:       # (a workspace that was passed is measured by the library)
+        workspace = torch.empty(int(lib().mgg_layer_workspace_bytes(part.handle, C.byref(d))), dtype=torch.uint8, device=x_local.device)
+    d_out = weights[-1].shape[1]
     if out is None:
-        out = torch.empty((int(part.info.n_own), int(weights[-1].shape[1])), dtype=out_dtype or torch.float32,
-                          device=x_local.device)
-    _check_tables(part, x_local, x_halo, None, int(weights[0].shape[0]))
-    if int(out.shape[0]) < int(part.info.n_own) or int(out.shape[1]) < int(weights[-1].shape[1]):
-        raise ValueError(f"out must hold at least {int(part.info.n_own)} x {int(weights[-1].shape[1])}, got {tuple(out.shape)}")
+        out = torch.empty((part._n_own, d_out), dtype=out_dtype or torch.float32, device=x_local.device)
+    _check_tables(part, x_local, x_halo, None, weights[0].shape[0])
+    if out.shape[0] < part._n_own or out.shape[1] < d_out:
+        raise ValueError(f"out must hold at least {part._n_own} x {d_out}, got {tuple(out.shape)}")
     _check(lib().mgg_layer_forward(part.handle, C.byref(d), _torch_dtype_code(x_local), _dev_ptr(x_local),
                                    _dev_ptr(x_halo), _ld(x_local), _dev_ptr(workspace), workspace.numel(),
                                    _torch_dtype_code(out), _dev_ptr(out), _ld(out), _stream(stream)))
