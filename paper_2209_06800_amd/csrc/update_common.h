@@ -37,6 +37,24 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
     return u >> 16;
 }
 
+// two values to bf16 bits, nearest even, in one instruction (the integer form above takes nine for a pair)
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const f32x2 f = {lo, hi};
+    union { bf16x2 b; uint32_t u; } r;
+    r.b = __builtin_convertvector(f, bf16x2);
+    return r.u;
+}
+
+// bias -> LDS, zeros where there is none, so that an epilogue reads it without a test per column
+template <int NC>
+__device__ __forceinline__ void stage_bias(float *lds, const float *bias, int n)
+{
+    for (int c = threadIdx.x; c < NC; c += blockDim.x) lds[c] = bias && c < n ? bias[c] : 0.f;
+}
+
 // Epilogue shared by both paths.  The kernels feed the W fragment as the first MFMA operand and
 // the A fragment as the second, so the 32x32 accumulator holds the TRANSPOSED tile: register r
 // of lane (m = lane % 32, h = lane / 32) is output row m, column 8*(r/4) + 4*h + r%4.  A lane

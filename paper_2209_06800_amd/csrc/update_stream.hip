@@ -46,9 +46,10 @@ __device__ __forceinline__ void wave_sync_lds()
 
 // Output tile: acc holds the transposed 32x32 tiles (register r of lane (m, h): row m, column
 // 8*(r/4) + 4*h + r%4).  Blocks of CW columns are written to the wavefront's LDS buffer as
-// fp32 [32][CW + 4] and read back with CW/4 (fp32 out) or CW/8 (bf16 out) lanes per row.
+// fp32 [32][CW + 4] and read back with CW/4 (fp32 out) or CW/8 (bf16 out) lanes per row, where bias (from LDS,
+// padded with zeros) and ReLU are applied.
 template <int NT, bool OUT_BF16>
-__device__ __forceinline__ void store_tile_lines(const UpdArgs &p, const f32x16 (&acc)[NT], float *cbuf, int64_t m0, int lane)
+__device__ __forceinline__ void store_tile_lines(const UpdArgs &p, const f32x16 (&acc)[NT], const float *bias, float *cbuf, int64_t m0, int lane)
 {
     constexpr int TPB = OUT_BF16 && NT >= 2 ? 2 : 1;      // 32-column tiles per block
     constexpr int CW = 32 * TPB, LDC = CW + 4;
@@ -63,14 +64,7 @@ __device__ __forceinline__ void store_tile_lines(const UpdArgs &p, const f32x16 
             const int t = b * TPB + tt;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int col = t * 32 + 8 * q + 4 * h;
-                float v[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    v[e] = acc[t][4 * q + e] + ((p.bias && col + e < p.d_out) ? p.bias[col + e] : 0.f);
-                    if (p.relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
-                }
-                *reinterpret_cast<float4 *>(cbuf + m * LDC + tt * 32 + 8 * q + 4 * h) = make_float4(v[0], v[1], v[2], v[3]);
+                *reinterpret_cast<float4 *>(cbuf + m * LDC + tt * 32 + 8 * q + 4 * h) = make_float4(acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]);
             }
         }
         wave_sync_lds();
@@ -83,7 +77,12 @@ __device__ __forceinline__ void store_tile_lines(const UpdArgs &p, const f32x16 
 #pragma unroll
             for (int e4 = 0; e4 < EPL / 4; ++e4) {
                 const float4 x = *reinterpret_cast<const float4 *>(cbuf + r * LDC + c + 4 * e4);
-                v[4 * e4] = x.x; v[4 * e4 + 1] = x.y; v[4 * e4 + 2] = x.z; v[4 * e4 + 3] = x.w;
+                const float4 y = *reinterpret_cast<const float4 *>(bias + col + 4 * e4);
+                v[4 * e4] = x.x + y.x; v[4 * e4 + 1] = x.y + y.y; v[4 * e4 + 2] = x.z + y.z; v[4 * e4 + 3] = x.w + y.w;
+            }
+            if (p.relu) {
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
             }
             if (row < p.n_rows && col < p.d_out) {
                 const bool full = p.out_vec_ok && col + EPL <= p.d_out;
@@ -91,10 +90,10 @@ __device__ __forceinline__ void store_tile_lines(const UpdArgs &p, const f32x16 
                     uint16_t *o = static_cast<uint16_t *>(p.out) + row * p.ld_out + col;
                     if (full && p.ld_out % 8 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 15u) == 0) {
                         uint4 pk;
-                        pk.x = f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16);
-                        pk.y = f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16);
-                        pk.z = f32_to_bf16_bits(v[4]) | (f32_to_bf16_bits(v[5]) << 16);
-                        pk.w = f32_to_bf16_bits(v[6]) | (f32_to_bf16_bits(v[7]) << 16);
+                        pk.x = pack_bf16(v[0], v[1]);
+                        pk.y = pack_bf16(v[2], v[3]);
+                        pk.z = pack_bf16(v[4], v[5]);
+                        pk.w = pack_bf16(v[6], v[7]);
                         *reinterpret_cast<uint4 *>(o) = pk;
                     } else {
 #pragma unroll
@@ -162,8 +161,8 @@ __device__ __forceinline__ void stage_slab(const Raw<A_BF16> &r, uint16_t *abuf,
             *reinterpret_cast<uint4 *>(abuf + row * LDA + chunk * 8) = r.v[j];
         } else {
             uint2 pk;
-            pk.x = f32_to_bf16_bits(__uint_as_float(r.v[j].x)) | (f32_to_bf16_bits(__uint_as_float(r.v[j].y)) << 16);
-            pk.y = f32_to_bf16_bits(__uint_as_float(r.v[j].z)) | (f32_to_bf16_bits(__uint_as_float(r.v[j].w)) << 16);
+            pk.x = pack_bf16(__uint_as_float(r.v[j].x), __uint_as_float(r.v[j].y));
+            pk.y = pack_bf16(__uint_as_float(r.v[j].z), __uint_as_float(r.v[j].w));
             *reinterpret_cast<uint2 *>(abuf + row * LDA + chunk * 4) = pk;
         }
     }
@@ -180,6 +179,8 @@ void update_bf16_stream_kernel(const UpdArgs p)
     const int i = lane & 31, h = lane >> 5;
     uint16_t *w_lds = reinterpret_cast<uint16_t *>(lds_all);
     uint16_t *abuf = reinterpret_cast<uint16_t *>(lds_all + W_BYTES + wave * WAVE_BYTES);
+    __shared__ __attribute__((aligned(16))) float bias[NC];
+    stage_bias<NC>(bias, p.bias, p.d_out);
     fill_w_bf16_t<NC>(w_lds, LDW, static_cast<const uint16_t *>(p.w), 0, NS * BK, 0, p);
     __syncthreads();
 
@@ -225,7 +226,7 @@ void update_bf16_stream_kernel(const UpdArgs p)
             }
             wave_sync_lds();
         }
-        store_tile_lines<NT, OUT_BF16>(p, acc, reinterpret_cast<float *>(abuf), tile * 32, lane);
+        store_tile_lines<NT, OUT_BF16>(p, acc, bias, reinterpret_cast<float *>(abuf), tile * 32, lane);
         tile += stride;
     };
     do_tile();                      // peeled: the loop below then meets the same pattern of pending
@@ -240,6 +241,11 @@ void update_bf16_stream_kernel(const UpdArgs p)
 // consecutive registers packed together are, as they stand, the A operand of one MFMA of the second
 // product.  MFMA sums over k in any order, so W2 is staged in LDS with its k index permuted to
 // match: within every group of 16, hidden column 8 a + 4 h + e sits at position 8 h + 4 a + e.
+// What bounds it is HBM (4.2 TB/s of 5.2 that a plain copy reaches) once the epilogues are lean: bias read from LDS instead of
+// tested and loaded column by column (a lane mask per column had 400 scalar registers spilled), pairs rounded to bf16 by
+// one instruction instead of nine.  524,288 rows, 128 -> 128 -> 128, fp32 out: 166 -> 126 us from fp32 rows, 150 -> 98 us
+// from bf16 rows; 300,000 rows, 64 -> 96 -> 40: 48 -> 33 us; the same bits.  A second slab of A in flight gains nothing
+// (126 and 101 us).
 constexpr int kMlpWaves = 8;
 constexpr int kMlpThreads = kWave * kMlpWaves;
 
@@ -262,10 +268,13 @@ void mlp_bf16_stream_kernel(const MlpArgs m)
     constexpr int WAVE_BYTES = wave_lds_bytes<NT2, OUT_BF16>(32 * LDA * 2);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 31, h = lane >> 5;
+    __shared__ __attribute__((aligned(16))) float bias1[H], bias2[NC2];
     uint16_t *w1_lds = reinterpret_cast<uint16_t *>(lds_all);
     uint16_t *w2_lds = reinterpret_cast<uint16_t *>(lds_all + W1_BYTES);
     uint16_t *abuf = reinterpret_cast<uint16_t *>(lds_all + W1_BYTES + W2_BYTES + wave * WAVE_BYTES);
     {
+        stage_bias<H>(bias1, m.b1, m.d_hid);
+        stage_bias<NC2>(bias2, m.b2, m.d_out);
         // W1^T [H][LDW1] and W2^T [NC2][LDW2] (k permuted), zero outside the matrices; pairs of k per dword
         uint32_t *l1 = reinterpret_cast<uint32_t *>(w1_lds), *l2 = reinterpret_cast<uint32_t *>(w2_lds);
         for (int id = threadIdx.x; id < (NS1 * BK / 2) * H; id += kMlpThreads) {
@@ -286,7 +295,7 @@ void mlp_bf16_stream_kernel(const MlpArgs m)
 
     UpdArgs pa{};           // what the slab loads and the epilogue read
     pa.a = m.a; pa.n_rows = m.n_rows; pa.ld_a = m.ld_a;
-    pa.out = m.out; pa.ld_out = m.ld_out; pa.d_out = m.d_out; pa.bias = m.b2; pa.relu = m.relu2; pa.out_vec_ok = m.out_vec_ok;
+    pa.out = m.out; pa.ld_out = m.ld_out; pa.d_out = m.d_out; pa.relu = m.relu2; pa.out_vec_ok = m.out_vec_ok;
 
     const int64_t n_tiles = (m.n_rows + 31) / 32, stride = static_cast<int64_t>(gridDim.x) * kMlpWaves;
     int64_t tile = static_cast<int64_t>(blockIdx.x) * kMlpWaves + wave;
@@ -334,13 +343,17 @@ void mlp_bf16_stream_kernel(const MlpArgs m)
             for (int qp = 0; qp < 2; ++qp) {
                 float v[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int col = t * 32 + 16 * qp + 8 * (e / 4) + 4 * h + e % 4;
-                    v[e] = acc[t][8 * qp + e] + ((m.b1 && col < m.d_hid) ? m.b1[col] : 0.f);
-                    if (m.relu1) v[e] = v[e] > 0.f ? v[e] : 0.f;
+                for (int q4 = 0; q4 < 2; ++q4) {
+                    const float4 y = *reinterpret_cast<const float4 *>(bias1 + t * 32 + 16 * qp + 8 * q4 + 4 * h);
+                    const float b[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        v[4 * q4 + e] = acc[t][8 * qp + 4 * q4 + e] + b[e];
+                        if (m.relu1) v[4 * q4 + e] = v[4 * q4 + e] > 0.f ? v[4 * q4 + e] : 0.f;
+                    }
                 }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) hf[t * 2 + qp].u[e] = f32_to_bf16_bits(v[2 * e]) | (f32_to_bf16_bits(v[2 * e + 1]) << 16);
+                for (int e = 0; e < 4; ++e) hf[t * 2 + qp].u[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
             }
         f32x16 acc2[NT2];
 #pragma unroll
@@ -355,7 +368,7 @@ void mlp_bf16_stream_kernel(const MlpArgs m)
                 bw.q = *reinterpret_cast<const uint4 *>(&w2_lds[(t * 32 + i) * LDW2 + 16 * g + 8 * h]);
                 acc2[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bw.v, hf[g].v, acc2[t], 0, 0, 0);
             }
-        store_tile_lines<NT2, OUT_BF16>(pa, acc2, reinterpret_cast<float *>(abuf), tile * 32, lane);
+        store_tile_lines<NT2, OUT_BF16>(pa, acc2, bias2, reinterpret_cast<float *>(abuf), tile * 32, lane);
         tile += stride;
     };
     do_tile();
