@@ -28,7 +28,7 @@ def reference(a, w, b):
 
 
 @pytest.mark.parametrize("n,d_in,d_out,ld,shift", [
-    (1, 4, 1, 4, 0), (31, 5, 3, 5, 1), (33, 16, 16, 16, 0), (64, 31, 33, 31, 3), (257, 33, 32, 33, 1), (1000, 75, 47, 75, 2),
+    (1, 1, 1, 1, 0), (1000, 3, 40, 3, 1), (1, 4, 1, 4, 0), (31, 5, 3, 5, 1), (33, 16, 16, 16, 0), (64, 31, 33, 31, 3), (257, 33, 32, 33, 1), (1000, 75, 47, 75, 2),
     (4097, 100, 256, 100, 0), (300, 256, 65, 256, 0), (2049, 602, 256, 608, 0), (513, 602, 255, 602, 1), (70000, 64, 64, 64, 0),
     (70001, 100, 200, 103, 1), (70003, 257, 129, 257, 0), (9000, 320, 64, 320, 0), (9000, 321, 64, 321, 0), (66000, 161, 128, 161, 0),
     (200, 1000, 300, 1000, 0), (70000, 40, 256, 40, 0)])
