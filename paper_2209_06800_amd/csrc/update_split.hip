@@ -5,7 +5,7 @@
 // wider than about 64 x 64.  An fp32 number is the exact sum of three bf16 numbers (24 = 8 + 8 + 8 bits of
 // significand; each part is rounded to nearest, so the next one is at most 2^-8 of it and of either sign), and
 // a product of two bf16 numbers is exact in fp32.  a w = (a1 + a2 + a3)(w1 + w2 + w3) is summed from its
-// six largest terms, small ones first; the three that are left out are below 2^-24 |a w| together and of
+// six largest terms, small ones first; the three that are left out are at most 2^-23 |a w| together, about 2^-27 as a rule, and of
 // random sign.  Six bf16 MFMAs cost 6/16 of the fp32 one, and 16 terms enter the accumulator per rounding
 // instead of 2.
 //
