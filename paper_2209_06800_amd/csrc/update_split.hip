@@ -11,9 +11,10 @@
 //
 // The split is exact while no part overflows or becomes denormal.  Per 32-row tile the kernel looks at the
 // largest magnitude of each row of A and of each column of W: if one is non-zero and below 2^-50, or
-// 2^127 and more (infinities included; a NaN needs no help, it stays one through the split), the tile is
-// computed again with the fp32 instruction from global memory -- slow, exact about infinities, and not
-// met by data of ordinary scale.
+// 2^127 and more (infinities included), the tile is computed again with the fp32 instruction from global
+// memory -- slow, exact about infinities, and not met by data of ordinary scale.  So it is where a sum is not finite:
+// near the largest fp32 number a1 w1 can pass it though a w does not, and beyond it the small terms may hold
+// the other sign, which makes a NaN of what is an infinity.
 //
 // What bounds it: HBM for narrow outputs, the matrix pipe and the operand traffic through LDS for wide ones (602 -> 256:
 // the pipe is busy 0.5 of the time at the 1.95 GHz the chip holds, of which 0.11 is the last, partly filled round of tiles).
@@ -396,6 +397,18 @@ __device__ __forceinline__ void exact_tile(const UpdArgs &p, float *cbuf, int64_
     }
 }
 
+// true where a sum of the tile is an infinity or a NaN
+template <int NT>
+__device__ __forceinline__ bool not_finite(const f32x16 (&acc)[NT])
+{
+    float z = 0.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z = fmaf(acc[t][r], 0.f, z);
+    return __ballot(z != 0.f) != 0;
+}
+
 template <int NC>
 __device__ __forceinline__ bool columns_out_of_range(const uint32_t *colmax, int lane)
 {
@@ -488,7 +501,7 @@ void update_split_resident_kernel(const UpdArgs p)
             });
         } while (++s < n_slabs);
         amax = fmaxf(amax, __shfl_xor(amax, 32));
-        const bool again = bad_w || __ballot(out_of_range(amax));
+        const bool again = bad_w || __ballot(out_of_range(amax)) || not_finite<NT>(acc);
         if constexpr (SOFTMAX) softmax_rows<NT>(opaque(p), acc, opaque(lane));
         store_lines<NT, SOFTMAX>(opaque(p), acc, abuf, tile * 32, n0, opaque(lane));
         if (again) exact_tile<SOFTMAX ? NT : 1, SOFTMAX>(opaque(p), abuf, tile * 32, n0, n0 + NC, opaque(lane));
@@ -567,7 +580,7 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
             cur ^= 1;
         } while (++ks < n_slabs);
         amax = fmaxf(amax, __shfl_xor(amax, 32));
-        const bool again = columns_out_of_range<NC>(colmax, lane) || __ballot(out_of_range(amax));
+        const bool again = columns_out_of_range<NC>(colmax, lane) || __ballot(out_of_range(amax)) || not_finite<NT>(acc);
         store_lines<NT, false>(opaque(p), acc, abuf, first_row(tile), n0, opaque(lane));
         if (again) exact_tile<1, false>(opaque(p), abuf, first_row(tile), n0, n0 + NC, opaque(lane));
         if (ntile >= n_tiles) break;

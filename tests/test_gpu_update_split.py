@@ -95,3 +95,48 @@ def test_update_split_softmax(n, d_in, d_out, tiny):
     assert torch.isnan(buf[:, d_out:]).all() and torch.isnan(buf[n:]).all()
     err = (buf[:n, :d_out].double().cpu() - ref).abs()
     assert (err <= 1e-6 + bound.amax(1, keepdim=True) * ref).all(), err.max()
+
+
+# One shape for each kernel form of the dispatch (and both for a single block of columns and for several side by side).
+FORMS = {
+    "narrow1": [(1000, 100, 16), (333, 64, 7)],
+    "narrow2": [(5000, 64, 24), (2000, 602, 256)],
+    "resident2": [(70001, 64, 64), (9001, 64, 47)],
+    "resident4": [(70003, 100, 200), (9003, 64, 128)],
+    "slab4": [(70003, 257, 129), (66001, 161, 128)],
+    "slab2": [(20001, 602, 256), (66001, 330, 64)],
+    "slab1": [(301, 1000, 300), (300, 1400, 9)],
+}
+SHAPES = [s for v in FORMS.values() for s in v]
+
+
+def one_product_per_element(n, d_in, d_out, pairs):
+    """Row r holds a single non-zero, at k = r % d_in, and W repeats a few values: every sum is one product.  The pairs (a, w)
+    sit in tiles of their own from both ends, in the first, the middle and the last column; all else is 1 * 1."""
+    a = torch.zeros(n, d_in, device=DEV)
+    w = torch.ones(d_in, d_out, device=DEV)
+    a[torch.arange(n, device=DEV), torch.arange(n, device=DEV) % d_in] = 1.0
+    rows = [(33 * i, n - 1 - 33 * i) for i in range(len(pairs))]             # a tile each
+    for (av, wv), rr in zip(pairs, rows):
+        for r in rr:
+            a[r, r % d_in] = av
+    k_of = torch.arange(n, device=DEV) % d_in
+    for (av, wv), rr in zip(pairs, rows):
+        for r in rr:
+            w[r % d_in, [0, d_out // 2, d_out - 1]] = wv
+    return a, w, a.gather(1, k_of[:, None]).double() * w[k_of].double()
+
+
+@pytest.mark.parametrize("act", ["none", "relu"])
+@pytest.mark.parametrize("n,d_in,d_out", SHAPES)
+def test_update_split_overflow(n, d_in, d_out, act):
+    """Products around the largest fp32 number: finite where fp32 is finite, an infinity of the right sign where it is not,
+    and never a NaN (which ReLU would turn into 0)."""
+    pairs = [(1.2345e25, 7.77e20), (-1.2345e25, 7.77e20), (1.844e19, 1.844e19), (1.9e19, -1.9e19), (3.4e38, 0.999), (1e20, 1e15), (-2.5e30, 1e8)]
+    a, w, ref = one_product_per_element(n, d_in, d_out, pairs)
+    out = binding.mgg_update(a, w, None, act)
+    ref = torch.relu(ref.float()) if act == "relu" else ref.float()           # (each element one product: rounded once)
+    assert torch.equal(torch.isinf(ref), torch.isinf(out)) and not torch.isnan(out).any()
+    assert torch.equal(ref[torch.isinf(ref)], out[torch.isinf(ref)])
+    fin = torch.isfinite(ref)
+    assert ((out - ref).abs()[fin] <= 2.0 ** -23 * ref.abs()[fin]).all()
