@@ -9,12 +9,12 @@
 // random sign.  Six bf16 MFMAs cost 6/16 of the fp32 one, and 16 terms enter the accumulator per rounding
 // instead of 2.
 //
-// The split is exact while no part overflows or becomes denormal.  Per 32-row tile the kernel looks at the
-// largest magnitude of each row of A and of each column of W: if one is non-zero and below 2^-50, or
-// 2^127 and more (infinities included), the tile is computed again with the fp32 instruction from global
-// memory -- slow, exact about infinities, and not met by data of ordinary scale.  So it is where a sum is not finite:
-// near the largest fp32 number a1 w1 can pass it though a w does not, and beyond it the small terms may hold
-// the other sign, which makes a NaN of what is an infinity.
+// Range.  Both operands are multiplied by 2^24 on their way into the parts and the sums by 2^-48 at the end, all exact:
+// the smallest fp32 number, 2^-149, has its last bit at 2^-125 then, so that no part of any element is denormal,
+// however small the element is beside others of its row, and what is lost at the low end of the sums is below 2^-149
+// after scaling back.  At the high end an element of 2^104, or sums of 2^80, overflow: a tile with a sum that is not finite
+// (infinities and NaN among the operands make such sums too) is computed again with the fp32 instruction from
+// global memory -- slow, exact about infinities, and not met by data of ordinary scale.
 //
 // What bounds it: HBM for narrow outputs, the matrix pipe and the operand traffic through LDS for wide ones (602 -> 256:
 // the pipe is busy 0.5 of the time at the 1.95 GHz the chip holds, of which 0.11 is the last, partly filled round of tiles).
@@ -53,7 +53,8 @@ using namespace upd;
 constexpr int kSWaves = 8, kSThreads = kWave * kSWaves;
 constexpr int kLda = 36;                                    // row of the per-wavefront buffer, in floats
 constexpr int kWaveBytes = 32 * kLda * 4;
-constexpr int kLdsMax = 160 * 1024 - 1024;                  // (colmax: 1 KB)
+constexpr int kLdsMax = 160 * 1024;
+constexpr float kScale = 0x1p24f, kUnscale = 0x1p-48f;       // of an operand; of a sum of products
 constexpr int w_slab_bytes(int nc) { return 3 * 4 * nc * 16; }
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -78,12 +79,12 @@ __device__ __forceinline__ uint32_t cvt_pk(float lo, float hi)
     return r.u;
 }
 
-// eight fp32 values -> three bf16 operands whose sum they are
+// eight fp32 values -> three bf16 operands whose sum they are, times kScale
 __device__ __forceinline__ void split8(const float (&f)[8], Frag (&o)[3])
 {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        float lo = f[2 * e], hi = f[2 * e + 1];
+        float lo = f[2 * e] * kScale, hi = f[2 * e + 1] * kScale;
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
             const uint32_t pk = cvt_pk(lo, hi);
@@ -92,8 +93,6 @@ __device__ __forceinline__ void split8(const float (&f)[8], Frag (&o)[3])
         }
     }
 }
-
-__device__ __forceinline__ bool out_of_range(float m) { return m != 0.f && !(m >= 0x1p-50f && m < 0x1p127f); }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_loose __attribute__((aligned(4)));       // in memory, at any element
@@ -159,29 +158,25 @@ __device__ __forceinline__ void load_w_unit(const UpdArgs &p, int k0, int id0, i
 
 // plane s of unit (kg, n) of a slab -> w[s][kg][n]
 template <int NC>
-__device__ __forceinline__ void store_w_unit(const UpdArgs &p, int k0, int id0, int lane, float (&f)[8], uint4 *w, uint32_t *colmax)
+__device__ __forceinline__ void store_w_unit(const UpdArgs &p, int k0, int id0, int lane, float (&f)[8], uint4 *w)
 {
     const int id = id0 + lane, pos = k0 + unit_pos<NC>(id0, lane);
-    float m = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         bool again;
         (void)w_row(pos + e, p.d_in, again);
         f[e] = again ? 0.f : f[e];
-        m = fmaxf(m, fabsf(f[e]));
     }
     Frag o[3];
     split8(f, o);
 #pragma unroll
     for (int s = 0; s < 3; ++s) w[s * 4 * NC + id % (4 * NC)] = o[s].q;
-    atomicMax(&colmax[id % NC], __float_as_uint(m));
 }
 
 // The A operands of a slab as the loop carries them: the first half (k 0..7 and 16..23 of the slab) split, the second raw.
 struct SlabA {
     Frag a0[3];
     float raw1[8];
-    float amax;              // largest magnitude of this lane's 16 values
 };
 
 __device__ __forceinline__ void read_raw(const float *abuf, int lane, int c, float (&f)[8])
@@ -241,9 +236,6 @@ __device__ __forceinline__ void next_a(RawA &q, int lane, float *abuf, SlabA &sa
         read_raw(abuf, lane, 1, sa.raw1);
     }
     if constexpr (x == S - 1) {
-        sa.amax = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sa.amax = fmaxf(fmaxf(sa.amax, fabsf(raw0[e])), fabsf(sa.raw1[e]));
         split8(raw0, sa.a0);
         wave_sync_lds();                                    // the buffer is free for the epilogue
     }
@@ -257,9 +249,6 @@ __device__ __forceinline__ void first_a(RawA &q, int lane, float *abuf, SlabA &s
     wave_sync_lds();
     read_raw(abuf, lane, 0, raw0);
     read_raw(abuf, lane, 1, sa.raw1);
-    sa.amax = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sa.amax = fmaxf(fmaxf(sa.amax, fabsf(raw0[e])), fabsf(sa.raw1[e]));
     split8(raw0, sa.a0);
     wave_sync_lds();
 }
@@ -397,24 +386,19 @@ __device__ __forceinline__ void exact_tile(const UpdArgs &p, float *cbuf, int64_
     }
 }
 
-// true where a sum of the tile is an infinity or a NaN
+// The tile's sums without the scale; true where one is an infinity or a NaN.
 template <int NT>
-__device__ __forceinline__ bool not_finite(const f32x16 (&acc)[NT])
+__device__ __forceinline__ bool unscale(f32x16 (&acc)[NT])
 {
     float z = 0.f;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) z = fmaf(acc[t][r], 0.f, z);
+        for (int r = 0; r < 16; ++r) {
+            acc[t][r] *= kUnscale;
+            z = fmaf(acc[t][r], 0.f, z);
+        }
     return __ballot(z != 0.f) != 0;
-}
-
-template <int NC>
-__device__ __forceinline__ bool columns_out_of_range(const uint32_t *colmax, int lane)
-{
-    bool bad = false;
-    for (int n = lane; n < NC; n += kWave) bad |= out_of_range(__uint_as_float(colmax[n]));
-    return __ballot(bad) != 0;
 }
 
 // What only depends on the arguments and the lane would be computed ahead of all loops and held in registers that
@@ -439,7 +423,6 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(MGG_S
 void update_split_resident_kernel(const UpdArgs p)
 {
     constexpr int NC = NT * 32, SLAB = w_slab_bytes(NC) / 16;
-    __shared__ uint32_t colmax[NC];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int n0 = static_cast<int>(blockIdx.y) * NC;
     const int n_slabs = (p.d_in + 31) / 32;
@@ -458,8 +441,6 @@ void update_split_resident_kernel(const UpdArgs p)
     };
     issue(q[0]);
     issue(q[1]);
-    for (int n = threadIdx.x; n < NC; n += kSThreads) colmax[n] = 0u;
-    __syncthreads();
     {
         const int units = n_slabs * 4 * NC;
         constexpr int B = 2;
@@ -472,12 +453,11 @@ void update_split_resident_kernel(const UpdArgs p)
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 const int id0 = base + b * kSThreads;                             // (units is a multiple of a wavefront)
-                if (id0 < units) store_w_unit<NC>(p, 0, id0, lane, f[b], w + id0 / (4 * NC) * SLAB, colmax);
+                if (id0 < units) store_w_unit<NC>(p, 0, id0, lane, f[b], w + id0 / (4 * NC) * SLAB);
             }
         }
     }
     __syncthreads();
-    const bool bad_w = columns_out_of_range<NC>(colmax, lane);
 
     if (tile >= n_tiles) return;
     SlabA sa;
@@ -490,18 +470,15 @@ void update_split_resident_kernel(const UpdArgs p)
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-        float amax = 0.f;
         int s = 0;
 #pragma unroll 1
         do {
-            amax = fmaxf(amax, sa.amax);
             float raw0[8];
             multiply_slab<NT>(acc, sa, w + s * SLAB, lane, [&](auto step) __attribute__((always_inline)) {
                 next_a<NT, decltype(step)::value>(q[0], lane, abuf, sa, raw0, [&]() __attribute__((always_inline)) { q[0] = q[1]; issue(q[1]); });
             });
         } while (++s < n_slabs);
-        amax = fmaxf(amax, __shfl_xor(amax, 32));
-        const bool again = bad_w || __ballot(out_of_range(amax)) || not_finite<NT>(acc);
+        const bool again = unscale<NT>(acc);
         if constexpr (SOFTMAX) softmax_rows<NT>(opaque(p), acc, opaque(lane));
         store_lines<NT, SOFTMAX>(opaque(p), acc, abuf, tile * 32, n0, opaque(lane));
         if (again) exact_tile<SOFTMAX ? NT : 1, SOFTMAX>(opaque(p), abuf, tile * 32, n0, n0 + NC, opaque(lane));
@@ -515,7 +492,6 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
 {
     constexpr int NC = NT * 32, SLAB = w_slab_bytes(NC) / 16;
     constexpr int UNITS = (4 * NC + kSThreads - 1) / kSThreads;          // of a slab, per thread
-    __shared__ uint32_t colmax[NC];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int n0 = static_cast<int>(blockIdx.y) * NC;
     const int n_slabs = (p.d_in + 31) / 32;
@@ -524,7 +500,7 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
     // (narrow slabs have fewer units than threads: some are staged twice, with the same values)
     auto unit0 = [&](int u) { return (u * kSThreads + wave * kWave) % (4 * NC); };
     auto load_w = [&](int ks, int u, float (&f)[8]) { load_w_unit<NC>(p, ks * 32, unit0(u), n0, lane, f); };
-    auto store_w = [&](int buf, int ks, int u, float (&f)[8]) { store_w_unit<NC>(p, ks * 32, unit0(u), lane, f, w + buf * SLAB, colmax); };
+    auto store_w = [&](int buf, int ks, int u, float (&f)[8]) { store_w_unit<NC>(p, ks * 32, unit0(u), lane, f, w + buf * SLAB); };
 
     int64_t tile = blockIdx.x;                                           // the host launches at most n_tiles workgroups
     auto first_row = [&](int64_t t) { return (t * kSWaves + wave) * 32; };
@@ -535,8 +511,6 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
         float wf[UNITS][8];
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) load_w(0, u, wf[u]);
-        for (int n = threadIdx.x; n < NC; n += kSThreads) colmax[n] = 0u;
-        __syncthreads();
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) store_w(0, 0, u, wf[u]);
     }
@@ -558,12 +532,10 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-        float amax = 0.f;
         const int64_t ntile = tile + gridDim.x;
         int ks = 0;
 #pragma unroll 1
         do {
-            amax = fmaxf(amax, sa.amax);
             const int nks = ks + 1 == n_slabs ? 0 : ks + 1;            // the slab after this one
             float raw0[8], wf[8];
             multiply_slab<NT>(acc, sa, w + cur * SLAB, lane, [&](auto step) __attribute__((always_inline)) {
@@ -579,8 +551,7 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
             __syncthreads();
             cur ^= 1;
         } while (++ks < n_slabs);
-        amax = fmaxf(amax, __shfl_xor(amax, 32));
-        const bool again = columns_out_of_range<NC>(colmax, lane) || __ballot(out_of_range(amax)) || not_finite<NT>(acc);
+        const bool again = unscale<NT>(acc);
         store_lines<NT, false>(opaque(p), acc, abuf, first_row(tile), n0, opaque(lane));
         if (again) exact_tile<1, false>(opaque(p), abuf, first_row(tile), n0, n0 + NC, opaque(lane));
         if (ntile >= n_tiles) break;
@@ -594,7 +565,7 @@ hipError_t launch_resident(const UpdArgs &p, int cus, hipStream_t s)
     const size_t lds = static_cast<size_t>((p.d_in + 31) / 32) * w_slab_bytes(NT * 32) + kSWaves * kWaveBytes;
     const int gy = (p.d_out + NT * 32 - 1) / (NT * 32);
     const int64_t n_tiles = (p.n_rows + 31) / 32;
-    const int64_t slots = static_cast<int64_t>(cus) * (NT < 4 && 2 * (lds + 1024) <= 160 * 1024 ? 2 : 1);
+    const int64_t slots = static_cast<int64_t>(cus) * (NT < 4 && 2 * lds <= kLdsMax ? 2 : 1);
     const dim3 grid(static_cast<unsigned>(n_tiles < slots ? n_tiles : slots), static_cast<unsigned>(gy));
     if (lds > 48 * 1024)                                     // beyond what a launch may take unasked
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_resident_kernel<NT, SOFTMAX>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));

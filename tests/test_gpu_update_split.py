@@ -140,3 +140,22 @@ def test_update_split_overflow(n, d_in, d_out, act):
     assert torch.equal(ref[torch.isinf(ref)], out[torch.isinf(ref)])
     fin = torch.isfinite(ref)
     assert ((out - ref).abs()[fin] <= 2.0 ** -23 * ref.abs()[fin]).all()
+
+
+@pytest.mark.parametrize("n,d_in,d_out", SHAPES)
+def test_update_split_small_beside_ordinary(n, d_in, d_out):
+    """Elements down to the denormal range beside ordinary ones, where the ordinary ones meet zero weights (and the same with
+    the roles of A and W exchanged): what is left is one product, right to fp32."""
+    g = torch.Generator(device=DEV).manual_seed(d_in)
+    v = torch.rand(n, device=DEV, generator=g) + 1.0
+    v.view(torch.int32)[::2] |= 1                                             # an odd last bit: all 24 are needed
+    for exp_a, exp_w in ((-115, 100), (-122, 100), (-130, 110), (-140, 120), (100, -122), (110, -135)):
+        a = torch.zeros(n, d_in, device=DEV)
+        w = torch.zeros(d_in, d_out, device=DEV)
+        a[:, 0] = 1.0                                                         # ordinary, meets zeros
+        w[2, :] = 1.0
+        a[:, 1] = v * 2.0 ** (exp_a // 2) * 2.0 ** (exp_a - exp_a // 2)       # (in two factors: 2^-140 itself is a denormal)
+        w[1, :] = 1.5 * 2.0 ** (exp_w // 2) * 2.0 ** (exp_w - exp_w // 2)
+        ref = a[:, 1:2].double() * w[1:2].double()
+        out = binding.mgg_update(a, w, None, "none").double()
+        assert ((out - ref).abs() <= 2.0 ** -23 * ref.abs() + 2.0 ** -149).all(), (exp_a, exp_w)
