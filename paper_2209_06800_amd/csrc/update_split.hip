@@ -4,10 +4,15 @@
 // v_mfma_f32_32x32x2_f32 runs at 1/16 of the bf16 rate (about 157 TFLOP/s), which bounded every fp32 shape
 // wider than about 64 x 64.  An fp32 number is the exact sum of three bf16 numbers (24 = 8 + 8 + 8 bits of
 // significand; each part is rounded to nearest, so the next one is at most 2^-8 of it and of either sign), and
-// a product of two bf16 numbers is exact in fp32.  a w = (a1 + a2 + a3)(w1 + w2 + w3) is summed from its
-// six largest terms, small ones first; the three that are left out are at most 2^-23 |a w| together, about 2^-27 as a rule, and of
-// random sign.  Six bf16 MFMAs cost 6/16 of the fp32 one, and 16 terms enter the accumulator per rounding
-// instead of 2.
+// a product of two bf16 numbers is exact in fp32.  Of a w = (a1 + a2 + a3)(w1 + w2 + w3) all terms but a3 w3 are
+// summed, which is at most 2^-32 |a w|.  (The six largest alone would leave out up to 2^-24 |a w| more, which shows
+// where a row has a single non-zero: 1.0e-7 of the result instead of 6.0e-8.)
+//
+// Two accumulators: a1 w1 goes into one, the seven small terms into the other, which is 2^-8 of the first, and they are
+// added at the end.  So 16 products round the large sum once; the fp32 instruction rounds it for every two products,
+// and one chain of all terms would round it eight times per 16 columns of A however many of them are zero.  2-norm
+// error against float64 at 602 columns: 4.4e-7 with the fp32 instruction, 1.4e-7 so; with one non-zero in 16
+// 1.1e-7 with the fp32 instruction, 2.3e-7 with a chain of six terms, 0.5e-7 so.
 //
 // Range.  Both operands are multiplied by 2^24 on their way into the parts and the sums by 2^-48 at the end, all exact:
 // the smallest fp32 number, 2^-149, has its last bit at 2^-125 then, so that no part of any element is denormal,
@@ -16,30 +21,29 @@
 // (infinities and NaN among the operands make such sums too) is computed again with the fp32 instruction from
 // global memory -- slow, exact about infinities, and not met by data of ordinary scale.
 //
-// What bounds it: HBM for narrow outputs, the matrix pipe and the operand traffic through LDS for wide ones (602 -> 256:
-// the pipe is busy 0.5 of the time at the 1.95 GHz the chip holds, of which 0.11 is the last, partly filled round of tiles).
-// Measured against the fp32-instruction kernels this file replaces (us before -> after, one MI355X; fp32 rows end to end
-// unless a leading dimension is given), and the 2-norm error against float64, which is lower at every shape tried:
-//   232,965 x 602 (ld 608) -> 256    718 -> 448     4.4e-7 -> 3.8e-7
-//   120,011 x 602 -> 256             428 -> 216     4.4e-7 -> 3.8e-7
-//   400,000 x 250 -> 250             968 -> 354     2.8e-7 -> 2.4e-7
-//   306,128 x 100 -> 256             231 -> 153     1.8e-7 -> 1.5e-7
-//   1,771,062 x 256 -> 47            688 -> 482     2.9e-7 -> 2.4e-7
-//   300,000 x 128 -> 128             156 ->  90     2.0e-7 -> 1.6e-7
-//   100,000 x 75 -> 33                41 ->  20     1.6e-7 -> 1.4e-7
-//   262,144 x 64 -> 64                38 ->  31     1.5e-7 -> 1.1e-7
-//   2,000 x 602 -> 256               117 ->  31     4.4e-7 -> 3.7e-7
-//   400,000 x 32 -> 16                20 ->  21     1.0e-7 -> 0.7e-7     (HBM; the narrowest gain nothing)
+// What bounds it: HBM for narrow outputs, the matrix pipe and the operand traffic through LDS for wide ones.
+// Against kernels on the fp32 instruction (us there -> here, one MI355X; fp32 rows end to end unless a leading
+// dimension is given), and the 2-norm error against float64:
+//   232,965 x 602 (ld 608) -> 256    674 -> 489     4.4e-7 -> 1.4e-7
+//   400,000 x 250 -> 250             970 -> 402     2.8e-7 -> 0.9e-7
+//   306,128 x 100 -> 256             231 -> 160     1.8e-7 -> 0.6e-7
+//   1,771,062 x 256 -> 47            685 -> 505     2.9e-7 -> 0.9e-7
+//   262,144 x 64 -> 64                38 ->  28     1.5e-7 -> 0.6e-7
+//   2,000 x 602 -> 256               116 ->  19     4.4e-7 -> 1.4e-7
+//   400,000 x 32 -> 16                20 ->  21     1.0e-7 -> 0.4e-7     (HBM; the narrowest gain nothing)
+// (Six terms would take 427 us on the first and 350 on the second.)
 //
-// Layout.  Eight wavefronts; a wavefront owns 32 rows x NT*32 columns.  A slab of 32 k values is read with 8
+// Layout.  Eight wavefronts; a wavefront owns 32 rows x NT*32 columns, at most 128: the two accumulators take 128
+// registers then.  A slab of 32 k values is read with 8
 // lanes per row (one whole 128-byte line per row and instruction, at any alignment: 16-byte loads need only
 // element alignment, and a vector that would pass the end of a ragged row is moved back to end with it), staged raw in a
-// per-wavefront LDS buffer, read back in operand layout and split there: every element of A is split once.
+// per-wavefront LDS buffer, read back in operand layout and split there: an element of A is split once per block of columns.
 // W is split while it is staged: three planes of 16-byte pieces [k / 8][column], so that operand reads and
 // staging writes are conflict-free and W needs no alignment.
-//   - RESIDENT: all of W in LDS, split once per workgroup; wavefronts walk over their tiles without a barrier;
-//   - otherwise two slabs of W in LDS: the next one is loaded into registers, split between the MFMAs of the
+//   - resident: all of W in LDS, split once per workgroup; wavefronts walk over their tiles without a barrier;
+//   - slab: two slabs of W in LDS; the next one is loaded into registers, split between the MFMAs of the
 //     current one and written to the other buffer; one barrier per slab.
+#include <algorithm>
 #include <utility>
 
 #include "update_common.h"
@@ -53,7 +57,7 @@ using namespace upd;
 constexpr int kSWaves = 8, kSThreads = kWave * kSWaves;
 constexpr int kLda = 36;                                    // row of the per-wavefront buffer, in floats
 constexpr int kWaveBytes = 32 * kLda * 4;
-constexpr int kLdsMax = 160 * 1024;
+constexpr int kLdsMax = 160 * 1024 - 1024;                  // (beside it: the bias)
 constexpr float kScale = 0x1p24f, kUnscale = 0x1p-48f;       // of an operand; of a sum of products
 constexpr int w_slab_bytes(int nc) { return 3 * 4 * nc * 16; }
 
@@ -173,6 +177,24 @@ __device__ __forceinline__ void store_w_unit(const UpdArgs &p, int k0, int id0, 
     for (int s = 0; s < 3; ++s) w[s * 4 * NC + id % (4 * NC)] = o[s].q;
 }
 
+// all of W (resident forms), two units per thread on their way at a time
+template <int NC>
+__device__ __forceinline__ void stage_w(const UpdArgs &p, int n_slabs, int n0, int wave, int lane, uint4 *w)
+{
+    constexpr int B = 2, SLAB = w_slab_bytes(NC) / 16;
+    const int units = n_slabs * 4 * NC;                      // (a multiple of a wavefront)
+    for (int base = wave * kWave; base < units; base += B * kSThreads) {
+        float f[B][8];
+#pragma unroll
+        for (int b = 0; b < B; ++b) load_w_unit<NC>(p, 0, base + b * kSThreads, n0, lane, f[b]);      // (past the end: the last row again, not kept)
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int id0 = base + b * kSThreads;
+            if (id0 < units) store_w_unit<NC>(p, 0, id0, lane, f[b], w + id0 / (4 * NC) * SLAB);
+        }
+    }
+}
+
 // The A operands of a slab as the loop carries them: the first half (k 0..7 and 16..23 of the slab) split, the second raw.
 struct SlabA {
     Frag a0[3];
@@ -188,12 +210,12 @@ __device__ __forceinline__ void read_raw(const float *abuf, int lane, int c, flo
     }
 }
 
-// Products of one K slab: acc += A slab * W slab, in 2 NT steps of six MFMAs.  The W operands of a step are read from LDS
+// Products of one K slab: hi + lo += A slab * W slab, in 2 NT steps of eight MFMAs.  The W operands of a step are read from LDS
 // one step ahead; between(x), called after step x, holds everything else the wavefront has to do, spread over the steps,
 // so that the matrix pipe is not left idle while a wavefront waits, converts or stores (the fences keep the compiler
 // from gathering it at the end).  In it, the next slab replaces `sa`: its raw half is used up by step NT - 1.
 template <int NT, class Between>
-__device__ __forceinline__ void multiply_slab(f32x16 (&acc)[NT], SlabA &sa, const uint4 *w, int lane, Between between)
+__device__ __forceinline__ void multiply_slab(f32x16 (&hi)[NT], f32x16 (&lo)[NT], SlabA &sa, const uint4 *w, int lane, Between between)
 {
     constexpr int NC = NT * 32, S = 2 * NT;
     const uint4 *wl = w + 2 * (lane >> 5) * NC + (lane & 31);
@@ -210,10 +232,11 @@ __device__ __forceinline__ void multiply_slab(f32x16 (&acc)[NT], SlabA &sa, cons
         if constexpr (x + 1 < S) load_b(x + 1);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (x == NT - 1) split8(sa.raw1, a1);
-        constexpr int wi[6] = {2, 0, 1, 1, 0, 0}, ai[6] = {0, 2, 1, 0, 1, 0};          // small terms first
+        constexpr int wi[7] = {2, 1, 2, 0, 1, 1, 0}, ai[7] = {1, 2, 0, 2, 1, 0, 1};          // small terms: w3 a2, w2 a3, w3 a1, ...
 #pragma unroll
-        for (int y = 0; y < 6; ++y)
-            acc[x % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[x & 1][wi[y]].v, x < NT ? a0[ai[y]].v : a1[ai[y]].v, acc[x % NT], 0, 0, 0);
+        for (int y = 0; y < 7; ++y)
+            lo[x % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[x & 1][wi[y]].v, x < NT ? a0[ai[y]].v : a1[ai[y]].v, lo[x % NT], 0, 0, 0);
+        hi[x % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[x & 1][0].v, x < NT ? a0[0].v : a1[0].v, hi[x % NT], 0, 0, 0);
         between(step);
         __builtin_amdgcn_sched_barrier(0);
     }, std::make_integer_sequence<int, S>{});
@@ -224,7 +247,7 @@ __device__ __forceinline__ void multiply_slab(f32x16 (&acc)[NT], SlabA &sa, cons
 template <int NT, int x, class Next>
 __device__ __forceinline__ void next_a(RawA &q, int lane, float *abuf, SlabA &sa, float (&raw0)[8], Next &&issue)
 {
-    constexpr int S = 2 * NT, X0 = S * 6 / 16, X1 = S > 4 ? S - 2 : S / 2;
+    constexpr int S = 2 * NT, X0 = S / 2, X1 = S > 4 ? S - 2 : S / 2;
     if constexpr (x == X0) {
         wave_sync_lds();
         stage_a(q, lane, abuf);
@@ -257,7 +280,7 @@ __device__ __forceinline__ void first_a(RawA &q, int lane, float *abuf, SlabA &s
 // through the wavefront's LDS buffer and leaves with 8 lanes per row, a whole line per row where rows are aligned.
 // PLAIN: as it is, without bias and ReLU.
 template <int NT, bool PLAIN>
-__device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc)[NT], float *cbuf, int64_t m0, int n0, int lane)
+__device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc)[NT], const float *bias, float *cbuf, int64_t m0, int n0, int lane)
 {
     const int m = lane & 31, h = lane >> 5, c = (lane & 7) * 4;
     const int rows = static_cast<int>(p.n_rows - m0 < 32 ? p.n_rows - m0 : 32);
@@ -271,20 +294,18 @@ __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc
             *reinterpret_cast<float4 *>(cbuf + m * kLda + 8 * q + 4 * h) = make_float4(acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]);
         wave_sync_lds();
         const int col = n0 + t * 32 + c;
-        float b[4] = {0.f, 0.f, 0.f, 0.f};
-        if (!PLAIN && p.bias) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (col + e < p.d_out) b[e] = p.bias[col + e];
-        }
+        const float4 b = *reinterpret_cast<const float4 *>(bias + t * 32 + c);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int r = j * 8 + (lane >> 3);
             const float4 x = *reinterpret_cast<const float4 *>(cbuf + r * kLda + c);
-            float v[4] = {x.x + b[0], x.y + b[1], x.z + b[2], x.w + b[3]};
-            if (!PLAIN && p.relu) {
+            float v[4] = {x.x, x.y, x.z, x.w};
+            if (!PLAIN) {
+                v[0] += b.x; v[1] += b.y; v[2] += b.z; v[3] += b.w;
+                if (p.relu) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+                    for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+                }
             }
             if (r >= rows || col >= p.d_out) continue;
             char *at = base + (static_cast<uint32_t>(r) * static_cast<uint32_t>(p.ld_out) + static_cast<uint32_t>(t * 32 + c)) * static_cast<uint32_t>(esz);
@@ -313,11 +334,11 @@ __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc
     }
 }
 
-// Row softmax on the accumulators (bias first), for outputs whose whole row one wavefront holds: row m lies in lanes m and
+// Row softmax on the accumulators (scale and bias first), for outputs whose whole row one wavefront holds: row m lies in lanes m and
 // m + 32, so maximum and sum need one exchange.  Saves the pass that would read and write every row again
 // (row_softmax_kernel: 7 us of a 65 us two-layer GCN on 30 k nodes).
 template <int NT>
-__device__ __forceinline__ void softmax_rows(const UpdArgs &p, f32x16 (&acc)[NT], int lane)
+__device__ __forceinline__ void softmax_rows(const UpdArgs &p, f32x16 (&acc)[NT], const float *bias, int lane)
 {
     const int h = lane >> 5;
     float m = -INFINITY;
@@ -327,7 +348,7 @@ __device__ __forceinline__ void softmax_rows(const UpdArgs &p, f32x16 (&acc)[NT]
         for (int r = 0; r < 16; ++r) {
             const int col = t * 32 + 8 * (r / 4) + 4 * h + r % 4;
             if (col < p.d_out) {
-                if (p.bias) acc[t][r] += p.bias[col];
+                acc[t][r] += bias[col];
             } else {
                 acc[t][r] = -INFINITY;
             }
@@ -354,7 +375,7 @@ __device__ __forceinline__ void softmax_rows(const UpdArgs &p, f32x16 (&acc)[NT]
 // The tile once more with the fp32 instruction, operands straight from global memory (any magnitude), NT*32 columns at a
 // time over what store_lines has written (the same lanes write the same places, so the order is theirs).
 template <int NT, bool SOFTMAX>
-__device__ __forceinline__ void exact_tile(const UpdArgs &p, float *cbuf, int64_t m0, int n0, int n_end, int lane)
+__device__ __forceinline__ void exact_tile(const UpdArgs &p, const float *bias, float *cbuf, int64_t m0, int n0, int n_end, int lane)
 {
     const int i = lane & 31, h = lane >> 5;
     if (m0 >= p.n_rows) return;                              // a wavefront of the last row tile that has no rows
@@ -362,7 +383,7 @@ __device__ __forceinline__ void exact_tile(const UpdArgs &p, float *cbuf, int64_
     const char *A = reinterpret_cast<const char *>(static_cast<const float *>(p.a) + m0 * p.ld_a), *W = static_cast<const char *>(p.w);
     const uint32_t aoff = (static_cast<uint32_t>(min(i, rows - 1)) * static_cast<uint32_t>(p.ld_a) + static_cast<uint32_t>(h)) * 4u;
 #pragma unroll 1
-    for (; n0 < n_end && n0 < p.d_out; n0 += NT * 32) {
+    for (const int first = n0; n0 < n_end && n0 < p.d_out; n0 += NT * 32) {
         f32x16 acc[NT];
         uint32_t woff[NT];
 #pragma unroll
@@ -381,22 +402,22 @@ __device__ __forceinline__ void exact_tile(const UpdArgs &p, float *cbuf, int64_
                 acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf, af, acc[t], 0, 0, 0);
             }
         }
-        if constexpr (SOFTMAX) softmax_rows<NT>(p, acc, lane);
-        store_lines<NT, SOFTMAX>(p, acc, cbuf, m0, n0, lane);
+        if constexpr (SOFTMAX) softmax_rows<NT>(p, acc, bias, lane);
+        store_lines<NT, SOFTMAX>(p, acc, bias + (n0 - first), cbuf, m0, n0, lane);
     }
 }
 
-// The tile's sums without the scale; true where one is an infinity or a NaN.
+// The tile's sums, hi + lo without the scale; true where one is an infinity or a NaN.
 template <int NT>
-__device__ __forceinline__ bool unscale(f32x16 (&acc)[NT])
+__device__ __forceinline__ bool combine(f32x16 (&hi)[NT], const f32x16 (&lo)[NT])
 {
     float z = 0.f;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            acc[t][r] *= kUnscale;
-            z = fmaf(acc[t][r], 0.f, z);
+            hi[t][r] = (hi[t][r] + lo[t][r]) * kUnscale;
+            z = fmaf(hi[t][r], 0.f, z);
         }
     return __ballot(z != 0.f) != 0;
 }
@@ -405,7 +426,11 @@ __device__ __forceinline__ bool unscale(f32x16 (&acc)[NT])
 // the accumulators need; the epilogue works on a copy the compiler cannot see through.
 __device__ __forceinline__ UpdArgs opaque(UpdArgs p)
 {
-    asm volatile("" : "+s"(p.out), "+s"(p.bias), "+s"(p.d_out), "+s"(p.w), "+s"(p.a), "+s"(p.ld_out), "+s"(p.ld_a));
+    int64_t zero = 0;                                        // (the pointers themselves through asm would be flat ones)
+    asm volatile("" : "+s"(zero), "+s"(p.d_out), "+s"(p.ld_out), "+s"(p.ld_a));
+    p.out = static_cast<char *>(p.out) + zero;
+    p.w = static_cast<const char *>(p.w) + zero;
+    p.a = static_cast<const char *>(p.a) + zero;
     return p;
 }
 
@@ -415,23 +440,36 @@ __device__ __forceinline__ int opaque(int lane)
     return lane;
 }
 
-// wavefronts per SIMD the registers are cut for: 2 where the accumulators alone take 128, else two workgroups per CU
-#define MGG_SPLIT_WAVES(NT) ((NT) >= 4 ? 2 : 4)
+struct Place {
+    int col, group, groups;
+};
+
+// Column blocks of the same rows run at the same time on one XCD (workgroups b, b + 8, ...), so that A reaches its L2 once;
+// side by side where there are too few rows for that.
+__device__ __forceinline__ Place place(int n_cols)
+{
+    const int b = static_cast<int>(blockIdx.x), groups = static_cast<int>(gridDim.x) / n_cols;
+    if (groups % 8) return {b % n_cols, b / n_cols, groups};
+    return {(b >> 3) % n_cols, (b >> 3) / n_cols * 8 + (b & 7), groups};
+}
 
 template <int NT, bool SOFTMAX>
-__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(MGG_SPLIT_WAVES(NT), MGG_SPLIT_WAVES(NT))))
-void update_split_resident_kernel(const UpdArgs p)
+__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(NT >= 2 ? 2 : 4, NT >= 2 ? 2 : 4)))
+void update_split_resident_kernel(const UpdArgs p, int n_cols)
 {
     constexpr int NC = NT * 32, SLAB = w_slab_bytes(NC) / 16;
+    __shared__ __attribute__((aligned(16))) float bias[NC];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-    const int n0 = static_cast<int>(blockIdx.y) * NC;
+    const Place at = place(n_cols);
+    const int n0 = at.col * NC;
     const int n_slabs = (p.d_in + 31) / 32;
     uint4 *w = reinterpret_cast<uint4 *>(lds_split);
     float *abuf = reinterpret_cast<float *>(lds_split + n_slabs * w_slab_bytes(NC) + wave * kWaveBytes);
 
     // tiles are dealt out workgroup by workgroup, so that a small call still spreads over the chip
-    const int64_t n_tiles = (p.n_rows + 31) / 32, stride = static_cast<int64_t>(gridDim.x) * kSWaves;
-    int64_t tile = static_cast<int64_t>(wave) * gridDim.x + blockIdx.x;
+    const int64_t n_tiles = (p.n_rows + 31) / 32, stride = static_cast<int64_t>(at.groups) * kSWaves;
+    int64_t tile = static_cast<int64_t>(wave) * at.groups + at.group;
+
     RawA q[2];
     int64_t itile = tile;                                    // issue cursor: the slab requested next
     int is = 0;
@@ -441,22 +479,8 @@ void update_split_resident_kernel(const UpdArgs p)
     };
     issue(q[0]);
     issue(q[1]);
-    {
-        const int units = n_slabs * 4 * NC;
-        constexpr int B = 2;
-        for (int base = wave * kWave; base < units; base += B * kSThreads) {
-            float f[B][8];
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                load_w_unit<NC>(p, 0, base + b * kSThreads, n0, lane, f[b]);      // (past the end: the last row again, not kept)
-            }
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const int id0 = base + b * kSThreads;                             // (units is a multiple of a wavefront)
-                if (id0 < units) store_w_unit<NC>(p, 0, id0, lane, f[b], w + id0 / (4 * NC) * SLAB);
-            }
-        }
-    }
+    stage_bias<NC>(bias, p.bias ? p.bias + n0 : nullptr, p.d_out - n0);
+    stage_w<NC>(p, n_slabs, n0, wave, lane, w);
     __syncthreads();
 
     if (tile >= n_tiles) return;
@@ -465,35 +489,37 @@ void update_split_resident_kernel(const UpdArgs p)
     q[0] = q[1];
     issue(q[1]);
     do {
-        f32x16 acc[NT];
+        f32x16 acc[NT], lo[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[t][r] = lo[t][r] = 0.f;
         int s = 0;
 #pragma unroll 1
         do {
             float raw0[8];
-            multiply_slab<NT>(acc, sa, w + s * SLAB, lane, [&](auto step) __attribute__((always_inline)) {
+            multiply_slab<NT>(acc, lo, sa, w + s * SLAB, lane, [&](auto step) __attribute__((always_inline)) {
                 next_a<NT, decltype(step)::value>(q[0], lane, abuf, sa, raw0, [&]() __attribute__((always_inline)) { q[0] = q[1]; issue(q[1]); });
             });
         } while (++s < n_slabs);
-        const bool again = unscale<NT>(acc);
-        if constexpr (SOFTMAX) softmax_rows<NT>(opaque(p), acc, opaque(lane));
-        store_lines<NT, SOFTMAX>(opaque(p), acc, abuf, tile * 32, n0, opaque(lane));
-        if (again) exact_tile<SOFTMAX ? NT : 1, SOFTMAX>(opaque(p), abuf, tile * 32, n0, n0 + NC, opaque(lane));
+        const bool again = combine<NT>(acc, lo);
+        if constexpr (SOFTMAX) softmax_rows<NT>(opaque(p), acc, bias, opaque(lane));
+        store_lines<NT, SOFTMAX>(opaque(p), acc, bias, abuf, tile * 32, n0, opaque(lane));
+        if (again) exact_tile<SOFTMAX ? NT : 1, SOFTMAX>(opaque(p), bias, abuf, tile * 32, n0, n0 + NC, opaque(lane));
         tile += stride;
     } while (tile < n_tiles);
 }
 
 template <int NT>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
+void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles, int n_cols)
 {
     constexpr int NC = NT * 32, SLAB = w_slab_bytes(NC) / 16;
     constexpr int UNITS = (4 * NC + kSThreads - 1) / kSThreads;          // of a slab, per thread
+    __shared__ __attribute__((aligned(16))) float bias[NC];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-    const int n0 = static_cast<int>(blockIdx.y) * NC;
+    const Place at = place(n_cols);
+    const int n0 = at.col * NC;
     const int n_slabs = (p.d_in + 31) / 32;
     uint4 *w = reinterpret_cast<uint4 *>(lds_split);                     // two slabs
     float *abuf = reinterpret_cast<float *>(lds_split + 2 * w_slab_bytes(NC) + wave * kWaveBytes);
@@ -502,7 +528,7 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
     auto load_w = [&](int ks, int u, float (&f)[8]) { load_w_unit<NC>(p, ks * 32, unit0(u), n0, lane, f); };
     auto store_w = [&](int buf, int ks, int u, float (&f)[8]) { store_w_unit<NC>(p, ks * 32, unit0(u), lane, f, w + buf * SLAB); };
 
-    int64_t tile = blockIdx.x;                                           // the host launches at most n_tiles workgroups
+    int64_t tile = at.group;                                             // the host launches at most n_tiles groups
     auto first_row = [&](int64_t t) { return (t * kSWaves + wave) * 32; };
     RawA q;
     SlabA sa;
@@ -511,6 +537,7 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
         float wf[UNITS][8];
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) load_w(0, u, wf[u]);
+        stage_bias<NC>(bias, p.bias ? p.bias + n0 : nullptr, p.d_out - n0);
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) store_w(0, 0, u, wf[u]);
     }
@@ -519,7 +546,7 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
     int64_t itile = tile;
     int is = 0;
     auto issue = [&]() __attribute__((always_inline)) {
-        if (++is == n_slabs) { is = 0; itile += gridDim.x; }
+        if (++is == n_slabs) { is = 0; itile += at.groups; }
         load_a(p, first_row(itile), is * 32, lane, q);
     };
     issue();
@@ -527,49 +554,57 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles)
     int cur = 0;
 #pragma unroll 1
     for (;;) {
-        f32x16 acc[NT];
+        f32x16 acc[NT], lo[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-        const int64_t ntile = tile + gridDim.x;
+            for (int r = 0; r < 16; ++r) acc[t][r] = lo[t][r] = 0.f;
+        const int64_t ntile = tile + at.groups;
         int ks = 0;
 #pragma unroll 1
         do {
             const int nks = ks + 1 == n_slabs ? 0 : ks + 1;            // the slab after this one
             float raw0[8], wf[8];
-            multiply_slab<NT>(acc, sa, w + cur * SLAB, lane, [&](auto step) __attribute__((always_inline)) {
-                // W: one unit after the other through the same registers, five sixteenths of the slab in flight each
+            multiply_slab<NT>(acc, lo, sa, w + cur * SLAB, lane, [&](auto step) __attribute__((always_inline)) {
+                // W: one unit after the other through the same registers, half of the slab in flight each
                 constexpr int S = 2 * NT, x = step;
 #pragma unroll
                 for (int u = 0; u < UNITS; ++u) {
                     if (x == u * 6 * S / 16) load_w(nks, u, wf);
-                    if (x == (u * 6 + 5) * S / 16) store_w(cur ^ 1, nks, u, wf);       // the other buffer: nobody reads it before the barrier
+                    if (x == u * 6 * S / 16 + S / 2) store_w(cur ^ 1, nks, u, wf);       // the other buffer: nobody reads it before the barrier
                 }
                 next_a<NT, x>(q, lane, abuf, sa, raw0, issue);
             });
             __syncthreads();
             cur ^= 1;
         } while (++ks < n_slabs);
-        const bool again = unscale<NT>(acc);
-        store_lines<NT, false>(opaque(p), acc, abuf, first_row(tile), n0, opaque(lane));
-        if (again) exact_tile<1, false>(opaque(p), abuf, first_row(tile), n0, n0 + NC, opaque(lane));
+        const bool again = combine<NT>(acc, lo);
+        store_lines<NT, false>(opaque(p), acc, bias, abuf, first_row(tile), n0, opaque(lane));
+        if (again) exact_tile<1, false>(opaque(p), bias, abuf, first_row(tile), n0, n0 + NC, opaque(lane));
         if (ntile >= n_tiles) break;
         tile = ntile;
     }
+}
+
+// Workgroups of a column block: as many as there are row tiles, or as fit the chip beside the other column blocks.
+int groups_of(int64_t n_tiles, int64_t slots, int n_cols)
+{
+    int64_t g = std::min(n_tiles, std::max<int64_t>(1, slots / n_cols));
+    if (n_cols > 1 && g > 8 && g < n_tiles) g = g / 8 * 8;                                  // (see place)
+    return static_cast<int>(g);
 }
 
 template <int NT, bool SOFTMAX>
 hipError_t launch_resident(const UpdArgs &p, int cus, hipStream_t s)
 {
     const size_t lds = static_cast<size_t>((p.d_in + 31) / 32) * w_slab_bytes(NT * 32) + kSWaves * kWaveBytes;
-    const int gy = (p.d_out + NT * 32 - 1) / (NT * 32);
+    const int n_cols = (p.d_out + NT * 32 - 1) / (NT * 32);
     const int64_t n_tiles = (p.n_rows + 31) / 32;
-    const int64_t slots = static_cast<int64_t>(cus) * (NT < 4 && 2 * lds <= kLdsMax ? 2 : 1);
-    const dim3 grid(static_cast<unsigned>(n_tiles < slots ? n_tiles : slots), static_cast<unsigned>(gy));
+    const int64_t slots = static_cast<int64_t>(cus) * (NT < 2 && 2 * lds <= kLdsMax ? 2 : 1);
+    const dim3 grid(static_cast<unsigned>(groups_of(n_tiles, slots, n_cols)) * n_cols);
     if (lds > 48 * 1024)                                     // beyond what a launch may take unasked
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_resident_kernel<NT, SOFTMAX>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    hipLaunchKernelGGL((update_split_resident_kernel<NT, SOFTMAX>), grid, dim3(kSThreads), lds, s, p);
+    hipLaunchKernelGGL((update_split_resident_kernel<NT, SOFTMAX>), grid, dim3(kSThreads), lds, s, p, n_cols);
     return hipGetLastError();
 }
 
@@ -577,12 +612,12 @@ template <int NT>
 hipError_t launch_slab(const UpdArgs &p, int cus, hipStream_t s)
 {
     constexpr int lds = 2 * w_slab_bytes(NT * 32) + kSWaves * kWaveBytes;
-    const int gy = (p.d_out + NT * 32 - 1) / (NT * 32);
+    const int n_cols = (p.d_out + NT * 32 - 1) / (NT * 32);
     const int64_t n_tiles = (p.n_rows + 32 * kSWaves - 1) / (32 * kSWaves);
-    const dim3 grid(static_cast<unsigned>(n_tiles < cus ? n_tiles : cus), static_cast<unsigned>(gy));
+    const dim3 grid(static_cast<unsigned>(groups_of(n_tiles, cus, n_cols)) * n_cols);
     if (lds > 48 * 1024)
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_slab_kernel<NT>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    hipLaunchKernelGGL((update_split_slab_kernel<NT>), grid, dim3(kSThreads), lds, s, p, n_tiles);
+    hipLaunchKernelGGL((update_split_slab_kernel<NT>), grid, dim3(kSThreads), lds, s, p, n_tiles, n_cols);
     return hipGetLastError();
 }
 
@@ -594,9 +629,7 @@ bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, boo
     if (p.d_in < 4 || p.d_out > (1 << 20) || p.ld_a > (1 << 24) || p.ld_out > (1 << 24) || static_cast<int64_t>(p.d_in) * p.d_out > (1 << 29)) return false;
     const int64_t n_slabs = (p.d_in + 31) / 32;
     auto resident = [&](int nt) { return n_slabs * w_slab_bytes(nt * 32) + kSWaves * kWaveBytes <= kLdsMax; };
-    // As many columns per wavefront as there are (up to 256), so that A is read and split once.  Few rows: narrower
-    // column blocks side by side until the workgroups cover the chip (the rows are re-read out of the caches).
-    int nt = p.d_out > 128 ? 8 : p.d_out > 64 ? 4 : p.d_out > 32 ? 2 : 1;
+    int nt = p.d_out > 64 ? 4 : p.d_out > 32 ? 2 : 1;
     auto groups = [&](int t) { return (resident(t) ? (p.n_rows + 31) / 32 : (p.n_rows + 255) / 256) * ((p.d_out + 32 * t - 1) / (32 * t)); };
     while (nt > 1 && groups(nt) < cus) nt /= 2;
     // softmax in the epilogue where a wavefront holds whole rows in few registers; elsewhere it stays the caller's second pass
@@ -605,10 +638,9 @@ bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, boo
         *err = nt == 2 ? launch_resident<2, true>(p, cus, stream) : launch_resident<1, true>(p, cus, stream);
         *softmax = false;
     } else if (resident(nt)) {
-        *err = nt == 8 ? launch_resident<8, false>(p, cus, stream) : nt == 4 ? launch_resident<4, false>(p, cus, stream)
-             : nt == 2 ? launch_resident<2, false>(p, cus, stream) : launch_resident<1, false>(p, cus, stream);
+        *err = nt == 4 ? launch_resident<4, false>(p, cus, stream) : nt == 2 ? launch_resident<2, false>(p, cus, stream) : launch_resident<1, false>(p, cus, stream);
     }
-    else *err = nt == 8 ? launch_slab<8>(p, cus, stream) : nt == 4 ? launch_slab<4>(p, cus, stream) : nt == 2 ? launch_slab<2>(p, cus, stream) : launch_slab<1>(p, cus, stream);
+    else *err = nt == 4 ? launch_slab<4>(p, cus, stream) : nt == 2 ? launch_slab<2>(p, cus, stream) : launch_slab<1>(p, cus, stream);
     return true;
 }
 

@@ -159,3 +159,25 @@ def test_update_split_small_beside_ordinary(n, d_in, d_out):
         ref = a[:, 1:2].double() * w[1:2].double()
         out = binding.mgg_update(a, w, None, "none").double()
         assert ((out - ref).abs() <= 2.0 ** -23 * ref.abs() + 2.0 ** -149).all(), (exp_a, exp_w)
+
+
+@pytest.mark.parametrize("n,d_in,d_out", SHAPES)
+def test_update_split_sparse_rows_keep_fp32_accuracy(n, d_in, d_out):
+    """Rows with one non-zero, two, and one in sixteen: the 2-norm error is no larger than that of a plain fp32 sum (each
+    product exact, one rounding per addition), and a single product is rounded once."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    w = torch.randn(d_in, d_out, device=DEV, generator=g) * 0.1
+    x = torch.randn(n, d_in, device=DEV, generator=g)
+    first = torch.randint(0, d_in, (n, 1), device=DEV, generator=g)
+    cols = torch.arange(d_in, device=DEV)
+    masks = {"one": cols == first, "two": (cols == first) | (cols == (first + d_in // 2) % d_in), "one in 16": (cols % 16 == 5).expand(n, -1)}
+    for name, keep in masks.items():
+        a = torch.where(keep, x, torch.zeros((), device=DEV))
+        out, ref = binding.mgg_update(a, w, None, "none").double(), a.double() @ w.double()
+        plain = torch.zeros(n, d_out, device=DEV)
+        for k in keep.any(0).nonzero().flatten().tolist():
+            plain = (plain.double() + a[:, k:k + 1].double() * w[k].double()).float()
+        # (2 % for the chance in a finite sample)
+        assert (out - ref).norm() <= 1.02 * (plain.double() - ref).norm(), name
+        if name == "one":
+            assert ((out - ref).abs() <= (1 + 2.0 ** -6) * 2.0 ** -24 * ref.abs()).all()
