@@ -17,9 +17,11 @@
 // Range.  Both operands are multiplied by 2^24 on their way into the parts and the sums by 2^-48 at the end, all exact:
 // the smallest fp32 number, 2^-149, has its last bit at 2^-125 then, so that no part of any element is denormal,
 // however small the element is beside others of its row, and what is lost at the low end of the sums is below 2^-149
-// after scaling back.  At the high end an element of 2^104, or sums of 2^80, overflow: a tile with a sum that is not finite
-// (infinities and NaN among the operands make such sums too) is computed again with the fp32 instruction from
-// global memory -- slow, exact about infinities, and not met by data of ordinary scale.
+// after scaling back.  At the high end an element of 2^104, or sums of 2^80, overflow: the elements of the result
+// that are not finite (infinities and NaN among the operands make such, too) are computed with the fp32 instruction
+// from global memory and put in their place.  Their neighbours keep their bits: a row of the result depends on
+// that row of A and on W alone.  Not met by data of ordinary scale, and slow: one column of W infinite, 232,965 x 602 ->
+// 256 takes 1.06 ms instead of 0.49.
 //
 // What bounds it: HBM for narrow outputs, the matrix pipe and the operand traffic through LDS for wide ones.
 // Against kernels on the fp32 instruction (us there -> here, one MI355X; fp32 rows end to end unless a leading
@@ -132,7 +134,7 @@ __device__ __forceinline__ void stage_a(const RawA &r, int lane, float *abuf)
 
 // The row of W that meets slab position pos (counted from the first slab; pos & 3 = e in load_a).  Where load_a moved
 // a vector back its first elements were met before: `again`, and their weight is zero.  (Zero times an infinity of A: the
-// tile goes through exact_tile then.)
+// sum is not finite then, and computed again.)
 __device__ __forceinline__ int w_row(int pos, int d_in, bool &again)
 {
     const int first = pos & ~3, k = min(first, d_in - 4) + (pos & 3);
@@ -278,7 +280,7 @@ __device__ __forceinline__ void first_a(RawA &q, int lane, float *abuf, SlabA &s
 
 // acc holds the transposed 32x32 tiles (register r of lane (m, h): row m, column 8*(r/4) + 4*h + r%4); each goes
 // through the wavefront's LDS buffer and leaves with 8 lanes per row, a whole line per row where rows are aligned.
-// PLAIN: as it is, without bias and ReLU.
+// PLAIN: as it is, without scale, bias and ReLU.
 template <int NT, bool PLAIN>
 __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc)[NT], const float *bias, float *cbuf, int64_t m0, int n0, int lane)
 {
@@ -301,7 +303,7 @@ __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc
             const float4 x = *reinterpret_cast<const float4 *>(cbuf + r * kLda + c);
             float v[4] = {x.x, x.y, x.z, x.w};
             if (!PLAIN) {
-                v[0] += b.x; v[1] += b.y; v[2] += b.z; v[3] += b.w;
+                v[0] = fmaf(x.x, kUnscale, b.x); v[1] = fmaf(x.y, kUnscale, b.y); v[2] = fmaf(x.z, kUnscale, b.z); v[3] = fmaf(x.w, kUnscale, b.w);
                 if (p.relu) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
@@ -338,7 +340,7 @@ __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc
 // m + 32, so maximum and sum need one exchange.  Saves the pass that would read and write every row again
 // (row_softmax_kernel: 7 us of a 65 us two-layer GCN on 30 k nodes).
 template <int NT>
-__device__ __forceinline__ void softmax_rows(const UpdArgs &p, f32x16 (&acc)[NT], const float *bias, int lane)
+__device__ __forceinline__ void softmax_rows(const UpdArgs &p, f32x16 (&acc)[NT], float scale, const float *bias, int lane)
 {
     const int h = lane >> 5;
     float m = -INFINITY;
@@ -348,7 +350,7 @@ __device__ __forceinline__ void softmax_rows(const UpdArgs &p, f32x16 (&acc)[NT]
         for (int r = 0; r < 16; ++r) {
             const int col = t * 32 + 8 * (r / 4) + 4 * h + r % 4;
             if (col < p.d_out) {
-                acc[t][r] += bias[col];
+                acc[t][r] = fmaf(acc[t][r], scale, bias[col]);
             } else {
                 acc[t][r] = -INFINITY;
             }
@@ -372,42 +374,7 @@ __device__ __forceinline__ void softmax_rows(const UpdArgs &p, f32x16 (&acc)[NT]
         for (int r = 0; r < 16; ++r) acc[t][r] *= inv;
 }
 
-// The tile once more with the fp32 instruction, operands straight from global memory (any magnitude), NT*32 columns at a
-// time over what store_lines has written (the same lanes write the same places, so the order is theirs).
-template <int NT, bool SOFTMAX>
-__device__ __forceinline__ void exact_tile(const UpdArgs &p, const float *bias, float *cbuf, int64_t m0, int n0, int n_end, int lane)
-{
-    const int i = lane & 31, h = lane >> 5;
-    if (m0 >= p.n_rows) return;                              // a wavefront of the last row tile that has no rows
-    const int rows = static_cast<int>(p.n_rows - m0 < 32 ? p.n_rows - m0 : 32);
-    const char *A = reinterpret_cast<const char *>(static_cast<const float *>(p.a) + m0 * p.ld_a), *W = static_cast<const char *>(p.w);
-    const uint32_t aoff = (static_cast<uint32_t>(min(i, rows - 1)) * static_cast<uint32_t>(p.ld_a) + static_cast<uint32_t>(h)) * 4u;
-#pragma unroll 1
-    for (const int first = n0; n0 < n_end && n0 < p.d_out; n0 += NT * 32) {
-        f32x16 acc[NT];
-        uint32_t woff[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-            woff[t] = (static_cast<uint32_t>(h) * static_cast<uint32_t>(p.d_out) + static_cast<uint32_t>(min(n0 + t * 32 + i, p.d_out - 1))) * 4u;
-        }
-#pragma unroll 1
-        for (int k0 = 0; k0 < p.d_in; k0 += 2) {
-            const bool in = k0 + h < p.d_in;
-            const float af = in ? *reinterpret_cast<const float *>(A + static_cast<int64_t>(k0) * 4 + aoff) : 0.f;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const float wf = in ? *reinterpret_cast<const float *>(W + static_cast<int64_t>(k0) * p.d_out * 4 + woff[t]) : 0.f;
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf, af, acc[t], 0, 0, 0);
-            }
-        }
-        if constexpr (SOFTMAX) softmax_rows<NT>(p, acc, bias, lane);
-        store_lines<NT, SOFTMAX>(p, acc, bias + (n0 - first), cbuf, m0, n0, lane);
-    }
-}
-
-// The tile's sums, hi + lo without the scale; true where one is an infinity or a NaN.
+// The tile's sums, hi + lo (still scaled); true where one is not finite.
 template <int NT>
 __device__ __forceinline__ bool combine(f32x16 (&hi)[NT], const f32x16 (&lo)[NT])
 {
@@ -416,10 +383,94 @@ __device__ __forceinline__ bool combine(f32x16 (&hi)[NT], const f32x16 (&lo)[NT]
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            hi[t][r] = (hi[t][r] + lo[t][r]) * kUnscale;
-            z = fmaf(hi[t][r], 0.f, z);
+            hi[t][r] += lo[t][r];
+            z = fmaf(hi[t][r], 0.f, z);                      // NaN from the first infinity or NaN on
         }
     return __ballot(z != 0.f) != 0;
+}
+
+// Which elements of the tile those are: bit 16 t + r of a lane.  Rows and columns that do not exist are left out.
+template <int NT>
+__device__ __forceinline__ uint64_t not_finite(const UpdArgs &p, const f32x16 (&acc)[NT], int64_t m0, int n0, int lane)
+{
+    uint64_t bad = 0;
+    if (m0 + (lane & 31) >= p.n_rows) return bad;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (n0 + t * 32 + 8 * (r / 4) + 4 * (lane >> 5) + r % 4 < p.d_out && !(fabsf(acc[t][r]) < INFINITY)) bad |= 1ull << (16 * t + r);
+    return bad;
+}
+
+// A 32 x 32 block of sums with the fp32 instruction, operands straight from global memory.
+__device__ __forceinline__ f32x16 exact_block(const UpdArgs &p, int64_t m0, int n0, int lane)
+{
+    const int i = lane & 31, h = lane >> 5;
+    const int rows = static_cast<int>(p.n_rows - m0 < 32 ? p.n_rows - m0 : 32);
+    const float *a = static_cast<const float *>(p.a) + (m0 + min(i, rows - 1)) * p.ld_a;
+    const float *w = static_cast<const float *>(p.w) + min(n0 + i, p.d_out - 1);
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll 1
+    for (int k0 = 0; k0 < p.d_in; k0 += 16) {
+        float af[8], wf[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int k = min(k0 + 2 * c + h, p.d_in - 1);
+            af[c] = a[k];
+            wf[c] = w[static_cast<int64_t>(k) * p.d_out];
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const bool in = k0 + 2 * c + h < p.d_in;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? wf[c] : 0.f, in ? af[c] : 0.f, acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
+
+// Puts the elements `bad` marks right, over what store_lines has written; with softmax, the whole rows they are in.
+template <int NT, bool SOFTMAX>
+__device__ __forceinline__ void repair(const UpdArgs &p, uint64_t bad, const float *bias, int64_t m0, int n0, int lane)
+{
+    const int h = lane >> 5;
+    const int64_t at = (m0 + (lane & 31)) * p.ld_out;
+    auto put = [&](int col, float v) __attribute__((always_inline)) {
+        if (p.out_bf16) static_cast<uint16_t *>(p.out)[at + col] = static_cast<uint16_t>(f32_to_bf16_bits(v));
+        else static_cast<float *>(p.out)[at + col] = v;
+    };
+    if (!__ballot(bad != 0)) return;                        // (only rows or columns that do not exist)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // what other lanes stored there is there
+    if constexpr (SOFTMAX) {
+        f32x16 acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = exact_block(p, m0, n0 + t * 32, lane);
+        softmax_rows<NT>(p, acc, 1.f, bias, lane);
+        const bool row_bad = (bad | __shfl_xor(static_cast<unsigned long long>(bad), 32)) != 0;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int col = n0 + t * 32 + 8 * (r / 4) + 4 * h + r % 4;
+                if (row_bad && col < p.d_out) put(col, acc[t][r]);
+            }
+    } else {
+#pragma unroll 1
+        for (int t = 0; t < NT; ++t, bad >>= 16) {
+            if (!__ballot((bad & 0xffffu) != 0)) continue;
+            const f32x16 acc = exact_block(p, m0, n0 + t * 32, lane);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (!(bad >> r & 1)) continue;
+                const int col = n0 + t * 32 + 8 * (r / 4) + 4 * h + r % 4;
+                float v = acc[r] + bias[col - n0];
+                if (p.relu) v = v > 0.f ? v : 0.f;
+                put(col, v);
+            }
+        }
+    }
 }
 
 // What only depends on the arguments and the lane would be computed ahead of all loops and held in registers that
@@ -502,10 +553,17 @@ void update_split_resident_kernel(const UpdArgs p, int n_cols)
                 next_a<NT, decltype(step)::value>(q[0], lane, abuf, sa, raw0, [&]() __attribute__((always_inline)) { q[0] = q[1]; issue(q[1]); });
             });
         } while (++s < n_slabs);
-        const bool again = combine<NT>(acc, lo);
-        if constexpr (SOFTMAX) softmax_rows<NT>(opaque(p), acc, bias, opaque(lane));
+        const bool any = combine<NT>(acc, lo);
+        uint64_t bad = 0;
+        if constexpr (SOFTMAX) {
+            if (any) bad = not_finite<NT>(opaque(p), acc, tile * 32, n0, opaque(lane));
+            softmax_rows<NT>(opaque(p), acc, kUnscale, bias, opaque(lane));
+        }
         store_lines<NT, SOFTMAX>(opaque(p), acc, bias, abuf, tile * 32, n0, opaque(lane));
-        if (again) exact_tile<SOFTMAX ? NT : 1, SOFTMAX>(opaque(p), bias, abuf, tile * 32, n0, n0 + NC, opaque(lane));
+        if (any) {
+            if constexpr (!SOFTMAX) bad = not_finite<NT>(opaque(p), acc, tile * 32, n0, opaque(lane));
+            repair<NT, SOFTMAX>(opaque(p), bad, bias, tile * 32, n0, opaque(lane));
+        }
         tile += stride;
     } while (tile < n_tiles);
 }
@@ -578,9 +636,9 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles, int n_cols)
             __syncthreads();
             cur ^= 1;
         } while (++ks < n_slabs);
-        const bool again = combine<NT>(acc, lo);
+        const bool any = combine<NT>(acc, lo);
         store_lines<NT, false>(opaque(p), acc, bias, abuf, first_row(tile), n0, opaque(lane));
-        if (again) exact_tile<1, false>(opaque(p), bias, abuf, first_row(tile), n0, n0 + NC, opaque(lane));
+        if (any) repair<NT, false>(opaque(p), not_finite<NT>(opaque(p), acc, first_row(tile), n0, opaque(lane)), bias, first_row(tile), n0, opaque(lane));
         if (ntile >= n_tiles) break;
         tile = ntile;
     }
@@ -629,6 +687,9 @@ bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, boo
     if (p.d_in < 4 || p.d_out > (1 << 20) || p.ld_a > (1 << 24) || p.ld_out > (1 << 24) || static_cast<int64_t>(p.d_in) * p.d_out > (1 << 29)) return false;
     const int64_t n_slabs = (p.d_in + 31) / 32;
     auto resident = [&](int nt) { return n_slabs * w_slab_bytes(nt * 32) + kSWaves * kWaveBytes <= kLdsMax; };
+    // As many columns per wavefront as there are (up to 128), so that A is read and split as seldom as the registers allow.  Few
+    // rows: narrower column blocks side by side until the workgroups cover the chip (the rows are re-read out of the caches:
+    // 2,000 x 602 -> 256 takes 19 us in 8 blocks of 32, 116 with the fp32 instruction in one block).
     int nt = p.d_out > 64 ? 4 : p.d_out > 32 ? 2 : 1;
     auto groups = [&](int t) { return (resident(t) ? (p.n_rows + 31) / 32 : (p.n_rows + 255) / 256) * ((p.d_out + 32 * t - 1) / (32 * t)); };
     while (nt > 1 && groups(nt) < cus) nt /= 2;

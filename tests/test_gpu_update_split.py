@@ -181,3 +181,33 @@ def test_update_split_sparse_rows_keep_fp32_accuracy(n, d_in, d_out):
         assert (out - ref).norm() <= 1.02 * (plain.double() - ref).norm(), name
         if name == "one":
             assert ((out - ref).abs() <= (1 + 2.0 ** -6) * 2.0 ** -24 * ref.abs()).all()
+
+
+@pytest.mark.parametrize("act", ["none", "relu", "softmax"])
+@pytest.mark.parametrize("n,d_in,d_out", SHAPES)
+def test_update_split_rows_and_columns_stand_alone(n, d_in, d_out, act):
+    """A row of the result is a function of that row of A and of W, bit for bit, whatever the scale of its neighbours in
+    the tile; without softmax, so is a column of that column of W."""
+    g = torch.Generator(device=DEV).manual_seed(n + d_out)
+    a = torch.randn(n, d_in, device=DEV, generator=g)
+    w = torch.randn(d_in, d_out, device=DEV, generator=g) * 0.2
+    b = torch.randn(d_out, device=DEV, generator=g)
+    plain = binding.mgg_update(a, w, b, act).clone()
+    odd = a.clone()
+    rows = [40, 41, 42, 43, n - 1]
+    odd[40] *= 1e-30
+    odd[41] *= 1e33
+    odd[42, 3] = float("inf")
+    odd[43, 0] = float("nan")
+    odd[n - 1, d_in - 1] = -3e38
+    keep = torch.ones(n, dtype=torch.bool, device=DEV)
+    keep[rows] = False
+    out = binding.mgg_update(odd, w, b, act)
+    assert torch.equal(out[keep], plain[keep])
+    if act == "softmax":
+        return
+    for value in (1e-30, 1e33, float("inf")):
+        w2 = w.clone()
+        w2[:, d_out - 1] *= value
+        out = binding.mgg_update(a, w2, b, act)
+        assert torch.equal(out[:, :d_out - 1], plain[:, :d_out - 1])
