@@ -32,7 +32,7 @@
 //   1,771,062 x 256 -> 47            685 -> 505     2.9e-7 -> 0.9e-7
 //   262,144 x 64 -> 64                38 ->  28     1.5e-7 -> 0.6e-7
 //   2,000 x 602 -> 256               116 ->  19     4.4e-7 -> 1.4e-7
-//   400,000 x 32 -> 16                20 ->  21     1.0e-7 -> 0.4e-7     (HBM; the narrowest gain nothing)
+//   400,000 x 32 -> 16                20 ->  16     1.0e-7 -> 0.4e-7
 // (Six terms would take 427 us on the first and 350 on the second.)
 //
 // Layout.  Eight wavefronts; a wavefront owns 32 rows x NT*32 columns, at most 128: the two accumulators take 128
@@ -44,7 +44,8 @@
 // staging writes are conflict-free and W needs no alignment.
 //   - resident: all of W in LDS, split once per workgroup; wavefronts walk over their tiles without a barrier;
 //   - slab: two slabs of W in LDS; the next one is loaded into registers, split between the MFMAs of the
-//     current one and written to the other buffer; one barrier per slab.
+//     current one and written to the other buffer; one barrier per slab;
+//   - narrow: up to 32 columns, resident, on the 16 x 16 instruction.
 #include <algorithm>
 #include <utility>
 
@@ -505,7 +506,7 @@ __device__ __forceinline__ Place place(int n_cols)
 }
 
 template <int NT, bool SOFTMAX>
-__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(NT >= 2 ? 2 : 4, NT >= 2 ? 2 : 4)))
+__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void update_split_resident_kernel(const UpdArgs p, int n_cols)
 {
     constexpr int NC = NT * 32, SLAB = w_slab_bytes(NC) / 16;
@@ -644,6 +645,222 @@ void update_split_slab_kernel(const UpdArgs p, int64_t n_tiles, int n_cols)
     }
 }
 
+// ---- up to 32 output columns: blocks of 16 --------------------------------------------------------
+// v_mfma_f32_16x16x32_bf16 on C blocks of 16 columns: a block of 32 on the 32 x 32 instruction, its accumulators through LDS to
+// whole lines, spent more on the epilogue than HBM leaves (400,000 x 32 -> 16: 21.3 us, 16.0 so; -> 8: 19.9, 15.0; 400,000 x 64 -> 8:
+// 27.4, 23; 400,000 x 16 -> 32: 18.0, 16.4).  The accumulator of a 16 x 16 tile (register r of lane (m, g) =
+// (lane % 16, lane / 16): row m, column 4 g + r) is stored as it stands: the four lanes of a row write consecutive columns.
+// W is resident; two slabs of A on their way are all the pipelining there is, which four wavefronts per SIMD make up for.
+template <int C>
+struct Sums {
+    f32x4 v[2][C];           // [rows 0..15 and 16..31 of the tile][block of columns]
+};
+
+template <int C>
+__device__ __forceinline__ void softmax_narrow(const UpdArgs &p, f32x4 (&v)[C], int lane)
+{
+    float m = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (16 * c + 4 * (lane >> 4) + e >= p.d_out) v[c][e] = -INFINITY;
+            m = fmaxf(m, v[c][e]);
+        }
+    m = fmaxf(m, __shfl_xor(m, 16));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    float sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[c][e] = 16 * c + 4 * (lane >> 4) + e < p.d_out ? expf(v[c][e] - m) : 0.f;
+            sum += v[c][e];
+        }
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
+    const float inv = 1.f / sum;
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] *= inv;
+}
+
+__device__ __forceinline__ f32x4 activate(const UpdArgs &p, const f32x4 &sum, float scale, const f32x4 &b)
+{
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[e] = fmaf(sum[e], scale, b[e]);
+        if (p.relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
+    }
+    return v;
+}
+
+// columns col .. col + 3 of a row: those that exist, and of these the ones whose bit in `which` is set
+__device__ __forceinline__ void store4(const UpdArgs &p, const f32x4 &v, int64_t row, int col, int which)
+{
+    if (row >= p.n_rows || col >= p.d_out) return;
+    const bool whole = which == 15 && col + 4 <= p.d_out;
+    if (p.out_bf16) {
+        uint16_t *o = static_cast<uint16_t *>(p.out) + row * p.ld_out + col;
+        const uint32_t pk[2] = {f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16), f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16)};
+        if (whole) {
+            __builtin_memcpy(__builtin_assume_aligned(o, 2), pk, 8);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((which >> e & 1) && col + e < p.d_out) o[e] = static_cast<uint16_t>(pk[e / 2] >> (16 * (e & 1)));
+        }
+    } else {
+        float *o = static_cast<float *>(p.out) + row * p.ld_out + col;
+        if (whole) {
+            *reinterpret_cast<f32x4_loose *>(o) = v;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((which >> e & 1) && col + e < p.d_out) o[e] = v[e];
+        }
+    }
+}
+
+// What `repair` does, for such a tile, 16 x 16 elements at a time.
+template <int C, bool SOFTMAX>
+__device__ __forceinline__ void repair_narrow(const UpdArgs &p, const Sums<C> &sum, const float *bias, int64_t m0, int n0, int lane)
+{
+    const int i = lane & 15, g = lane >> 4;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // what was stored there is there
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const int64_t row = m0 + 16 * x + i;
+        int bad[C], any = 0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            bad[c] = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (!(fabsf(sum.v[x][c][e]) < INFINITY) && row < p.n_rows && n0 + 16 * c + 4 * g + e < p.d_out) bad[c] |= 1 << e;
+            any |= bad[c];
+        }
+        if (!__ballot(any != 0)) continue;
+        if constexpr (SOFTMAX) {                             // a row as a whole
+            any |= __shfl_xor(any, 16);
+            any |= __shfl_xor(any, 32);
+        }
+        const float *a = static_cast<const float *>(p.a) + min(row, p.n_rows - 1) * p.ld_a;
+        f32x4 v[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const float *w = static_cast<const float *>(p.w) + min(n0 + 16 * c + i, p.d_out - 1);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int k0 = 0; k0 < p.d_in; k0 += 32) {
+                float af[8], wf[8];
+#pragma unroll
+                for (int k8 = 0; k8 < 8; ++k8) {
+                    const int k = min(k0 + 4 * k8 + g, p.d_in - 1);
+                    af[k8] = a[k];
+                    wf[k8] = w[static_cast<int64_t>(k) * p.d_out];
+                }
+#pragma unroll
+                for (int k8 = 0; k8 < 8; ++k8) {
+                    const bool in = k0 + 4 * k8 + g < p.d_in;
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? wf[k8] : 0.f, in ? af[k8] : 0.f, acc, 0, 0, 0);
+                }
+            }
+            v[c] = activate(p, acc, 1.f, *reinterpret_cast<const f32x4 *>(bias + 16 * c + 4 * g));
+        }
+        if constexpr (SOFTMAX) softmax_narrow<C>(p, v, lane);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int which = SOFTMAX ? (any ? 15 : 0) : bad[c];
+            if (which) store4(p, v[c], row, n0 + 16 * c + 4 * g, which);
+        }
+    }
+}
+
+template <int C, bool SOFTMAX>
+__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void update_split_narrow_kernel(const UpdArgs p, int n_cols)
+{
+    constexpr int NC = 16 * C, SLAB = w_slab_bytes(NC) / 16;
+    __shared__ __attribute__((aligned(16))) float bias[NC];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int i = lane & 15, g = lane >> 4;
+    const Place at = place(n_cols);
+    const int n0 = at.col * NC;
+    const int n_slabs = (p.d_in + 31) / 32;
+    uint4 *w = reinterpret_cast<uint4 *>(lds_split);
+    float *abuf = reinterpret_cast<float *>(lds_split + n_slabs * w_slab_bytes(NC) + wave * kWaveBytes);
+
+    // tiles are dealt out workgroup by workgroup, so that a small call still spreads over the chip
+    const int64_t n_tiles = (p.n_rows + 31) / 32, stride = static_cast<int64_t>(at.groups) * kSWaves;
+    int64_t tile = static_cast<int64_t>(wave) * at.groups + at.group;
+    RawA q[2];
+    int64_t itile = tile;                                    // issue cursor: the slab requested next
+    int is = 0;
+    auto issue = [&](RawA &r) __attribute__((always_inline)) {
+        load_a(p, itile * 32, is * 32, lane, r);             // (past the last tile: rows are clamped)
+        if (++is == n_slabs) { is = 0; itile += stride; }
+    };
+    issue(q[0]);
+    issue(q[1]);
+    stage_bias<NC>(bias, p.bias ? p.bias + n0 : nullptr, p.d_out - n0);
+    stage_w<NC>(p, n_slabs, n0, wave, lane, w);
+    __syncthreads();
+
+    for (; tile < n_tiles; tile += stride) {
+        Sums<C> hi{}, lo{};
+#pragma unroll 1
+        for (int s = 0; s < n_slabs; ++s) {
+            Frag a[2][3];
+            stage_a(q[0], lane, abuf);
+            wave_sync_lds();
+            float raw[2][8];
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 y = *reinterpret_cast<const f32x4 *>(abuf + (16 * x + i) * kLda + 8 * g + 4 * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) raw[x][4 * h + e] = y[e];
+                }
+            wave_sync_lds();                                 // the buffer is free for the next slab
+            q[0] = q[1];
+            issue(q[1]);
+            split8(raw[0], a[0]);
+            split8(raw[1], a[1]);
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                Frag wf[3];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) wf[t].q = w[s * SLAB + t * 4 * NC + g * NC + 16 * c + i];
+                constexpr int wi[7] = {2, 1, 2, 0, 1, 1, 0}, ai[7] = {1, 2, 0, 2, 1, 0, 1};          // (multiply_slab)
+#pragma unroll
+                for (int y = 0; y < 7; ++y)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) lo.v[x][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[wi[y]].v, a[x][ai[y]].v, lo.v[x][c], 0, 0, 0);
+#pragma unroll
+                for (int x = 0; x < 2; ++x) hi.v[x][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[0].v, a[x][0].v, hi.v[x][c], 0, 0, 0);
+            }
+        }
+        float z = 0.f;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            f32x4 v[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                hi.v[x][c] += lo.v[x][c];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) z = fmaf(hi.v[x][c][e], 0.f, z);      // NaN from the first infinity or NaN on
+                v[c] = activate(p, hi.v[x][c], kUnscale, *reinterpret_cast<const f32x4 *>(bias + 16 * c + 4 * g));
+            }
+            if constexpr (SOFTMAX) softmax_narrow<C>(p, v, lane);
+#pragma unroll
+            for (int c = 0; c < C; ++c) store4(p, v[c], tile * 32 + 16 * x + i, n0 + 16 * c + 4 * g, 15);
+        }
+        if (__ballot(z != 0.f)) repair_narrow<C, SOFTMAX>(p, hi, bias, tile * 32, n0, lane);
+    }
+}
+
 // Workgroups of a column block: as many as there are row tiles, or as fit the chip beside the other column blocks.
 int groups_of(int64_t n_tiles, int64_t slots, int n_cols)
 {
@@ -658,8 +875,7 @@ hipError_t launch_resident(const UpdArgs &p, int cus, hipStream_t s)
     const size_t lds = static_cast<size_t>((p.d_in + 31) / 32) * w_slab_bytes(NT * 32) + kSWaves * kWaveBytes;
     const int n_cols = (p.d_out + NT * 32 - 1) / (NT * 32);
     const int64_t n_tiles = (p.n_rows + 31) / 32;
-    const int64_t slots = static_cast<int64_t>(cus) * (NT < 2 && 2 * lds <= kLdsMax ? 2 : 1);
-    const dim3 grid(static_cast<unsigned>(groups_of(n_tiles, slots, n_cols)) * n_cols);
+    const dim3 grid(static_cast<unsigned>(groups_of(n_tiles, cus, n_cols)) * n_cols);
     if (lds > 48 * 1024)                                     // beyond what a launch may take unasked
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_resident_kernel<NT, SOFTMAX>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     hipLaunchKernelGGL((update_split_resident_kernel<NT, SOFTMAX>), grid, dim3(kSThreads), lds, s, p, n_cols);
@@ -679,6 +895,19 @@ hipError_t launch_slab(const UpdArgs &p, int cus, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int C, bool SOFTMAX>
+hipError_t launch_narrow(const UpdArgs &p, int cus, hipStream_t s)
+{
+    const size_t lds = static_cast<size_t>((p.d_in + 31) / 32) * w_slab_bytes(16 * C) + kSWaves * kWaveBytes;
+    const int n_cols = (p.d_out + 16 * C - 1) / (16 * C);
+    const int64_t n_tiles = (p.n_rows + 31) / 32, slots = static_cast<int64_t>(cus) * (2 * lds <= kLdsMax ? 2 : 1);
+    const dim3 grid(static_cast<unsigned>(groups_of(n_tiles, slots, n_cols)) * n_cols);
+    if (lds > 48 * 1024)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_narrow_kernel<C, SOFTMAX>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    hipLaunchKernelGGL((update_split_narrow_kernel<C, SOFTMAX>), grid, dim3(kSThreads), lds, s, p, n_cols);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, bool *softmax, hipError_t *err)
@@ -687,6 +916,12 @@ bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, boo
     if (p.d_in < 4 || p.d_out > (1 << 20) || p.ld_a > (1 << 24) || p.ld_out > (1 << 24) || static_cast<int64_t>(p.d_in) * p.d_out > (1 << 29)) return false;
     const int64_t n_slabs = (p.d_in + 31) / 32;
     auto resident = [&](int nt) { return n_slabs * w_slab_bytes(nt * 32) + kSWaves * kWaveBytes <= kLdsMax; };
+    // One block of 16 columns where that is all (narrow, above); blocks of 32 as the smallest of the sizes below.
+    if (p.d_out <= 16 && n_slabs * w_slab_bytes(16) + kSWaves * kWaveBytes <= kLdsMax) {
+        *err = *softmax ? launch_narrow<1, true>(p, cus, stream) : launch_narrow<1, false>(p, cus, stream);
+        *softmax = false;
+        return true;
+    }
     // As many columns per wavefront as there are (up to 128), so that A is read and split as seldom as the registers allow.  Few
     // rows: narrower column blocks side by side until the workgroups cover the chip (the rows are re-read out of the caches:
     // 2,000 x 602 -> 256 takes 19 us in 8 blocks of 32, 116 with the fp32 instruction in one block).
@@ -696,10 +931,10 @@ bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, boo
     // softmax in the epilogue where a wavefront holds whole rows in few registers; elsewhere it stays the caller's second pass
     const bool fused = *softmax && nt <= 2 && p.d_out <= nt * 32 && resident(nt);
     if (fused) {
-        *err = nt == 2 ? launch_resident<2, true>(p, cus, stream) : launch_resident<1, true>(p, cus, stream);
+        *err = nt == 2 ? launch_resident<2, true>(p, cus, stream) : launch_narrow<2, true>(p, cus, stream);
         *softmax = false;
     } else if (resident(nt)) {
-        *err = nt == 4 ? launch_resident<4, false>(p, cus, stream) : nt == 2 ? launch_resident<2, false>(p, cus, stream) : launch_resident<1, false>(p, cus, stream);
+        *err = nt == 4 ? launch_resident<4, false>(p, cus, stream) : nt == 2 ? launch_resident<2, false>(p, cus, stream) : launch_narrow<2, false>(p, cus, stream);
     }
     else *err = nt == 4 ? launch_slab<4>(p, cus, stream) : nt == 2 ? launch_slab<2>(p, cus, stream) : launch_slab<1>(p, cus, stream);
     return true;

@@ -1,5 +1,5 @@
-"""Update with fp32 weights on the bf16 matrix instruction: tile edges, ragged and unaligned operands, both kernel
-forms, and magnitudes the split into bf16 parts does not cover."""
+"""Update with fp32 weights on the bf16 matrix instruction: every kernel form at its tile edges, ragged and unaligned
+operands, its accuracy on dense and sparse rows, and magnitudes out to infinities and denormals."""
 import numpy as np
 import pytest
 import torch
@@ -110,6 +110,27 @@ FORMS = {
 SHAPES = [s for v in FORMS.values() for s in v]
 
 
+def form(n, d_in, d_out):
+    """The dispatch rule of the fp32 Update, as its comment states it."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    slabs = -(-d_in // 32)
+
+    def resident(cols):
+        return slabs * 192 * cols + 8 * 4608 <= 159 * 1024
+
+    if d_out <= 16 and resident(16):
+        return "narrow1"
+    nt = 4 if d_out > 64 else 2 if d_out > 32 else 1
+    while nt > 1 and -(-n // (32 if resident(32 * nt) else 256)) * -(-d_out // (32 * nt)) < cus:
+        nt //= 2
+    return ("narrow2" if nt == 1 else f"resident{nt}") if resident(32 * nt) else f"slab{nt}"
+
+
+def test_every_form_of_the_split_kernel_has_its_shapes():
+    for name, shapes in FORMS.items():
+        assert [form(*s) for s in shapes] == [name] * len(shapes)
+
+
 def one_product_per_element(n, d_in, d_out, pairs):
     """Row r holds a single non-zero, at k = r % d_in, and W repeats a few values: every sum is one product.  The pairs (a, w)
     sit in tiles of their own from both ends, in the first, the middle and the last column; all else is 1 * 1."""
@@ -211,3 +232,53 @@ def test_update_split_rows_and_columns_stand_alone(n, d_in, d_out, act):
         w2[:, d_out - 1] *= value
         out = binding.mgg_update(a, w2, b, act)
         assert torch.equal(out[:, :d_out - 1], plain[:, :d_out - 1])
+
+
+@pytest.mark.parametrize("n,d_in,d_out", SHAPES)
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 1e30, 1e-30, 1e-37])
+def test_update_split_magnitudes_in_every_form(n, d_in, d_out, value):
+    """Rows of A in the first and the last tile, or the last column of W, of extreme magnitude."""
+    g = torch.Generator(device=DEV).manual_seed(d_in)
+    for where in ("a", "w"):
+        a = torch.rand(n, d_in, device=DEV, generator=g) + 0.5
+        w = torch.rand(d_in, d_out, device=DEV, generator=g) + 0.5
+        rows = [3, n - 1]
+        if where == "a":
+            if abs(value) < 1:
+                a[rows] *= value
+            else:
+                a[rows, d_in - 1] = value
+        elif abs(value) < 1:
+            w[:, d_out - 1] *= value
+        else:
+            w[3, d_out - 1] = value
+        out = binding.mgg_update(a, w, None, "none").double()
+        a, w = a.double(), w.double()
+        # (float64 products of 0 and what is not there do not arise: all operands are positive or the value itself)
+        ref, bound = a @ w, 2.0 * (d_in + 2) * 2.0 ** -24 * (a.abs() @ w.abs())
+        fin = torch.isfinite(ref)
+        assert torch.equal(torch.isnan(ref), torch.isnan(out))
+        assert torch.equal(ref[torch.isinf(ref)], out[torch.isinf(ref)])
+        assert ((out - ref).abs()[fin] <= bound[fin] + d_in * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 32, 33, 8193])
+@pytest.mark.parametrize("d_in,d_out", [(4, 1), (5, 3), (31, 4), (32, 15), (33, 16), (100, 17), (64, 20), (65, 31), (600, 32)])
+def test_update_split_narrow_edges(n, d_in, d_out):
+    """Up to 32 columns: every remainder of rows, k and columns, rows of A and out at any element, each activation and
+    output type; nothing past the edges."""
+    g = torch.Generator(device=DEV).manual_seed(100 * d_in + d_out + n)
+    a = place(torch.randn(n, d_in, device=DEV, generator=g), d_in + 1, 1)
+    w = place(torch.randn(d_in, d_out, device=DEV, generator=g) * 0.3, d_out, 3)
+    b = torch.randn(d_out, device=DEV, generator=g)
+    ref, bound = reference(a, w, b)
+    for act in ("none", "relu", "softmax"):
+        want = torch.relu(ref) if act == "relu" else torch.softmax(ref, 1) if act == "softmax" else ref
+        # (a softmax moves by at most half the change of its logits; 1e-6 for expf, the sum and the division)
+        tol = 1e-6 + bound.amax(1, keepdim=True) * want if act == "softmax" else bound
+        for out_dtype in (torch.float32, torch.bfloat16):
+            buf = torch.full((n + 1, d_out + 3), float("nan"), dtype=out_dtype, device=DEV)
+            binding.mgg_update(a, w, b, act, out=buf[:n, :d_out])
+            assert torch.isnan(buf[:, d_out:]).all() and torch.isnan(buf[n:]).all()
+            extra = 0 if out_dtype == torch.float32 else 2.0 ** -8 * want.abs()        # half a unit in the last place of bf16
+            assert ((buf[:n, :d_out].double().cpu() - want).abs() <= tol + extra).all(), (act, out_dtype)
