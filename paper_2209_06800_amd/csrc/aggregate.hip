@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kBlock) void fixup_kernel(const SplitRow *split_row
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (k + e < dim) {
-                    if (out_bf16) ob[e] = static_cast<uint16_t>(f32_to_bf16_bits(r[e]));
+                    if (out_bf16) ob[e] = to_bf16(r[e]);
                     else o[e] = r[e];
                 }
         }

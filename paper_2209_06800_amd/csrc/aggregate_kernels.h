@@ -115,12 +115,18 @@ __device__ __forceinline__ void store_vec(float *dst, const float (&v)[VEC])
     }
 }
 
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
+// To bf16 bits, nearest even, a NaN to a NaN, in one instruction for one value or two.  (Rounding in integers takes nine for a
+// pair and carries a NaN whose low bits are set over into -0.)
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);       // round to nearest, ties to even
-    return u >> 16;
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const f32x2 f = {lo, hi};
+    union { bf16x2 b; uint32_t u; } r;
+    r.b = __builtin_convertvector(f, bf16x2);
+    return r.u;
 }
+__device__ __forceinline__ uint16_t to_bf16(float f) { return static_cast<uint16_t>(pack_bf16(f, 0.f)); }
 
 // bf16 output: the same VEC values, rounded, as one 2*VEC-byte store
 template <int VEC>
@@ -129,11 +135,11 @@ __device__ __forceinline__ void store_vec_bf16(uint16_t *dst, const float (&v)[V
     if constexpr (VEC >= 2) {
         uint32_t pk[VEC / 2];
 #pragma unroll
-        for (int e = 0; e < VEC / 2; ++e) pk[e] = f32_to_bf16_bits(v[2 * e]) | (f32_to_bf16_bits(v[2 * e + 1]) << 16);
+        for (int e = 0; e < VEC / 2; ++e) pk[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
         if constexpr (VEC == 8) store_loose<uint4, 2>(dst, make_uint4(pk[0], pk[1], pk[2], pk[3]));
         else store_loose<uint2, 2>(dst, make_uint2(pk[0], pk[1]));
     } else {
-        dst[0] = static_cast<uint16_t>(f32_to_bf16_bits(v[0]));
+        dst[0] = to_bf16(v[0]);
     }
 }
 
@@ -354,7 +360,7 @@ __device__ __forceinline__ void write_final(const AggArgs &a, bool gcn, const Ac
 #pragma unroll
                 for (int e = 0; e < K::VEC; ++e)
                     if (col0 + e >= own0 && col0 + e < a.out_dim) {
-                        if (a.out_bf16) ob[col0 + e] = static_cast<uint16_t>(f32_to_bf16_bits(r[e]));
+                        if (a.out_bf16) ob[col0 + e] = to_bf16(r[e]);
                         else o[col0 + e] = r[e];
                     }
             }

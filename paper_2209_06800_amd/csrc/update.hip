@@ -147,7 +147,7 @@ __device__ __forceinline__ void load_a_bf16(const UpdArgs &p, const void *arow_v
                 for (int e = 0; e < 8; ++e) f[e] = k + e < p.d_in ? arow[k + e] : 0.f;
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) af[c].u[e] = f32_to_bf16_bits(f[2 * e]) | (f32_to_bf16_bits(f[2 * e + 1]) << 16);
+            for (int e = 0; e < 4; ++e) af[c].u[e] = pack_bf16(f[2 * e], f[2 * e + 1]);
         }
     }
 }
@@ -263,10 +263,10 @@ __device__ __forceinline__ void raw_to_frags(const RawB16<A_BF16> &r, Frag8 (&af
             af[c].u[0] = r.v[c].x; af[c].u[1] = r.v[c].y; af[c].u[2] = r.v[c].z; af[c].u[3] = r.v[c].w;
         } else {
             const uint4 lo = r.v[2 * c], hi = r.v[2 * c + 1];
-            af[c].u[0] = f32_to_bf16_bits(__uint_as_float(lo.x)) | (f32_to_bf16_bits(__uint_as_float(lo.y)) << 16);
-            af[c].u[1] = f32_to_bf16_bits(__uint_as_float(lo.z)) | (f32_to_bf16_bits(__uint_as_float(lo.w)) << 16);
-            af[c].u[2] = f32_to_bf16_bits(__uint_as_float(hi.x)) | (f32_to_bf16_bits(__uint_as_float(hi.y)) << 16);
-            af[c].u[3] = f32_to_bf16_bits(__uint_as_float(hi.z)) | (f32_to_bf16_bits(__uint_as_float(hi.w)) << 16);
+            af[c].u[0] = pack_bf16(__uint_as_float(lo.x), __uint_as_float(lo.y));
+            af[c].u[1] = pack_bf16(__uint_as_float(lo.z), __uint_as_float(lo.w));
+            af[c].u[2] = pack_bf16(__uint_as_float(hi.x), __uint_as_float(hi.y));
+            af[c].u[3] = pack_bf16(__uint_as_float(hi.z), __uint_as_float(hi.w));
         }
     }
 }
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(kThreads) void row_softmax_kernel(void *x, int64_t 
     for (int c = 0; c < CPL; ++c) {
         const int col = c * kWave + lane;
         if (col < d) {
-            if constexpr (BF16) static_cast<uint16_t *>(x)[row * ld + col] = static_cast<uint16_t>(f32_to_bf16_bits(v[c] * inv));
+            if constexpr (BF16) static_cast<uint16_t *>(x)[row * ld + col] = to_bf16(v[c] * inv);
             else static_cast<float *>(x)[row * ld + col] = v[c] * inv;
         }
     }

@@ -30,14 +30,8 @@ struct UpdArgs {
     int32_t out_vec_ok; // rows of out allow 16-byte (fp32) / 8-byte (bf16) stores
 };
 
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);       // round to nearest, ties to even
-    return u >> 16;
-}
-
-// two values to bf16 bits, nearest even, in one instruction (the integer form above takes nine for a pair)
+// To bf16 bits, nearest even, a NaN to a NaN, in one instruction for one value or two.  (Rounding in integers takes nine for a
+// pair and carries a NaN whose low bits are set over into -0.)
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -47,6 +41,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     r.b = __builtin_convertvector(f, bf16x2);
     return r.u;
 }
+__device__ __forceinline__ uint16_t to_bf16(float f) { return static_cast<uint16_t>(pack_bf16(f, 0.f)); }
 
 // bias -> LDS, zeros where there is none, so that an epilogue reads it without a test per column
 template <int NC>
@@ -83,13 +78,13 @@ __device__ __forceinline__ void store_tiles(const UpdArgs &p, const f32x16 (&acc
                 uint16_t *o = static_cast<uint16_t *>(p.out) + row * p.ld_out + col;
                 if (full) {
                     uint2 pk;
-                    pk.x = f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16);
-                    pk.y = f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16);
+                    pk.x = pack_bf16(v[0], v[1]);
+                    pk.y = pack_bf16(v[2], v[3]);
                     *reinterpret_cast<uint2 *>(o) = pk;
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (col + e < p.d_out) o[e] = static_cast<uint16_t>(f32_to_bf16_bits(v[e]));
+                        if (col + e < p.d_out) o[e] = to_bf16(v[e]);
                 }
             } else {
                 float *o = static_cast<float *>(p.out) + row * p.ld_out + col;

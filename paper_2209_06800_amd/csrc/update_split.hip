@@ -64,8 +64,6 @@ constexpr int kLdsMax = 160 * 1024 - 1024;                  // (beside it: the b
 constexpr float kScale = 0x1p24f, kUnscale = 0x1p-48f;       // of an operand; of a sum of products
 constexpr int w_slab_bytes(int nc) { return 3 * 4 * nc * 16; }
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 union Frag { uint32_t u[4]; uint4 q; bf16x8 v; };
 
 extern __shared__ __attribute__((aligned(16))) unsigned char lds_split[];
@@ -78,14 +76,6 @@ __device__ __forceinline__ void wave_sync_lds()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ uint32_t cvt_pk(float lo, float hi)
-{
-    const f32x2 f = {lo, hi};
-    union { bf16x2 b; uint32_t u; } r;
-    r.b = __builtin_convertvector(f, bf16x2);              // round to nearest even
-    return r.u;
-}
-
 // eight fp32 values -> three bf16 operands whose sum they are, times kScale
 __device__ __forceinline__ void split8(const float (&f)[8], Frag (&o)[3])
 {
@@ -94,7 +84,7 @@ __device__ __forceinline__ void split8(const float (&f)[8], Frag (&o)[3])
         float lo = f[2 * e] * kScale, hi = f[2 * e + 1] * kScale;
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
-            const uint32_t pk = cvt_pk(lo, hi);
+            const uint32_t pk = pack_bf16(lo, hi);
             o[s].u[e] = pk;
             if (s < 2) { lo -= __uint_as_float(pk << 16); hi -= __uint_as_float(pk & 0xffff0000u); }
         }
@@ -315,12 +305,12 @@ __device__ __forceinline__ void store_lines(const UpdArgs &p, const f32x16 (&acc
             if (p.out_bf16) {
                 uint16_t *o = reinterpret_cast<uint16_t *>(at);
                 if (col + 4 <= p.d_out) {
-                    const uint32_t pk[2] = {f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16), f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16)};
+                    const uint32_t pk[2] = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
                     __builtin_memcpy(__builtin_assume_aligned(o, 2), pk, 8);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (col + e < p.d_out) o[e] = static_cast<uint16_t>(f32_to_bf16_bits(v[e]));
+                        if (col + e < p.d_out) o[e] = to_bf16(v[e]);
                 }
             } else {
                 float *o = reinterpret_cast<float *>(at);
@@ -439,7 +429,7 @@ __device__ __forceinline__ void repair(const UpdArgs &p, uint64_t bad, const flo
     const int h = lane >> 5;
     const int64_t at = (m0 + (lane & 31)) * p.ld_out;
     auto put = [&](int col, float v) __attribute__((always_inline)) {
-        if (p.out_bf16) static_cast<uint16_t *>(p.out)[at + col] = static_cast<uint16_t>(f32_to_bf16_bits(v));
+        if (p.out_bf16) static_cast<uint16_t *>(p.out)[at + col] = to_bf16(v);
         else static_cast<float *>(p.out)[at + col] = v;
     };
     if (!__ballot(bad != 0)) return;                        // (only rows or columns that do not exist)
@@ -702,7 +692,7 @@ __device__ __forceinline__ void store4(const UpdArgs &p, const f32x4 &v, int64_t
     const bool whole = which == 15 && col + 4 <= p.d_out;
     if (p.out_bf16) {
         uint16_t *o = static_cast<uint16_t *>(p.out) + row * p.ld_out + col;
-        const uint32_t pk[2] = {f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16), f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16)};
+        const uint32_t pk[2] = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
         if (whole) {
             __builtin_memcpy(__builtin_assume_aligned(o, 2), pk, 8);
         } else {

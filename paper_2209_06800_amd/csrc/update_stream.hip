@@ -98,7 +98,7 @@ __device__ __forceinline__ void store_tile_lines(const UpdArgs &p, const f32x16 
                     } else {
 #pragma unroll
                         for (int e = 0; e < EPL; ++e)
-                            if (col + e < p.d_out) o[e] = static_cast<uint16_t>(f32_to_bf16_bits(v[e]));
+                            if (col + e < p.d_out) o[e] = to_bf16(v[e]);
                     }
                 } else {
                     float *o = static_cast<float *>(p.out) + row * p.ld_out + col;

@@ -370,6 +370,53 @@ def test_aggregate_bf16_output_is_the_rounded_fp32_output(dim, bf16_in, mode, bu
         part.destroy()
 
 
+NAN_BITS = (0x7fffffff, -1, 0x7f800001, 0x7fc00000)       # quiet and signalling, low bits set or not
+
+
+def nan_of(bits):
+    return torch.tensor([bits], dtype=torch.int32, device=DEV).view(torch.float32)
+
+
+@pytest.mark.parametrize("dim,mode,build", [(64, "gcn", {}), (47, "gin", dict(ps=7, dist=2)), (2, "gcn", {}), (602, "gin", dict(xcd_min_deg=30))])
+def test_aggregate_bf16_output_keeps_nan(dim, mode, build):
+    """A NaN of any bits in a table is a NaN in every bf16 output row it reaches, as in the fp32 output."""
+    row_ptr, col, rng = small_rmat(seed=32)
+    n = row_ptr.size - 1
+    bounds = inputs.equal_node_bounds(n, 2)
+    x = to_dev(rng.standard_normal((n, dim)).astype(np.float32))
+    for i, bits in enumerate(NAN_BITS):
+        x[i::97, i % dim] = nan_of(bits)
+    part = binding.mgg_build_partition(row_ptr, col, 2, 0, bounds, **build)
+    hg = torch.from_numpy(part.export()["halo_gid"].astype(np.int64)).to(DEV)
+    f32 = binding.mgg_aggregate(part, mode, x[:bounds[1]].contiguous(), x[hg].contiguous(), eps=0.5)
+    b16 = binding.mgg_aggregate(part, mode, x[:bounds[1]].contiguous(), x[hg].contiguous(), eps=0.5, out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    assert torch.isnan(f32).any() and torch.equal(torch.isnan(f32), torch.isnan(b16))
+    part.destroy()
+
+
+@pytest.mark.parametrize("d_in,d_out,w_bf16", [(64, 70, True), (64, 64, True), (50, 20, True), (50, 300, True), (64, 70, False), (64, 16, False),
+                                               (3, 40, False)])
+def test_update_to_bf16_keeps_nan(d_in, d_out, w_bf16):
+    """A NaN of any bits in a row of A or in the bias is a NaN in bf16 output, in whole vectors and in the columns
+    left over; the rest does not change."""
+    g = torch.Generator(device=DEV).manual_seed(d_out)
+    a = torch.randn(100, d_in, device=DEV, generator=g)
+    w = torch.randn(d_in, d_out, device=DEV, generator=g).to(torch.bfloat16 if w_bf16 else torch.float32)
+    b = torch.randn(d_out, device=DEV, generator=g)
+    plain = binding.mgg_update(a, w, b, "none", out_dtype=torch.bfloat16)
+    for bits in NAN_BITS:
+        a2, b2 = a.clone(), b.clone()
+        a2[[7, 99], d_in - 1] = nan_of(bits)
+        b2[[0, d_out // 2, d_out - 1]] = nan_of(bits)
+        want = torch.zeros(100, d_out, dtype=torch.bool, device=DEV)
+        want[[7, 99]] = True
+        want[:, [0, d_out // 2, d_out - 1]] = True
+        out = binding.mgg_update(a2, w, b2, "none", out_dtype=torch.bfloat16)
+        assert torch.equal(torch.isnan(out), want), hex(bits)
+        assert torch.equal(out[~want], plain[~want])
+
+
 # ----------------------------------------------------------------------------- update
 def update_bound(a64, w64, k, bf16):
     s = np.abs(a64) @ np.abs(w64)
