@@ -233,9 +233,10 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     if (out_dim <= 0) out_dim = dim;
     int vec = bf16 ? 8 : 4;
     int32_t last_col;
+    const bool rows_aligned = ld_x % vec == 0 && aligned(x_local, 16) && aligned(xh, 16);
     {
         const int64_t padded = (static_cast<int64_t>(dim) + vec - 1) / vec * vec;
-        if (padded <= ld_x && ld_x % vec == 0 && aligned(x_local, 16) && aligned(xh, 16)) {
+        if (rows_aligned && padded <= ld_x) {
             dim = static_cast<int32_t>(padded);
         } else if (dim < vec) {
             vec = 1;
@@ -345,7 +346,8 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
         int grid_x = a.n_item_blocks + static_cast<int>((short_waves + wpb - 1) / wpb);
         if (n_slabs > 1) grid_x = (grid_x + kXcd - 1) / kXcd * kXcd;   // keeps workgroup x on XCD x mod 8 in every slab
         const dim3 grid(static_cast<unsigned>(grid_x), static_cast<unsigned>(n_slabs));
-        const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty();
+        // (16-byte loads from memory into LDS want aligned addresses, unlike those into registers)
+        const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned;
         if (grid_x > 0) {
             hipError_t e;
             if (bf16) e = launch_aggregate_bf16(a, gcn, vec, grid, wpb, stream, lpr, ch, lds);

@@ -289,6 +289,19 @@ def test_lds_staged_halo_rows_give_the_same_answer(lds_halo, dim, bf16, build):
         check_aggregate(row_ptr, col, 4, p, bounds, x, mode, build=build, what=f"lds dim {dim} {build} part {p}")
 
 
+@pytest.mark.parametrize("dim,bf16,misalign", [(129, True, 1), (64, True, 1), (130, True, 0), (128, True, 3), (75, False, 0), (64, False, 1), (66, False, 2)])
+def test_lds_staged_halo_rows_at_any_element_boundary(dim, bf16, misalign):
+    """With the switch on, tables whose rows are not 16-byte aligned go through registers: the same bits as with it off."""
+    row_ptr, col, rng = small_rmat(seed=310 + dim)
+    n = row_ptr.size - 1
+    x = rng.standard_normal((n, dim)).astype(np.float32)
+    if bf16:
+        x = inputs.to_bf16_bits(x)
+    bounds = inputs.equal_node_bounds(n, 4)
+    got = [check_aggregate(row_ptr, col, 4, 0, bounds, x, "gin", misalign=misalign, options={"lds_halo": on}, what=f"lds {on} dim {dim}") for on in (0, 1)]
+    assert np.array_equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("slab_bytes", [64, 128, 256, 1024])
 @pytest.mark.parametrize("dim,bf16", [(64, False), (100, False), (602, False), (608, False), (47, False), (128, True), (520, True), (130, True)])
 def test_column_slab_passes_give_the_same_answer(slab_bytes, dim, bf16):
