@@ -221,8 +221,9 @@ __device__ __forceinline__ void fill_w_bf16_t(uint16_t *lds, int ldw, const uint
 // not covered and nothing was launched.
 bool launch_update_stream(const upd::UpdArgs &p, bool w_bf16, bool a_bf16, int cus, hipStream_t stream, hipError_t *err);
 
-// fp32 weights on the bf16 matrix instruction (update_split.hip); returns false when the shape is not
-// covered (d_in < 4) and nothing was launched.  *softmax: a row softmax is wanted; cleared if the kernel does it.
+// fp32 weights on the bf16 matrix instruction (update_split.hip); returns false, with nothing launched, when the shape is
+// not covered: d_in < 4, or offsets that 32 bits do not hold (leading dimensions above 2^24, more than 2^20 columns, W of
+// more than 2^29 elements).  *softmax: a row softmax is wanted; cleared if the kernel does it.
 bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, bool *softmax, hipError_t *err);
 
 // Two linears with bf16 weights in one kernel, hidden tile kept in registers (update_stream.hip);

@@ -31,7 +31,7 @@
 //   306,128 x 100 -> 256             231 -> 160     1.8e-7 -> 0.6e-7
 //   1,771,062 x 256 -> 47            685 -> 505     2.9e-7 -> 0.9e-7
 //   262,144 x 64 -> 64                38 ->  28     1.5e-7 -> 0.6e-7
-//   2,000 x 602 -> 256               116 ->  19     4.4e-7 -> 1.4e-7
+//   2,000 x 602 -> 256               116 ->  17     4.4e-7 -> 1.4e-7
 //   400,000 x 32 -> 16                20 ->  16     1.0e-7 -> 0.4e-7
 // (Six terms would take 427 us on the first and 350 on the second.)
 //
@@ -495,8 +495,9 @@ __device__ __forceinline__ Place place(int n_cols)
     return {(b >> 3) % n_cols, (b >> 3) / n_cols * 8 + (b & 7), groups};
 }
 
+// (wavefronts per SIMD the registers are cut for: two; four, two workgroups per CU, with accumulators of 32 registers)
 template <int NT, bool SOFTMAX>
-__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(NT >= 2 ? 2 : 4, NT >= 2 ? 2 : 4)))
 void update_split_resident_kernel(const UpdArgs p, int n_cols)
 {
     constexpr int NC = NT * 32, SLAB = w_slab_bytes(NC) / 16;
@@ -714,7 +715,7 @@ __device__ __forceinline__ void store4(const UpdArgs &p, const f32x4 &v, int64_t
 
 // What `repair` does, for such a tile, 16 x 16 elements at a time.
 template <int C, bool SOFTMAX>
-__device__ __forceinline__ void repair_narrow(const UpdArgs &p, const Sums<C> &sum, const float *bias, int64_t m0, int n0, int lane)
+__device__ __forceinline__ void repair_narrow(const UpdArgs &p, const Sums<C> &sum, const float *bias, int64_t m0, int lane)
 {
     const int i = lane & 15, g = lane >> 4;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // what was stored there is there
@@ -727,7 +728,7 @@ __device__ __forceinline__ void repair_narrow(const UpdArgs &p, const Sums<C> &s
             bad[c] = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (!(fabsf(sum.v[x][c][e]) < INFINITY) && row < p.n_rows && n0 + 16 * c + 4 * g + e < p.d_out) bad[c] |= 1 << e;
+                if (!(fabsf(sum.v[x][c][e]) < INFINITY) && row < p.n_rows && 16 * c + 4 * g + e < p.d_out) bad[c] |= 1 << e;
             any |= bad[c];
         }
         if (!__ballot(any != 0)) continue;
@@ -739,7 +740,7 @@ __device__ __forceinline__ void repair_narrow(const UpdArgs &p, const Sums<C> &s
         f32x4 v[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const float *w = static_cast<const float *>(p.w) + min(n0 + 16 * c + i, p.d_out - 1);
+            const float *w = static_cast<const float *>(p.w) + min(16 * c + i, p.d_out - 1);
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
             for (int k0 = 0; k0 < p.d_in; k0 += 32) {
@@ -762,28 +763,26 @@ __device__ __forceinline__ void repair_narrow(const UpdArgs &p, const Sums<C> &s
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int which = SOFTMAX ? (any ? 15 : 0) : bad[c];
-            if (which) store4(p, v[c], row, n0 + 16 * c + 4 * g, which);
+            if (which) store4(p, v[c], row, 16 * c + 4 * g, which);
         }
     }
 }
 
 template <int C, bool SOFTMAX>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void update_split_narrow_kernel(const UpdArgs p, int n_cols)
+void update_split_narrow_kernel(const UpdArgs p)
 {
     constexpr int NC = 16 * C, SLAB = w_slab_bytes(NC) / 16;
     __shared__ __attribute__((aligned(16))) float bias[NC];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int i = lane & 15, g = lane >> 4;
-    const Place at = place(n_cols);
-    const int n0 = at.col * NC;
     const int n_slabs = (p.d_in + 31) / 32;
     uint4 *w = reinterpret_cast<uint4 *>(lds_split);
     float *abuf = reinterpret_cast<float *>(lds_split + n_slabs * w_slab_bytes(NC) + wave * kWaveBytes);
 
     // tiles are dealt out workgroup by workgroup, so that a small call still spreads over the chip
-    const int64_t n_tiles = (p.n_rows + 31) / 32, stride = static_cast<int64_t>(at.groups) * kSWaves;
-    int64_t tile = static_cast<int64_t>(wave) * at.groups + at.group;
+    const int64_t n_tiles = (p.n_rows + 31) / 32, stride = static_cast<int64_t>(gridDim.x) * kSWaves;
+    int64_t tile = static_cast<int64_t>(wave) * gridDim.x + blockIdx.x;
     RawA q[2];
     int64_t itile = tile;                                    // issue cursor: the slab requested next
     int is = 0;
@@ -793,8 +792,8 @@ void update_split_narrow_kernel(const UpdArgs p, int n_cols)
     };
     issue(q[0]);
     issue(q[1]);
-    stage_bias<NC>(bias, p.bias ? p.bias + n0 : nullptr, p.d_out - n0);
-    stage_w<NC>(p, n_slabs, n0, wave, lane, w);
+    stage_bias<NC>(bias, p.bias, p.d_out);
+    stage_w<NC>(p, n_slabs, 0, wave, lane, w);
     __syncthreads();
 
     for (; tile < n_tiles; tile += stride) {
@@ -845,9 +844,9 @@ void update_split_narrow_kernel(const UpdArgs p, int n_cols)
             }
             if constexpr (SOFTMAX) softmax_narrow<C>(p, v, lane);
 #pragma unroll
-            for (int c = 0; c < C; ++c) store4(p, v[c], tile * 32 + 16 * x + i, n0 + 16 * c + 4 * g, 15);
+            for (int c = 0; c < C; ++c) store4(p, v[c], tile * 32 + 16 * x + i, 16 * c + 4 * g, 15);
         }
-        if (__ballot(z != 0.f)) repair_narrow<C, SOFTMAX>(p, hi, bias, tile * 32, n0, lane);
+        if (__ballot(z != 0.f)) repair_narrow<C, SOFTMAX>(p, hi, bias, tile * 32, lane);
     }
 }
 
@@ -865,7 +864,8 @@ hipError_t launch_resident(const UpdArgs &p, int cus, hipStream_t s)
     const size_t lds = static_cast<size_t>((p.d_in + 31) / 32) * w_slab_bytes(NT * 32) + kSWaves * kWaveBytes;
     const int n_cols = (p.d_out + NT * 32 - 1) / (NT * 32);
     const int64_t n_tiles = (p.n_rows + 31) / 32;
-    const dim3 grid(static_cast<unsigned>(groups_of(n_tiles, cus, n_cols)) * n_cols);
+    const int64_t slots = static_cast<int64_t>(cus) * (NT < 2 && 2 * lds <= kLdsMax ? 2 : 1);
+    const dim3 grid(static_cast<unsigned>(groups_of(n_tiles, slots, n_cols)) * n_cols);
     if (lds > 48 * 1024)                                     // beyond what a launch may take unasked
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_resident_kernel<NT, SOFTMAX>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     hipLaunchKernelGGL((update_split_resident_kernel<NT, SOFTMAX>), grid, dim3(kSThreads), lds, s, p, n_cols);
@@ -889,12 +889,11 @@ template <int C, bool SOFTMAX>
 hipError_t launch_narrow(const UpdArgs &p, int cus, hipStream_t s)
 {
     const size_t lds = static_cast<size_t>((p.d_in + 31) / 32) * w_slab_bytes(16 * C) + kSWaves * kWaveBytes;
-    const int n_cols = (p.d_out + 16 * C - 1) / (16 * C);
     const int64_t n_tiles = (p.n_rows + 31) / 32, slots = static_cast<int64_t>(cus) * (2 * lds <= kLdsMax ? 2 : 1);
-    const dim3 grid(static_cast<unsigned>(groups_of(n_tiles, slots, n_cols)) * n_cols);
+    const dim3 grid(static_cast<unsigned>(std::min(n_tiles, slots)));
     if (lds > 48 * 1024)
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&update_split_narrow_kernel<C, SOFTMAX>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    hipLaunchKernelGGL((update_split_narrow_kernel<C, SOFTMAX>), grid, dim3(kSThreads), lds, s, p, n_cols);
+    hipLaunchKernelGGL((update_split_narrow_kernel<C, SOFTMAX>), grid, dim3(kSThreads), lds, s, p);
     return hipGetLastError();
 }
 
@@ -905,27 +904,28 @@ bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, boo
     // a row shorter than a 16-byte vector, or 32-bit offsets inside W or a 32-row tile of A or out that could overflow
     if (p.d_in < 4 || p.d_out > (1 << 20) || p.ld_a > (1 << 24) || p.ld_out > (1 << 24) || static_cast<int64_t>(p.d_in) * p.d_out > (1 << 29)) return false;
     const int64_t n_slabs = (p.d_in + 31) / 32;
-    auto resident = [&](int nt) { return n_slabs * w_slab_bytes(nt * 32) + kSWaves * kWaveBytes <= kLdsMax; };
-    // One block of 16 columns where that is all (narrow, above); blocks of 32 as the smallest of the sizes below.
-    if (p.d_out <= 16 && n_slabs * w_slab_bytes(16) + kSWaves * kWaveBytes <= kLdsMax) {
-        *err = *softmax ? launch_narrow<1, true>(p, cus, stream) : launch_narrow<1, false>(p, cus, stream);
+    auto resident = [&](int cols) { return n_slabs * w_slab_bytes(cols) + kSWaves * kWaveBytes <= kLdsMax; };
+    // The matrix instruction and the place of the softmax decide how a sum is rounded: they depend on d_in and d_out alone,
+    // so that a row has the same bits in a call of any number of rows.  Up to 32 columns: the narrow form where W fits.
+    if (p.d_out <= 32 && resident(p.d_out <= 16 ? 16 : 32)) {
+        if (p.d_out <= 16) *err = *softmax ? launch_narrow<1, true>(p, cus, stream) : launch_narrow<1, false>(p, cus, stream);
+        else *err = *softmax ? launch_narrow<2, true>(p, cus, stream) : launch_narrow<2, false>(p, cus, stream);
+        *softmax = false;
+        return true;
+    }
+    // Softmax in the epilogue where a wavefront holds whole rows in few registers; elsewhere it stays the caller's second pass.
+    if (*softmax && p.d_out > 32 && p.d_out <= 64 && resident(64)) {
+        *err = launch_resident<2, true>(p, cus, stream);
         *softmax = false;
         return true;
     }
     // As many columns per wavefront as there are (up to 128), so that A is read and split as seldom as the registers allow.  Few
     // rows: narrower column blocks side by side until the workgroups cover the chip (the rows are re-read out of the caches:
-    // 2,000 x 602 -> 256 takes 19 us in 8 blocks of 32, 116 with the fp32 instruction in one block).
+    // 2,000 x 602 -> 256 takes 17.5 us in 8 blocks of 32, 116 with the fp32 instruction in one block).
     int nt = p.d_out > 64 ? 4 : p.d_out > 32 ? 2 : 1;
-    auto groups = [&](int t) { return (resident(t) ? (p.n_rows + 31) / 32 : (p.n_rows + 255) / 256) * ((p.d_out + 32 * t - 1) / (32 * t)); };
+    auto groups = [&](int t) { return (resident(32 * t) ? (p.n_rows + 31) / 32 : (p.n_rows + 255) / 256) * ((p.d_out + 32 * t - 1) / (32 * t)); };
     while (nt > 1 && groups(nt) < cus) nt /= 2;
-    // softmax in the epilogue where a wavefront holds whole rows in few registers; elsewhere it stays the caller's second pass
-    const bool fused = *softmax && nt <= 2 && p.d_out <= nt * 32 && resident(nt);
-    if (fused) {
-        *err = nt == 2 ? launch_resident<2, true>(p, cus, stream) : launch_narrow<2, true>(p, cus, stream);
-        *softmax = false;
-    } else if (resident(nt)) {
-        *err = nt == 4 ? launch_resident<4, false>(p, cus, stream) : nt == 2 ? launch_resident<2, false>(p, cus, stream) : launch_narrow<2, false>(p, cus, stream);
-    }
+    if (resident(32 * nt)) *err = nt == 4 ? launch_resident<4, false>(p, cus, stream) : nt == 2 ? launch_resident<2, false>(p, cus, stream) : launch_resident<1, false>(p, cus, stream);
     else *err = nt == 4 ? launch_slab<4>(p, cus, stream) : nt == 2 ? launch_slab<2>(p, cus, stream) : launch_slab<1>(p, cus, stream);
     return true;
 }

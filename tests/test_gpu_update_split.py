@@ -100,7 +100,8 @@ def test_update_split_softmax(n, d_in, d_out, tiny):
 # One shape for each kernel form of the dispatch (and both for a single block of columns and for several side by side).
 FORMS = {
     "narrow1": [(1000, 100, 16), (333, 64, 7)],
-    "narrow2": [(5000, 64, 24), (2000, 602, 256)],
+    "narrow2": [(5000, 64, 24), (9001, 640, 32)],
+    "resident1": [(2000, 602, 256), (301, 64, 40)],
     "resident2": [(70001, 64, 64), (9001, 64, 47)],
     "resident4": [(70003, 100, 200), (9003, 64, 128)],
     "slab4": [(70003, 257, 129), (66001, 161, 128)],
@@ -111,7 +112,7 @@ SHAPES = [s for v in FORMS.values() for s in v]
 
 
 def form(n, d_in, d_out):
-    """The dispatch rule of the fp32 Update, as its comment states it."""
+    """The dispatch rule of the fp32 Update without softmax, as its comment states it."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     slabs = -(-d_in // 32)
 
@@ -120,10 +121,12 @@ def form(n, d_in, d_out):
 
     if d_out <= 16 and resident(16):
         return "narrow1"
+    if d_out <= 32 and resident(32):
+        return "narrow2"
     nt = 4 if d_out > 64 else 2 if d_out > 32 else 1
     while nt > 1 and -(-n // (32 if resident(32 * nt) else 256)) * -(-d_out // (32 * nt)) < cus:
         nt //= 2
-    return ("narrow2" if nt == 1 else f"resident{nt}") if resident(32 * nt) else f"slab{nt}"
+    return ("resident" if resident(32 * nt) else "slab") + str(nt)
 
 
 def test_every_form_of_the_split_kernel_has_its_shapes():
@@ -282,3 +285,16 @@ def test_update_split_narrow_edges(n, d_in, d_out):
             assert torch.isnan(buf[:, d_out:]).all() and torch.isnan(buf[n:]).all()
             extra = 0 if out_dtype == torch.float32 else 2.0 ** -8 * want.abs()        # half a unit in the last place of bf16
             assert ((buf[:n, :d_out].double().cpu() - want).abs() <= tol + extra).all(), (act, out_dtype)
+
+
+@pytest.mark.parametrize("act", ["none", "softmax"])
+@pytest.mark.parametrize("d_in,d_out", [(64, 7), (100, 24), (64, 33), (100, 47), (100, 64), (320, 64), (602, 64), (602, 128), (64, 200), (602, 256)])
+def test_update_split_rows_do_not_depend_on_how_many_there_are(d_in, d_out, act):
+    """A row has the same bits in a call of any number of rows, whichever kernel form that number selects."""
+    g = torch.Generator(device=DEV).manual_seed(d_in + d_out)
+    a = torch.randn(70001, d_in, device=DEV, generator=g)
+    w = torch.randn(d_in, d_out, device=DEV, generator=g) * 0.2
+    b = torch.randn(d_out, device=DEV, generator=g)
+    whole = binding.mgg_update(a, w, b, act)
+    for n in (1, 33, 2000, 9001, 20001):
+        assert torch.equal(binding.mgg_update(a[:n], w, b, act), whole[:n]), n
