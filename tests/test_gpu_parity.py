@@ -488,9 +488,10 @@ def test_update_bf16(n_rows, d_in, d_out, a_is_bf16):
     (70000, 128, 100, False, False, False), (515, 128, 128, True, False, True), (515, 128, 128, True, True, False),
     (31, 64, 40, True, True, True), (2049, 256, 96, True, False, False), (300, 64, 128, True, True, True)])
 def test_update_whole_line_kernels(n_rows, d_in, d_out, w_bf16, a_bf16, out_bf16):
-    """Shapes the whole-line kernels cover (whole K slabs, 33..128 output columns): against the
-    oracle, and bit for bit against the register-resident kernels, which contract in the same order;
-    the output view has padded rows so that a store past the last column would be seen."""
+    """Shapes of whole K slabs and 33..128 output columns: against the oracle, with bf16 weights bit for bit
+    between the whole-line and the register-resident kernels, which contract in the same order (fp32 weights
+    take the same kernels either way: for them the two runs only say that the switch changes nothing); the
+    output view has padded rows so that a store past the last column would be seen."""
     rng = np.random.default_rng(n_rows + d_in)
     a = rng.standard_normal((n_rows, d_in)).astype(np.float32)
     w = (0.1 * rng.standard_normal((d_in, d_out))).astype(np.float32)

@@ -298,3 +298,18 @@ def test_update_split_rows_do_not_depend_on_how_many_there_are(d_in, d_out, act)
     whole = binding.mgg_update(a, w, b, act)
     for n in (1, 33, 2000, 9001, 20001):
         assert torch.equal(binding.mgg_update(a[:n], w, b, act), whole[:n]), n
+
+
+@pytest.mark.parametrize("n", [1, 129, 1000])
+@pytest.mark.parametrize("d_in,d_out", [(1, 1), (2, 32), (3, 33), (3, 64), (1, 65), (2, 128), (3, 129), (2, 256), (3, 300)])
+def test_update_of_rows_shorter_than_a_vector(n, d_in, d_out):
+    """d_in below 4 stays with the fp32 instruction: all its column widths, operands at any element."""
+    g = torch.Generator(device=DEV).manual_seed(d_in + d_out)
+    a = place(torch.randn(n, d_in, device=DEV, generator=g), d_in + 1, 1)
+    w = place(torch.randn(d_in, d_out, device=DEV, generator=g), d_out, 2)
+    b = torch.randn(d_out, device=DEV, generator=g)
+    ref, bound = reference(a, w, b)
+    buf = torch.full((n + 1, d_out + 3), float("nan"), device=DEV)
+    binding.mgg_update(a, w, b, "relu", out=buf[:n, :d_out])
+    assert torch.isnan(buf[:, d_out:]).all() and torch.isnan(buf[n:]).all()
+    assert ((buf[:n, :d_out].double().cpu() - torch.relu(ref)).abs() <= bound).all()
