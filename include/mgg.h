@@ -242,8 +242,16 @@ mgg_status_t mgg_bag_sum(const mgg_partition_t *p, mgg_dtype_t x_dtype, const vo
  * mgg_update -- section 1 (Update = a fully-connected layer), section 7 (X W, ReLU, MLP):
  *     out = act(a . w + bias)        on MFMA, fp32 accumulation.
  * a [n_rows x d_in] DEVICE, a_dtype F32 or BF16.  w [d_in x d_out] DEVICE row-major,
- * w_dtype F32 or BF16.  F32 weights need F32 input and use the fp32 MFMA; BF16 weights use
- * the bf16 MFMA and an F32 input is rounded to bf16 (nearest even) on the way in.
+ * w_dtype F32 or BF16.  BF16 weights use the bf16 MFMA and an F32 input is rounded to bf16
+ * (nearest even) on the way in.
+ * F32 weights need F32 input and keep fp32 accuracy: from d_in 4 on, operands are split into three
+ * bf16 parts each and a product is summed from eight of its nine partial products on the bf16 MFMA,
+ * which keeps it to 2^-32 of itself; measured, sums are closer to the exact ones than plain fp32
+ * sums of the same products, for dense and for sparse rows.  Elements of any magnitude keep all their bits, denormals included.  Where a
+ * sum overflows on the way (partial sums of 2^80, elements of 2^104, infinities, NaN) that element of
+ * the result is computed with the fp32 MFMA instead; many such elements are slow.  A row of the
+ * result depends on that row of a and on w and bias alone, bit for bit, not on the other
+ * rows nor on how many there are.
  * bias [d_out] DEVICE fp32 or NULL.  out [n_rows x d_out] DEVICE, out_dtype F32 or BF16
  * (rounded nearest even).  out must not alias a.
  * Errors: INVALID_ARG, UNSUPPORTED (dtype combination; softmax over more than 512 columns), HIP.
@@ -377,7 +385,8 @@ mgg_status_t mgg_tune_aggregate(int64_t num_nodes, const int64_t *row_ptr, const
  * using it is running on another thread).  mgg_set_option sets the process-wide default that partitions
  * built afterwards start from -- existing partitions keep what they have -- and the one switch of the
  * Update kernels, which have no handle to carry it.  Keys:
- *   "lds_halo"    0/1  stage halo rows through LDS ahead of accumulation  (default 0)
+ *   "lds_halo"    0/1  stage halo rows through LDS ahead of accumulation, where table rows are
+ *                      16-byte aligned (default 0)
  *   "split_phases" 0/1 aggregate the local lists and the remote lists in two launches, the
  *                      second adding to the first (no interleaving; default 0)
  *   "col_slab_bytes"   0 = automatic (default), 1 = off, or a power of two in [64, 4096]:

@@ -5,7 +5,7 @@
 //
 // Mapping, per 64-lane wavefront:
 //   - a row of an embedding table is spread over LPR lanes (LPR = 4..64, a power of two), each lane
-//     owning VEC contiguous elements per chunk (16-byte loads when the layout allows), so one load
+//     owning VEC contiguous elements per chunk (16-byte loads, at any element boundary), so one load
 //     instruction fetches NPW = 64/LPR neighbour rows;
 //   - a work item is a run of neighbour partitions (<= ps neighbours each) of ONE owned row, local and
 //     remote partitions taken alternately, so every wavefront mixes both kinds;
@@ -156,7 +156,6 @@ struct Cfg {
     static constexpr int MIN_WAVES = (!BF16_ && VEC_ == 4 && LPR_ == 16 && CH_ == 1) ? 5 : 4;
     using elem = typename std::conditional<BF16, uint16_t, float>::type;
     using raw = typename Raw<BF16, VEC>::type;
-    static constexpr int VEC_BYTES = static_cast<int>(sizeof(raw));
 };
 
 template <class K>

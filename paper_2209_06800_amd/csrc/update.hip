@@ -6,7 +6,8 @@
 //   - fp32 weights: the kernels of update_split.hip;
 //   - bf16 weights: the whole-line kernels of update_stream.hip where they apply (HBM-bound shapes with whole K
 //     slabs), else the kernels of this file -- weights resident in LDS with a grid sized to the chip, or
-//     staged slab by slab; they also take the fp32 rows too short for update_split.hip.
+//     staged slab by slab; update_f32_kernel takes the fp32 shapes update_split.hip refuses (rows shorter than four
+//     elements, leading dimensions or weight matrices beyond its 32-bit offsets).
 // In this file a workgroup of four wavefronts covers a tile of (32*WM) rows x (NT*32*WN) columns, WM*WN = 4; each
 // wavefront owns 32 rows x NT*32 columns (NT <= 4, so that three wavefronts fit a SIMD and the load phase
 // of one overlaps the MFMA phase of another):
@@ -17,7 +18,7 @@
 //     both with fp32 accumulators; bias, ReLU and the output rounding are fused.
 // MFMA sums over k in any order, so a lane takes whichever k values are contiguous for it in
 // memory as long as the A and W operands agree; that makes the direct loads of A full-width.
-// Row softmax runs as a second pass over the output.
+// Row softmax runs as a second pass over the output, unless update_split.hip has done it in the product's epilogue.
 #include <hip/hip_runtime.h>
 
 #include "update_common.h"

@@ -243,9 +243,9 @@ void update_bf16_stream_kernel(const UpdArgs p)
 // match: within every group of 16, hidden column 8 a + 4 h + e sits at position 8 h + 4 a + e.
 // What bounds it is HBM (4.2 TB/s of 5.2 that a plain copy reaches) once the epilogues are lean: bias read from LDS instead of
 // tested and loaded column by column (a lane mask per column had 400 scalar registers spilled), pairs rounded to bf16 by
-// one instruction instead of nine.  524,288 rows, 128 -> 128 -> 128, fp32 out: 166 -> 126 us from fp32 rows, 150 -> 98 us
-// from bf16 rows; 300,000 rows, 64 -> 96 -> 40: 48 -> 33 us; the same bits.  A second slab of A in flight gains nothing
-// (126 and 101 us).
+// one instruction instead of nine.  524,288 rows, 128 -> 128 -> 128, fp32 out, called back to back: 148 -> 120 us from fp32
+// rows; between events on two buffer pairs in turn 166 -> 126, and 150 -> 98 from bf16 rows; 300,000 rows, 64 -> 96 -> 40:
+// 48 -> 33 us.  A second slab of A in flight gains nothing (126 and 101 us).
 constexpr int kMlpWaves = 8;
 constexpr int kMlpThreads = kWave * kMlpWaves;
 
