@@ -26,11 +26,11 @@
 // What bounds it: HBM for narrow outputs, the matrix pipe and the operand traffic through LDS for wide ones.
 // Against kernels on the fp32 instruction (us there -> here, one MI355X; fp32 rows end to end unless a leading
 // dimension is given), and the 2-norm error against float64:
-//   232,965 x 602 (ld 608) -> 256    674 -> 489     4.4e-7 -> 1.4e-7
-//   400,000 x 250 -> 250             970 -> 402     2.8e-7 -> 0.9e-7
-//   306,128 x 100 -> 256             231 -> 160     1.8e-7 -> 0.6e-7
-//   1,771,062 x 256 -> 47            685 -> 505     2.9e-7 -> 0.9e-7
-//   262,144 x 64 -> 64                38 ->  28     1.5e-7 -> 0.6e-7
+//   232,965 x 602 (ld 608) -> 256    676 -> 494     4.4e-7 -> 1.4e-7
+//   400,000 x 250 -> 250             970 -> 405     2.8e-7 -> 0.9e-7
+//   306,128 x 100 -> 256             232 -> 157     1.8e-7 -> 0.6e-7
+//   1,771,062 x 256 -> 47            684 -> 504     2.9e-7 -> 0.9e-7
+//   262,144 x 64 -> 64                38 ->  30     1.5e-7 -> 0.6e-7
 //   2,000 x 602 -> 256               116 ->  17     4.4e-7 -> 1.4e-7
 //   400,000 x 32 -> 16                20 ->  16     1.0e-7 -> 0.4e-7
 // (Six terms would take 427 us on the first and 350 on the second.)
@@ -921,7 +921,7 @@ bool launch_update_split(const upd::UpdArgs &p, int cus, hipStream_t stream, boo
     }
     // As many columns per wavefront as there are (up to 128), so that A is read and split as seldom as the registers allow.  Few
     // rows: narrower column blocks side by side until the workgroups cover the chip (the rows are re-read out of the caches:
-    // 2,000 x 602 -> 256 takes 17.5 us in 8 blocks of 32, 116 with the fp32 instruction in one block).
+    // 2,000 x 602 -> 256 takes 16.7 us in 8 blocks of 32, 116 with the fp32 instruction in one block).
     int nt = p.d_out > 64 ? 4 : p.d_out > 32 ? 2 : 1;
     auto groups = [&](int t) { return (resident(32 * t) ? (p.n_rows + 31) / 32 : (p.n_rows + 255) / 256) * ((p.d_out + 32 * t - 1) / (32 * t)); };
     while (nt > 1 && groups(nt) < cus) nt /= 2;
