@@ -299,9 +299,8 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     }
 
     AggArgs a{};
-    a.local_row_ptr = p->d.local_row_ptr; a.local_col = p->d.local_col;
-    a.remote_row_ptr = p->d.remote_row_ptr; a.remote_col = p->d.remote_col;
-    a.dinv_own = p->d.dinv_own; a.w_local = p->d.w_local; a.w_remote = p->d.w_remote;
+    a.cols = p->d.cols; a.wts = p->d.wts;
+    a.dinv_own = p->d.dinv_own;
     a.short_desc = p->d.short_desc; a.items = p->d.items;
     a.x_local = x_local; a.x_halo = xh;
     a.out = out; a.scratch = scratch;
@@ -326,11 +325,6 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     a.n_item_blocks = static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * a.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * a.items_per_wave) * kXcd);
     a.ps = p->ps;
     const bool gcn = mode == MGG_AGG_GCN_SYM;
-    // row offsets inside a table are 32-bit unless a table reaches beyond 4 GB
-    {
-        const uint64_t rows = static_cast<uint64_t>(std::max<int64_t>(p->n_local_rows, static_cast<int64_t>(p->halo_gid.size())));
-        a.wide = rows * static_cast<uint64_t>(ld_x) * esz >= (1ull << 32) ? 1 : 0;
-    }
     a.self_w = p->bags ? 0.f : 1.f + eps;
     a.no_self = p->bags ? 1 : 0;
     a.bias = bias;

@@ -7,17 +7,18 @@
 //   - a row of an embedding table is spread over LPR lanes (LPR = 4..64, a power of two), each lane
 //     owning VEC contiguous elements per chunk (16-byte loads, at any element boundary), so one load
 //     instruction fetches NPW = 64/LPR neighbour rows;
-//   - a work item is a run of neighbour partitions (<= ps neighbours each) of ONE owned row, local and
-//     remote partitions taken alternately, so every wavefront mixes both kinds;
-//   - the ids of a partition are loaded one per lane; the lane that holds an id turns it into the byte
-//     offset of its table row once, and the offsets (and GCN factors) reach the lanes that gather
-//     through cross-lane reads.  A gather is then one add and one load with a 32-bit offset from a
-//     wave-uniform base, and the inner loop of full batches carries no predicate at all;
-//   - the NPW sub-wave accumulators are combined with cross-lane shuffles at the end;
+//   - a work item is a run of neighbours of ONE owned row, its local partitions followed by its remote ones,
+//     taken ps (<= 64) at a time, so every wavefront mixes both kinds;
+//   - the ids are loaded one per lane; the lane that holds an id turns it into the
+//     address of its table row once, and the addresses (and GCN factors) reach the lanes that gather
+//     through DPP row broadcasts, which cost no LDS access and no wait;
+//   - the NPW sub-wave accumulators are combined with lane swaps at the end;
 //   - short rows are handled one per sub-wave (several rows per wavefront);
 //   - rows cut into several items leave raw partial sums in scratch rows, and a second small kernel
 //     adds them in a fixed order (results do not depend on scheduling).
-// Bound by the memory hierarchy (about 0.5 flop per byte): no MFMA here.
+// Bound by the memory hierarchy (about 0.5 flop per byte): no MFMA here.  A bare gather loop of this form delivers
+// 28.8 TB/s of 256-byte rows out of L2 (2 MB table, ids from the Infinity Cache), 22.4 with ids from HBM, 13.5 from an
+// 8 MB table and 7.6 from 64 MB; one dword per lane and row, ids in scalar registers, stays at 18.5 TB/s out of L2.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -37,11 +38,10 @@ constexpr int kStageSlots = 8;      // LDS-staged variant: load instructions (1 
 constexpr int kStageWpb = 8;        // LDS-staged variant: most wavefronts per workgroup (a wavefront owns 2 stages of 8 KB)
 
 struct AggArgs {
-    const int32_t *local_row_ptr, *local_col, *remote_row_ptr, *remote_col;
+    const uint32_t *cols;                // table rows of the neighbours in the order of the work (bit 31 set: halo table)
+    const float *wts;                    // GCN: factor of the neighbour, one per entry of cols
     const float *dinv_own;               // 1/sqrt(deg+1) of the owned rows (the row factor of GCN)
-    const float *w_local, *w_remote;     // GCN: factor of the neighbour, one per entry of the column arrays
-    const int32_t *short_rows;
-    const WorkItem *items;
+    const DeviceItem *items;
     const void *x_local, *x_halo;
     void *out;               // fp32, or bf16 when out_bf16 (rounded to nearest even)
     float *scratch;
@@ -51,9 +51,8 @@ struct AggArgs {
     int32_t n_items, n_item_blocks, n_short;
     int32_t items_per_wave;  // work items a wavefront takes one after the other (M)
     int32_t short_per_wave;  // groups of 64/LPR short rows a wavefront takes one after the other
-    const int4 *short_desc;  // per short row: row, start in local_col, start in remote_col, local count | remote count << 16
+    const int4 *short_desc;  // per short row: row, start in cols, local neighbours, all neighbours
     int32_t ps;
-    int32_t wide;            // a table reaches beyond 4 GB: row offsets are 64-bit
     float self_w;            // GIN: 1 + eps
     int32_t out_bf16;
     int32_t no_self;         // bags: the owned row has no embedding of its own, x_local is only a table
@@ -149,7 +148,7 @@ struct Cfg {
     static constexpr bool BF16 = BF16_;
     static constexpr int VEC = VEC_, LPR = LPR_, CH = CH_;
     static constexpr int NPW = kWave / LPR;                 // neighbour rows per load instruction
-    static constexpr int U = (MGG_AGG_INFLIGHT / CH) > 0 ? (MGG_AGG_INFLIGHT / CH) : 1;   // neighbour rows in flight per lane
+    static constexpr int U = MGG_AGG_INFLIGHT / CH < LPR ? MGG_AGG_INFLIGHT / CH : LPR;   // neighbour rows in flight per lane
     // Wavefronts per SIMD the register allocation must allow.  The workgroup limit (16 wavefronts) gives 4;
     // the 256-byte fp32 variant sits one register above the budget of 5 and loses nothing when held to it
     // (2 % faster on the 602-column workload); the others would spill.
@@ -189,13 +188,14 @@ struct Acc {
 // memory, never written back), so that no load of the inner loop needs a predicate.
 template <class K>
 struct Lanes {
-    int sub;                    // which neighbour row of a load instruction
+    int sub, slot;              // which neighbour row of a load instruction; the lane's place in its sub-wave
     int lis;                    // first vector of the row this lane owns
     int vend;                   // end of the column slab (in vectors)
     uint32_t col_off[K::CH];    // byte offset of each chunk in a table row
     __device__ __forceinline__ void init(const AggArgs &a, int lane)
     {
         sub = lane / K::LPR;
+        slot = lane % K::LPR;
         lis = lane % K::LPR + static_cast<int>(blockIdx.y) * a.slab_vecs;
         vend = min(a.nvec, (static_cast<int>(blockIdx.y) + 1) * a.slab_vecs);
 #pragma unroll
@@ -203,112 +203,224 @@ struct Lanes {
     }
 };
 
-// value of lane j of the wavefront; j is wave-uniform when one row takes the whole wavefront
+// Loads from an address and an offset as global memory, aligned to an element only (an address that is the same in all
+// lanes stays in scalar registers).
+template <int ALIGN> struct Vec16;
+template <> struct Vec16<4> { typedef uint32_t type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct Vec16<2> { typedef uint32_t type __attribute__((ext_vector_type(4), aligned(2))); };
+template <class T, int ALIGN>
+__device__ __forceinline__ T load_at(uint64_t addr, uint32_t off)
+{
+    T v;
+    const auto at = reinterpret_cast<const __attribute__((address_space(1))) char *>(addr) + off;
+    if constexpr (sizeof(T) == 16) {
+        const auto q = *reinterpret_cast<const __attribute__((address_space(1))) typename Vec16<ALIGN>::type *>(at);
+        __builtin_memcpy(&v, &q, sizeof v);
+    } else {
+        v = *reinterpret_cast<const __attribute__((address_space(1))) T *>(at);
+    }
+    return v;
+}
+
+// ---- neighbours of a sub-wave: one per slot ---------------------------------------------------
+// Lane `slot` of a sub-wave holds one neighbour: the address of its table row and, for GCN, its factor.  Step T of
+// the gather takes the neighbour in slot T of every sub-wave; its address reaches the lanes of the sub-wave through
+// DPP row broadcasts (a DPP row is 16 lanes; a sub-wave of 8 or 4 lanes takes one masked broadcast per sub-wave of
+// a row, one of 32 lanes keeps its upper 16 slots in a second register so that both its rows hold all of them), or
+// through v_readlane where a row takes the whole wavefront.  Against handing offsets round with ds_bpermute this takes
+// no LDS instruction and no wait for one: with the joint runs of both tables and the order of the ids it is worth 2.16
+// against 2.30 ms on 37 M neighbours at 100 columns, 140 against 155 us on 3.2 M at 75, 0.352 against 0.374 ms on 17.8 M
+// at 64.  A broadcast reads lanes that must be active: it is never placed under a lane mask.
 template <class K>
-__device__ __forceinline__ uint32_t lane_read(uint32_t v, int j)
+struct Slots {
+    static constexpr int NR = K::LPR == 32 ? 2 : 1;
+    static constexpr int COUNT = K::LPR;
+    uint32_t lo[NR], hi[NR], w[NR];
+};
+
+template <int N, int BANKS>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t old, uint32_t v)     // lane N of every DPP row, to the lanes of BANKS
 {
-    if constexpr (K::NPW == 1) return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), j));
-    else return static_cast<uint32_t>(__shfl(static_cast<int>(v), j));
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(old), static_cast<int>(v), 0x150 + N, 0xf, BANKS, BANKS == 0xf));
 }
 
-template <class K, bool WIDE>
-__device__ __forceinline__ typename K::raw load_row_chunk(const char *table, uint32_t off_lo, uint32_t off_hi, uint32_t col)
+// slot T of the lane's sub-wave (t0 + T where a row takes the whole wavefront; t0 is wave-uniform)
+template <class K, int T>
+__device__ __forceinline__ uint32_t from_slot(const uint32_t (&v)[Slots<K>::NR], int t0)
 {
-    constexpr int AL = sizeof(typename K::elem);
-    if constexpr (WIDE) {
-        const uint64_t off = (static_cast<uint64_t>(off_hi) << 32 | off_lo) + col;
-        return load_loose<typename K::raw, AL>(table + off);
-    } else if constexpr (K::NPW == 1) {
-        return load_loose<typename K::raw, AL>((table + off_lo) + col);   // the row's address is wave-uniform
+    if constexpr (K::LPR == 64) return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v[0]), t0 + T));
+    else if constexpr (K::LPR == 32) return row_bcast<T % 16, 0xf>(0, v[T / 16]);
+    else if constexpr (K::LPR == 16) return row_bcast<T, 0xf>(0, v[0]);
+    else if constexpr (K::LPR == 8) return row_bcast<8 + T, 0xc>(row_bcast<T, 0x3>(0, v[0]), v[0]);
+    else return row_bcast<12 + T, 0x8>(row_bcast<8 + T, 0x4>(row_bcast<4 + T, 0x2>(row_bcast<T, 0x1>(0, v[0]), v[0]), v[0]), v[0]);
+}
+
+// both rows of a 32-lane sub-wave: slots 0-15 in v[0], 16-31 in v[1]
+template <class K>
+__device__ __forceinline__ void spread(uint32_t (&v)[Slots<K>::NR])
+{
+    if constexpr (K::LPR == 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v[0], v[0], false, false);
+        v[0] = r[0]; v[1] = r[1];
+    }
+}
+
+// id of a neighbour (bit 31: halo table) -> address of its table row
+template <class K>
+__device__ __forceinline__ void set_slots(Slots<K> &s, uint32_t id, float w, const char *xl, const char *xh, uint64_t ldb)
+{
+    const uint64_t base = reinterpret_cast<uint64_t>(static_cast<int32_t>(id) < 0 ? xh : xl);
+    id &= 0x7fffffffu;
+    uint64_t addr = base + static_cast<uint64_t>(id) * static_cast<uint32_t>(ldb);
+    if (ldb >> 32) addr += static_cast<uint64_t>(id * static_cast<uint32_t>(ldb >> 32)) << 32;
+    s.lo[0] = static_cast<uint32_t>(addr); s.hi[0] = static_cast<uint32_t>(addr >> 32); s.w[0] = __float_as_uint(w);
+    spread<K>(s.lo); spread<K>(s.hi); spread<K>(s.w);
+}
+
+template <class K, int T>
+__device__ __forceinline__ void load_step(const Slots<K> &s, int t0, const Lanes<K> &ln, typename K::raw (&r)[K::CH])
+{
+    const uint64_t row = static_cast<uint64_t>(from_slot<K, T>(s.hi, t0)) << 32 | from_slot<K, T>(s.lo, t0);
+#pragma unroll
+    for (int c = 0; c < K::CH; ++c) {
+        uint32_t off = ln.col_off[c];
+        if constexpr (K::LPR == 64) asm("" : "+v"(off));      // stays 32 bits wide: one instruction adds it to the scalar address
+        r[c] = load_at<typename K::raw, sizeof(typename K::elem)>(row, off);
+    }
+}
+
+// MASKED: only sub-waves with more than T neighbours in this block (cnt) add theirs; the others add exactly nothing
+template <class K, bool GCN, int T, bool MASKED>
+__device__ __forceinline__ void add_step(Acc<K> &acc, const Slots<K> &s, int t0, const typename K::raw (&r)[K::CH], int cnt)
+{
+    const float w = GCN ? __uint_as_float(from_slot<K, T>(s.w, t0)) : 1.f;
+#pragma unroll
+    for (int c = 0; c < K::CH; ++c) {
+        if constexpr (MASKED) {
+            float f[K::VEC];
+            unpack<K::BF16, K::VEC>(r[c], f);
+#pragma unroll
+            for (int e = 0; e < K::VEC; ++e) acc.v[c][e] = fmaf(w, t0 + T < cnt ? f[e] : 0.f, acc.v[c][e]);
+        } else if constexpr (GCN) {
+            acc.add(c, r[c], w);
+        } else {
+            acc.add(c, r[c]);
+        }
+    }
+}
+
+template <class K, int T0, int U>
+__device__ __forceinline__ void load_steps(const Slots<K> &s, int t0, const Lanes<K> &ln, typename K::raw (&r)[K::U][K::CH])
+{
+    if constexpr (U > 0) {
+        load_steps<K, T0, U - 1>(s, t0, ln, r);
+        load_step<K, T0 + U - 1>(s, t0, ln, r[U - 1]);
+    }
+}
+template <class K, bool GCN, int T0, int U, bool MASKED>
+__device__ __forceinline__ void add_steps(Acc<K> &acc, const Slots<K> &s, int t0, const typename K::raw (&r)[K::U][K::CH], int cnt)
+{
+    if constexpr (U > 0) {
+        add_steps<K, GCN, T0, U - 1, MASKED>(acc, s, t0, r, cnt);
+        add_step<K, GCN, T0 + U - 1, MASKED>(acc, s, t0, r[U - 1], cnt);
+    }
+}
+
+// Steps T0 .. T0 + n - 1 (n wave-uniform, 1 <= n): the loads of up to K::U of them first, then the sums.  No step that
+// has nothing to gather is issued.
+template <class K, int T0, int U, int I = 0>
+__device__ __forceinline__ void load_some(const Slots<K> &s, int t0, int n, const Lanes<K> &ln, typename K::raw (&r)[K::U][K::CH])
+{
+    if constexpr (I < U) {
+        if (I < n) {
+            load_step<K, T0 + I>(s, t0, ln, r[I]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < K::CH; ++c) __builtin_memset(&r[I][c], 0, sizeof r[I][c]);
+        }
+        load_some<K, T0, U, I + 1>(s, t0, n, ln, r);
+    }
+}
+template <class K, bool GCN, int T0, int U, bool MASKED, int I = 0>
+__device__ __forceinline__ void add_some(Acc<K> &acc, const Slots<K> &s, int t0, int n, const typename K::raw (&r)[K::U][K::CH], int cnt)
+{
+    if constexpr (I < U) {
+        if (I < n) add_step<K, GCN, T0 + I, MASKED>(acc, s, t0, r[I], cnt);
+        add_some<K, GCN, T0, U, MASKED, I + 1>(acc, s, t0, n, r, cnt);
+    }
+}
+template <class K, bool GCN, int T0, bool MASKED>
+__device__ __forceinline__ void batch(Acc<K> &acc, const Slots<K> &s, int t0, int n, const Lanes<K> &ln, int cnt)
+{
+    typename K::raw r[K::U][K::CH];
+    if (n >= K::U) {
+        load_steps<K, T0, K::U>(s, t0, ln, r);
+        __builtin_amdgcn_sched_barrier(0);          // every load is on its way before the first sum waits for one
+        add_steps<K, GCN, T0, K::U, MASKED>(acc, s, t0, r, cnt);
     } else {
-        return load_loose<typename K::raw, AL>(table + (off_lo + col));   // 32-bit offset from a uniform base
+        load_some<K, T0, K::U - 1>(s, t0, n, ln, r);
+        __builtin_amdgcn_sched_barrier(0);
+        add_some<K, GCN, T0, K::U - 1, MASKED>(acc, s, t0, n, r, cnt);
     }
 }
 
-// Accumulate one neighbour partition.  `len` (<= 64) neighbours: lane i holds the byte offset of the
-// table row of neighbour i (off_lo / off_hi) and, for GCN, its factor; sub-wave `sub` takes neighbours
-// sub, sub + NPW, ...  Batches of U load steps; the batches in which every sub-wave has a neighbour run
-// without predicates, at most one last batch clamps the neighbour index and drops what it must not add.
-template <class K, bool GCN, bool WIDE>
-__device__ __forceinline__ void accumulate_partition(Acc<K> &acc, const char *table, uint32_t off_lo, uint32_t off_hi,
-                                                     float my_w, int len, const Lanes<K> &ln)
+// n steps (n wave-uniform, 0 <= n <= COUNT) from slot T0 on, K::U at a time
+template <class K, bool GCN, bool MASKED, int T0 = 0>
+__device__ __forceinline__ void steps(Acc<K> &acc, const Slots<K> &s, int n, const Lanes<K> &ln, int cnt = 0)
 {
-    const int full_steps = len / K::NPW, steps = (len + K::NPW - 1) / K::NPW;
-    int t0 = 0;
-    for (; t0 + K::U <= full_steps; t0 += K::U) {
-        typename K::raw r[K::U][K::CH];
-        float w[K::U];
-#pragma unroll
-        for (int u = 0; u < K::U; ++u) {
-            const int j = (t0 + u) * K::NPW + ln.sub;
-            const uint32_t lo = lane_read<K>(off_lo, j);
-            const uint32_t hi = WIDE ? lane_read<K>(off_hi, j) : 0u;
-            if constexpr (GCN) w[u] = __uint_as_float(lane_read<K>(__float_as_uint(my_w), j));
-#pragma unroll
-            for (int c = 0; c < K::CH; ++c) r[u][c] = load_row_chunk<K, WIDE>(table, lo, hi, ln.col_off[c]);
+    if constexpr (K::LPR == 64) {
+        for (int t0 = 0; t0 < n; t0 += K::U) batch<K, GCN, 0, MASKED>(acc, s, t0, n - t0, ln, cnt);
+    } else if constexpr (T0 < Slots<K>::COUNT) {
+        if (n > T0) {
+            batch<K, GCN, T0, MASKED>(acc, s, 0, n - T0, ln, cnt);
+            steps<K, GCN, MASKED, T0 + K::U>(acc, s, n, ln, cnt);
         }
-#pragma unroll
-        for (int u = 0; u < K::U; ++u)
-#pragma unroll
-            for (int c = 0; c < K::CH; ++c) {
-                if constexpr (GCN) acc.add(c, r[u][c], w[u]);
-                else acc.add(c, r[u][c]);
-            }
-    }
-    if (t0 < steps) {                       // at most U steps are left
-        typename K::raw r[K::U][K::CH];
-        float w[K::U];
-        bool ok[K::U];
-#pragma unroll
-        for (int u = 0; u < K::U; ++u) {
-            const int j = (t0 + u) * K::NPW + ln.sub;
-            ok[u] = j < len;
-            const int jj = ok[u] ? j : 0;   // neighbour 0 exists: its row is valid memory
-            const uint32_t lo = lane_read<K>(off_lo, jj);
-            const uint32_t hi = WIDE ? lane_read<K>(off_hi, jj) : 0u;
-            w[u] = GCN ? __uint_as_float(lane_read<K>(__float_as_uint(my_w), jj)) : 1.f;
-            if ((t0 + u) * K::NPW < len) {  // wave-uniform
-#pragma unroll
-                for (int c = 0; c < K::CH; ++c) r[u][c] = load_row_chunk<K, WIDE>(table, lo, hi, ln.col_off[c]);
-            } else {
-#pragma unroll
-                for (int c = 0; c < K::CH; ++c) __builtin_memset(&r[u][c], 0, sizeof r[u][c]);
-                ok[u] = false;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < K::U; ++u)
-#pragma unroll
-            for (int c = 0; c < K::CH; ++c) {
-                float f[K::VEC];
-                unpack<K::BF16, K::VEC>(r[u][c], f);
-#pragma unroll
-                for (int e = 0; e < K::VEC; ++e) acc.v[c][e] = fmaf(w[u], ok[u] ? f[e] : 0.f, acc.v[c][e]);   // a dropped row adds exactly nothing
-            }
     }
 }
 
-// Ids (and GCN factors) of the partition starting at `pos`, one per lane; both arrays are read as
-// coalesced streams (the factors are stored per edge, in the order of the column array).
+// Accumulate one run of `len` (1 .. 64) neighbours of one row, neighbour i in lane i.  64 of them are taken as they
+// lie, slot by slot of every sub-wave.  Fewer are first dealt round the sub-waves (slot i of sub-wave s: neighbour
+// i NPW + s), so that all of them finish within a step of each other; what does not fill a step waits in the last
+// slot and is added under a lane mask.
+template <class K, bool GCN>
+__device__ __forceinline__ void gather_run(Acc<K> &acc, uint32_t id, float w, int len, const char *xl, const char *xh, uint64_t ldb, const Lanes<K> &ln)
+{
+    Slots<K> s;
+    if constexpr (K::NPW == 1) {
+        set_slots<K>(s, id, w, xl, xh, ldb);
+        steps<K, GCN, false>(acc, s, len, ln);
+    } else {
+        if (len == kWave) {
+            set_slots<K>(s, id, w, xl, xh, ldb);
+            steps<K, GCN, false>(acc, s, Slots<K>::COUNT, ln);
+            return;
+        }
+        const int whole = len / K::NPW, left = len % K::NPW;
+        const int from = ln.slot == K::LPR - 1 ? (ln.sub < left ? whole * K::NPW + ln.sub : 0) : ln.slot * K::NPW + ln.sub;
+        id = static_cast<uint32_t>(__shfl(static_cast<int>(id), from));
+        if constexpr (GCN) w = __shfl(w, from);
+        set_slots<K>(s, id, w, xl, xh, ldb);
+        typename K::raw last[K::CH];
+        if (left) load_step<K, K::LPR - 1>(s, 0, ln, last);
+        steps<K, GCN, false>(acc, s, whole, ln);
+        if (left) {
+            const float wl = GCN ? __uint_as_float(from_slot<K, K::LPR - 1>(s.w, 0)) : 1.f;
+            if (ln.sub < left) {
+#pragma unroll
+                for (int c = 0; c < K::CH; ++c) acc.add(c, last[c], wl);
+            }
+        }
+    }
+}
+
+// Neighbour `lane` of the `len` (1 .. 64) from position `at` on.  Lanes beyond them read the first one again: what
+// they hold is always a row of a table.  Both arrays are read as coalesced streams (the factors are stored per edge).
 template <bool GCN>
-__device__ __forceinline__ void load_partition_ids(const int32_t *col, const float *wts, int pos, int len, int lane, int &idx, float &w)
+__device__ __forceinline__ void load_run(const AggArgs &a, int at, int len, int lane, uint32_t &id, float &w)
 {
-    idx = 0; w = 0.f;
-    if (lane < len) {
-        idx = col[pos + lane];
-        if constexpr (GCN) w = wts[pos + lane];
-    }
-}
-
-template <bool WIDE>
-__device__ __forceinline__ void row_offset(int idx, uint64_t ldb, uint32_t &lo, uint32_t &hi)
-{
-    if constexpr (WIDE) {
-        const uint64_t o = static_cast<uint64_t>(static_cast<uint32_t>(idx)) * ldb;
-        lo = static_cast<uint32_t>(o); hi = static_cast<uint32_t>(o >> 32);
-    } else {
-        lo = static_cast<uint32_t>(idx) * static_cast<uint32_t>(ldb); hi = 0u;
-    }
+    const int p = lane < len ? lane : 0;
+    id = (a.cols + at)[p];
+    if constexpr (GCN) w = (a.wts + at)[p];
 }
 
 // Final value of an owned row from its neighbour sum: adds the self term and the row factor.
@@ -386,6 +498,215 @@ __device__ __forceinline__ void write_partial(const AggArgs &a, const Acc<K> &ac
     }
 }
 
+// combine the sub-wave accumulators: lanes with equal `lis` hold the same columns
+template <class K>
+__device__ __forceinline__ float sum_subwaves(float v)
+{
+    if constexpr (K::LPR <= 8) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true));    // row_ror:8
+    if constexpr (K::LPR <= 4) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, true));    // row_ror:4
+    if constexpr (K::LPR <= 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    if constexpr (K::LPR <= 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    return v;
+}
+
+// ---- the kernel -----------------------------------------------------------------------------------
+// One work item after the other, M (a.items_per_wave) per wavefront, as a software pipeline: while the
+// rows of one run of neighbours are gathered, the ids of the next run -- of the same item or of the
+// wavefront's next item -- are already on their way, the descriptor of the item after next has been
+// requested, and the owned row's own embedding (needed only when the item is written out) was
+// requested when the item began.  Nothing a wavefront needs next is first asked for when it is needed.
+//
+// Item descriptors travel as one dword per lane (lane f mod 8 holds field f of the 32-byte record)
+// through the vector memory path, whose loads return in order behind the gathers already in flight.
+struct ItemFields {
+    int row, beg, n_l, n, slot;
+};
+__device__ __forceinline__ ItemFields item_fields(const AggArgs &a, int d)
+{
+    ItemFields f;
+    f.row = __builtin_amdgcn_readlane(d, 0); f.beg = __builtin_amdgcn_readlane(d, 1); f.n_l = __builtin_amdgcn_readlane(d, 2);
+    f.n = __builtin_amdgcn_readlane(d, 3); f.slot = __builtin_amdgcn_readlane(d, 4);
+    if (a.phase == 1) f.n = f.n_l;
+    if (a.phase == 2) { f.beg += f.n_l; f.n -= f.n_l; f.n_l = 0; }
+    if (f.row < 0) f.n = 0;
+    return f;
+}
+
+// Work items are taken M per wavefront.  Workgroup b runs on XCD b mod 8 and takes M consecutive groups (of wpb
+// items) of that XCD's queue; groups are interleaved XCD by XCD in `items`.
+struct ItemQueue {
+    const int32_t *items32;
+    int first, stride, M, n_items, lane;
+    __device__ __forceinline__ void init(const AggArgs &a, int wave, int wpb, int lane_)
+    {
+        M = a.items_per_wave;
+        items32 = reinterpret_cast<const int32_t *>(a.items);
+        const int qb = static_cast<int>(blockIdx.x) / kXcd, xc = static_cast<int>(blockIdx.x) % kXcd;
+        first = (qb * M * kXcd + xc) * wpb + wave; stride = kXcd * wpb; n_items = a.n_items; lane = lane_;
+    }
+    __device__ __forceinline__ int load(int k) const
+    {
+        const int id = first + k * stride;                                  // wave-uniform
+        if (k < M && id < n_items) return items32[static_cast<int64_t>(id) * 8 + (lane & 7)];
+        return -1;                                                          // nothing there: reads as a padding item
+    }
+};
+
+// the owned row's own embedding, requested ahead of its use in write_final
+template <class K>
+__device__ __forceinline__ void load_self_row(const AggArgs &a, int32_t row, const Lanes<K> &ln, typename K::raw (&xs)[K::CH])
+{
+    const char *base = static_cast<const char *>(a.x_local) + static_cast<int64_t>(row) * a.ld_x * static_cast<int64_t>(sizeof(typename K::elem));
+#pragma unroll
+    for (int c = 0; c < K::CH; ++c) xs[c] = load_loose<typename K::raw, sizeof(typename K::elem)>(base + ln.col_off[c]);
+}
+
+template <class K>
+__device__ __forceinline__ void sum_subwaves(Acc<K> &acc)
+{
+    if constexpr (K::NPW > 1) {
+#pragma unroll
+        for (int c = 0; c < K::CH; ++c)
+#pragma unroll
+            for (int e = 0; e < K::VEC; ++e) acc.v[c][e] = sum_subwaves<K>(acc.v[c][e]);
+    }
+}
+
+template <class K>
+__device__ __forceinline__ void finish_item(const AggArgs &a, bool gcn, Acc<K> &acc, const typename K::raw (&xs)[K::CH], int row, int slot, const Lanes<K> &ln)
+{
+    sum_subwaves<K>(acc);
+    if (ln.sub == 0) {
+        if (slot < 0) write_final<K>(a, gcn, acc, xs, row, ln);
+        else write_partial<K>(a, acc, slot, ln);
+    }
+}
+
+// ---- short rows: one per sub-wave, a.short_per_wave groups of NPW rows per wavefront --------------
+// A 16-byte record per short row (row, start of its two lists, their lengths) is requested two groups
+// ahead, the first ids one group ahead.  A row's two lists are taken as one: the rows of a wavefront have
+// about the same number of neighbours (they are sorted by it) while the split between the tables differs
+// from row to row, so the wavefront runs that many steps instead of the longest local list plus the
+// longest remote one (43,423 bags of 34 lookups, 16 bf16 columns: 44 -> 23 us).
+template <class K, bool GCN>
+__device__ __forceinline__ void short_rows(const AggArgs &a, int wave, int wpb, int lane, const Lanes<K> &ln, const char *xl, const char *xh, uint64_t ldb)
+{
+    const int Ms = a.short_per_wave;
+    const int sw = (static_cast<int>(blockIdx.x) - a.n_item_blocks) * wpb + wave;
+    Acc<K> acc;
+    typename K::raw xs[K::CH];
+    auto load_sd = [&](int k) -> int4 {
+        const int64_t s_id = (static_cast<int64_t>(sw) * Ms + k) * K::NPW + ln.sub;
+        int4 sd = make_int4(-1, 0, 0, 0);
+        if (k < Ms && s_id < a.n_short) sd = a.short_desc[s_id];
+        if (a.phase == 1) sd.w = sd.z;
+        if (a.phase == 2) { sd.y += sd.z; sd.w -= sd.z; }
+        return sd;
+    };
+    auto load_ids = [&](const int4 &sd, int b0, uint32_t &id, float &w) {
+        id = 0; w = 0.f;
+        const int p = b0 + ln.slot;
+        if (p < sd.w) {
+            id = a.cols[sd.y + p];
+            if constexpr (GCN) w = a.wts[sd.y + p];
+        }
+    };
+    int4 sd_cur = load_sd(0), sd_nxt = load_sd(1);
+    uint32_t id;
+    float w;
+    load_ids(sd_cur, 0, id, w);
+    for (int k = 0; k < Ms; ++k) {
+        if ((static_cast<int64_t>(sw) * Ms + k) * K::NPW >= a.n_short) break;       // wave-uniform: nothing left
+        const int4 sd_nn = load_sd(k + 2);
+        uint32_t nid;
+        float nw;
+        load_ids(sd_nxt, 0, nid, nw);
+        const bool have = sd_cur.x >= 0;
+        const int32_t row = have ? sd_cur.x : 0;
+        if (have && !a.no_self && a.phase != 2) load_self_row<K>(a, row, ln, xs);
+        acc.clear();
+        const int n = sd_cur.w;
+        // longest and shortest list among the sub-waves of this wavefront (wave-uniform)
+        int n_max = n, n_min = n;
+#pragma unroll
+        for (int off = K::LPR; off < kWave; off <<= 1) { n_max = max(n_max, __shfl_xor(n_max, off)); n_min = min(n_min, __shfl_xor(n_min, off)); }
+        n_max = __builtin_amdgcn_readfirstlane(n_max);
+        n_min = __builtin_amdgcn_readfirstlane(n_min);
+        for (int b0 = 0; b0 < n_max; b0 += K::LPR) {
+            if (b0 > 0) load_ids(sd_cur, b0, id, w);                  // lists longer than a sub-wave: fetched as they come
+            // slots without a neighbour gather the row of one that exists, and drop it
+            const bool mine = b0 + ln.slot < n;
+            const int any = __builtin_ctzll(__ballot(mine));          // b0 < n_max: some lane has one
+            id = mine ? id : static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(id), any));
+            Slots<K> s;
+            set_slots<K>(s, id, w, xl, xh, ldb);
+            const int cnt_max = min(K::LPR, n_max - b0);
+            if (n_min - b0 >= cnt_max) steps<K, GCN, false>(acc, s, cnt_max, ln);
+            else steps<K, GCN, true>(acc, s, cnt_max, ln, n - b0);
+        }
+        if (have) write_final<K>(a, GCN, acc, xs, row, ln);
+        sd_cur = sd_nxt; sd_nxt = sd_nn;
+        id = nid; w = nw;
+    }
+}
+
+template <class K, bool GCN>
+__global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu(K::MIN_WAVES))) void aggregate_kernel(const AggArgs a)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+    const int wpb = static_cast<int>(blockDim.x) / kWave;   // wavefronts per workgroup
+    Lanes<K> ln;
+    ln.init(a, lane);
+    const char *xl = static_cast<const char *>(a.x_local);
+    const char *xh = static_cast<const char *>(a.x_halo);
+    const uint64_t ldb = static_cast<uint64_t>(a.ld_x) * sizeof(typename K::elem);
+    if (static_cast<int>(blockIdx.x) >= a.n_item_blocks) {
+        short_rows<K, GCN>(a, wave, wpb, lane, ln, xl, xh, ldb);
+        return;
+    }
+    const int ps = a.ps;
+    Acc<K> acc;
+    typename K::raw xs[K::CH];
+    ItemQueue q;
+    q.init(a, wave, wpb, lane);
+    int d_cur = q.load(0), d_nxt = q.load(1);
+    bool ids_ready = false;
+    uint32_t id = 0;
+    float w = 0.f;
+    for (int k = 0; k < q.M; ++k) {
+        const int d_nn = q.load(k + 2);
+        const ItemFields it = item_fields(a, d_cur);
+        if (it.row >= 0) {
+            const int n = it.n;
+            if (!ids_ready && n > 0) load_run<GCN>(a, it.beg, min(ps, n), lane, id, w);
+            const ItemFields nx = item_fields(a, d_nxt);
+            if (it.slot < 0 && !a.no_self && a.phase != 2) load_self_row<K>(a, it.row, ln, xs);
+            acc.clear();
+            for (int pos = 0; pos < n; pos += ps) {
+                // ids of the next run -- of this item, or the first one of the next
+                uint32_t nid = 0;
+                float nw = 0.f;
+                if (pos + ps < n) load_run<GCN>(a, it.beg + pos + ps, min(ps, n - pos - ps), lane, nid, nw);
+                else if (nx.n > 0) load_run<GCN>(a, nx.beg, min(ps, nx.n), lane, nid, nw);
+                gather_run<K, GCN>(acc, id, w, min(ps, n - pos), xl, xh, ldb, ln);
+                id = nid; w = nw;
+            }
+            ids_ready = n > 0 && nx.n > 0;
+            finish_item<K>(a, GCN, acc, xs, it.row, it.slot, ln);
+        } else {
+            ids_ready = false;
+        }
+        d_cur = d_nxt; d_nxt = d_nn;
+    }
+}
+
 // ---- LDS staging of halo rows (section 5.2, "pipelined memory operation") -----------------------
 // A wavefront owns two LDS stages of kStageSlots load instructions (1 KB each: NPW rows).  The rows of
 // a remote partition are requested with global_load_lds -- memory to LDS, holding no registers while in
@@ -399,26 +720,21 @@ typedef __attribute__((address_space(3))) void *lptr_t;
 template <int N> __device__ __forceinline__ void wait_vmcnt()
 {
     if constexpr (N <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if constexpr (N == 1) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
-    else if constexpr (N == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-    else if constexpr (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     else if constexpr (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-    else if constexpr (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // requests (up to) kStageSlots load steps of a remote partition, starting at step t0, into `stage`;
 // always issues exactly kStageSlots instructions so that outstanding loads can be counted
 template <class K>
-__device__ __forceinline__ void stage_halo_batch(uint4 (*stage)[kWave], const char *table, uint32_t off_lo, int len, int t0,
+__device__ __forceinline__ void stage_halo_batch(uint4 (*stage)[kWave], const char *table, uint32_t id, uint64_t ldb, int len, int t0,
                                                  const Lanes<K> &ln)
 {
 #pragma unroll
     for (int u = 0; u < kStageSlots; ++u) {
         const int j = (t0 + u) * K::NPW + ln.sub;
-        const int jj = j < len ? j : 0;                       // neighbour 0 exists whenever a batch is staged
-        const uint32_t lo = lane_read<K>(off_lo, jj);
-        const char *src = table + (lo + ln.col_off[0]);
+        const uint32_t row = static_cast<uint32_t>(__shfl(static_cast<int>(id), j < len ? j : 0)) & 0x7fffffffu;   // neighbour 0 exists whenever a batch is staged
+        const char *src = table + (static_cast<uint64_t>(row) * ldb + ln.col_off[0]);
         __builtin_amdgcn_global_load_lds((gptr_t)(const void *)src, (lptr_t)(void *)&stage[u][0], 16, 0, 0);
     }
 }
@@ -430,7 +746,7 @@ __device__ __forceinline__ void consume_stage(Acc<K> &acc, uint4 (*stage)[kWave]
     for (int u = 0; u < kStageSlots; ++u) {
         const int j = (t0 + u) * K::NPW + ln.sub;
         const bool ok = j < len;
-        const float wj = GCN ? __uint_as_float(lane_read<K>(__float_as_uint(my_w), ok ? j : 0)) : 1.f;
+        const float wj = GCN ? __shfl(my_w, ok ? j : 0) : 1.f;
         const uint4 q = stage[u][lane];
         typename K::raw r;
         __builtin_memcpy(&r, &q, sizeof r);
@@ -441,247 +757,68 @@ __device__ __forceinline__ void consume_stage(Acc<K> &acc, uint4 (*stage)[kWave]
     }
 }
 
-// ---- the kernel -----------------------------------------------------------------------------------
-// One work item after the other, M (a.items_per_wave) per wavefront, as a software pipeline: while the
-// rows of one pair of partitions are gathered, the ids of the next pair -- of the same item or of the
-// wavefront's next item -- are already on their way, the descriptor of the item after next has been
-// requested, and the owned row's own embedding (needed only when the item is written out) was
-// requested when the item began.  Nothing a wavefront needs next is first asked for when it is needed.
-//
-// Item descriptors travel as one dword per lane (lane f mod 8 holds field f of the 32-byte record)
-// through the vector memory path, whose loads return in order behind the gathers already in flight.
-struct ItemFields {
-    int row, lbeg, lend, rbeg, rend, slot;
-};
-__device__ __forceinline__ ItemFields item_fields(int d)
+// The items of aggregate_kernel with their halo rows through LDS (option lds_halo); local partitions through registers.
+template <class K, bool GCN>
+__global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu(K::MIN_WAVES))) void aggregate_lds_kernel(const AggArgs a)
 {
-    ItemFields f;
-    f.row = __builtin_amdgcn_readlane(d, 0); f.lbeg = __builtin_amdgcn_readlane(d, 1); f.lend = __builtin_amdgcn_readlane(d, 2);
-    f.rbeg = __builtin_amdgcn_readlane(d, 3); f.rend = __builtin_amdgcn_readlane(d, 4); f.slot = __builtin_amdgcn_readlane(d, 5);
-    return f;
-}
-
-// the owned row's own embedding, requested ahead of its use in write_final
-template <class K>
-__device__ __forceinline__ void load_self_row(const AggArgs &a, int32_t row, const Lanes<K> &ln, typename K::raw (&xs)[K::CH])
-{
-    const char *base = static_cast<const char *>(a.x_local) + static_cast<int64_t>(row) * a.ld_x * static_cast<int64_t>(sizeof(typename K::elem));
-#pragma unroll
-    for (int c = 0; c < K::CH; ++c) xs[c] = load_loose<typename K::raw, sizeof(typename K::elem)>(base + ln.col_off[c]);
-}
-
-template <class K, bool GCN, bool WIDE>
-__device__ __forceinline__ void gather_pair(Acc<K> &acc, const char *xl, const char *xh, uint64_t ldb, int idx_l, float w_l, int len_l,
-                                            int idx_r, float w_r, int len_r, const Lanes<K> &ln)
-{
-    uint32_t lo, hi;
-    if (len_l > 0) { row_offset<WIDE>(idx_l, ldb, lo, hi); accumulate_partition<K, GCN, WIDE>(acc, xl, lo, hi, w_l, len_l, ln); }
-    if (len_r > 0) { row_offset<WIDE>(idx_r, ldb, lo, hi); accumulate_partition<K, GCN, WIDE>(acc, xh, lo, hi, w_r, len_r, ln); }
-}
-
-template <class K, bool GCN, bool LDSH>
-__global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu(K::MIN_WAVES))) void aggregate_kernel(const AggArgs a)
-{
-    extern __shared__ uint4 stage_all[];        // LDS-staged variant: two stages of kStageSlots load instructions per wavefront
+    extern __shared__ uint4 stage_all[];        // two stages of kStageSlots load instructions per wavefront
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
-    const int wpb = static_cast<int>(blockDim.x) / kWave;   // wavefronts per workgroup
+    const int wpb = static_cast<int>(blockDim.x) / kWave;
     Lanes<K> ln;
     ln.init(a, lane);
     const char *xl = static_cast<const char *>(a.x_local);
     const char *xh = static_cast<const char *>(a.x_halo);
     const uint64_t ldb = static_cast<uint64_t>(a.ld_x) * sizeof(typename K::elem);
+    if (static_cast<int>(blockIdx.x) >= a.n_item_blocks) {
+        short_rows<K, GCN>(a, wave, wpb, lane, ln, xl, xh, ldb);
+        return;
+    }
+    uint4 (*stage)[kStageSlots][kWave] = reinterpret_cast<uint4 (*)[kStageSlots][kWave]>(stage_all + static_cast<size_t>(wave) * 2 * kStageSlots * kWave);
     const int ps = a.ps;
     Acc<K> acc;
     typename K::raw xs[K::CH];
-
-    if (static_cast<int>(blockIdx.x) < a.n_item_blocks) {
-        // ---- work items: M per wavefront.  Workgroup b runs on XCD b mod 8 and takes M consecutive
-        // groups (of wpb items) of that XCD's queue; groups are interleaved XCD by XCD in `items`.
-        const int M = a.items_per_wave;
-        const int qb = static_cast<int>(blockIdx.x) / kXcd, xc = static_cast<int>(blockIdx.x) % kXcd;
-        const int32_t *items32 = reinterpret_cast<const int32_t *>(a.items);
-        auto load_desc = [&](int k) -> int {
-            const int id = ((qb * M + k) * kXcd + xc) * wpb + wave;        // wave-uniform
-            if (k < M && id < a.n_items) return items32[static_cast<int64_t>(id) * 8 + (lane & 7)];
-            return -1;                                                      // nothing there: reads as a padding item
-        };
-        int d_cur = load_desc(0), d_nxt = load_desc(1);
-        bool ids_ready = false;
-        int idx_l = 0, idx_r = 0;
+    ItemQueue q;
+    q.init(a, wave, wpb, lane);
+    int d_cur = q.load(0);
+    for (int k = 0; k < q.M; ++k) {
+        const int d_nxt = q.load(k + 1);
+        const ItemFields it = item_fields(a, d_cur);
+        d_cur = d_nxt;
+        if (it.row < 0) continue;
+        const int n_l = it.n_l, n_r = it.n - it.n_l;
+        if (it.slot < 0 && !a.no_self && a.phase != 2) load_self_row<K>(a, it.row, ln, xs);
+        acc.clear();
+        const int lbeg = it.beg, rbeg = it.beg + n_l;
+        uint32_t id_l = 0, id_r = 0;
         float w_l = 0.f, w_r = 0.f;
-        for (int k = 0; k < M; ++k) {
-            const int d_nn = load_desc(k + 2);
-            const ItemFields it = item_fields(d_cur);
-            if (it.row >= 0) {
-                const int n_l = a.phase == 2 ? 0 : it.lend - it.lbeg, n_r = a.phase == 1 ? 0 : it.rend - it.rbeg;
-                const int g_l = (n_l + ps - 1) / ps, g_r = (n_r + ps - 1) / ps;
-                const int g_n = g_l > g_r ? g_l : g_r;
-                if (!ids_ready) {
-                    load_partition_ids<GCN>(a.local_col, a.w_local, it.lbeg, min(ps, n_l), lane, idx_l, w_l);
-                    load_partition_ids<GCN>(a.remote_col, a.w_remote, it.rbeg, min(ps, n_r), lane, idx_r, w_r);
+        if (n_l > 0) load_run<GCN>(a, lbeg, min(ps, n_l), lane, id_l, w_l);
+        if (n_r > 0) load_run<GCN>(a, rbeg, min(ps, n_r), lane, id_r, w_r);
+        for (int pos = 0; pos < max(n_l, n_r); pos += ps) {
+            uint32_t nid_l = 0, nid_r = 0;
+            float nw_l = 0.f, nw_r = 0.f;
+            if (pos + ps < n_l) load_run<GCN>(a, lbeg + pos + ps, min(ps, n_l - pos - ps), lane, nid_l, nw_l);
+            if (pos + ps < n_r) load_run<GCN>(a, rbeg + pos + ps, min(ps, n_r - pos - ps), lane, nid_r, nw_r);
+            const int len_l = min(ps, n_l - pos), len_r = min(ps, n_r - pos);
+            // remote rows travel into LDS one batch ahead of their accumulation; the local partition
+            // of the pair is gathered through registers while the first batch is in flight
+            const int steps_r = len_r > 0 ? (len_r + K::NPW - 1) / K::NPW : 0;
+            if (steps_r > 0) stage_halo_batch<K>(stage[0], xh, id_r, ldb, len_r, 0, ln);
+            if (len_l > 0) gather_run<K, GCN>(acc, id_l, w_l, len_l, xl, xh, ldb, ln);
+            int buf = 0;
+            for (int t0 = 0; t0 < steps_r; t0 += kStageSlots, buf ^= 1) {
+                if (t0 + kStageSlots < steps_r) {
+                    stage_halo_batch<K>(stage[buf ^ 1], xh, id_r, ldb, len_r, t0 + kStageSlots, ln);
+                    wait_vmcnt<kStageSlots>();          // everything but the batch just requested has landed
+                } else {
+                    wait_vmcnt<0>();
                 }
-                const ItemFields nx = item_fields(d_nxt);
-                const int nn_l = a.phase == 2 ? 0 : nx.lend - nx.lbeg, nn_r = a.phase == 1 ? 0 : nx.rend - nx.rbeg;
-                const bool wants_self = it.slot < 0 && !a.no_self && a.phase != 2;
-                if (wants_self) load_self_row<K>(a, it.row, ln, xs);
-                acc.clear();
-                for (int g = 0; g < g_n; ++g) {
-                    // ids of the next pair -- of this item, or the first pair of the next one
-                    int nidx_l = 0, nidx_r = 0;
-                    float nw_l = 0.f, nw_r = 0.f;
-                    if (g + 1 < g_n) {
-                        const int off = (g + 1) * ps;
-                        load_partition_ids<GCN>(a.local_col, a.w_local, it.lbeg + off, min(ps, n_l - off), lane, nidx_l, nw_l);
-                        load_partition_ids<GCN>(a.remote_col, a.w_remote, it.rbeg + off, min(ps, n_r - off), lane, nidx_r, nw_r);
-                    } else if (nx.row >= 0) {
-                        load_partition_ids<GCN>(a.local_col, a.w_local, nx.lbeg, min(ps, nn_l), lane, nidx_l, nw_l);
-                        load_partition_ids<GCN>(a.remote_col, a.w_remote, nx.rbeg, min(ps, nn_r), lane, nidx_r, nw_r);
-                    }
-                    const int len_l = min(ps, n_l - g * ps), len_r = min(ps, n_r - g * ps);
-                    if (a.wide) {
-                        gather_pair<K, GCN, true>(acc, xl, xh, ldb, idx_l, w_l, len_l, idx_r, w_r, len_r, ln);
-                    } else if constexpr (LDSH) {
-                        // remote rows travel into LDS one batch ahead of their accumulation; the local partition
-                        // of the pair is gathered through registers while the first batch is in flight
-                        uint4 (*stage)[kStageSlots][kWave] = reinterpret_cast<uint4 (*)[kStageSlots][kWave]>(stage_all + static_cast<size_t>(wave) * 2 * kStageSlots * kWave);
-                        uint32_t lo_l, lo_r, hi;
-                        row_offset<false>(idx_l, ldb, lo_l, hi);
-                        row_offset<false>(idx_r, ldb, lo_r, hi);
-                        const int steps_r = len_r > 0 ? (len_r + K::NPW - 1) / K::NPW : 0;
-                        if (steps_r > 0) stage_halo_batch<K>(stage[0], xh, lo_r, len_r, 0, ln);
-                        if (len_l > 0) accumulate_partition<K, GCN, false>(acc, xl, lo_l, 0u, w_l, len_l, ln);
-                        int buf = 0;
-                        for (int t0 = 0; t0 < steps_r; t0 += kStageSlots, buf ^= 1) {
-                            if (t0 + kStageSlots < steps_r) {
-                                stage_halo_batch<K>(stage[buf ^ 1], xh, lo_r, len_r, t0 + kStageSlots, ln);
-                                wait_vmcnt<kStageSlots>();          // everything but the batch just requested has landed
-                            } else {
-                                wait_vmcnt<0>();
-                            }
-                            consume_stage<K, GCN>(acc, stage[buf], w_r, len_r, t0, ln, lane);
-                            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this stage is free again
-                        }
-                    } else {
-                        gather_pair<K, GCN, false>(acc, xl, xh, ldb, idx_l, w_l, len_l, idx_r, w_r, len_r, ln);
-                    }
-                    idx_l = nidx_l; w_l = nw_l; idx_r = nidx_r; w_r = nw_r;
-                }
-                ids_ready = g_n > 0 && nx.row >= 0;
-                // combine the sub-wave accumulators: lanes with equal `lis` hold the same columns
-#pragma unroll
-                for (int off = K::LPR; off < kWave; off <<= 1)
-#pragma unroll
-                    for (int c = 0; c < K::CH; ++c)
-#pragma unroll
-                        for (int e = 0; e < K::VEC; ++e) acc.v[c][e] += __shfl_xor(acc.v[c][e], off);
-                if (ln.sub == 0) {
-                    if (it.slot < 0) write_final<K>(a, GCN, acc, xs, it.row, ln);
-                    else write_partial<K>(a, acc, it.slot, ln);
-                }
-            } else {
-                ids_ready = false;
+                consume_stage<K, GCN>(acc, stage[buf], w_r, len_r, t0, ln, lane);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this stage is free again
             }
-            d_cur = d_nxt; d_nxt = d_nn;
+            id_l = nid_l; w_l = nw_l; id_r = nid_r; w_r = nw_r;
         }
-    } else {
-        // ---- short rows: one per sub-wave, a.short_per_wave groups of NPW rows per wavefront --------
-        // A 16-byte record per short row (row, start of its two lists, their lengths) is requested two
-        // groups ahead, the first ids of both lists one group ahead.  The sub-wave's lanes fetch ids LPR
-        // at a time, turn them into row offsets and hand them round inside the sub-wave.
-        const int Ms = a.short_per_wave;
-        const int sw = (static_cast<int>(blockIdx.x) - a.n_item_blocks) * wpb + wave;
-        const int lane_in_sub = lane % K::LPR, sub_base = lane - lane_in_sub;
-        auto load_sd = [&](int k) -> int4 {
-            const int64_t s_id = (static_cast<int64_t>(sw) * Ms + k) * K::NPW + ln.sub;
-            if (k < Ms && s_id < a.n_short) return a.short_desc[s_id];
-            return make_int4(-1, 0, 0, 0);
-        };
-        // first block of ids of both lists of the row described by sd
-        auto load_first_ids = [&](const int4 &sd, int &il, float &wl, int &ir, float &wr) {
-            il = 0; ir = 0; wl = 0.f; wr = 0.f;
-            if (sd.x < 0) return;
-            const int nl = a.phase == 2 ? 0 : (sd.w & 0xffff), nr = a.phase == 1 ? 0 : static_cast<int>(static_cast<uint32_t>(sd.w) >> 16);
-            if (lane_in_sub < nl) { il = a.local_col[sd.y + lane_in_sub]; if constexpr (GCN) wl = a.w_local[sd.y + lane_in_sub]; }
-            if (lane_in_sub < nr) { ir = a.remote_col[sd.z + lane_in_sub]; if constexpr (GCN) wr = a.w_remote[sd.z + lane_in_sub]; }
-        };
-        int4 sd_cur = load_sd(0), sd_nxt = load_sd(1);
-        int fi_l, fi_r;
-        float fw_l, fw_r;
-        load_first_ids(sd_cur, fi_l, fw_l, fi_r, fw_r);
-        for (int k = 0; k < Ms; ++k) {
-            if ((static_cast<int64_t>(sw) * Ms + k) * K::NPW >= a.n_short) break;       // wave-uniform: nothing left
-            const int4 sd_nn = load_sd(k + 2);
-            int ni_l, ni_r;
-            float nw_l, nw_r;
-            load_first_ids(sd_nxt, ni_l, nw_l, ni_r, nw_r);
-            const bool have = sd_cur.x >= 0;
-            const int32_t row = have ? sd_cur.x : 0;
-            if (have && !a.no_self && a.phase != 2) load_self_row<K>(a, row, ln, xs);
-            acc.clear();
-            for (int side = 0; side < 2; ++side) {
-                if (side == 0 ? a.phase == 2 : a.phase == 1) continue;
-                const int32_t *col = side == 0 ? a.local_col : a.remote_col;
-                const float *wts = side == 0 ? a.w_local : a.w_remote;
-                const char *table = side == 0 ? xl : xh;
-                const int beg = side == 0 ? sd_cur.y : sd_cur.z;
-                const int n = have ? (side == 0 ? (sd_cur.w & 0xffff) : static_cast<int>(static_cast<uint32_t>(sd_cur.w) >> 16)) : 0;
-                // longest list among the sub-waves of this wavefront (wave-uniform loop bound)
-                int n_max = n;
-#pragma unroll
-                for (int off = K::LPR; off < kWave; off <<= 1) n_max = max(n_max, __shfl_xor(n_max, off));
-                n_max = __builtin_amdgcn_readfirstlane(n_max);
-                for (int b0 = 0; b0 < n_max; b0 += K::LPR) {
-                    int idx = side == 0 ? fi_l : fi_r;
-                    float w = side == 0 ? fw_l : fw_r;
-                    if (b0 > 0) {                                     // lists longer than a sub-wave: fetched as they come
-                        idx = 0; w = 0.f;
-                        if (b0 + lane_in_sub < n) {
-                            idx = col[beg + b0 + lane_in_sub];
-                            if constexpr (GCN) w = wts[beg + b0 + lane_in_sub];
-                        }
-                    }
-                    uint32_t lo, hi;
-                    if (a.wide) row_offset<true>(idx, ldb, lo, hi); else row_offset<false>(idx, ldb, lo, hi);
-                    const int cnt = min(K::LPR, n - b0);                     // this sub-wave's neighbours in the block (may be <= 0)
-                    const int cnt_max = min(K::LPR, n_max - b0);             // wave-uniform
-                    for (int j0 = 0; j0 < cnt_max; j0 += K::U) {
-                        typename K::raw r[K::U][K::CH];
-                        float wv[K::U];
-                        bool ok[K::U];
-#pragma unroll
-                        for (int u = 0; u < K::U; ++u) {
-                            ok[u] = j0 + u < cnt;
-                            const int src = sub_base + (ok[u] ? j0 + u : 0);
-                            const uint32_t l = static_cast<uint32_t>(__shfl(static_cast<int>(lo), src));
-                            const uint32_t h = a.wide ? static_cast<uint32_t>(__shfl(static_cast<int>(hi), src)) : 0u;
-                            wv[u] = GCN ? __shfl(w, src) : 1.f;
-                            if (j0 + u < cnt_max) {     // wave-uniform; a sub-wave with nothing left re-reads a row it has and drops it
-#pragma unroll
-                                for (int c = 0; c < K::CH; ++c)
-                                    r[u][c] = a.wide ? load_row_chunk<K, true>(table, l, h, ln.col_off[c]) : load_row_chunk<K, false>(table, l, 0u, ln.col_off[c]);
-                            } else {
-#pragma unroll
-                                for (int c = 0; c < K::CH; ++c) __builtin_memset(&r[u][c], 0, sizeof r[u][c]);
-                                ok[u] = false;
-                            }
-                        }
-#pragma unroll
-                        for (int u = 0; u < K::U; ++u)
-#pragma unroll
-                            for (int c = 0; c < K::CH; ++c) {
-                                float f[K::VEC];
-                                unpack<K::BF16, K::VEC>(r[u][c], f);
-#pragma unroll
-                                for (int e = 0; e < K::VEC; ++e) acc.v[c][e] = fmaf(wv[u], ok[u] ? f[e] : 0.f, acc.v[c][e]);
-                            }
-                    }
-                }
-            }
-            if (have) write_final<K>(a, GCN, acc, xs, row, ln);
-            sd_cur = sd_nxt; sd_nxt = sd_nn;
-            fi_l = ni_l; fw_l = nw_l; fi_r = ni_r; fw_r = nw_r;
-        }
+        finish_item<K>(a, GCN, acc, xs, it.row, it.slot, ln);
     }
 }
 
@@ -689,15 +826,15 @@ template <class K>
 hipError_t launch_cfg(const AggArgs &a, bool gcn, dim3 grid, int wpb, hipStream_t stream, bool lds_halo)
 {
     if constexpr (K::CH == 1 && sizeof(typename K::raw) == 16) {
-        if (lds_halo && wpb <= kStageWpb && !a.wide) {
+        if (lds_halo && wpb <= kStageWpb) {
             const size_t lds = static_cast<size_t>(wpb) * 2 * kStageSlots * kWave * sizeof(uint4);     // 16 KB per wavefront
-            if (gcn) hipLaunchKernelGGL((aggregate_kernel<K, true, true>), grid, dim3(kWave * wpb), lds, stream, a);
-            else hipLaunchKernelGGL((aggregate_kernel<K, false, true>), grid, dim3(kWave * wpb), lds, stream, a);
+            if (gcn) hipLaunchKernelGGL((aggregate_lds_kernel<K, true>), grid, dim3(kWave * wpb), lds, stream, a);
+            else hipLaunchKernelGGL((aggregate_lds_kernel<K, false>), grid, dim3(kWave * wpb), lds, stream, a);
             return hipGetLastError();
         }
     }
-    if (gcn) hipLaunchKernelGGL((aggregate_kernel<K, true, false>), grid, dim3(kWave * wpb), 0, stream, a);
-    else hipLaunchKernelGGL((aggregate_kernel<K, false, false>), grid, dim3(kWave * wpb), 0, stream, a);
+    if (gcn) hipLaunchKernelGGL((aggregate_kernel<K, true>), grid, dim3(kWave * wpb), 0, stream, a);
+    else hipLaunchKernelGGL((aggregate_kernel<K, false>), grid, dim3(kWave * wpb), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -23,7 +23,13 @@ struct WorkItem {
     int32_t slot;
     int32_t pad0, pad1;
 };
-static_assert(sizeof(WorkItem) == 32, "WorkItem is read as two 16-byte words");
+
+// The same on the device, where an item's neighbours lie in one run of `cols`: the local ones, then the remote ones.
+struct DeviceItem {
+    int32_t row, beg, n_local, n, slot;
+    int32_t pad[3];
+};
+static_assert(sizeof(DeviceItem) == 32, "a wavefront reads an item as eight dwords");
 
 // A row that was cut into several items: its partial sums sit in scratch rows
 // [first_slot, first_slot + n_slots) and are combined in that order.
@@ -46,12 +52,11 @@ constexpr int kColdClass = 255;
 constexpr int64_t kHotBytesPerXcd = 3 << 20;   // of the 4 MB L2 of one XCD, what the hot rows of a phase may fill
 
 struct DeviceArrays {
-    int32_t *local_row_ptr = nullptr, *local_col = nullptr;
-    int32_t *remote_row_ptr = nullptr, *remote_col = nullptr;
+    uint32_t *cols = nullptr;          // table rows of the neighbours in the order of the work (bit 31 set: row of the halo table)
+    float *wts = nullptr;              // 1/sqrt(deg+1) of the neighbour, per entry of cols
     float *dinv_own = nullptr;
-    float *w_local = nullptr, *w_remote = nullptr;   // 1/sqrt(deg+1) of the neighbour, per entry of the column arrays
-    int4 *short_desc = nullptr;        // per short row: row, start in local_col, start in remote_col, counts (local | remote << 16)
-    WorkItem *items = nullptr;
+    int4 *short_desc = nullptr;        // per short row: row, start in cols, local neighbours, all neighbours
+    DeviceItem *items = nullptr;
     SplitRow *split_rows = nullptr;
     float *scratch = nullptr;          // [n_split_items x scratch_ld] partial sums
     int64_t scratch_ld = 0;

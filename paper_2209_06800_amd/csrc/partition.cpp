@@ -5,7 +5,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
+#include <thread>
 
 #include "mgg_internal.h"
 
@@ -30,64 +32,113 @@ mgg_status_t hip_fail(hipError_t e, const char *what)
 const char *last_error() { return g_err; }
 
 template <typename T>
-static mgg_status_t upload(const std::vector<T> &h, T **d)
+static mgg_status_t upload(const T *h, size_t n, T **d)
 {
     *d = nullptr;
     // one element at least, so that kernels never receive a null table pointer
-    size_t bytes = std::max<size_t>(h.size(), 1) * sizeof(T);
+    size_t bytes = std::max<size_t>(n, 1) * sizeof(T);
     hipError_t e = hipMalloc(reinterpret_cast<void **>(d), bytes);
     if (e != hipSuccess) return fail(MGG_ERR_ALLOC, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
-    if (!h.empty()) MGG_HIP_TRY(hipMemcpy(*d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
+    if (n > 0) MGG_HIP_TRY(hipMemcpy(*d, h, n * sizeof(T), hipMemcpyHostToDevice));
     return MGG_OK;
+}
+template <typename T>
+static mgg_status_t upload(const std::vector<T> &h, T **d) { return upload(h.data(), h.size(), d); }
+
+// body(begin, end) over [0, n) on up to 8 threads; on this one alone when `work` is little or no thread can be had
+template <typename F>
+static void parallel_for(size_t n, size_t work, const F &body)
+{
+    const size_t n_threads = work < (1 << 17) ? 1 : std::max<size_t>(1, std::min<size_t>({8, n, std::thread::hardware_concurrency()}));
+    std::vector<std::thread> threads;
+    size_t done = 0;
+    try {
+        for (size_t t = 1; t < n_threads; ++t) {
+            const size_t b = done, e = n * t / n_threads;
+            threads.emplace_back([&body, b, e] { body(b, e); });
+            done = e;
+        }
+    } catch (const std::exception &) {       // the rest runs here
+    }
+    body(done, n);
+    for (std::thread &t : threads) t.join();
 }
 
 static void free_device(mgg_partition *p)
 {
     if (p->device < 0) return;
     DeviceArrays &d = p->d;
-    void *ptrs[] = {d.local_row_ptr, d.local_col, d.remote_row_ptr, d.remote_col, d.dinv_own, d.w_local,
-                    d.w_remote,      d.short_desc, d.items,         d.split_rows, d.scratch};
+    void *ptrs[] = {d.cols, d.wts, d.dinv_own, d.short_desc, d.items, d.split_rows, d.scratch};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     d = DeviceArrays{};
 }
 
-static mgg_status_t upload_all(mgg_partition *p)
+static mgg_status_t upload_arrays(mgg_partition *p)
 {
     int dev = 0;
     MGG_HIP_TRY(hipGetDevice(&dev));
     p->device = dev;
     mgg_status_t s;
-    if ((s = upload(p->local_row_ptr, &p->d.local_row_ptr)) != MGG_OK) return s;
-    if ((s = upload(p->sched_local_col.empty() ? p->local_col : p->sched_local_col, &p->d.local_col)) != MGG_OK) return s;
-    if ((s = upload(p->remote_row_ptr, &p->d.remote_row_ptr)) != MGG_OK) return s;
-    if ((s = upload(p->sched_remote_col.empty() ? p->remote_col : p->sched_remote_col, &p->d.remote_col)) != MGG_OK) return s;
     if ((s = upload(p->dinv_own, &p->d.dinv_own)) != MGG_OK) return s;
-    {
-        // the neighbour's factor, stored per edge in the order the kernel walks the columns: a
-        // coalesced stream instead of a 4-byte gather per neighbour
-        const std::vector<int32_t> &lc = p->sched_local_col.empty() ? p->local_col : p->sched_local_col;
-        const std::vector<int32_t> &rc = p->sched_remote_col.empty() ? p->remote_col : p->sched_remote_col;
-        std::vector<float> w(p->bags ? 0 : lc.size());      // a bag partition has no factors: plain sums only
-        for (size_t i = 0; i < w.size(); ++i) w[i] = p->dinv_own[lc[i]];
-        if ((s = upload(w, &p->d.w_local)) != MGG_OK) return s;
-        w.resize(p->bags ? 0 : rc.size());
-        for (size_t i = 0; i < w.size(); ++i) w[i] = p->dinv_halo[rc[i]];
-        if ((s = upload(w, &p->d.w_remote)) != MGG_OK) return s;
+    // The neighbours in the order in which they are walked: XCD by XCD the items of its queue, one after the other, then
+    // the short rows; of each the local ones, then the remote ones, with the factor of each edge beside them.  Wavefronts
+    // that run at the same time on one XCD then read one stream front to back, and every line of it is fetched once (in the
+    // order of the rows a line was wanted by up to eight XCDs: 37 M neighbours at 100 columns 2.22 -> 2.16 ms).
+    const std::vector<int32_t> &lc = p->sched_local_col.empty() ? p->local_col : p->sched_local_col;
+    const std::vector<int32_t> &rc = p->sched_remote_col.empty() ? p->remote_col : p->sched_remote_col;
+    const size_t nnz = lc.size() + rc.size();
+    std::unique_ptr<uint32_t[]> cols(new uint32_t[nnz]);
+    std::unique_ptr<float[]> w(new float[p->bags ? 0 : nnz]);       // a bag partition has no factors: plain sums only
+    auto put = [&](int32_t at, int32_t l0, int32_t l1, int32_t r0, int32_t r1) {
+        int32_t k = at;
+        for (int32_t i = l0; i < l1; ++i) cols[k++] = static_cast<uint32_t>(lc[i]);
+        for (int32_t i = r0; i < r1; ++i) cols[k++] = static_cast<uint32_t>(rc[i]) | 0x80000000u;
+        if (p->bags) return;
+        for (int32_t i = l0; i < l1; ++i) w[at++] = p->dinv_own[lc[i]];
+        for (int32_t i = r0; i < r1; ++i) w[at++] = p->dinv_halo[rc[i]];
+    };
+    int32_t at = 0;
+    std::vector<DeviceItem> items(p->items.size());
+    for (int x = 0; x < kXcd; ++x)
+        for (size_t g = static_cast<size_t>(x) * p->wpb; g < items.size(); g += static_cast<size_t>(kXcd) * p->wpb)
+            for (size_t i = g; i < std::min(items.size(), g + p->wpb); ++i) {
+                const WorkItem &it = p->items[i];
+                items[i] = DeviceItem{it.row, at, it.lend - it.lbeg, it.lend - it.lbeg + it.rend - it.rbeg, it.slot, {0, 0, 0}};
+                at += items[i].n;
+            }
+    // one 16-byte record per short row, so that the kernel needs no dependent look-up of row pointers
+    std::vector<int4> sd(p->short_rows.size());
+    for (size_t i = 0; i < sd.size(); ++i) {
+        const int32_t v = p->short_rows[i], nl = p->local_row_ptr[v + 1] - p->local_row_ptr[v], nr = p->remote_row_ptr[v + 1] - p->remote_row_ptr[v];
+        sd[i] = make_int4(v, at, nl, nl + nr);
+        at += nl + nr;
     }
-    {
-        // one 16-byte record per short row, so that the kernel needs no dependent look-up of row pointers
-        std::vector<int4> sd(p->short_rows.size());
-        for (size_t i = 0; i < sd.size(); ++i) {
-            const int32_t v = p->short_rows[i];
-            const int32_t nl = p->local_row_ptr[v + 1] - p->local_row_ptr[v], nr = p->remote_row_ptr[v + 1] - p->remote_row_ptr[v];
-            sd[i] = make_int4(v, p->local_row_ptr[v], p->remote_row_ptr[v], nl | (nr << 16));
+    // the lists themselves are independent of each other: several threads where there is enough to copy
+    parallel_for(items.size(), nnz, [&](size_t b, size_t e) {
+        for (size_t i = b; i < e; ++i) put(items[i].beg, p->items[i].lbeg, p->items[i].lend, p->items[i].rbeg, p->items[i].rend);
+    });
+    parallel_for(sd.size(), nnz, [&](size_t b, size_t e) {
+        for (size_t i = b; i < e; ++i) {
+            const int32_t v = sd[i].x;
+            put(sd[i].y, p->local_row_ptr[v], p->local_row_ptr[v + 1], p->remote_row_ptr[v], p->remote_row_ptr[v + 1]);
         }
-        if ((s = upload(sd, &p->d.short_desc)) != MGG_OK) return s;
-    }
-    if ((s = upload(p->items, &p->d.items)) != MGG_OK) return s;
+    });
+    if ((s = upload(cols.get(), nnz, &p->d.cols)) != MGG_OK) return s;
+    if ((s = upload(w.get(), p->bags ? 0 : nnz, &p->d.wts)) != MGG_OK) return s;
+    if ((s = upload(sd, &p->d.short_desc)) != MGG_OK) return s;
+    if ((s = upload(items, &p->d.items)) != MGG_OK) return s;
     if ((s = upload(p->split_rows, &p->d.split_rows)) != MGG_OK) return s;
     return MGG_OK;
+}
+
+static mgg_status_t upload_all(mgg_partition *p)
+{
+    try {
+        return upload_arrays(p);
+    } catch (const std::bad_alloc &) {
+        return fail(MGG_ERR_ALLOC, "out of host memory while laying out the partition");
+    }
 }
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

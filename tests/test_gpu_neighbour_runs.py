@@ -1,0 +1,71 @@
+"""Runs of neighbours at every length: what does not fill a load step, a batch of steps or a run of 64, rows whose run
+crosses from the local to the halo table, wavefronts whose short rows differ in length, at every number of lanes a table
+row can take.  Reference: the sum in float64, row by row.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2209_06800_amd import binding
+
+pytestmark = pytest.mark.gpu
+U = 2.0 ** -24
+
+
+def _graph(n, top, rng):
+    """Row v of the first half has v mod (top + 1) neighbours anywhere; the others are only gathered."""
+    lens = np.concatenate([np.arange(n // 2) % (top + 1), np.zeros(n - n // 2, dtype=np.int64)])
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    row = np.repeat(np.arange(n), lens)
+    col = rng.integers(0, n - 1, ptr[-1])
+    return ptr, (col + (col >= row)).astype(np.int32)               # no self-loops
+
+
+@pytest.mark.parametrize("short_max", [-1, 16, 200])
+@pytest.mark.parametrize("dim,bf16", [(3, False), (16, False), (30, False), (64, False), (75, False), (128, False), (210, False), (300, False),
+                                      (5, True), (32, True), (60, True), (128, True), (250, True), (400, True)])
+def test_runs_of_every_length(dim, bf16, short_max):
+    rng = np.random.default_rng(dim + short_max)
+    n, top = 600, 149
+    ptr, col = _graph(n, top, rng)
+    x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
+    if bf16:
+        x = x.bfloat16()
+    bounds = np.array([0, 400, n], dtype=np.int64)                  # owned rows 0..399, some neighbours on the other side
+    part = binding.mgg_build_partition(ptr, col, 2, 0, bounds, short_max=short_max)
+    e = part.export()
+    halo = torch.from_numpy(e["halo_gid"].astype(np.int64)).cuda()
+    xd = x.double().cpu()
+    for mode in ("gin", "gcn"):
+        got = binding.mgg_aggregate(part, mode, x[:400].contiguous(), x[halo].contiguous(), eps=0.25).double().cpu()
+        dinv = torch.from_numpy(1.0 / np.sqrt(np.diff(ptr) + 1.0))
+        for v in range(400):
+            nb = torch.from_numpy(col[ptr[v]:ptr[v + 1]].astype(np.int64))
+            if mode == "gin":
+                want, scale = xd[nb].sum(0) + 1.25 * xd[v], xd[nb].abs().sum(0) + 1.25 * xd[v].abs()
+            else:
+                w = dinv[nb][:, None] * dinv[v]
+                want, scale = (w * xd[nb]).sum(0) + dinv[v] ** 2 * xd[v], (w * xd[nb].abs()).sum(0) + dinv[v] ** 2 * xd[v].abs()
+            # at most one rounding per term on the way, and four for factors, self term and row factor
+            assert ((got[v] - want).abs() <= (len(nb) + 5) * U * scale).all(), (mode, v)
+
+
+@pytest.mark.parametrize("dim,bf16", [(16, False), (64, False), (100, False), (200, False), (128, True)])
+def test_a_row_that_is_not_gathered_does_not_count(dim, bf16):
+    """Lanes without a neighbour of their own gather a row that exists and drop it: an infinity there reaches only the
+    rows whose neighbour it is."""
+    rng = np.random.default_rng(dim)
+    n, top = 600, 70
+    ptr, col = _graph(n, top, rng)
+    x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
+    bad = [0, 1, 399, 450]
+    x[bad] = float("inf")
+    if bf16:
+        x = x.bfloat16()
+    part = binding.mgg_build_partition(ptr, col, 2, 0, np.array([0, 400, n], dtype=np.int64))
+    halo = torch.from_numpy(part.export()["halo_gid"].astype(np.int64)).cuda()
+    for mode in ("gin", "gcn"):
+        got = binding.mgg_aggregate(part, mode, x[:400].contiguous(), x[halo].contiguous()).cpu()
+        for v in range(400):
+            touched = v in bad or bool(np.isin(col[ptr[v]:ptr[v + 1]], bad).any())
+            assert bool(torch.isinf(got[v]).all()) if touched else bool(torch.isfinite(got[v]).all()), (mode, v)
