@@ -309,20 +309,29 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     a.last_col = last_col;
     a.slab_vecs = slab_vecs;
     a.n_items = static_cast<int32_t>(p->items.size());
-    const int wpb = p->wpb;
+    int wpb = p->wpb;
     a.n_short = static_cast<int32_t>(p->short_rows.size());
     // Work per wavefront: M items (or groups of short rows) one after the other, pipelined.  More per
     // wavefront amortises its start-up latencies; fewer leaves more workgroups for the hardware to
     // balance.  Automatic: 2 where the launch still has about 8192 workgroups (measured on MI355X: 0.3-2.5 %
     // faster than 1 and than 8 on every workload tried), else 1.
-    const int64_t n_groups = (a.n_items + wpb - 1) / wpb;
+    // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel).  The chip holds some 5000
+    // wavefronts of these kernels, and a team is worth its barrier and its additions while its members have a batch
+    // of loads each and find a place at once: 8 or 4 to an item up to 4096 wavefronts in all (6480 rows, 11.0 us with
+    // and without; 370 rows of 115, 8.7 us at 2700 wavefronts and 10.2 at 5400), 2 up to 8192 (4389 rows, 12.0 ->
+    // 10.6 us at 6800).
+    bool team = false;
+    if (ch == 1 && p->opt_lds_halo == 0 && p->opt_items_per_wave == 0)
+        for (int t = kMaxTeam; t >= 2 && !team; t /= 2)
+            if (p->n_work_items * n_slabs * t <= (t == 2 ? 8192 : 4096) && p->longest_item >= t * 8 * (64 / lpr)) { team = true; wpb = t; }
+    const int64_t n_groups = team ? a.n_items : (a.n_items + wpb - 1) / wpb;
     const int64_t short_groups = (a.n_short + 64 / lpr - 1) / (64 / lpr);
     {
         auto pick = [&](int32_t opt, int64_t units, int64_t most) { return static_cast<int32_t>(opt > 0 ? opt : std::min<int64_t>(most, std::max<int64_t>(1, units * n_slabs / 8192))); };
-        a.items_per_wave = pick(p->opt_items_per_wave, n_groups, 2);
+        a.items_per_wave = team ? 1 : pick(p->opt_items_per_wave, n_groups, 2);
         a.short_per_wave = pick(p->opt_short_per_wave, (short_groups + wpb - 1) / wpb, 2);
     }
-    a.n_item_blocks = static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * a.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * a.items_per_wave) * kXcd);
+    a.n_item_blocks = team ? a.n_items : static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * a.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * a.items_per_wave) * kXcd);
     a.ps = p->ps;
     const bool gcn = mode == MGG_AGG_GCN_SYM;
     a.self_w = p->bags ? 0.f : 1.f + eps;
@@ -344,8 +353,8 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
         const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned;
         if (grid_x > 0) {
             hipError_t e;
-            if (bf16) e = launch_aggregate_bf16(a, gcn, vec, grid, wpb, stream, lpr, ch, lds);
-            else e = launch_aggregate_f32(a, gcn, vec, grid, wpb, stream, lpr, ch, lds);
+            if (bf16) e = launch_aggregate_bf16(a, gcn, vec, grid, wpb, stream, lpr, ch, lds, team);
+            else e = launch_aggregate_f32(a, gcn, vec, grid, wpb, stream, lpr, ch, lds, team);
             if (e != hipSuccess) return hip_fail(e, "aggregate kernel launch");
         }
         const int32_t n_split = static_cast<int32_t>(p->split_rows.size());

@@ -34,6 +34,7 @@ namespace mgg {
 #endif
 constexpr int kWave = 64;
 constexpr int kMaxWpb = 16;         // wavefronts per workgroup of the aggregation kernel
+constexpr int kMaxTeam = 8;         // wavefronts that take one item together in a small launch
 constexpr int kStageSlots = 8;      // LDS-staged variant: load instructions (1 KB each) per wavefront stage
 constexpr int kStageWpb = 8;        // LDS-staged variant: most wavefronts per workgroup (a wavefront owns 2 stages of 8 KB)
 
@@ -707,6 +708,60 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
     }
 }
 
+// Launches with too few items to fill the chip: all wavefronts of a workgroup take one item together, a share of its
+// neighbours each, and the first one adds up what the others leave in LDS, in a fixed order.  What such a launch costs is
+// the chain of loads behind its longest item (466 rows of up to 255 neighbours, 210 fp32 columns: 11.4 -> 4.8 us; 1,592
+// rows, 192 columns: 16.7 -> 9.6 us with the fix-up; 2,125 rows, 139 bf16 columns: 12.1 -> 10.4).
+template <class K, bool GCN>
+__global__ __launch_bounds__(kWave * kMaxTeam) void aggregate_team_kernel(const AggArgs a)
+{
+    __shared__ float sums[kMaxTeam - 1][K::LPR][K::VEC];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+    const int team = static_cast<int>(blockDim.x) / kWave;
+    Lanes<K> ln;
+    ln.init(a, lane);
+    const char *xl = static_cast<const char *>(a.x_local);
+    const char *xh = static_cast<const char *>(a.x_halo);
+    const uint64_t ldb = static_cast<uint64_t>(a.ld_x) * sizeof(typename K::elem);
+    if (static_cast<int>(blockIdx.x) >= a.n_item_blocks) {
+        short_rows<K, GCN>(a, wave, team, lane, ln, xl, xh, ldb);
+        return;
+    }
+    const ItemFields it = item_fields(a, reinterpret_cast<const int32_t *>(a.items)[static_cast<int64_t>(blockIdx.x) * 8 + (lane & 7)]);
+    if (it.row < 0) return;                                  // padding: the whole workgroup leaves
+    const int ps = a.ps;
+    const int share = (it.n + team * K::NPW - 1) / (team * K::NPW) * K::NPW;
+    const int end = min(it.n, (wave + 1) * share);
+    Acc<K> acc;
+    typename K::raw xs[K::CH];
+    if (wave == 0 && it.slot < 0 && !a.no_self && a.phase != 2) load_self_row<K>(a, it.row, ln, xs);
+    acc.clear();
+    uint32_t id = 0;
+    float w = 0.f;
+    int pos = wave * share;
+    if (pos < end) load_run<GCN>(a, it.beg + pos, min(ps, end - pos), lane, id, w);
+    for (; pos < end; pos += ps) {
+        uint32_t nid = 0;
+        float nw = 0.f;
+        if (pos + ps < end) load_run<GCN>(a, it.beg + pos + ps, min(ps, end - pos - ps), lane, nid, nw);
+        gather_run<K, GCN>(acc, id, w, min(ps, end - pos), xl, xh, ldb, ln);
+        id = nid; w = nw;
+    }
+    sum_subwaves<K>(acc);
+    if (wave > 0 && ln.sub == 0) {
+#pragma unroll
+        for (int e = 0; e < K::VEC; ++e) sums[wave - 1][ln.slot][e] = acc.v[0][e];
+    }
+    __syncthreads();
+    if (wave > 0 || ln.sub > 0) return;
+    for (int t = 0; t < team - 1; ++t)
+#pragma unroll
+        for (int e = 0; e < K::VEC; ++e) acc.v[0][e] += sums[t][ln.slot][e];
+    if (it.slot < 0) write_final<K>(a, GCN, acc, xs, it.row, ln);
+    else write_partial<K>(a, acc, it.slot, ln);
+}
+
 // ---- LDS staging of halo rows (section 5.2, "pipelined memory operation") -----------------------
 // A wavefront owns two LDS stages of kStageSlots load instructions (1 KB each: NPW rows).  The rows of
 // a remote partition are requested with global_load_lds -- memory to LDS, holding no registers while in
@@ -823,8 +878,15 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
 }
 
 template <class K>
-hipError_t launch_cfg(const AggArgs &a, bool gcn, dim3 grid, int wpb, hipStream_t stream, bool lds_halo)
+hipError_t launch_cfg(const AggArgs &a, bool gcn, dim3 grid, int wpb, hipStream_t stream, bool lds_halo, bool team)
 {
+    if constexpr (K::CH == 1) {
+        if (team) {
+            if (gcn) hipLaunchKernelGGL((aggregate_team_kernel<K, true>), grid, dim3(kWave * wpb), 0, stream, a);
+            else hipLaunchKernelGGL((aggregate_team_kernel<K, false>), grid, dim3(kWave * wpb), 0, stream, a);
+            return hipGetLastError();
+        }
+    }
     if constexpr (K::CH == 1 && sizeof(typename K::raw) == 16) {
         if (lds_halo && wpb <= kStageWpb) {
             const size_t lds = static_cast<size_t>(wpb) * 2 * kStageSlots * kWave * sizeof(uint4);     // 16 KB per wavefront
@@ -840,19 +902,19 @@ hipError_t launch_cfg(const AggArgs &a, bool gcn, dim3 grid, int wpb, hipStream_
 
 // LPR = smallest power of two >= the vectors of a slab (at least 4, at most 64); CH = chunks per lane.
 template <bool BF16, int VEC>
-hipError_t dispatch_shape(const AggArgs &a, bool gcn, dim3 grid, int wpb, hipStream_t stream, int lpr, int ch, bool lds)
+hipError_t dispatch_shape(const AggArgs &a, bool gcn, dim3 grid, int wpb, hipStream_t stream, int lpr, int ch, bool lds, bool team)
 {
-    if (lpr == 4) return launch_cfg<Cfg<BF16, VEC, 4, 1>>(a, gcn, grid, wpb, stream, lds);
-    if (lpr == 8) return launch_cfg<Cfg<BF16, VEC, 8, 1>>(a, gcn, grid, wpb, stream, lds);
-    if (lpr == 16) return launch_cfg<Cfg<BF16, VEC, 16, 1>>(a, gcn, grid, wpb, stream, lds);
-    if (lpr == 32) return launch_cfg<Cfg<BF16, VEC, 32, 1>>(a, gcn, grid, wpb, stream, lds);
-    if (ch == 1) return launch_cfg<Cfg<BF16, VEC, 64, 1>>(a, gcn, grid, wpb, stream, lds);
-    if (ch == 2) return launch_cfg<Cfg<BF16, VEC, 64, 2>>(a, gcn, grid, wpb, stream, lds);
-    return launch_cfg<Cfg<BF16, VEC, 64, 4>>(a, gcn, grid, wpb, stream, lds);      // ch <= 4: the host cuts wider rows into slabs
+    if (lpr == 4) return launch_cfg<Cfg<BF16, VEC, 4, 1>>(a, gcn, grid, wpb, stream, lds, team);
+    if (lpr == 8) return launch_cfg<Cfg<BF16, VEC, 8, 1>>(a, gcn, grid, wpb, stream, lds, team);
+    if (lpr == 16) return launch_cfg<Cfg<BF16, VEC, 16, 1>>(a, gcn, grid, wpb, stream, lds, team);
+    if (lpr == 32) return launch_cfg<Cfg<BF16, VEC, 32, 1>>(a, gcn, grid, wpb, stream, lds, team);
+    if (ch == 1) return launch_cfg<Cfg<BF16, VEC, 64, 1>>(a, gcn, grid, wpb, stream, lds, team);
+    if (ch == 2) return launch_cfg<Cfg<BF16, VEC, 64, 2>>(a, gcn, grid, wpb, stream, lds, team);
+    return launch_cfg<Cfg<BF16, VEC, 64, 4>>(a, gcn, grid, wpb, stream, lds, team);      // ch <= 4: the host cuts wider rows into slabs
 }
 
 // one translation unit per element type (aggregate_f32.hip, aggregate_bf16.hip)
-hipError_t launch_aggregate_f32(const AggArgs &a, bool gcn, int vec, dim3 grid, int wpb, hipStream_t stream, int lpr, int ch, bool lds);
-hipError_t launch_aggregate_bf16(const AggArgs &a, bool gcn, int vec, dim3 grid, int wpb, hipStream_t stream, int lpr, int ch, bool lds);
+hipError_t launch_aggregate_f32(const AggArgs &a, bool gcn, int vec, dim3 grid, int wpb, hipStream_t stream, int lpr, int ch, bool lds, bool team);
+hipError_t launch_aggregate_bf16(const AggArgs &a, bool gcn, int vec, dim3 grid, int wpb, hipStream_t stream, int lpr, int ch, bool lds, bool team);
 
 }  // namespace mgg

@@ -352,6 +352,12 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
             else cold.push_back(ri.first);
         }
     }
+    auto count_items = [&](const std::vector<WorkItem> &list) {
+        p->n_work_items += static_cast<int64_t>(list.size());
+        for (const WorkItem &it : list) p->longest_item = std::max(p->longest_item, it.lend - it.lbeg + it.rend - it.rbeg);
+    };
+    count_items(cold);
+    for (const auto &b : bucket) count_items(b);
     // heavy items first, so that the tail of the launch is made of small ones
     std::stable_sort(cold.begin(), cold.end(), [&](const WorkItem &a, const WorkItem &b) { return item_work(a) > item_work(b); });
     if (!use_classes) {
@@ -496,15 +502,19 @@ mgg_status_t mgg_build_partition(int64_t num_nodes, const int64_t *row_ptr, cons
             return d;
         };
         p->deg_own.resize(n_own); p->dinv_own.resize(n_own);
-        for (int64_t v = 0; v < n_own; ++v) {
-            p->deg_own[v] = degree_of(lb + v);
-            p->dinv_own[v] = static_cast<float>(1.0 / std::sqrt(static_cast<double>(p->deg_own[v]) + 1.0));
-        }
+        parallel_for(static_cast<size_t>(n_own), static_cast<size_t>(nnz), [&](size_t b, size_t e) {
+            for (size_t v = b; v < e; ++v) {
+                p->deg_own[v] = degree_of(lb + static_cast<int64_t>(v));
+                p->dinv_own[v] = static_cast<float>(1.0 / std::sqrt(static_cast<double>(p->deg_own[v]) + 1.0));
+            }
+        });
         p->deg_halo.resize(num_halo); p->dinv_halo.resize(num_halo);
-        for (int64_t h = 0; h < num_halo; ++h) {
-            p->deg_halo[h] = degree_of(p->halo_gid[h]);
-            p->dinv_halo[h] = static_cast<float>(1.0 / std::sqrt(static_cast<double>(p->deg_halo[h]) + 1.0));
-        }
+        parallel_for(static_cast<size_t>(num_halo), static_cast<size_t>(nnz), [&](size_t b, size_t e) {
+            for (size_t h = b; h < e; ++h) {
+                p->deg_halo[h] = degree_of(p->halo_gid[h]);
+                p->dinv_halo[h] = static_cast<float>(1.0 / std::sqrt(static_cast<double>(p->deg_halo[h]) + 1.0));
+            }
+        });
 
         build_schedule(p, knobs);
     } catch (const std::bad_alloc &) {

@@ -1,6 +1,7 @@
 """Runs of neighbours at every length: what does not fill a load step, a batch of steps or a run of 64, rows whose run
 crosses from the local to the halo table, wavefronts whose short rows differ in length, at every number of lanes a table
-row can take.  Reference: the sum in float64, row by row.
+row can take; items taken by a team of wavefronts, as a launch this small does by itself, and one after the other by one
+(items_per_wave given).  Reference: the sum in float64, row by row.
 """
 import numpy as np
 import pytest
@@ -21,10 +22,10 @@ def _graph(n, top, rng):
     return ptr, (col + (col >= row)).astype(np.int32)               # no self-loops
 
 
-@pytest.mark.parametrize("short_max", [-1, 16, 200])
+@pytest.mark.parametrize("short_max,per_wave", [(-1, 0), (-1, 2), (16, 0), (200, 0)])
 @pytest.mark.parametrize("dim,bf16", [(3, False), (16, False), (30, False), (64, False), (75, False), (128, False), (210, False), (300, False),
                                       (5, True), (32, True), (60, True), (128, True), (250, True), (400, True)])
-def test_runs_of_every_length(dim, bf16, short_max):
+def test_runs_of_every_length(dim, bf16, short_max, per_wave):
     rng = np.random.default_rng(dim + short_max)
     n, top = 600, 149
     ptr, col = _graph(n, top, rng)
@@ -33,6 +34,7 @@ def test_runs_of_every_length(dim, bf16, short_max):
         x = x.bfloat16()
     bounds = np.array([0, 400, n], dtype=np.int64)                  # owned rows 0..399, some neighbours on the other side
     part = binding.mgg_build_partition(ptr, col, 2, 0, bounds, short_max=short_max)
+    part.set_option("items_per_wave", per_wave)
     e = part.export()
     halo = torch.from_numpy(e["halo_gid"].astype(np.int64)).cuda()
     xd = x.double().cpu()
@@ -50,8 +52,9 @@ def test_runs_of_every_length(dim, bf16, short_max):
             assert ((got[v] - want).abs() <= (len(nb) + 5) * U * scale).all(), (mode, v)
 
 
+@pytest.mark.parametrize("per_wave", [0, 1])
 @pytest.mark.parametrize("dim,bf16", [(16, False), (64, False), (100, False), (200, False), (128, True)])
-def test_a_row_that_is_not_gathered_does_not_count(dim, bf16):
+def test_a_row_that_is_not_gathered_does_not_count(dim, bf16, per_wave):
     """Lanes without a neighbour of their own gather a row that exists and drop it: an infinity there reaches only the
     rows whose neighbour it is."""
     rng = np.random.default_rng(dim)
@@ -63,9 +66,38 @@ def test_a_row_that_is_not_gathered_does_not_count(dim, bf16):
     if bf16:
         x = x.bfloat16()
     part = binding.mgg_build_partition(ptr, col, 2, 0, np.array([0, 400, n], dtype=np.int64))
+    part.set_option("items_per_wave", per_wave)
     halo = torch.from_numpy(part.export()["halo_gid"].astype(np.int64)).cuda()
     for mode in ("gin", "gcn"):
         got = binding.mgg_aggregate(part, mode, x[:400].contiguous(), x[halo].contiguous()).cpu()
         for v in range(400):
             touched = v in bad or bool(np.isin(col[ptr[v]:ptr[v + 1]], bad).any())
             assert bool(torch.isinf(got[v]).all()) if touched else bool(torch.isfinite(got[v]).all()), (mode, v)
+
+
+@pytest.mark.parametrize("dim,bf16", [(16, False), (30, False), (64, False), (100, False), (200, False), (128, True), (300, True)])
+def test_teams_of_every_size(dim, bf16):
+    """Launches that take teams of 8, 4 and 2 wavefronts, with rows cut at 1024 neighbours beside whole ones, against
+    one wavefront per item: equal up to the order of the sums."""
+    rng = np.random.default_rng(dim)
+    for rows in (40, 300, 900, 2500):
+        n = 3000
+        lens = np.zeros(n, dtype=np.int64)
+        lens[:rows] = rng.integers(17, 600, rows)
+        lens[rng.integers(0, rows, 3)] = 2500
+        ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        row = np.repeat(np.arange(n), lens)
+        col = rng.integers(0, n - 1, ptr[-1])
+        col = (col + (col >= row)).astype(np.int32)
+        x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
+        if bf16:
+            x = x.bfloat16()
+        part = binding.mgg_build_partition(ptr, col, xcd_min_deg=-1)
+        for mode in ("gin", "gcn"):
+            out = []
+            for per_wave in (0, 2):
+                part.set_option("items_per_wave", per_wave)
+                out.append(binding.mgg_aggregate(part, mode, x, eps=0.5).double())
+            scale = binding.mgg_aggregate(part, mode, x.abs(), eps=0.5).double()
+            bound = 2 * (torch.from_numpy(lens).cuda()[:, None] + 5) * U * scale
+            assert ((out[0] - out[1]).abs() <= bound).all(), (rows, mode)
