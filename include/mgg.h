@@ -157,7 +157,8 @@ mgg_status_t mgg_partition_info(const mgg_partition_t *p, mgg_partition_info_t *
  * columns wide.  Rows with many neighbours are cut into several wavefront work items (section
  * 4.1 Step-3: neighbour partitions; section 5.1: a wavefront takes a few of them), whose partial
  * sums pass through this buffer: mgg_aggregate_scratch_bytes(p, dim) bytes, nothing when no row
- * is cut.  Host, synchronous (it may wait for the device and allocate); never shrinks.  The
+ * is cut (up to three times that where there is room: a schedule with more and smaller pieces, taken for large
+ * shares).  Host, synchronous (it may wait for the device and allocate); never shrinks.  The
  * device calls below allocate nothing: mgg_aggregate / mgg_aggregate_to / mgg_bag_sum /
  * mgg_time_aggregate on a width that was not reserved fail with MGG_ERR_INVALID_ARG.
  * mgg_layer_forward does not use this buffer (its workspace holds the partial sums).

@@ -283,8 +283,12 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     // scratch rows for the partial sums of split rows: the caller's buffer, else the partition's own;
     // nothing is allocated here
     int64_t scratch_ld = 0;
+    // the fine schedule where its partial sums have room
+    bool fine = p->n_fine_sums > 0;
     if (p->n_split_items > 0) {
         scratch_ld = scratch_ld_for(dim);
+        const size_t fine_need = static_cast<size_t>(p->n_split_items + p->n_fine_sums) * static_cast<size_t>(scratch_ld) * sizeof(float);
+        if (scratch ? scratch_bytes < fine_need : p->d.scratch_rows < p->n_split_items + p->n_fine_sums) fine = false;
         const size_t need = static_cast<size_t>(p->n_split_items) * static_cast<size_t>(scratch_ld) * sizeof(float);
         if (scratch) {
             if (scratch_bytes < need) return fail(MGG_ERR_INVALID_ARG, "scratch of %zu bytes given, width %d needs %zu", scratch_bytes, dim, need);
@@ -301,14 +305,14 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     AggArgs a{};
     a.cols = p->d.cols; a.wts = p->d.wts;
     a.dinv_own = p->d.dinv_own;
-    a.short_desc = p->d.short_desc; a.items = p->d.items;
+    a.short_desc = p->d.short_desc; a.items = fine ? p->d.fine_items : p->d.items;
     a.x_local = x_local; a.x_halo = xh;
     a.out = out; a.scratch = scratch;
     a.ld_x = ld_x; a.ld_out = ld_out; a.scratch_ld = scratch_ld;
     a.nvec = nvec;
     a.last_col = last_col;
     a.slab_vecs = slab_vecs;
-    a.n_items = static_cast<int32_t>(p->items.size());
+    a.n_items = static_cast<int32_t>(fine ? p->fine_items.size() : p->items.size());
     int wpb = p->wpb;
     a.n_short = static_cast<int32_t>(p->short_rows.size());
     // Work per wavefront: M items (or groups of short rows) one after the other, pipelined.  More per
@@ -357,7 +361,7 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
             else e = launch_aggregate_f32(a, gcn, vec, grid, wpb, stream, lpr, ch, lds, team);
             if (e != hipSuccess) return hip_fail(e, "aggregate kernel launch");
         }
-        const int32_t n_split = static_cast<int32_t>(p->split_rows.size());
+        const int32_t n_split = static_cast<int32_t>(p->split_rows.size() + (fine ? p->fine_split_rows.size() : 0));
         if (n_split > 0) {
             const dim3 fgrid(static_cast<unsigned>((n_split + kWavesPerBlock - 1) / kWavesPerBlock));
             if (bf16)

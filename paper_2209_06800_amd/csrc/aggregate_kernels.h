@@ -414,6 +414,10 @@ __device__ __forceinline__ void gather_run(Acc<K> &acc, uint32_t id, float w, in
     }
 }
 
+struct ItemFields {
+    int row, beg, n_l, n, slot, rbeg;      // local neighbours from beg on, the others from rbeg on
+};
+
 // Neighbour `lane` of the `len` (1 .. 64) from position `at` on.  Lanes beyond them read the first one again: what
 // they hold is always a row of a table.  Both arrays are read as coalesced streams (the factors are stored per edge).
 template <bool GCN>
@@ -422,6 +426,14 @@ __device__ __forceinline__ void load_run(const AggArgs &a, int at, int len, int 
     const int p = lane < len ? lane : 0;
     id = (a.cols + at)[p];
     if constexpr (GCN) w = (a.wts + at)[p];
+}
+// The same from position `pos` of an item on, whose remote neighbours may lie apart from its local ones.
+template <bool GCN>
+__device__ __forceinline__ void load_run(const AggArgs &a, const ItemFields &it, int pos, int len, int lane, uint32_t &id, float &w)
+{
+    const int p = pos + (lane < len ? lane : 0), at = p < it.n_l ? it.beg + p : it.rbeg + p - it.n_l;
+    id = a.cols[at];
+    if constexpr (GCN) w = a.wts[at];
 }
 
 // Final value of an owned row from its neighbour sum: adds the self term and the row factor.
@@ -525,16 +537,13 @@ __device__ __forceinline__ float sum_subwaves(float v)
 //
 // Item descriptors travel as one dword per lane (lane f mod 8 holds field f of the 32-byte record)
 // through the vector memory path, whose loads return in order behind the gathers already in flight.
-struct ItemFields {
-    int row, beg, n_l, n, slot;
-};
 __device__ __forceinline__ ItemFields item_fields(const AggArgs &a, int d)
 {
     ItemFields f;
     f.row = __builtin_amdgcn_readlane(d, 0); f.beg = __builtin_amdgcn_readlane(d, 1); f.n_l = __builtin_amdgcn_readlane(d, 2);
-    f.n = __builtin_amdgcn_readlane(d, 3); f.slot = __builtin_amdgcn_readlane(d, 4);
+    f.n = __builtin_amdgcn_readlane(d, 3); f.slot = __builtin_amdgcn_readlane(d, 4); f.rbeg = __builtin_amdgcn_readlane(d, 5);
     if (a.phase == 1) f.n = f.n_l;
-    if (a.phase == 2) { f.beg += f.n_l; f.n -= f.n_l; f.n_l = 0; }
+    if (a.phase == 2) { f.n -= f.n_l; f.n_l = 0; }
     if (f.row < 0) f.n = 0;
     return f;
 }
@@ -686,7 +695,7 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
         const ItemFields it = item_fields(a, d_cur);
         if (it.row >= 0) {
             const int n = it.n;
-            if (!ids_ready && n > 0) load_run<GCN>(a, it.beg, min(ps, n), lane, id, w);
+            if (!ids_ready && n > 0) load_run<GCN>(a, it, 0, min(ps, n), lane, id, w);
             const ItemFields nx = item_fields(a, d_nxt);
             if (it.slot < 0 && !a.no_self && a.phase != 2) load_self_row<K>(a, it.row, ln, xs);
             acc.clear();
@@ -694,8 +703,8 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
                 // ids of the next run -- of this item, or the first one of the next
                 uint32_t nid = 0;
                 float nw = 0.f;
-                if (pos + ps < n) load_run<GCN>(a, it.beg + pos + ps, min(ps, n - pos - ps), lane, nid, nw);
-                else if (nx.n > 0) load_run<GCN>(a, nx.beg, min(ps, nx.n), lane, nid, nw);
+                if (pos + ps < n) load_run<GCN>(a, it, pos + ps, min(ps, n - pos - ps), lane, nid, nw);
+                else if (nx.n > 0) load_run<GCN>(a, nx, 0, min(ps, nx.n), lane, nid, nw);
                 gather_run<K, GCN>(acc, id, w, min(ps, n - pos), xl, xh, ldb, ln);
                 id = nid; w = nw;
             }
@@ -740,11 +749,11 @@ __global__ __launch_bounds__(kWave * kMaxTeam) void aggregate_team_kernel(const 
     uint32_t id = 0;
     float w = 0.f;
     int pos = wave * share;
-    if (pos < end) load_run<GCN>(a, it.beg + pos, min(ps, end - pos), lane, id, w);
+    if (pos < end) load_run<GCN>(a, it, pos, min(ps, end - pos), lane, id, w);
     for (; pos < end; pos += ps) {
         uint32_t nid = 0;
         float nw = 0.f;
-        if (pos + ps < end) load_run<GCN>(a, it.beg + pos + ps, min(ps, end - pos - ps), lane, nid, nw);
+        if (pos + ps < end) load_run<GCN>(a, it, pos + ps, min(ps, end - pos - ps), lane, nid, nw);
         gather_run<K, GCN>(acc, id, w, min(ps, end - pos), xl, xh, ldb, ln);
         id = nid; w = nw;
     }
@@ -844,7 +853,7 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
         const int n_l = it.n_l, n_r = it.n - it.n_l;
         if (it.slot < 0 && !a.no_self && a.phase != 2) load_self_row<K>(a, it.row, ln, xs);
         acc.clear();
-        const int lbeg = it.beg, rbeg = it.beg + n_l;
+        const int lbeg = it.beg, rbeg = it.rbeg;
         uint32_t id_l = 0, id_r = 0;
         float w_l = 0.f, w_r = 0.f;
         if (n_l > 0) load_run<GCN>(a, lbeg, min(ps, n_l), lane, id_l, w_l);

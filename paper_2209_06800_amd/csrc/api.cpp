@@ -95,6 +95,7 @@ struct LayerPlan {
     size_t agg_bytes = 0, hid_bytes = 0;        // aggregation result (width dims[0], or dims[1] when update_first), hidden activations
     size_t t_local_bytes = 0, t_halo_bytes = 0; // update_first: X w[0] of the two tables, leading dimension ld_agg
     size_t scratch_bytes = 0;                   // partial sums of rows cut into several work items (last in the workspace)
+    size_t least_scratch_bytes = 0;             // those of the schedule that has fewer
     mgg_dtype_t hid_dtype = MGG_F32;
     size_t total() const { return agg_bytes + hid_bytes + t_local_bytes + t_halo_bytes + scratch_bytes; }
     size_t scratch_offset() const { return agg_bytes + hid_bytes + t_local_bytes + t_halo_bytes; }
@@ -119,7 +120,8 @@ static bool plan_layer(const mgg_partition *p, const mgg_layer_desc_t *l, mgg_dt
         pl->t_halo_bytes = round_up(p->halo_gid.size() * static_cast<size_t>(pl->ld_agg) * sizeof(float), 256);
         if (l->n_linear == 1) pl->agg_bytes = 0;       // aggregated rows are the layer's output
     }
-    pl->scratch_bytes = round_up(scratch_bytes_for(p, static_cast<int32_t>(pl->ld_agg)), 256);
+    pl->scratch_bytes = round_up(scratch_bytes_wanted(p, static_cast<int32_t>(pl->ld_agg)), 256);
+    pl->least_scratch_bytes = round_up(scratch_bytes_for(p, static_cast<int32_t>(pl->ld_agg)), 256);
     if (l->n_linear == 2 && !pl->update_first) {
         pl->hid_dtype = l->w_dtype == MGG_BF16 ? MGG_BF16 : MGG_F32;
         pl->ld_hid = static_cast<int64_t>(round_up(static_cast<size_t>(l->dims[1]), 8));
@@ -190,11 +192,19 @@ mgg_status_t mgg_partition_reserve(mgg_partition_t *p, int32_t dim)
     if (p->n_split_items == 0 || p->d.scratch_ld >= need_ld) return MGG_OK;
     // work already enqueued may still use the old buffer
     MGG_HIP_TRY(hipDeviceSynchronize());
-    if (p->d.scratch) { (void)hipFree(p->d.scratch); p->d.scratch = nullptr; p->d.scratch_ld = 0; }
-    const size_t bytes = static_cast<size_t>(p->n_split_items) * static_cast<size_t>(need_ld) * sizeof(float);
+    if (p->d.scratch) { (void)hipFree(p->d.scratch); p->d.scratch = nullptr; p->d.scratch_ld = 0; p->d.scratch_rows = 0; }
+    size_t bytes = scratch_bytes_wanted(p, dim);
+    int64_t rows = p->n_split_items + p->n_fine_sums;
     hipError_t e = hipMalloc(reinterpret_cast<void **>(&p->d.scratch), bytes);
+    if (e != hipSuccess && p->n_fine_sums > 0) {        // the schedule with fewer partial sums will do
+        (void)hipGetLastError();
+        rows = p->n_split_items;
+        bytes = scratch_bytes_for(p, dim);
+        e = hipMalloc(reinterpret_cast<void **>(&p->d.scratch), bytes);
+    }
     if (e != hipSuccess) { p->reserved_dim = 0; return fail(MGG_ERR_ALLOC, "hipMalloc(%zu bytes of scratch): %s", bytes, hipGetErrorString(e)); }
     p->d.scratch_ld = need_ld;
+    p->d.scratch_rows = rows;
     return MGG_OK;
 }
 
@@ -241,6 +251,7 @@ mgg_status_t mgg_layer_forward(const mgg_partition_t *p, const mgg_layer_desc_t 
     if (!dtype_ok(x_dtype) || !dtype_ok(out_dtype)) return fail(MGG_ERR_INVALID_ARG, "unknown dtype");
     if (!plan_layer(p, layer, x_dtype, out_dtype, &pl)) return fail(MGG_ERR_INVALID_ARG, "bad layer description");
     if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256) return fail(MGG_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
+    if (workspace_bytes < pl.total()) pl.scratch_bytes = pl.least_scratch_bytes;
     if (workspace_bytes < pl.total()) return fail(MGG_ERR_INVALID_ARG, "workspace too small: %zu < %zu", workspace_bytes, pl.total());
     const int32_t d0 = layer->dims[0], d1 = layer->dims[1], d2 = layer->dims[2];
     hipStream_t st = static_cast<hipStream_t>(stream);

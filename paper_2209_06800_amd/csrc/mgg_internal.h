@@ -25,9 +25,10 @@ struct WorkItem {
 };
 
 // The same on the device, where an item's neighbours lie in one run of `cols`: the local ones, then the remote ones.
+// (Pieces of rows that are whole items in the other schedule leave the remote ones where they are: `rbeg`.)
 struct DeviceItem {
-    int32_t row, beg, n_local, n, slot;
-    int32_t pad[3];
+    int32_t row, beg, n_local, n, slot, rbeg;
+    int32_t pad[2];
 };
 static_assert(sizeof(DeviceItem) == 32, "a wavefront reads an item as eight dwords");
 
@@ -43,6 +44,8 @@ struct SplitRow {
 constexpr int kXcd = 8;             // accelerator complex dies of an MI355X, each with its own L2
 constexpr int kDefaultWpb = 2;      // work items (wavefronts) per workgroup of the aggregation kernel
 constexpr int kDefaultXcdMinDeg = 256;
+constexpr int kFineXcdMinDeg = 128;         // rows regrouped in the fine schedule too
+constexpr int64_t kFineMinNeighbours = 8 << 20;   // shares of fewer neighbours have none
 constexpr int kDefaultHotPhases = 0;        // automatic choice between hash classes and popularity phases
 constexpr int kAutoHotPhases = 4;           // phases when the automatic choice takes popularity classes
 constexpr int kMaxHotPhases = 31;           // class index phase * 8 + XCD has to stay below kColdClass
@@ -57,9 +60,10 @@ struct DeviceArrays {
     float *dinv_own = nullptr;
     int4 *short_desc = nullptr;        // per short row: row, start in cols, local neighbours, all neighbours
     DeviceItem *items = nullptr;
-    SplitRow *split_rows = nullptr;
-    float *scratch = nullptr;          // [n_split_items x scratch_ld] partial sums
-    int64_t scratch_ld = 0;
+    DeviceItem *fine_items = nullptr;
+    SplitRow *split_rows = nullptr;    // those of the fine schedule alone follow the others
+    float *scratch = nullptr;          // [scratch_rows x scratch_ld] partial sums
+    int64_t scratch_ld = 0, scratch_rows = 0;
 };
 
 }  // namespace mgg
@@ -83,6 +87,11 @@ struct mgg_partition {
     std::vector<mgg::WorkItem> items;
     std::vector<mgg::SplitRow> split_rows;
     int64_t n_split_items = 0;
+    // The fine schedule (empty: none): rows of kFineXcdMinDeg to 255 neighbours are pieces by source class, too.  It is taken
+    // where the scratch at hand holds its partial sums, which are at most three times as many.
+    std::vector<mgg::WorkItem> fine_items;
+    std::vector<mgg::SplitRow> fine_split_rows;      // of those rows; their partial sums follow the others
+    int64_t n_fine_sums = 0;
     int64_t n_work_items = 0;         // items without the padding of the XCD queues
     int32_t longest_item = 0;         // neighbours of the longest one
     // run-time switches of this partition's aggregations: the process-wide defaults at build time, then mgg_partition_set_option
@@ -123,6 +132,8 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
 // scratch / scratch_bytes: where the partial sums of rows cut into several items go; NULL = the partition's
 // own buffer (mgg_partition_reserve).  The launch allocates nothing: too small a buffer is an error.
 inline int64_t scratch_ld_for(int32_t dim) { return (static_cast<int64_t>(dim) + 7) / 8 * 8; }   // rows of partial sums start on 32-byte boundaries
+// (the least an aggregation can do with, and what it has a use for)
+inline size_t scratch_bytes_wanted(const mgg_partition *p, int32_t dim) { return static_cast<size_t>(p->n_split_items + p->n_fine_sums) * static_cast<size_t>(scratch_ld_for(dim)) * sizeof(float); }
 inline size_t scratch_bytes_for(const mgg_partition *p, int32_t dim) { return static_cast<size_t>(p->n_split_items) * static_cast<size_t>(scratch_ld_for(dim)) * sizeof(float); }
 // the library's fixed scratch array on the current device (aggregate.hip); NULL + error set on failure
 float *static_scratch(size_t *bytes);

@@ -68,7 +68,7 @@ static void free_device(mgg_partition *p)
 {
     if (p->device < 0) return;
     DeviceArrays &d = p->d;
-    void *ptrs[] = {d.cols, d.wts, d.dinv_own, d.short_desc, d.items, d.split_rows, d.scratch};
+    void *ptrs[] = {d.cols, d.wts, d.dinv_own, d.short_desc, d.items, d.fine_items, d.split_rows, d.scratch};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     d = DeviceArrays{};
@@ -104,7 +104,8 @@ static mgg_status_t upload_arrays(mgg_partition *p)
         for (size_t g = static_cast<size_t>(x) * p->wpb; g < items.size(); g += static_cast<size_t>(kXcd) * p->wpb)
             for (size_t i = g; i < std::min(items.size(), g + p->wpb); ++i) {
                 const WorkItem &it = p->items[i];
-                items[i] = DeviceItem{it.row, at, it.lend - it.lbeg, it.lend - it.lbeg + it.rend - it.rbeg, it.slot, {0, 0, 0}};
+                const int32_t nl = it.lend - it.lbeg;
+                items[i] = DeviceItem{it.row, at, nl, nl + it.rend - it.rbeg, it.slot, at + nl, {0, 0}};
                 at += items[i].n;
             }
     // one 16-byte record per short row, so that the kernel needs no dependent look-up of row pointers
@@ -128,7 +129,35 @@ static mgg_status_t upload_arrays(mgg_partition *p)
     if ((s = upload(w.get(), p->bags ? 0 : nnz, &p->d.wts)) != MGG_OK) return s;
     if ((s = upload(sd, &p->d.short_desc)) != MGG_OK) return s;
     if ((s = upload(items, &p->d.items)) != MGG_OK) return s;
-    if ((s = upload(p->split_rows, &p->d.split_rows)) != MGG_OK) return s;
+    {
+        std::vector<SplitRow> rows(p->split_rows);
+        rows.insert(rows.end(), p->fine_split_rows.begin(), p->fine_split_rows.end());
+        if ((s = upload(rows, &p->d.split_rows)) != MGG_OK) return s;
+    }
+    if (!p->fine_items.empty()) {
+        // its items lie in the same stream: where the items of that row begin there, plus the distance to the piece
+        std::vector<int32_t> where(static_cast<size_t>(p->n_own), -1);          // whole rows
+        std::vector<int32_t> of_slot(static_cast<size_t>(p->n_split_items), -1);
+        for (const DeviceItem &it : items) {
+            if (it.row < 0) continue;
+            if (it.slot < 0) where[it.row] = it.beg;
+            else of_slot[it.slot] = it.beg;
+        }
+        std::vector<DeviceItem> fine(p->fine_items.size());
+        for (size_t i = 0; i < fine.size(); ++i) {
+            const WorkItem &it = p->fine_items[i];
+            const int32_t nl = it.lend - it.lbeg, n = nl + it.rend - it.rbeg;
+            int32_t beg = 0, rbeg = 0;
+            if (it.row >= 0 && it.slot >= 0 && it.slot < p->n_split_items) {
+                beg = of_slot[it.slot]; rbeg = beg + nl;
+            } else if (it.row >= 0) {
+                const int32_t l0 = p->local_row_ptr[it.row], r0 = p->remote_row_ptr[it.row], row_nl = p->local_row_ptr[it.row + 1] - l0;
+                beg = where[it.row] + it.lbeg - l0; rbeg = where[it.row] + row_nl + it.rbeg - r0;
+            }
+            fine[i] = DeviceItem{it.row, beg, nl, n, it.slot, rbeg, {0, 0}};
+        }
+        if ((s = upload(fine, &p->d.fine_items)) != MGG_OK) return s;
+    }
     return MGG_OK;
 }
 
@@ -170,6 +199,7 @@ struct Knobs {
     int32_t ps = 64, dist = 8, short_max = 16, host_only = 0, xcd_min_deg = kDefaultXcdMinDeg, wpb = kDefaultWpb;
     int32_t hot_rows = 0, hot_phases = kDefaultHotPhases, min_piece = kDefaultMinPiece, hot_min_count = kDefaultHotMinCount;
     int32_t reserve_dim = 0;
+    bool fine = true;              // a fine schedule beside the other one where it pays (not with knobs of the caller)
 };
 
 static mgg_status_t parse_opts(const mgg_build_opts_t *opts, Knobs *k)
@@ -188,6 +218,7 @@ static mgg_status_t parse_opts(const mgg_build_opts_t *opts, Knobs *k)
         if (opts->short_max) short_max = opts->short_max;
         host_only = opts->host_only;
         if (opts->xcd_min_deg) xcd_min_deg = opts->xcd_min_deg;
+        k->fine = !opts->xcd_min_deg && !opts->min_piece;
         if (opts->wpb) wpb = opts->wpb;
         k->reserve_dim = opts->reserve_dim;
     }
@@ -207,6 +238,46 @@ static mgg_status_t parse_opts(const mgg_build_opts_t *opts, Knobs *k)
     if (hot_min_count < 1) return fail(MGG_ERR_INVALID_ARG, "hot_min_count %d below 1", hot_min_count);
     if (k->reserve_dim < 0) return fail(MGG_ERR_INVALID_ARG, "reserve_dim %d below 0", k->reserve_dim);
     return MGG_OK;
+}
+
+// Items in the order of the launch.  n_hot < 0: no classes.
+static std::vector<WorkItem> lay_out(const mgg_partition *p, std::vector<std::vector<WorkItem>> &bucket, std::vector<WorkItem> &cold, int n_hot)
+{
+    const int32_t wpb = p->wpb;
+    auto item_work = [](const WorkItem &it) { return static_cast<int64_t>(it.lend - it.lbeg) + (it.rend - it.rbeg) + 8; };
+    std::vector<WorkItem> items;
+    // heavy items first, so that the tail of the launch is made of small ones
+    std::stable_sort(cold.begin(), cold.end(), [&](const WorkItem &a, const WorkItem &b) { return item_work(a) > item_work(b); });
+    if (n_hot < 0) return std::move(cold);
+    {
+        // XCD x takes the hot items of classes (0, x), (1, x), ... in that order; cold items then
+        // go, largest first, to whichever XCD has the least work so far (a gather that hits in L2
+        // is taken as half the cost of one that does not)
+        std::vector<std::vector<WorkItem>> queue(kXcd);
+        std::vector<int64_t> queue_work(kXcd, 0);
+        for (int c = 0; c < n_hot; ++c) {
+            std::vector<WorkItem> &q = queue[c % kXcd];
+            for (const WorkItem &it : bucket[c]) queue_work[c % kXcd] += item_work(it);
+            q.insert(q.end(), bucket[c].begin(), bucket[c].end());
+        }
+        for (int c = 0; c < kXcd; ++c) queue_work[c] /= 2;
+        for (const WorkItem &it : cold) {
+            const int c = static_cast<int>(std::min_element(queue_work.begin(), queue_work.end()) - queue_work.begin());
+            queue[c].push_back(it);
+            queue_work[c] += item_work(it);
+        }
+        // launch order: workgroup b (wpb items) runs on XCD b mod kXcd; pad with empty items
+        size_t longest = 0;
+        for (auto &q : queue) longest = std::max(longest, q.size());
+        longest = (longest + wpb - 1) / wpb * wpb;
+        const WorkItem dummy{-1, 0, 0, 0, 0, -1, 0, 0};
+        for (auto &q : queue) q.resize(longest, dummy);
+        items.reserve(longest * kXcd);
+        for (size_t g = 0; g < longest; g += wpb)
+            for (int c = 0; c < kXcd; ++c)
+                items.insert(items.end(), queue[c].begin() + g, queue[c].begin() + g + wpb);
+    }
+    return items;
 }
 
 // Source classes, work items and the short-row bin of a partition whose two CSRs are in place
@@ -290,7 +361,6 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
     std::vector<std::vector<WorkItem>> bucket(static_cast<size_t>(std::max(n_hot, 1)));   // hot items by class
     std::vector<WorkItem> cold;                              // cold pieces and whole rows
     std::vector<std::vector<int32_t>> by_len(short_max >= 0 ? short_max + 1 : 0);
-    auto item_work = [](const WorkItem &it) { return static_cast<int64_t>(it.lend - it.lbeg) + (it.rend - it.rbeg) + 8; };
     std::vector<int32_t> n_in(static_cast<size_t>(n_hot) + 1), lcut(static_cast<size_t>(n_hot) + 2), rcut(static_cast<size_t>(n_hot) + 2), pos(static_cast<size_t>(n_hot) + 1), tmp;
     std::vector<uint8_t> final_class(static_cast<size_t>(n_hot) + 1);
     // stable counting sort of col[b, e) by final class of the table row `base + col`; cut[c] = start of class c
@@ -304,6 +374,24 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
         for (int32_t u : tmp) col[pos[final_class[std::min<int>(p->src_class[base + u], n_hot)]]++] = u;
     };
     std::vector<std::pair<WorkItem, int>> row_items;         // item, class (n_hot = cold)
+    // The fine schedule costs a partial sum per class and row and keeps the gathers of these rows in one XCD's L2.  From 128
+    // neighbours on (16 per class) it pays on large shares (233 k rows, 602 columns: 18.27 -> 17.63 ms; 120 k rows, 256
+    // columns: 2.93 -> 2.70; 17.8 M neighbours at 64 columns: 356 -> 346 us; 28 M at 128 in bf16: 736 -> 722; from 64 on
+    // nothing more; 3.2 M at 75 columns: 137.4 -> 138.5).  With popularity classes it changes nothing.
+    const int64_t nnz = static_cast<int64_t>(p->local_col.size()) + static_cast<int64_t>(p->remote_col.size());
+    bool fine = k.fine && p->class_mode == 1 && n_phase == 1 && nnz >= kFineMinNeighbours && xcd_min_deg == kDefaultXcdMinDeg && run >= kDefaultXcdMinDeg;
+    std::vector<std::vector<WorkItem>> fine_bucket(fine ? bucket.size() : 0);
+    std::vector<WorkItem> fine_cold;
+    // the pieces of a row by class: cuts of its two regrouped lists
+    auto cut_by_class = [&](int32_t l0, int32_t l1, int32_t r0, int32_t r1) {
+        std::fill(n_in.begin(), n_in.end(), 0);
+        for (int32_t i = l0; i < l1; ++i) ++n_in[std::min<int>(p->src_class[p->local_col[i]], n_hot)];
+        for (int32_t i = r0; i < r1; ++i) ++n_in[std::min<int>(p->src_class[n_loc + p->remote_col[i]], n_hot)];
+        for (int c = 0; c < n_hot; ++c) final_class[c] = static_cast<uint8_t>(n_in[c] >= min_piece ? c : n_hot);
+        final_class[n_hot] = static_cast<uint8_t>(n_hot);
+        regroup(p->sched_local_col, l0, l1, 0, lcut);
+        regroup(p->sched_remote_col, r0, r1, n_loc, rcut);
+    };
     for (int64_t v = 0; v < n_own; ++v) {
         const int32_t l0 = p->local_row_ptr[v], l1 = p->local_row_ptr[v + 1];
         const int32_t r0 = p->remote_row_ptr[v], r1 = p->remote_row_ptr[v + 1];
@@ -314,13 +402,7 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
         // the pieces of this row: one per surviving class if it is regrouped, otherwise the whole row
         int first_piece = n_hot, n_piece_end = n_hot + 1;     // default: only the cold piece = the whole row
         if (use_classes && n_hot > 0 && dl + dr >= xcd_min_deg) {
-            std::fill(n_in.begin(), n_in.end(), 0);
-            for (int32_t i = l0; i < l1; ++i) ++n_in[std::min<int>(p->src_class[p->local_col[i]], n_hot)];
-            for (int32_t i = r0; i < r1; ++i) ++n_in[std::min<int>(p->src_class[n_loc + p->remote_col[i]], n_hot)];
-            for (int c = 0; c < n_hot; ++c) final_class[c] = static_cast<uint8_t>(n_in[c] >= min_piece ? c : n_hot);
-            final_class[n_hot] = static_cast<uint8_t>(n_hot);
-            regroup(p->sched_local_col, l0, l1, 0, lcut);
-            regroup(p->sched_remote_col, r0, r1, n_loc, rcut);
+            cut_by_class(l0, l1, r0, r1);
             first_piece = 0;
         } else {
             lcut[n_hot] = l0; lcut[n_hot + 1] = l1; rcut[n_hot] = r0; rcut[n_hot + 1] = r1;
@@ -351,6 +433,25 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
             if (ri.second < n_hot) bucket[ri.second].push_back(ri.first);
             else cold.push_back(ri.first);
         }
+        if (!fine) continue;
+        if (dl + dr >= kFineXcdMinDeg && dl + dr < xcd_min_deg) {
+            cut_by_class(l0, l1, r0, r1);
+            const size_t first = p->fine_split_rows.size();
+            int32_t pieces = 0;
+            for (int c = 0; c <= n_hot; ++c) pieces += lcut[c + 1] - lcut[c] + rcut[c + 1] - rcut[c] > 0;
+            for (int c = 0; c <= n_hot; ++c) {
+                if (lcut[c + 1] - lcut[c] + rcut[c + 1] - rcut[c] == 0) continue;
+                const WorkItem it{static_cast<int32_t>(v), lcut[c], lcut[c + 1], rcut[c], rcut[c + 1], pieces > 1 ? static_cast<int32_t>(p->n_fine_sums++) : -1, 0, 0};
+                if (pieces > 1 && p->fine_split_rows.size() == first) p->fine_split_rows.push_back(SplitRow{it.row, it.slot, pieces, 0});
+                if (c < n_hot) fine_bucket[c].push_back(it);
+                else fine_cold.push_back(it);
+            }
+        } else {
+            for (auto &ri : row_items) {
+                if (ri.second < n_hot) fine_bucket[ri.second].push_back(ri.first);
+                else fine_cold.push_back(ri.first);
+            }
+        }
     }
     auto count_items = [&](const std::vector<WorkItem> &list) {
         p->n_work_items += static_cast<int64_t>(list.size());
@@ -358,37 +459,24 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
     };
     count_items(cold);
     for (const auto &b : bucket) count_items(b);
-    // heavy items first, so that the tail of the launch is made of small ones
-    std::stable_sort(cold.begin(), cold.end(), [&](const WorkItem &a, const WorkItem &b) { return item_work(a) > item_work(b); });
-    if (!use_classes) {
-        p->items = std::move(cold);
+    p->items = lay_out(p, bucket, cold, use_classes ? n_hot : -1);
+    // (kept where scratch grows to three times its size at most)
+    fine = fine && p->n_fine_sums > 0 && p->n_fine_sums <= 2 * p->n_split_items;
+    if (fine) {
+        const int32_t first_fine = static_cast<int32_t>(p->n_split_items);      // its slots follow the others
+        auto shift = [&](std::vector<WorkItem> &list) {
+            for (WorkItem &it : list) {
+                const int64_t d = static_cast<int64_t>(p->local_row_ptr[it.row + 1]) - p->local_row_ptr[it.row] + p->remote_row_ptr[it.row + 1] - p->remote_row_ptr[it.row];
+                if (it.slot >= 0 && d < xcd_min_deg) it.slot += first_fine;
+            }
+        };
+        for (auto &b : fine_bucket) shift(b);
+        shift(fine_cold);
+        for (SplitRow &r : p->fine_split_rows) r.first_slot += first_fine;
+        p->fine_items = lay_out(p, fine_bucket, fine_cold, n_hot);
     } else {
-        // XCD x takes the hot items of classes (0, x), (1, x), ... in that order; cold items then
-        // go, largest first, to whichever XCD has the least work so far (a gather that hits in L2
-        // is taken as half the cost of one that does not)
-        std::vector<std::vector<WorkItem>> queue(kXcd);
-        std::vector<int64_t> queue_work(kXcd, 0);
-        for (int c = 0; c < n_hot; ++c) {
-            std::vector<WorkItem> &q = queue[c % kXcd];
-            for (const WorkItem &it : bucket[c]) queue_work[c % kXcd] += item_work(it);
-            q.insert(q.end(), bucket[c].begin(), bucket[c].end());
-        }
-        for (int c = 0; c < kXcd; ++c) queue_work[c] /= 2;
-        for (const WorkItem &it : cold) {
-            const int c = static_cast<int>(std::min_element(queue_work.begin(), queue_work.end()) - queue_work.begin());
-            queue[c].push_back(it);
-            queue_work[c] += item_work(it);
-        }
-        // launch order: workgroup b (wpb items) runs on XCD b mod kXcd; pad with empty items
-        size_t longest = 0;
-        for (auto &q : queue) longest = std::max(longest, q.size());
-        longest = (longest + wpb - 1) / wpb * wpb;
-        const WorkItem dummy{-1, 0, 0, 0, 0, -1, 0, 0};
-        for (auto &q : queue) q.resize(longest, dummy);
-        p->items.reserve(longest * kXcd);
-        for (size_t g = 0; g < longest; g += wpb)
-            for (int c = 0; c < kXcd; ++c)
-                p->items.insert(p->items.end(), queue[c].begin() + g, queue[c].begin() + g + wpb);
+        p->n_fine_sums = 0;
+        p->fine_split_rows.clear();
     }
     for (int32_t len = short_max; len >= 0; --len)         // longest first, isolated rows last
         p->short_rows.insert(p->short_rows.end(), by_len[len].begin(), by_len[len].end());

@@ -101,3 +101,37 @@ def test_teams_of_every_size(dim, bf16):
             scale = binding.mgg_aggregate(part, mode, x.abs(), eps=0.5).double()
             bound = 2 * (torch.from_numpy(lens).cuda()[:, None] + 5) * U * scale
             assert ((out[0] - out[1]).abs() <= bound).all(), (rows, mode)
+
+
+def test_fine_schedule():
+    """A share large enough for the schedule that regroups rows of 128 neighbours on: in the partition's own buffer and in
+    a layer's workspace there is room for its partial sums, in the fixed array of the static call there is not, and a
+    workspace that holds those of the other schedule is still enough."""
+    rng = np.random.default_rng(8)
+    n, own, dim = 60000, 34000, 80
+    lens = np.concatenate([rng.integers(100, 256, own // 2), rng.integers(256, 440, own // 2), np.zeros(n - own, dtype=np.int64)])
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    row = np.repeat(np.arange(n), lens)
+    col = rng.integers(0, n - 1, ptr[-1])
+    col = (col + (col >= row)).astype(np.int32)
+    bounds = np.array([0, own, n], dtype=np.int64)
+    part = binding.mgg_build_partition(ptr, col, 2, 0, bounds)
+    coarse = binding.mgg_build_partition(ptr, col, 2, 0, bounds, xcd_min_deg=256)
+    need = binding.mgg_aggregate_scratch_bytes(part, dim)
+    assert ptr[-1] > 8 << 20 and need == binding.mgg_aggregate_scratch_bytes(coarse, dim) and need <= 64 << 20
+    x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
+    halo = torch.from_numpy(part.export()["halo_gid"].astype(np.int64)).cuda()
+    xl, xh = x[:own].contiguous(), x[halo].contiguous()
+    for mode in ("gin", "gcn"):
+        scale = binding.mgg_aggregate(coarse, mode, xl.abs(), xh.abs()).double()
+        bound = 2 * (torch.from_numpy(lens[:own]).cuda()[:, None] + 5) * U * scale
+        want = binding.mgg_aggregate(coarse, mode, xl, xh)
+        got, static = binding.mgg_aggregate(part, mode, xl, xh), binding.mgg_aggregate_static(part, mode, xl, xh)
+        assert not torch.equal(got, static), mode                    # another order of the sums: the two schedules
+        assert ((got.double() - want.double()).abs() <= bound).all() and ((static.double() - want.double()).abs() <= bound).all(), mode
+    w = torch.eye(dim, device="cuda")
+    full = binding.mgg_layer_workspace_bytes(part, "gcn", [w], ["none"])
+    least = binding.mgg_layer_workspace_bytes(coarse, "gcn", [w], ["none"])
+    assert least < full <= least + 2 * need
+    outs = [binding.mgg_layer_forward(part, "gcn", xl, xh, [w], ["none"], workspace=torch.empty(b, dtype=torch.uint8, device="cuda")) for b in (full, least)]
+    assert torch.equal(outs[0], got) and torch.equal(outs[1], static)
