@@ -324,8 +324,10 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     // of loads each and find a place at once: 8 or 4 to an item up to 4096 wavefronts in all (6480 rows, 11.0 us with
     // and without; 370 rows of 115, 8.7 us at 2700 wavefronts and 10.2 at 5400), 2 up to 8192 (4389 rows, 12.0 ->
     // 10.6 us at 6800).
+    // (16-byte loads from memory into LDS want aligned addresses, unlike those into registers)
+    const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned;
     bool team = false;
-    if (ch == 1 && p->opt_lds_halo == 0 && p->opt_items_per_wave == 0)
+    if (ch == 1 && !lds && p->opt_items_per_wave == 0)
         for (int t = kMaxTeam; t >= 2 && !team; t /= 2)
             if (p->n_work_items * n_slabs * t <= (t == 2 ? 8192 : 4096) && p->longest_item >= t * 8 * (64 / lpr)) { team = true; wpb = t; }
     const int64_t n_groups = team ? a.n_items : (a.n_items + wpb - 1) / wpb;
@@ -353,8 +355,6 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
         int grid_x = a.n_item_blocks + static_cast<int>((short_waves + wpb - 1) / wpb);
         if (n_slabs > 1) grid_x = (grid_x + kXcd - 1) / kXcd * kXcd;   // keeps workgroup x on XCD x mod 8 in every slab
         const dim3 grid(static_cast<unsigned>(grid_x), static_cast<unsigned>(n_slabs));
-        // (16-byte loads from memory into LDS want aligned addresses, unlike those into registers)
-        const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned;
         if (grid_x > 0) {
             hipError_t e;
             if (bf16) e = launch_aggregate_bf16(a, gcn, vec, grid, wpb, stream, lpr, ch, lds, team);
