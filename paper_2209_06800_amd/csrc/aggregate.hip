@@ -319,13 +319,13 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     // wavefront amortises its start-up latencies; fewer leaves more workgroups for the hardware to
     // balance.  Automatic: 2 where the launch still has about 8192 workgroups (measured on MI355X: 0.3-2.5 %
     // faster than 1 and than 8 on every workload tried), else 1.
+    // (16-byte loads from memory into LDS want aligned addresses, unlike those into registers)
+    const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned;
     // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel).  The chip holds some 5000
     // wavefronts of these kernels, and a team is worth its barrier and its additions while its members have a batch
     // of loads each and find a place at once: 8 or 4 to an item up to 4096 wavefronts in all (6480 rows, 11.0 us with
     // and without; 370 rows of 115, 8.7 us at 2700 wavefronts and 10.2 at 5400), 2 up to 8192 (4389 rows, 12.0 ->
     // 10.6 us at 6800).
-    // (16-byte loads from memory into LDS want aligned addresses, unlike those into registers)
-    const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned;
     bool team = false;
     if (ch == 1 && !lds && p->opt_items_per_wave == 0)
         for (int t = kMaxTeam; t >= 2 && !team; t /= 2)
@@ -335,7 +335,9 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     {
         auto pick = [&](int32_t opt, int64_t units, int64_t most) { return static_cast<int32_t>(opt > 0 ? opt : std::min<int64_t>(most, std::max<int64_t>(1, units * n_slabs / 8192))); };
         a.items_per_wave = team ? 1 : pick(p->opt_items_per_wave, n_groups, 2);
-        a.short_per_wave = pick(p->opt_short_per_wave, (short_groups + wpb - 1) / wpb, 2);
+        // (groups of short rows: one, since the ids of a group are all requested ahead in it; 26-lookup bags 147.6 -> 144.5 us,
+        // flat elsewhere)
+        a.short_per_wave = pick(p->opt_short_per_wave, (short_groups + wpb - 1) / wpb, 1);
     }
     a.n_item_blocks = team ? a.n_items : static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * a.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * a.items_per_wave) * kXcd);
     a.ps = p->ps;
