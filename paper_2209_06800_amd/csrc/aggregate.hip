@@ -250,6 +250,7 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     // row.  Costs one more pass over the ids per slab; output columns of different slabs are
     // disjoint, so nothing has to be combined.
     int slab_vecs = nvec;
+    int64_t n_chunks = 1;
     {
         const int64_t opt = p->opt_col_slab_bytes;
         const int64_t vec_bytes = static_cast<int64_t>(vec) * static_cast<int64_t>(esz);
@@ -263,8 +264,19 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
             // without slabs) the gain is small but still there; narrower rows lose to the extra passes.
             const int64_t table_rows = p->n_own + static_cast<int64_t>(p->halo_gid.size());
             const int64_t class_rows = (p->xcd_min_deg > 0 ? table_rows / kXcd : table_rows) + 1;
+            // Where 256-byte slabs of a class fit one L2 the gathers hit, and what is left to wait for is the id stream: read
+            // once per slab, from HBM if it does not stay in the Infinity Cache (bare gathers out of L2: 28.8 TB/s with ids
+            // from there, 22.4 from HBM).  Chunks of the work then go through all slabs one after the other, their ids some
+            // 36 MB (120 k rows of 1 KB, 46 M neighbours: 2.70 ms with 512-byte slabs, 2.57 so, 2.83 with 256-byte slabs in
+            // one chunk; of 2 KB 5.36 -> 5.21).  Rows off line boundaries pay a line more per slab: 512 (1200-byte rows: 4.14
+            // against 4.17 ms).
+            const int64_t id_bytes = (static_cast<int64_t>(p->local_col.size()) + static_cast<int64_t>(p->remote_col.size())) * (mode == MGG_AGG_GCN_SYM ? 8 : 4);
+            const bool on_lines = ld_x * static_cast<int64_t>(esz) % 128 == 0 && aligned(x_local, 128) && aligned(xh, 128);
             if (static_cast<int64_t>(dim) * static_cast<int64_t>(esz) >= 1024) {
-                if (class_rows * 512 > (8 << 20) && class_rows * 256 <= (8 << 20)) slab_bytes = 256;
+                if (class_rows * 256 <= (4 << 20) && id_bytes >= (static_cast<int64_t>(128) << 20) && on_lines) {
+                    slab_bytes = 256;
+                    n_chunks = (id_bytes + (36 << 20) - 1) / (36 << 20);
+                } else if (class_rows * 512 > (8 << 20) && class_rows * 256 <= (8 << 20)) slab_bytes = 256;
                 else slab_bytes = 512;
             }
         } else if (opt >= 64) {
@@ -356,7 +368,10 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
         const int64_t short_waves = (short_groups + a.short_per_wave - 1) / a.short_per_wave;
         int grid_x = a.n_item_blocks + static_cast<int>((short_waves + wpb - 1) / wpb);
         if (n_slabs > 1) grid_x = (grid_x + kXcd - 1) / kXcd * kXcd;   // keeps workgroup x on XCD x mod 8 in every slab
-        const dim3 grid(static_cast<unsigned>(grid_x), static_cast<unsigned>(n_slabs));
+        a.n_slabs = n_slabs;
+        n_chunks = std::max<int64_t>(1, std::min<int64_t>({n_chunks, grid_x / kXcd, 65535 / n_slabs}));
+        const int chunk_x = n_chunks == 1 ? grid_x : static_cast<int>((grid_x + n_chunks * kXcd - 1) / (n_chunks * kXcd) * kXcd);
+        const dim3 grid(static_cast<unsigned>(chunk_x), static_cast<unsigned>(n_slabs * ((grid_x + chunk_x - 1) / std::max(chunk_x, 1))));
         if (grid_x > 0) {
             hipError_t e;
             if (bf16) e = launch_aggregate_bf16(a, gcn, vec, grid, wpb, stream, lpr, ch, lds, team);

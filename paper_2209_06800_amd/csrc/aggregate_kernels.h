@@ -48,7 +48,8 @@ struct AggArgs {
     float *scratch;
     int64_t ld_x, ld_out, scratch_ld;
     int32_t nvec;            // vectors of VEC elements per row (dim / VEC)
-    int32_t slab_vecs;       // vectors per column slab; blockIdx.y selects the slab (= nvec: one slab)
+    int32_t slab_vecs;       // vectors per column slab (= nvec: one slab)
+    int32_t n_slabs;         // blockIdx.y counts the slabs of one chunk of the work (gridDim.x workgroups), then those of the next
     int32_t n_items, n_item_blocks, n_short;
     int32_t items_per_wave;  // work items a wavefront takes one after the other (M)
     int32_t short_per_wave;  // groups of 64/LPR short rows a wavefront takes one after the other
@@ -150,6 +151,7 @@ struct Cfg {
     static constexpr int VEC = VEC_, LPR = LPR_, CH = CH_;
     static constexpr int NPW = kWave / LPR;                 // neighbour rows per load instruction
     static constexpr int U = MGG_AGG_INFLIGHT / CH < LPR ? MGG_AGG_INFLIGHT / CH : LPR;   // neighbour rows in flight per lane
+    static_assert(U > 0 && LPR % U == 0, "batches have to divide the slots of a sub-wave");
     // Wavefronts per SIMD the register allocation must allow.  The workgroup limit (16 wavefronts) gives 4;
     // the 256-byte fp32 variant sits one register above the budget of 5 and loses nothing when held to it
     // (2 % faster on the 602-column workload); the others would spill.
@@ -192,13 +194,16 @@ struct Lanes {
     int sub, slot;              // which neighbour row of a load instruction; the lane's place in its sub-wave
     int lis;                    // first vector of the row this lane owns
     int vend;                   // end of the column slab (in vectors)
+    int block;                  // workgroup of its slab
     uint32_t col_off[K::CH];    // byte offset of each chunk in a table row
     __device__ __forceinline__ void init(const AggArgs &a, int lane)
     {
         sub = lane / K::LPR;
         slot = lane % K::LPR;
-        lis = lane % K::LPR + static_cast<int>(blockIdx.y) * a.slab_vecs;
-        vend = min(a.nvec, (static_cast<int>(blockIdx.y) + 1) * a.slab_vecs);
+        const int chunk = static_cast<int>(blockIdx.y) / a.n_slabs, slab = static_cast<int>(blockIdx.y) - chunk * a.n_slabs;
+        block = chunk * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);      // (past the last one: no short row is left)
+        lis = lane % K::LPR + slab * a.slab_vecs;
+        vend = min(a.nvec, (slab + 1) * a.slab_vecs);
 #pragma unroll
         for (int c = 0; c < K::CH; ++c) col_off[c] = static_cast<uint32_t>(min(min(c * K::LPR + lis, vend - 1) * K::VEC, a.last_col)) * static_cast<uint32_t>(sizeof(typename K::elem));
     }
@@ -553,11 +558,11 @@ __device__ __forceinline__ ItemFields item_fields(const AggArgs &a, int d)
 struct ItemQueue {
     const int32_t *items32;
     int first, stride, M, n_items, lane;
-    __device__ __forceinline__ void init(const AggArgs &a, int wave, int wpb, int lane_)
+    __device__ __forceinline__ void init(const AggArgs &a, int block, int wave, int wpb, int lane_)
     {
         M = a.items_per_wave;
         items32 = reinterpret_cast<const int32_t *>(a.items);
-        const int qb = static_cast<int>(blockIdx.x) / kXcd, xc = static_cast<int>(blockIdx.x) % kXcd;
+        const int qb = block / kXcd, xc = block % kXcd;
         first = (qb * M * kXcd + xc) * wpb + wave; stride = kXcd * wpb; n_items = a.n_items; lane = lane_;
     }
     __device__ __forceinline__ int load(int k) const
@@ -608,7 +613,7 @@ template <class K, bool GCN>
 __device__ __forceinline__ void short_rows(const AggArgs &a, int wave, int wpb, int lane, const Lanes<K> &ln, const char *xl, const char *xh, uint64_t ldb)
 {
     const int Ms = a.short_per_wave;
-    const int sw = (static_cast<int>(blockIdx.x) - a.n_item_blocks) * wpb + wave;
+    const int sw = (ln.block - a.n_item_blocks) * wpb + wave;
     Acc<K> acc;
     typename K::raw xs[K::CH];
     auto load_sd = [&](int k) -> int4 {
@@ -687,7 +692,7 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
     const char *xl = static_cast<const char *>(a.x_local);
     const char *xh = static_cast<const char *>(a.x_halo);
     const uint64_t ldb = static_cast<uint64_t>(a.ld_x) * sizeof(typename K::elem);
-    if (static_cast<int>(blockIdx.x) >= a.n_item_blocks) {
+    if (ln.block >= a.n_item_blocks) {
         short_rows<K, GCN>(a, wave, wpb, lane, ln, xl, xh, ldb);
         return;
     }
@@ -695,7 +700,7 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
     Acc<K> acc;
     typename K::raw xs[K::CH];
     ItemQueue q;
-    q.init(a, wave, wpb, lane);
+    q.init(a, ln.block, wave, wpb, lane);
     int d_cur = q.load(0), d_nxt = q.load(1);
     bool ids_ready = false;
     uint32_t id = 0;
@@ -743,11 +748,11 @@ __global__ __launch_bounds__(kWave * kMaxTeam) void aggregate_team_kernel(const 
     const char *xl = static_cast<const char *>(a.x_local);
     const char *xh = static_cast<const char *>(a.x_halo);
     const uint64_t ldb = static_cast<uint64_t>(a.ld_x) * sizeof(typename K::elem);
-    if (static_cast<int>(blockIdx.x) >= a.n_item_blocks) {
+    if (ln.block >= a.n_item_blocks) {
         short_rows<K, GCN>(a, wave, team, lane, ln, xl, xh, ldb);
         return;
     }
-    const ItemFields it = item_fields(a, reinterpret_cast<const int32_t *>(a.items)[static_cast<int64_t>(blockIdx.x) * 8 + (lane & 7)]);
+    const ItemFields it = item_fields(a, reinterpret_cast<const int32_t *>(a.items)[static_cast<int64_t>(ln.block) * 8 + (lane & 7)]);
     if (it.row < 0) return;                                  // padding: the whole workgroup leaves
     const int ps = a.ps;
     const int share = (it.n + team * K::NPW - 1) / (team * K::NPW) * K::NPW;
@@ -844,7 +849,7 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
     const char *xl = static_cast<const char *>(a.x_local);
     const char *xh = static_cast<const char *>(a.x_halo);
     const uint64_t ldb = static_cast<uint64_t>(a.ld_x) * sizeof(typename K::elem);
-    if (static_cast<int>(blockIdx.x) >= a.n_item_blocks) {
+    if (ln.block >= a.n_item_blocks) {
         short_rows<K, GCN>(a, wave, wpb, lane, ln, xl, xh, ldb);
         return;
     }
@@ -853,7 +858,7 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
     Acc<K> acc;
     typename K::raw xs[K::CH];
     ItemQueue q;
-    q.init(a, wave, wpb, lane);
+    q.init(a, ln.block, wave, wpb, lane);
     int d_cur = q.load(0);
     for (int k = 0; k < q.M; ++k) {
         const int d_nxt = q.load(k + 1);

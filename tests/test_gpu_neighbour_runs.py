@@ -135,3 +135,21 @@ def test_fine_schedule():
     assert least < full <= least + 2 * need
     outs = [binding.mgg_layer_forward(part, "gcn", xl, xh, [w], ["none"], workspace=torch.empty(b, dtype=torch.uint8, device="cuda")) for b in (full, least)]
     assert torch.equal(outs[0], got) and torch.equal(outs[1], static)
+
+
+def test_slabs_in_chunks():
+    """Rows of 1 KB, a table whose 256-byte slabs fit the L2s and more ids than 128 MB: the launch walks chunks of the work
+    through all slabs.  Against the same slabs asked for, which are walked in one chunk: the same bits."""
+    rng = np.random.default_rng(4)
+    n, dim = 60000, 256
+    lens = rng.integers(0, 600, n)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    row = np.repeat(np.arange(n), lens)
+    col = rng.integers(0, n - 1, ptr[-1])
+    col = (col + (col >= row)).astype(np.int32)
+    assert ptr[-1] * 8 >= 128 << 20
+    x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
+    part = binding.mgg_build_partition(ptr, col)
+    got = binding.mgg_aggregate(part, "gcn", x)
+    part.set_option("col_slab_bytes", 256)
+    assert torch.equal(got, binding.mgg_aggregate(part, "gcn", x))
