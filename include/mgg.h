@@ -194,7 +194,7 @@ mgg_status_t mgg_aggregate(const mgg_partition_t *p, mgg_agg_t mode, float eps, 
 
 /* mgg_aggregate for callers that cannot allocate and hold no reserved partition: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and result as
- * mgg_aggregate; the partial sums of cut rows go to a fixed 64 MiB array inside the library's device
+ * mgg_aggregate (up to the order of the sums where that has room for a schedule with more pieces); the partial sums of cut rows go to a fixed 64 MiB array inside the library's device
  * code (one copy per GPU, held until the process ends) instead of the partition's buffer, so the call
  * allocates nothing whatever was or was not reserved.  A partition whose partial sums at this width
  * (mgg_aggregate_scratch_bytes) exceed 64 MiB is refused with MGG_ERR_UNSUPPORTED.  The first call on
