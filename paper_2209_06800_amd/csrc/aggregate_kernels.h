@@ -152,9 +152,9 @@ struct Cfg {
     static constexpr int NPW = kWave / LPR;                 // neighbour rows per load instruction
     static constexpr int U = MGG_AGG_INFLIGHT / CH < LPR ? MGG_AGG_INFLIGHT / CH : LPR;   // neighbour rows in flight per lane
     static_assert(U > 0 && LPR % U == 0, "batches have to divide the slots of a sub-wave");
-    // Wavefronts per SIMD the register allocation must allow.  The workgroup limit (16 wavefronts) gives 4;
-    // the 256-byte fp32 variant sits one register above the budget of 5 and loses nothing when held to it
-    // (2 % faster on the 602-column workload); the others would spill.
+    // Wavefronts per SIMD the register allocation must allow.  The workgroup limit (16 wavefronts) gives 4; the
+    // 256-byte fp32 variant is held to 5.  More spills or starves the batches: 602 columns, 116 M neighbours, 17.58 ms
+    // so, 17.7 at 6, 19.2 at 7, 18.5 at 8 with batches of 4 loads, 18.7 at 4 with batches of 16.
     static constexpr int MIN_WAVES = (!BF16_ && VEC_ == 4 && LPR_ == 16 && CH_ == 1) ? 5 : 4;
     using elem = typename std::conditional<BF16, uint16_t, float>::type;
     using raw = typename Raw<BF16, VEC>::type;
