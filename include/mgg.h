@@ -87,6 +87,12 @@ typedef struct {
                               cold piece; 0 = default 16 */
     int32_t hot_min_count; /* table rows gathered fewer times than this are cold; 0 = default 8 */
     int32_t reserve_dim;   /* > 0: the build ends with mgg_partition_reserve(p, reserve_dim) */
+    int32_t fine_min_neighbours;   /* shares with at least this many neighbours and classes by hash have a second,
+                              fine schedule beside the one that xcd_min_deg describes: rows of 128 neighbours on
+                              are regrouped, too, for up to twice as many partial sums on top.  It runs where the
+                              scratch at hand holds them (mgg_aggregate_plan says which one does).  0 = default
+                              2^23, negative = never: one schedule, the same bits whatever the scratch.  Not with
+                              an xcd_min_deg or min_piece of the caller's. */
 } mgg_build_opts_t;
 
 typedef struct {
@@ -105,6 +111,8 @@ typedef struct {
     int64_t n_local_rows;                     /* rows of the local table: n_own, or the local slice of a bag partition */
     int32_t is_bags;                          /* built by mgg_build_bags                      */
     int32_t reserved_dim;                     /* widest mgg_partition_reserve so far (0: none) */
+    int64_t n_fine_items;                     /* work items of the fine schedule incl. padding, 0: there is none */
+    int64_t n_fine_split_rows, n_fine_split_items;   /* what it cuts besides the n_split_rows / n_split_items above */
 } mgg_partition_info_t;
 
 /* Caller-allocated HOST buffers for mgg_partition_export(); a NULL member is skipped.
@@ -129,6 +137,16 @@ typedef struct {
     int32_t *item_slot;       /* [n_items] -1: the item is the whole row; else partial slot  */
     int32_t *src_class_local; /* [n_own]    class of each local table row: phase * 8 + XCD, -1 = cold */
     int32_t *src_class_halo;  /* [num_halo] same for the halo table                                   */
+    /* The schedule as the kernels read it (for checks; laid out anew when one of these is asked for).  Records are
+     * rows of int32. */
+    uint32_t *launch_cols;    /* [nnz] table rows in the order of the work, bit 31 set: halo table */
+    float    *launch_wts;     /* [nnz] 1/sqrt(degree + 1) of the neighbour; not written for bags  */
+    int32_t  *launch_short;   /* [n_short_rows x 4] row, start in launch_cols, local neighbours, all neighbours */
+    int32_t  *launch_items;   /* [n_items x 8] row (-1: padding), start of the local neighbours, their number, number of
+                                 all, partial slot (-1: the whole row), start of the remote neighbours, 0, 0 */
+    int32_t  *launch_fine_items;   /* [n_fine_items x 8] the same of the fine schedule */
+    int32_t  *launch_split_rows;   /* [(n_split_rows + n_fine_split_rows) x 4] row, first slot, slots, 0: those of the
+                                      fine schedule alone come last */
 } mgg_partition_arrays_t;
 
 /* ---------------------------------------------------------------------------------------

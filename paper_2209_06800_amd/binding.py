@@ -44,7 +44,8 @@ class MggError(RuntimeError):
 class BuildOpts(C.Structure):
     _fields_ = [("ps", C.c_int32), ("dist", C.c_int32), ("short_max", C.c_int32), ("host_only", C.c_int32),
                 ("wpb", C.c_int32), ("xcd_min_deg", C.c_int32), ("hot_row_bytes", C.c_int32), ("hot_rows", C.c_int32),
-                ("hot_phases", C.c_int32), ("min_piece", C.c_int32), ("hot_min_count", C.c_int32), ("reserve_dim", C.c_int32)]
+                ("hot_phases", C.c_int32), ("min_piece", C.c_int32), ("hot_min_count", C.c_int32), ("reserve_dim", C.c_int32),
+                ("fine_min_neighbours", C.c_int32)]
 
 
 class PartitionInfo(C.Structure):
@@ -58,7 +59,8 @@ class PartitionInfo(C.Structure):
                 ("n_groups_local", C.c_int64), ("n_groups_remote", C.c_int64),
                 ("n_short_rows", C.c_int64), ("n_items", C.c_int64),
                 ("n_split_rows", C.c_int64), ("n_split_items", C.c_int64),
-                ("n_local_rows", C.c_int64), ("is_bags", C.c_int32), ("reserved_dim", C.c_int32)]
+                ("n_local_rows", C.c_int64), ("is_bags", C.c_int32), ("reserved_dim", C.c_int32),
+                ("n_fine_items", C.c_int64), ("n_fine_split_rows", C.c_int64), ("n_fine_split_items", C.c_int64)]
 
 
 _ARRAY_FIELDS = ["local_row_ptr", "local_col", "remote_row_ptr", "remote_col", "halo_gid", "halo_peer_ptr",
@@ -66,7 +68,8 @@ _ARRAY_FIELDS = ["local_row_ptr", "local_col", "remote_row_ptr", "remote_col", "
                  "grp_remote_row", "grp_remote_start", "grp_remote_end", "short_rows",
                  "sched_local_col", "sched_remote_col",
                  "item_row", "item_lbeg", "item_lend", "item_rbeg", "item_rend", "item_slot",
-                 "src_class_local", "src_class_halo"]
+                 "src_class_local", "src_class_halo",
+                 "launch_cols", "launch_wts", "launch_short", "launch_items", "launch_fine_items", "launch_split_rows"]
 
 
 class PartitionArrays(C.Structure):
@@ -273,7 +276,19 @@ class Partition:
         }
         out = {k: np.zeros(max(int(n), 0), dtype=np.int64 if k == "halo_peer_ptr" else np.int32)
                for k, n in sizes.items()}
-        arrs = PartitionArrays(**{k: out[k].ctypes.data for k in _ARRAY_FIELDS})
+        arrs = PartitionArrays(**{k: v.ctypes.data for k, v in out.items()})
+        _check(lib().mgg_partition_export(self.handle, C.byref(arrs)))
+        return out
+
+    def export_launch(self) -> dict:
+        """The schedule as the kernels read it (the launch_* arrays of mgg_partition_export), records as rows."""
+        i = self.info
+        nnz = i.nnz_local + i.nnz_remote
+        out = {"launch_cols": np.zeros(nnz, dtype=np.uint32), "launch_wts": np.zeros(nnz, dtype=np.float32),
+               "launch_short": np.zeros((i.n_short_rows, 4), dtype=np.int32), "launch_items": np.zeros((i.n_items, 8), dtype=np.int32),
+               "launch_fine_items": np.zeros((i.n_fine_items, 8), dtype=np.int32),
+               "launch_split_rows": np.zeros((i.n_split_rows + i.n_fine_split_rows, 4), dtype=np.int32)}
+        arrs = PartitionArrays(**{k: v.ctypes.data for k, v in out.items()})
         _check(lib().mgg_partition_export(self.handle, C.byref(arrs)))
         return out
 
@@ -282,7 +297,8 @@ def mgg_build_partition(row_ptr: np.ndarray, col_idx: np.ndarray, num_parts: int
                         bounds: Optional[Sequence[int]] = None, *, ps: int = 0, dist: int = 0,
                         short_max: int = 0, host_only: bool = False, xcd_min_deg: int = 0, wpb: int = 0,
                         hot_row_bytes: int = 0, hot_rows: int = 0, hot_phases: int = 0, min_piece: int = 0,
-                        hot_min_count: int = 0, reserve_dim: int = 0, num_nodes: Optional[int] = None) -> Partition:
+                        hot_min_count: int = 0, reserve_dim: int = 0, num_nodes: Optional[int] = None,
+                        fine_min_neighbours: int = 0) -> Partition:
     row_ptr = np.ascontiguousarray(row_ptr, dtype=np.int64)
     col_idx = np.ascontiguousarray(col_idx, dtype=np.int32)
     n = row_ptr.size - 1 if num_nodes is None else num_nodes
@@ -290,7 +306,7 @@ def mgg_build_partition(row_ptr: np.ndarray, col_idx: np.ndarray, num_parts: int
     if b is not None and b.size != num_parts + 1:
         raise MggError(ERR_INVALID_ARG, "bounds must have num_parts + 1 entries")
     opts = BuildOpts(ps, dist, short_max, int(host_only), wpb, xcd_min_deg, hot_row_bytes, hot_rows, hot_phases,
-                     min_piece, hot_min_count, reserve_dim)
+                     min_piece, hot_min_count, reserve_dim, fine_min_neighbours)
     h = C.c_void_p()
     _check(lib().mgg_build_partition(n, _np_ptr(row_ptr), _np_ptr(col_idx) if col_idx.size else None,
                                      num_parts, part_id, _np_ptr(b), C.byref(opts), C.byref(h)))

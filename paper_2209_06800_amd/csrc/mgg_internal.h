@@ -6,6 +6,7 @@
 
 #include <cstdarg>
 #include <cstdint>
+#include <memory>
 #include <vector>
 
 #include "mgg.h"
@@ -64,6 +65,16 @@ struct DeviceArrays {
     SplitRow *split_rows = nullptr;    // those of the fine schedule alone follow the others
     float *scratch = nullptr;          // [scratch_rows x scratch_ld] partial sums
     int64_t scratch_ld = 0, scratch_rows = 0;
+};
+
+// What the device arrays are filled with, laid out on the host (lay_out_device).
+struct DeviceLayout {
+    size_t nnz = 0;
+    std::unique_ptr<uint32_t[]> cols;
+    std::unique_ptr<float[]> wts;      // empty for bags: plain sums only
+    std::vector<int4> short_desc;
+    std::vector<DeviceItem> items, fine_items;
+    std::vector<SplitRow> split_rows;
 };
 
 }  // namespace mgg

@@ -74,22 +74,21 @@ static void free_device(mgg_partition *p)
     d = DeviceArrays{};
 }
 
-static mgg_status_t upload_arrays(mgg_partition *p)
+// The layout of the device arrays (may throw std::bad_alloc; no GPU is touched).
+static DeviceLayout lay_out_device(const mgg_partition *p)
 {
-    int dev = 0;
-    MGG_HIP_TRY(hipGetDevice(&dev));
-    p->device = dev;
-    mgg_status_t s;
-    if ((s = upload(p->dinv_own, &p->d.dinv_own)) != MGG_OK) return s;
+    DeviceLayout l;
     // The neighbours in the order in which they are walked: XCD by XCD the items of its queue, one after the other, then
     // the short rows; of each the local ones, then the remote ones, with the factor of each edge beside them.  Wavefronts
     // that run at the same time on one XCD then read one stream front to back, and every line of it is fetched once (in the
     // order of the rows a line was wanted by up to eight XCDs: 37 M neighbours at 100 columns 2.22 -> 2.16 ms).
     const std::vector<int32_t> &lc = p->sched_local_col.empty() ? p->local_col : p->sched_local_col;
     const std::vector<int32_t> &rc = p->sched_remote_col.empty() ? p->remote_col : p->sched_remote_col;
-    const size_t nnz = lc.size() + rc.size();
-    std::unique_ptr<uint32_t[]> cols(new uint32_t[nnz]);
-    std::unique_ptr<float[]> w(new float[p->bags ? 0 : nnz]);       // a bag partition has no factors: plain sums only
+    const size_t nnz = l.nnz = lc.size() + rc.size();
+    l.cols.reset(new uint32_t[nnz]);
+    l.wts.reset(new float[p->bags ? 0 : nnz]);
+    uint32_t *cols = l.cols.get();
+    float *w = l.wts.get();
     auto put = [&](int32_t at, int32_t l0, int32_t l1, int32_t r0, int32_t r1) {
         int32_t k = at;
         for (int32_t i = l0; i < l1; ++i) cols[k++] = static_cast<uint32_t>(lc[i]);
@@ -99,7 +98,8 @@ static mgg_status_t upload_arrays(mgg_partition *p)
         for (int32_t i = r0; i < r1; ++i) w[at++] = p->dinv_halo[rc[i]];
     };
     int32_t at = 0;
-    std::vector<DeviceItem> items(p->items.size());
+    std::vector<DeviceItem> &items = l.items;
+    items.resize(p->items.size());
     for (int x = 0; x < kXcd; ++x)
         for (size_t g = static_cast<size_t>(x) * p->wpb; g < items.size(); g += static_cast<size_t>(kXcd) * p->wpb)
             for (size_t i = g; i < std::min(items.size(), g + p->wpb); ++i) {
@@ -109,7 +109,8 @@ static mgg_status_t upload_arrays(mgg_partition *p)
                 at += items[i].n;
             }
     // one 16-byte record per short row, so that the kernel needs no dependent look-up of row pointers
-    std::vector<int4> sd(p->short_rows.size());
+    std::vector<int4> &sd = l.short_desc;
+    sd.resize(p->short_rows.size());
     for (size_t i = 0; i < sd.size(); ++i) {
         const int32_t v = p->short_rows[i], nl = p->local_row_ptr[v + 1] - p->local_row_ptr[v], nr = p->remote_row_ptr[v + 1] - p->remote_row_ptr[v];
         sd[i] = make_int4(v, at, nl, nl + nr);
@@ -125,15 +126,8 @@ static mgg_status_t upload_arrays(mgg_partition *p)
             put(sd[i].y, p->local_row_ptr[v], p->local_row_ptr[v + 1], p->remote_row_ptr[v], p->remote_row_ptr[v + 1]);
         }
     });
-    if ((s = upload(cols.get(), nnz, &p->d.cols)) != MGG_OK) return s;
-    if ((s = upload(w.get(), p->bags ? 0 : nnz, &p->d.wts)) != MGG_OK) return s;
-    if ((s = upload(sd, &p->d.short_desc)) != MGG_OK) return s;
-    if ((s = upload(items, &p->d.items)) != MGG_OK) return s;
-    {
-        std::vector<SplitRow> rows(p->split_rows);
-        rows.insert(rows.end(), p->fine_split_rows.begin(), p->fine_split_rows.end());
-        if ((s = upload(rows, &p->d.split_rows)) != MGG_OK) return s;
-    }
+    l.split_rows = p->split_rows;
+    l.split_rows.insert(l.split_rows.end(), p->fine_split_rows.begin(), p->fine_split_rows.end());
     if (!p->fine_items.empty()) {
         // its items lie in the same stream: where the items of that row begin there, plus the distance to the piece
         std::vector<int32_t> where(static_cast<size_t>(p->n_own), -1);          // whole rows
@@ -143,7 +137,8 @@ static mgg_status_t upload_arrays(mgg_partition *p)
             if (it.slot < 0) where[it.row] = it.beg;
             else of_slot[it.slot] = it.beg;
         }
-        std::vector<DeviceItem> fine(p->fine_items.size());
+        std::vector<DeviceItem> &fine = l.fine_items;
+        fine.resize(p->fine_items.size());
         for (size_t i = 0; i < fine.size(); ++i) {
             const WorkItem &it = p->fine_items[i];
             const int32_t nl = it.lend - it.lbeg, n = nl + it.rend - it.rbeg;
@@ -156,8 +151,24 @@ static mgg_status_t upload_arrays(mgg_partition *p)
             }
             fine[i] = DeviceItem{it.row, beg, nl, n, it.slot, rbeg, {0, 0}};
         }
-        if ((s = upload(fine, &p->d.fine_items)) != MGG_OK) return s;
     }
+    return l;
+}
+
+static mgg_status_t upload_arrays(mgg_partition *p)
+{
+    int dev = 0;
+    MGG_HIP_TRY(hipGetDevice(&dev));
+    p->device = dev;
+    const DeviceLayout l = lay_out_device(p);
+    mgg_status_t s;
+    if ((s = upload(p->dinv_own, &p->d.dinv_own)) != MGG_OK) return s;
+    if ((s = upload(l.cols.get(), l.nnz, &p->d.cols)) != MGG_OK) return s;
+    if ((s = upload(l.wts.get(), p->bags ? 0 : l.nnz, &p->d.wts)) != MGG_OK) return s;
+    if ((s = upload(l.short_desc, &p->d.short_desc)) != MGG_OK) return s;
+    if ((s = upload(l.items, &p->d.items)) != MGG_OK) return s;
+    if ((s = upload(l.split_rows, &p->d.split_rows)) != MGG_OK) return s;
+    if (!l.fine_items.empty() && (s = upload(l.fine_items, &p->d.fine_items)) != MGG_OK) return s;
     return MGG_OK;
 }
 
@@ -199,7 +210,7 @@ struct Knobs {
     int32_t ps = 64, dist = 8, short_max = 16, host_only = 0, xcd_min_deg = kDefaultXcdMinDeg, wpb = kDefaultWpb;
     int32_t hot_rows = 0, hot_phases = kDefaultHotPhases, min_piece = kDefaultMinPiece, hot_min_count = kDefaultHotMinCount;
     int32_t reserve_dim = 0;
-    bool fine = true;              // a fine schedule beside the other one where it pays (not with knobs of the caller)
+    int64_t fine_min = kFineMinNeighbours;       // neighbours from which a share has a fine schedule
 };
 
 static mgg_status_t parse_opts(const mgg_build_opts_t *opts, Knobs *k)
@@ -218,7 +229,9 @@ static mgg_status_t parse_opts(const mgg_build_opts_t *opts, Knobs *k)
         if (opts->short_max) short_max = opts->short_max;
         host_only = opts->host_only;
         if (opts->xcd_min_deg) xcd_min_deg = opts->xcd_min_deg;
-        k->fine = !opts->xcd_min_deg && !opts->min_piece;
+        // (a caller who chooses how rows are cut gets just that)
+        if (opts->fine_min_neighbours) k->fine_min = opts->fine_min_neighbours;
+        if (opts->xcd_min_deg || opts->min_piece) k->fine_min = -1;
         if (opts->wpb) wpb = opts->wpb;
         k->reserve_dim = opts->reserve_dim;
     }
@@ -379,7 +392,7 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
     // columns: 2.93 -> 2.70; 17.8 M neighbours at 64 columns: 356 -> 346 us; 28 M at 128 in bf16: 736 -> 722; from 64 on
     // nothing more; 3.2 M at 75 columns: 137.4 -> 138.5).  With popularity classes it changes nothing.
     const int64_t nnz = static_cast<int64_t>(p->local_col.size()) + static_cast<int64_t>(p->remote_col.size());
-    bool fine = k.fine && p->class_mode == 1 && n_phase == 1 && nnz >= kFineMinNeighbours && xcd_min_deg == kDefaultXcdMinDeg && run >= kDefaultXcdMinDeg;
+    bool fine = k.fine_min > 0 && nnz >= k.fine_min && p->class_mode == 1 && n_phase == 1 && xcd_min_deg == kDefaultXcdMinDeg && run >= kDefaultXcdMinDeg;
     std::vector<std::vector<WorkItem>> fine_bucket(fine ? bucket.size() : 0);
     std::vector<WorkItem> fine_cold;
     // the pieces of a row by class: cuts of its two regrouped lists
@@ -711,6 +724,9 @@ mgg_status_t mgg_partition_info(const mgg_partition_t *p, mgg_partition_info_t *
     o->n_split_rows = static_cast<int64_t>(p->split_rows.size());
     o->n_split_items = p->n_split_items;
     o->reserved_dim = p->reserved_dim;
+    o->n_fine_items = static_cast<int64_t>(p->fine_items.size());
+    o->n_fine_split_rows = static_cast<int64_t>(p->fine_split_rows.size());
+    o->n_fine_split_items = p->n_fine_sums;
     return MGG_OK;
 }
 
@@ -748,6 +764,19 @@ mgg_status_t mgg_partition_export(const mgg_partition_t *p, mgg_partition_arrays
         if (a->item_rbeg) a->item_rbeg[i] = it.rbeg;
         if (a->item_rend) a->item_rend[i] = it.rend;
         if (a->item_slot) a->item_slot[i] = it.slot;
+    }
+    if (!a->launch_cols && !a->launch_wts && !a->launch_short && !a->launch_items && !a->launch_fine_items && !a->launch_split_rows) return MGG_OK;
+    try {
+        const DeviceLayout l = lay_out_device(p);
+        auto raw = [](const void *src, size_t bytes, void *dst) { if (dst && bytes) std::memcpy(dst, src, bytes); };
+        raw(l.cols.get(), l.nnz * sizeof(uint32_t), a->launch_cols);
+        raw(l.wts.get(), p->bags ? 0 : l.nnz * sizeof(float), a->launch_wts);
+        raw(l.short_desc.data(), l.short_desc.size() * sizeof(int4), a->launch_short);
+        raw(l.items.data(), l.items.size() * sizeof(DeviceItem), a->launch_items);
+        raw(l.fine_items.data(), l.fine_items.size() * sizeof(DeviceItem), a->launch_fine_items);
+        raw(l.split_rows.data(), l.split_rows.size() * sizeof(SplitRow), a->launch_split_rows);
+    } catch (const std::bad_alloc &) {
+        return fail(MGG_ERR_ALLOC, "out of host memory while laying out the partition");
     }
     return MGG_OK;
 }

@@ -31,7 +31,7 @@ int mgg_oracle_bag_sum(int64_t num_bags, const int64_t *bag_ptr, const int32_t *
 int mgg_oracle_split_edge_balanced(int64_t n, const int64_t *row_ptr, int32_t parts, int64_t *bounds);
 }
 
-static int g_fail = 0;
+static int g_fail = 0, g_fine = 0;      // failed checks; partitions that had a fine schedule
 #define CHECK(cond, ...)                                      \
     do {                                                      \
         if (!(cond)) {                                        \
@@ -133,6 +133,49 @@ static void check_partition(const Graph &g, int32_t parts, int32_t part_id, cons
         std::sort(x.begin(), x.end()); std::sort(y.begin(), y.end());
         CHECK(x == y, "scheduled local row %lld is not a permutation", (long long)v);
     }
+    // the arrays as the kernels read them: both item tables and the short rows over one neighbour stream
+    std::vector<uint32_t> cols(nl + nr);
+    std::vector<float> wts(nl + nr);
+    std::vector<int32_t> l_short(4 * info.n_short_rows), l_items(8 * info.n_items), l_fine(8 * info.n_fine_items), l_split(4 * (info.n_split_rows + info.n_fine_split_rows));
+    std::memset(&a, 0, sizeof a);
+    a.launch_cols = cols.data(); a.launch_wts = wts.data(); a.launch_short = l_short.data();
+    a.launch_items = l_items.data(); a.launch_fine_items = l_fine.data(); a.launch_split_rows = l_split.data();
+    CHECK(mgg_partition_export(p, &a) == MGG_OK, "export: %s", mgg_last_error());
+    for (int which = 0; which < (info.n_fine_items > 0 ? 2 : 1); ++which) {
+        const std::vector<int32_t> &items = which ? l_fine : l_items;
+        std::vector<int32_t> seen(nl + nr, 0);
+        std::vector<int64_t> got_l(n_own, 0), got_r(n_own, 0);       // neighbours of each row, as sums of (id + 1)
+        auto walk = [&](int32_t v, int64_t beg, int64_t end, bool remote) {
+            CHECK(beg >= 0 && beg <= end && end <= nl + nr, "run of row %d leaves the stream", v);
+            for (int64_t e = beg; e < end; ++e) {
+                ++seen[e];
+                CHECK((cols[e] >> 31) == (remote ? 1u : 0u), "row %d: table of entry %lld", v, (long long)e);
+                const int32_t u = static_cast<int32_t>(cols[e] & 0x7fffffffu);
+                CHECK(u < (remote ? nh : n_own), "row %d: id %d", v, u);
+                (remote ? got_r : got_l)[v] += u + 1;
+                CHECK(wts[e] == static_cast<float>(1.0 / std::sqrt(static_cast<double>((remote ? d_halo[u] : d_own[u])) + 1.0)), "factor of entry %lld", (long long)e);
+            }
+        };
+        for (size_t i = 0; i + 8 <= items.size(); i += 8) {
+            const int32_t *it = &items[i];
+            if (it[0] < 0) continue;
+            walk(it[0], it[1], it[1] + it[2], false);
+            walk(it[0], it[5], it[5] + it[3] - it[2], true);
+        }
+        for (size_t i = 0; i + 4 <= l_short.size(); i += 4) {
+            const int32_t *sd = &l_short[i];
+            walk(sd[0], sd[1], sd[1] + sd[2], false);
+            walk(sd[0], sd[1] + sd[2], sd[1] + sd[3], true);
+        }
+        for (int64_t e = 0; e < nl + nr; ++e) CHECK(seen[e] == 1, "schedule %d: entry %lld walked %d times", which, (long long)e, seen[e]);
+        for (int64_t v = 0; v < n_own; ++v) {
+            int64_t wl = 0, wr = 0;
+            for (int32_t e = lrp[v]; e < lrp[v + 1]; ++e) wl += lc[e] + 1;
+            for (int32_t e = rrp[v]; e < rrp[v + 1]; ++e) wr += rc_[e] + 1;
+            CHECK(got_l[v] == wl && got_r[v] == wr, "schedule %d: neighbours of row %lld", which, (long long)v);
+        }
+    }
+    g_fine += info.n_fine_items > 0;
     CHECK(mgg_aggregate_scratch_bytes(p, 20) == static_cast<size_t>(info.n_split_items) * 24 * 4, "scratch bytes");
     mgg_partition_destroy(p);
 }
@@ -159,6 +202,18 @@ int main()
         o.hot_rows = static_cast<int32_t>(rng() % 40);
         for (int32_t q = 0; q < parts; ++q) check_partition(g, parts, q, bounds, o);
     }
+    // ---- the default cuts with the fine schedule, laid out by several threads -------------------
+    for (int trial = 0; trial < 3; ++trial) {
+        const Graph g = random_graph(rng, 1500);
+        const int32_t parts = 1 + trial;
+        std::vector<int64_t> bounds(parts + 1);
+        for (int32_t q = 0; q <= parts; ++q) bounds[q] = g.n * q / parts;
+        mgg_build_opts_t o;
+        std::memset(&o, 0, sizeof o);
+        o.host_only = 1; o.hot_phases = -1; o.fine_min_neighbours = 1; o.wpb = 1 << trial;
+        for (int32_t q = 0; q < parts; ++q) check_partition(g, parts, q, bounds, o);
+    }
+    CHECK(g_fine > 0, "no partition had a fine schedule");
     // ---- the oracle's arithmetic on one graph: aggregation in both modes and dtypes, update, bags ----
     {
         const Graph g = random_graph(rng, 300);

@@ -1,0 +1,129 @@
+"""The schedule as the kernels read it, on the CPU: the neighbour stream in the order of the work, the two item tables over
+it (whole and cut rows, and the fine schedule that regroups rows of 128 neighbours too), the short rows and the
+partial-sum slots.  Reference: the canonical row lists of the same partition, which the builder tests compare with the oracle.
+"""
+import numpy as np
+import pytest
+
+from paper_2209_06800_amd import binding, inputs
+
+HALO = np.uint32(1 << 31)
+
+
+def _graph(n, top, seed, hubs=0):
+    """Directed rows of 0 .. top neighbours, `hubs` of them with up to 3000; duplicates, no self-loops."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, top + 1, n)
+    lens[:n // 4] = rng.integers(0, 20, n // 4)
+    lens[rng.permutation(n)[:hubs]] = rng.integers(600, 3000, hubs)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    row = np.repeat(np.arange(n), lens)
+    col = rng.integers(0, n - 1, ptr[-1])
+    return ptr, (col + (col >= row)).astype(np.int32)
+
+
+def _runs(beg, length):
+    """Positions of runs [beg, beg + length), one after the other."""
+    return np.repeat(beg - np.concatenate([[0], np.cumsum(length)[:-1]]), length) + np.arange(length.sum())
+
+
+def _check_cover(part, e, l, items, which):
+    """Every (row, neighbour, table) once in these items and the short rows; slots of cut rows in order."""
+    info = part.info
+    nnz = int(info.nnz_local + info.nnz_remote)
+    it = items[items[:, 0] >= 0].astype(np.int64)
+    assert np.all(items[items[:, 0] < 0][:, 3:5] == [0, -1])                    # padding: nothing to do
+    row, beg, nl, n, slot, rbeg = it[:, :6].T
+    assert np.all(nl >= 0) and np.all(n >= nl) and np.all(beg >= 0) and np.all(beg + nl <= nnz)
+    assert np.all(rbeg >= 0) and np.all(rbeg + n - nl <= nnz)
+    sh = l["launch_short"].astype(np.int64)
+    assert np.array_equal(sh[:, 0], e["short_rows"]) and np.all(sh[:, 2] <= sh[:, 3])
+    pos = np.concatenate([_runs(beg, nl), _runs(rbeg, n - nl), _runs(sh[:, 1], sh[:, 3])])
+    assert np.array_equal(np.sort(pos), np.arange(nnz)), which                  # each place of the stream once
+    rows = np.concatenate([np.repeat(row, nl), np.repeat(row, n - nl), np.repeat(sh[:, 0], sh[:, 3])])
+    remote = np.concatenate([np.zeros(nl.sum()), np.ones((n - nl).sum()), (np.arange(sh[:, 3].sum()) - np.repeat(np.cumsum(sh[:, 3]) - sh[:, 3], sh[:, 3]) >=
+                                                                          np.repeat(sh[:, 2], sh[:, 3]))]).astype(bool)
+    got = l["launch_cols"][pos]
+    assert np.array_equal(got >= HALO, remote), which                           # the bit says the table that the counts say
+    key = rows * (1 << 33) + (got & ~HALO).astype(np.int64) * 2 + remote
+    n_own = int(info.n_own)
+    want = np.concatenate([np.repeat(np.arange(n_own), np.diff(e[f"{k}_row_ptr"])) * (1 << 33) + e[f"{k}_col"].astype(np.int64) * 2 + b
+                           for b, k in enumerate(("local", "remote"))])
+    assert np.array_equal(np.sort(key), np.sort(want)), which
+    # cut rows: the slots of a SplitRow are its items', contiguous and nobody else's
+    sr = l["launch_split_rows"].astype(np.int64)
+    if which == "coarse":
+        sr = sr[:info.n_split_rows]
+    cut = slot >= 0
+    owner = np.full(int(sr[:, 2].sum()), -1)
+    for r, first, count, _ in sr:
+        assert np.all(owner[first:first + count] == -1)
+        owner[first:first + count] = r
+    assert np.all(owner >= 0) and np.array_equal(np.sort(slot[cut]), np.arange(owner.size)), which
+    assert np.array_equal(owner[slot[cut]], row[cut]) and np.unique(sr[:, 0]).size == sr.shape[0]
+    whole = np.concatenate([row[~cut], sr[:, 0], sh[:, 0]])
+    assert np.array_equal(np.sort(whole), np.arange(n_own)), which              # every row is written once
+    return it, pos
+
+
+@pytest.mark.parametrize("parts,part_id,wpb,seed,bags", [(1, 0, 0, 1, False), (2, 0, 1, 2, False), (3, 1, 4, 3, False), (2, 1, 16, 4, False), (1, 0, 2, 5, True)])
+def test_launch_arrays_hold_every_neighbour_once(parts, part_id, wpb, seed, bags):
+    n = 1500
+    ptr, col = _graph(n, 330, seed, hubs=20)
+    kw = dict(host_only=True, wpb=wpb, hot_phases=-1, fine_min_neighbours=1)
+    if bags:
+        part = binding.mgg_build_bags(ptr, col, n, 200, 900, **kw)
+    else:
+        part = binding.mgg_build_partition(ptr, col, parts, part_id, **kw)
+    info, e, l = part.info, part.export(), part.export_launch()
+    assert info.n_fine_items > 0 and info.n_fine_split_items > 0 and info.n_short_rows > 0
+    assert int(info.nnz_local + info.nnz_remote) >= 1 << 17 or parts > 1       # laid out by several threads, too
+    assert info.n_fine_split_items <= 2 * info.n_split_items
+    _, _ = _check_cover(part, e, l, l["launch_items"], "coarse")
+    it, _ = _check_cover(part, e, l, l["launch_fine_items"], "fine")
+    # the coarse table is the exported one, item by item, and its stream runs front to back in the queue of each XCD
+    li = l["launch_items"].astype(np.int64)
+    assert np.array_equal(li[:, 0], e["item_row"]) and np.array_equal(li[:, 4], e["item_slot"])
+    assert np.array_equal(li[:, 2], e["item_lend"] - e["item_lbeg"]) and np.array_equal(li[:, 3] - li[:, 2], e["item_rend"] - e["item_rbeg"])
+    xcd = (np.arange(li.shape[0]) // info.wpb) % 8
+    queue = np.concatenate([np.nonzero(xcd == x)[0] for x in range(8)])
+    begs = np.concatenate([li[queue, 1], l["launch_short"][:, 1]])
+    ends = np.concatenate([li[queue, 1] + li[queue, 3], l["launch_short"][:, 1] + l["launch_short"][:, 3]])
+    assert begs[0] == 0 and np.array_equal(begs[1:], ends[:-1])
+    # the fine table: rows of 128 to 255 are pieces of one class on its XCD (or the rest of the row), the others as they were
+    fi = l["launch_fine_items"].astype(np.int64)
+    assert fi.shape[0] % (8 * info.wpb) == 0
+    deg = np.diff(e["local_row_ptr"]) + np.diff(e["remote_row_ptr"])
+    cls = np.concatenate([e["src_class_local"], e["src_class_halo"]])
+    n_local = e["src_class_local"].size
+    for i, (row, beg, nl, cnt, slot, rbeg) in enumerate(fi[:, :6]):
+        if row < 0 or not 128 <= deg[row] < 256:
+            continue
+        place = np.concatenate([np.arange(beg, beg + nl), np.arange(rbeg, rbeg + cnt - nl)])
+        u = l["launch_cols"][place]
+        c = cls[np.where(u >= HALO, (u & ~HALO) + n_local, u).astype(np.int64)]
+        count = np.bincount(cls[np.concatenate([e["local_col"][e["local_row_ptr"][row]:e["local_row_ptr"][row + 1]],
+                                                n_local + e["remote_col"][e["remote_row_ptr"][row]:e["remote_row_ptr"][row + 1]]])], minlength=8)
+        if np.all(c == c[0]) and count[c[0]] >= info.min_piece:
+            assert c[0] == (i // info.wpb) % 8 and count[c[0]] == c.size
+        else:
+            assert np.all(count[c] < info.min_piece)
+    other = {tuple(r[[0, 1, 2, 3, 4]]) for r in li if r[0] >= 0 and not 128 <= deg[r[0]] < 256}
+    assert other == {tuple(r[[0, 1, 2, 3, 4]]) for r in fi if r[0] >= 0 and not 128 <= deg[r[0]] < 256}
+    # the factor beside every neighbour is that neighbour's
+    if not bags:
+        u = l["launch_cols"]
+        d = np.where(u >= HALO, e["deg_halo"][np.minimum(u & ~HALO, max(int(info.num_halo) - 1, 0))] if info.num_halo else 0, e["deg_own"][np.minimum(u, info.n_own - 1)])
+        assert np.array_equal(l["launch_wts"], (1.0 / np.sqrt(d + 1.0)).astype(np.float32))
+
+
+def test_the_fine_schedule_is_for_large_shares_with_the_default_cuts():
+    ptr, col = _graph(1500, 330, 7, hubs=20)
+    build = lambda **kw: binding.mgg_build_partition(ptr, col, host_only=True, hot_phases=-1, **kw).info
+    nnz = int(ptr[-1])
+    assert build().n_fine_items == 0                                            # 2^23 neighbours by default
+    assert build(fine_min_neighbours=nnz).n_fine_items > 0 and build(fine_min_neighbours=nnz + 1).n_fine_items == 0
+    for kw in (dict(xcd_min_deg=256), dict(min_piece=16), dict(xcd_min_deg=-1)):
+        assert build(fine_min_neighbours=1, **kw).n_fine_items == 0, kw
+    info = build(fine_min_neighbours=-1)
+    assert (info.n_fine_items, info.n_fine_split_rows, info.n_fine_split_items) == (0, 0, 0)
