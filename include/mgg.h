@@ -210,6 +210,26 @@ mgg_status_t mgg_aggregate(const mgg_partition_t *p, mgg_agg_t mode, float eps, 
                            const void *x_local, const void *x_halo, int32_t dim, int64_t ld_x,
                            float *out, int64_t ld_out, void *stream);
 
+/* What an aggregation of this width launches, for looking into it: host arithmetic only, host-only
+ * partitions too.  ld_x as in mgg_aggregate; base_align: the bytes (a power of two) that both tables'
+ * addresses are multiples of; scratch_bytes: the room there is for partial sums (SIZE_MAX: as much as
+ * it has a use for, as after mgg_partition_reserve; 64 MiB for mgg_aggregate_static; the part of a
+ * layer's workspace beyond its other buffers).  Which of the two schedules runs, and with it the order
+ * of the sums, depends on that room alone.  Errors: INVALID_ARG, UNSUPPORTED (too wide). */
+typedef struct {
+    int32_t lanes_per_row, vectors_per_lane;   /* lanes of a wavefront a table row takes, and what each gathers of it */
+    int32_t slab_bytes, n_slabs;               /* column slabs: their bytes of a row, how many passes */
+    int32_t n_chunks;                          /* chunks of the work that go through all slabs one after the other */
+    int32_t team;                              /* wavefronts that take one work item together (1: each its own) */
+    int32_t wpb;                               /* wavefronts per workgroup */
+    int32_t items_per_wave, short_per_wave;
+    int32_t fine;                              /* 1: the fine schedule (fine_min_neighbours above) */
+    int32_t lds_halo;                          /* 1: halo rows go through LDS */
+    int64_t n_workgroups;
+} mgg_aggregate_plan_t;
+mgg_status_t mgg_aggregate_plan(const mgg_partition_t *p, mgg_agg_t mode, mgg_dtype_t x_dtype, int32_t dim, int64_t ld_x,
+                                int32_t base_align, size_t scratch_bytes, mgg_aggregate_plan_t *out);
+
 /* mgg_aggregate for callers that cannot allocate and hold no reserved partition: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and result as
  * mgg_aggregate (up to the order of the sums where that has room for a schedule with more pieces); the partial sums of cut rows go to a fixed 64 MiB array inside the library's device

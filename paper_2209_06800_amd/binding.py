@@ -27,7 +27,7 @@ _STATUS_NAME = ["OK", "INVALID_ARG", "BAD_GRAPH", "UNSUPPORTED", "ALLOC", "HIP"]
 
 EXPORTED_SYMBOLS = [
     "mgg_build_partition", "mgg_partition_info", "mgg_partition_export", "mgg_partition_destroy",
-    "mgg_partition_reserve", "mgg_aggregate_scratch_bytes", "mgg_aggregate", "mgg_aggregate_static", "mgg_aggregate_to", "mgg_build_bags", "mgg_bag_sum", "mgg_update", "mgg_update_mlp", "mgg_layer_workspace_bytes", "mgg_layer_forward",
+    "mgg_partition_reserve", "mgg_aggregate_plan", "mgg_aggregate_scratch_bytes", "mgg_aggregate", "mgg_aggregate_static", "mgg_aggregate_to", "mgg_build_bags", "mgg_bag_sum", "mgg_update", "mgg_update_mlp", "mgg_layer_workspace_bytes", "mgg_layer_forward",
     "mgg_split_edge_balanced", "mgg_set_option", "mgg_get_option", "mgg_partition_set_option", "mgg_partition_get_option", "mgg_time_aggregate", "mgg_probe_gather",
     "mgg_model_evaluate", "mgg_tuner_create", "mgg_tuner_set_constraint", "mgg_tuner_next", "mgg_tuner_report", "mgg_tuner_result",
     "mgg_tuner_table", "mgg_tuner_destroy", "mgg_tune_aggregate",
@@ -76,6 +76,11 @@ class PartitionArrays(C.Structure):
     _fields_ = [(name, C.c_void_p) for name in _ARRAY_FIELDS]
 
 
+class AggregatePlan(C.Structure):
+    _fields_ = [(name, C.c_int32) for name in ("lanes_per_row", "vectors_per_lane", "slab_bytes", "n_slabs", "n_chunks", "team", "wpb",
+                                               "items_per_wave", "short_per_wave", "fine", "lds_halo")] + [("n_workgroups", C.c_int64)]
+
+
 class Knobs(C.Structure):
     _fields_ = [("ps", C.c_int32), ("dist", C.c_int32), ("wpb", C.c_int32)]
 
@@ -119,6 +124,7 @@ def lib():
                                     C.c_int64, C.c_void_p, C.c_int64, C.c_void_p]
         L.mgg_aggregate_static.argtypes = L.mgg_aggregate.argtypes
         L.mgg_partition_reserve.argtypes = [C.c_void_p, C.c_int32]
+        L.mgg_aggregate_plan.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int32, C.c_int64, C.c_int32, C.c_size_t, C.POINTER(AggregatePlan)]
         L.mgg_aggregate_scratch_bytes.restype = C.c_size_t
         L.mgg_aggregate_scratch_bytes.argtypes = [C.c_void_p, C.c_int32]
         L.mgg_aggregate_to.argtypes = [C.c_void_p, C.c_int, C.c_float, C.c_int, C.c_void_p, C.c_void_p, C.c_int32,
@@ -426,6 +432,16 @@ def mgg_aggregate_static(part: Partition, mode: str, x_local, x_halo=None, *, ep
     _check(lib().mgg_aggregate_static(part.handle, _MODE[mode], eps, _torch_dtype_code(x_local), _dev_ptr(x_local),
                                       _dev_ptr(x_halo), dim, _ld(x_local), _dev_ptr(out), _ld(out), _stream(stream)))
     return out
+
+
+def mgg_aggregate_plan(part: Partition, mode: str, dim: int, *, ld: Optional[int] = None, bf16: bool = False, base_align: int = 256,
+                       scratch_bytes: Optional[int] = None) -> AggregatePlan:
+    """What an aggregation of this width launches (host arithmetic only; `ld` defaults to contiguous rows, `scratch_bytes` to
+    what a reserved partition has)."""
+    plan = AggregatePlan()
+    _check(lib().mgg_aggregate_plan(part.handle, _MODE[mode], BF16 if bf16 else F32, dim, dim if ld is None else ld, base_align,
+                                    C.c_size_t(-1).value if scratch_bytes is None else scratch_bytes, C.byref(plan)))
+    return plan
 
 
 def mgg_aggregate_scratch_bytes(part: Partition, dim: int) -> int:

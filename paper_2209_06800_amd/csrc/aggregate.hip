@@ -214,15 +214,26 @@ mgg_status_t probe_gather(int64_t table_bytes, int32_t row_bytes, int64_t n_gath
     return st;
 }
 
-mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps, mgg_dtype_t x_dtype,
-                              const void *x_local, const void *x_halo, int32_t dim, int64_t ld_x, void *out,
-                              int64_t ld_out, hipStream_t stream, const float *bias, mgg_act_t act, int32_t out_dim,
-                              mgg_dtype_t out_dtype, float *scratch, size_t scratch_bytes)
-{
-    const bool bf16 = x_dtype == MGG_BF16;
-    const size_t esz = bf16 ? 2 : 4;
-    const void *xh = x_halo ? x_halo : x_local;   // never dereferenced when there is no halo
+namespace {
 
+// What one aggregation launches, decided by plan_aggregate: arithmetic on the host alone.
+struct Plan {
+    int vec, nvec;               // elements of a vector, vectors of a row
+    int32_t last_col;            // first column of the last vector
+    int slab_vecs, n_slabs;      // vectors of a column slab
+    int64_t n_chunks;            // chunks of the work that go through all slabs one after the other
+    int lpr, ch;                 // lanes of a table row, vectors a lane takes of it
+    bool lds, team, fine;        // halo rows through LDS; a workgroup takes one item; the fine schedule
+    int wpb;                     // wavefronts per workgroup
+    int32_t n_items, items_per_wave, short_per_wave, n_item_blocks;
+    int grid_x, chunk_x;         // workgroups of a slab, of a slab and chunk
+};
+
+// `bases`: the addresses of the two tables, or-ed; scratch_rows: rows of partial sums there is room for
+mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, int32_t dim, int64_t ld_x, uint64_t bases, int64_t scratch_rows, Plan *out)
+{
+    Plan pl{};
+    const size_t esz = bf16 ? 2 : 4;
     // 16 bytes per lane whatever the layout.  Where the padding between dim and ld_x completes the last
     // vector (and rows and bases are aligned) the padding is read; its values only reach output columns
     // that do not exist.  Elsewhere -- a plain contiguous tensor of an odd width -- the last vector is
@@ -230,10 +241,8 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     // that are its own.  Such loads and stores are aligned to an element only, which global memory takes at
     // full width (260 k-node R-MAT, half share, 75 contiguous fp32 columns: 226 us element by element, 167 us).
     // Rows shorter than a vector go element by element.
-    if (out_dim <= 0) out_dim = dim;
     int vec = bf16 ? 8 : 4;
-    int32_t last_col;
-    const bool rows_aligned = ld_x % vec == 0 && aligned(x_local, 16) && aligned(xh, 16);
+    const bool rows_aligned = ld_x % vec == 0 && bases % 16 == 0;
     {
         const int64_t padded = (static_cast<int64_t>(dim) + vec - 1) / vec * vec;
         if (rows_aligned && padded <= ld_x) {
@@ -241,7 +250,7 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
         } else if (dim < vec) {
             vec = 1;
         }
-        last_col = dim - vec;
+        pl.last_col = dim - vec;
     }
     const int nvec = (dim + vec - 1) / vec;
     // Column slabs: when one XCD's share of the table rows does not fit its L2 at full width, the
@@ -271,7 +280,7 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
             // one chunk; of 2 KB 5.36 -> 5.21).  Rows off line boundaries pay a line more per slab: 512 (1200-byte rows: 4.14
             // against 4.17 ms).
             const int64_t id_bytes = (static_cast<int64_t>(p->local_col.size()) + static_cast<int64_t>(p->remote_col.size())) * (mode == MGG_AGG_GCN_SYM ? 8 : 4);
-            const bool on_lines = ld_x * static_cast<int64_t>(esz) % 128 == 0 && aligned(x_local, 128) && aligned(xh, 128);
+            const bool on_lines = ld_x * static_cast<int64_t>(esz) % 128 == 0 && bases % 128 == 0;
             if (static_cast<int64_t>(dim) * static_cast<int64_t>(esz) >= 1024) {
                 if (class_rows * 256 <= (4 << 20) && id_bytes >= (static_cast<int64_t>(128) << 20) && on_lines) {
                     slab_bytes = 256;
@@ -292,15 +301,66 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     while (lpr < slab_vecs && lpr < 64) lpr <<= 1;
     const int ch = (slab_vecs + 63) / 64;
 
+    // the fine schedule where its partial sums have room
+    pl.fine = p->n_fine_sums > 0 && scratch_rows >= p->n_split_items + p->n_fine_sums;
+    pl.n_items = static_cast<int32_t>(pl.fine ? p->fine_items.size() : p->items.size());
+    const int32_t n_short = static_cast<int32_t>(p->short_rows.size());
+    // Work per wavefront: M items (or groups of short rows) one after the other, pipelined.  More per
+    // wavefront amortises its start-up latencies; fewer leaves more workgroups for the hardware to
+    // balance.  Automatic: 2 where the launch still has about 8192 workgroups (measured on MI355X: 0.3-2.5 %
+    // faster than 1 and than 8 on every workload tried), else 1.
+    // (16-byte loads from memory into LDS want aligned addresses, unlike those into registers)
+    const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned;
+    // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel).  The chip holds some 5000
+    // wavefronts of these kernels, and a team is worth its barrier and its additions while its members have a batch
+    // of loads each and find a place at once: 8 or 4 to an item up to 4096 wavefronts in all (6480 rows, 11.0 us with
+    // and without; 370 rows of 115, 8.7 us at 2700 wavefronts and 10.2 at 5400), 2 up to 8192 (4389 rows, 12.0 ->
+    // 10.6 us at 6800).
+    bool team = false;
+    int wpb = p->wpb;
+    if (ch == 1 && !lds && p->opt_items_per_wave == 0)
+        for (int t = kMaxTeam; t >= 2 && !team; t /= 2)
+            if (p->n_work_items * n_slabs * t <= (t == 2 ? 8192 : 4096) && p->longest_item >= t * 8 * (64 / lpr)) { team = true; wpb = t; }
+    const int64_t n_groups = team ? pl.n_items : (pl.n_items + wpb - 1) / wpb;
+    const int64_t short_groups = (n_short + 64 / lpr - 1) / (64 / lpr);
+    {
+        auto pick = [&](int32_t opt, int64_t units, int64_t most) { return static_cast<int32_t>(opt > 0 ? opt : std::min<int64_t>(most, std::max<int64_t>(1, units * n_slabs / 8192))); };
+        pl.items_per_wave = team ? 1 : pick(p->opt_items_per_wave, n_groups, 2);
+        // (groups of short rows: one, since the ids of a group are all requested ahead in it; 26-lookup bags 147.6 -> 144.5 us,
+        // flat elsewhere)
+        pl.short_per_wave = pick(p->opt_short_per_wave, (short_groups + wpb - 1) / wpb, 1);
+    }
+    pl.n_item_blocks = team ? pl.n_items : static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * pl.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * pl.items_per_wave) * kXcd);
+    const int64_t short_waves = (short_groups + pl.short_per_wave - 1) / pl.short_per_wave;
+    pl.grid_x = pl.n_item_blocks + static_cast<int>((short_waves + wpb - 1) / wpb);
+    if (n_slabs > 1) pl.grid_x = (pl.grid_x + kXcd - 1) / kXcd * kXcd;   // keeps workgroup x on XCD x mod 8 in every slab
+    pl.n_chunks = std::max<int64_t>(1, std::min<int64_t>({n_chunks, pl.grid_x / kXcd, 65535 / n_slabs}));
+    pl.chunk_x = pl.n_chunks == 1 ? pl.grid_x : static_cast<int>((pl.grid_x + pl.n_chunks * kXcd - 1) / (pl.n_chunks * kXcd) * kXcd);
+    if (pl.chunk_x > 0) pl.n_chunks = (pl.grid_x + pl.chunk_x - 1) / pl.chunk_x;
+    pl.vec = vec; pl.nvec = nvec; pl.slab_vecs = slab_vecs; pl.n_slabs = n_slabs; pl.lpr = lpr; pl.ch = ch;
+    pl.lds = lds; pl.team = team; pl.wpb = wpb;
+    *out = pl;
+    return MGG_OK;
+}
+
+}  // namespace
+
+mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps, mgg_dtype_t x_dtype,
+                              const void *x_local, const void *x_halo, int32_t dim, int64_t ld_x, void *out,
+                              int64_t ld_out, hipStream_t stream, const float *bias, mgg_act_t act, int32_t out_dim,
+                              mgg_dtype_t out_dtype, float *scratch, size_t scratch_bytes)
+{
+    const bool bf16 = x_dtype == MGG_BF16;
+    const void *xh = x_halo ? x_halo : x_local;   // never dereferenced when there is no halo
+    if (out_dim <= 0) out_dim = dim;
     // scratch rows for the partial sums of split rows: the caller's buffer, else the partition's own;
     // nothing is allocated here
-    int64_t scratch_ld = 0;
-    // the fine schedule where its partial sums have room
-    bool fine = p->n_fine_sums > 0;
+    int64_t scratch_ld = scratch_ld_for(dim), scratch_rows = p->d.scratch_rows;
+    if (scratch) scratch_rows = static_cast<int64_t>(scratch_bytes / (static_cast<size_t>(scratch_ld) * sizeof(float)));
+    Plan pl;
+    mgg_status_t s = plan_aggregate(p, mode, bf16, dim, ld_x, reinterpret_cast<uint64_t>(x_local) | reinterpret_cast<uint64_t>(xh), scratch_rows, &pl);
+    if (s != MGG_OK) return s;
     if (p->n_split_items > 0) {
-        scratch_ld = scratch_ld_for(dim);
-        const size_t fine_need = static_cast<size_t>(p->n_split_items + p->n_fine_sums) * static_cast<size_t>(scratch_ld) * sizeof(float);
-        if (scratch ? scratch_bytes < fine_need : p->d.scratch_rows < p->n_split_items + p->n_fine_sums) fine = false;
         const size_t need = static_cast<size_t>(p->n_split_items) * static_cast<size_t>(scratch_ld) * sizeof(float);
         if (scratch) {
             if (scratch_bytes < need) return fail(MGG_ERR_INVALID_ARG, "scratch of %zu bytes given, width %d needs %zu", scratch_bytes, dim, need);
@@ -317,41 +377,14 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     AggArgs a{};
     a.cols = p->d.cols; a.wts = p->d.wts;
     a.dinv_own = p->d.dinv_own;
-    a.short_desc = p->d.short_desc; a.items = fine ? p->d.fine_items : p->d.items;
+    a.short_desc = p->d.short_desc; a.items = pl.fine ? p->d.fine_items : p->d.items;
     a.x_local = x_local; a.x_halo = xh;
     a.out = out; a.scratch = scratch;
     a.ld_x = ld_x; a.ld_out = ld_out; a.scratch_ld = scratch_ld;
-    a.nvec = nvec;
-    a.last_col = last_col;
-    a.slab_vecs = slab_vecs;
-    a.n_items = static_cast<int32_t>(fine ? p->fine_items.size() : p->items.size());
-    int wpb = p->wpb;
-    a.n_short = static_cast<int32_t>(p->short_rows.size());
-    // Work per wavefront: M items (or groups of short rows) one after the other, pipelined.  More per
-    // wavefront amortises its start-up latencies; fewer leaves more workgroups for the hardware to
-    // balance.  Automatic: 2 where the launch still has about 8192 workgroups (measured on MI355X: 0.3-2.5 %
-    // faster than 1 and than 8 on every workload tried), else 1.
-    // (16-byte loads from memory into LDS want aligned addresses, unlike those into registers)
-    const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned;
-    // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel).  The chip holds some 5000
-    // wavefronts of these kernels, and a team is worth its barrier and its additions while its members have a batch
-    // of loads each and find a place at once: 8 or 4 to an item up to 4096 wavefronts in all (6480 rows, 11.0 us with
-    // and without; 370 rows of 115, 8.7 us at 2700 wavefronts and 10.2 at 5400), 2 up to 8192 (4389 rows, 12.0 ->
-    // 10.6 us at 6800).
-    bool team = false;
-    if (ch == 1 && !lds && p->opt_items_per_wave == 0)
-        for (int t = kMaxTeam; t >= 2 && !team; t /= 2)
-            if (p->n_work_items * n_slabs * t <= (t == 2 ? 8192 : 4096) && p->longest_item >= t * 8 * (64 / lpr)) { team = true; wpb = t; }
-    const int64_t n_groups = team ? a.n_items : (a.n_items + wpb - 1) / wpb;
-    const int64_t short_groups = (a.n_short + 64 / lpr - 1) / (64 / lpr);
-    {
-        auto pick = [&](int32_t opt, int64_t units, int64_t most) { return static_cast<int32_t>(opt > 0 ? opt : std::min<int64_t>(most, std::max<int64_t>(1, units * n_slabs / 8192))); };
-        a.items_per_wave = team ? 1 : pick(p->opt_items_per_wave, n_groups, 2);
-        // (groups of short rows: one, since the ids of a group are all requested ahead in it; 26-lookup bags 147.6 -> 144.5 us,
-        // flat elsewhere)
-        a.short_per_wave = pick(p->opt_short_per_wave, (short_groups + wpb - 1) / wpb, 1);
-    }
-    a.n_item_blocks = team ? a.n_items : static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * a.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * a.items_per_wave) * kXcd);
+    a.nvec = pl.nvec; a.last_col = pl.last_col; a.slab_vecs = pl.slab_vecs; a.n_slabs = pl.n_slabs;
+    a.n_items = pl.n_items; a.n_item_blocks = pl.n_item_blocks; a.items_per_wave = pl.items_per_wave;
+    a.n_short = static_cast<int32_t>(p->short_rows.size()); a.short_per_wave = pl.short_per_wave;
+    const dim3 grid(static_cast<unsigned>(pl.chunk_x), static_cast<unsigned>(pl.n_slabs * pl.n_chunks));
     a.ps = p->ps;
     const bool gcn = mode == MGG_AGG_GCN_SYM;
     a.self_w = p->bags ? 0.f : 1.f + eps;
@@ -365,20 +398,13 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     const bool two_phases = p->opt_split_phases != 0 && !p->halo_gid.empty() && out_dtype != MGG_BF16;   // phase 2 reads `out` back
     for (int phase = two_phases ? 1 : 0; phase <= (two_phases ? 2 : 0); ++phase) {
         a.phase = phase;
-        const int64_t short_waves = (short_groups + a.short_per_wave - 1) / a.short_per_wave;
-        int grid_x = a.n_item_blocks + static_cast<int>((short_waves + wpb - 1) / wpb);
-        if (n_slabs > 1) grid_x = (grid_x + kXcd - 1) / kXcd * kXcd;   // keeps workgroup x on XCD x mod 8 in every slab
-        a.n_slabs = n_slabs;
-        n_chunks = std::max<int64_t>(1, std::min<int64_t>({n_chunks, grid_x / kXcd, 65535 / n_slabs}));
-        const int chunk_x = n_chunks == 1 ? grid_x : static_cast<int>((grid_x + n_chunks * kXcd - 1) / (n_chunks * kXcd) * kXcd);
-        const dim3 grid(static_cast<unsigned>(chunk_x), static_cast<unsigned>(n_slabs * ((grid_x + chunk_x - 1) / std::max(chunk_x, 1))));
-        if (grid_x > 0) {
+        if (pl.grid_x > 0) {
             hipError_t e;
-            if (bf16) e = launch_aggregate_bf16(a, gcn, vec, grid, wpb, stream, lpr, ch, lds, team);
-            else e = launch_aggregate_f32(a, gcn, vec, grid, wpb, stream, lpr, ch, lds, team);
+            if (bf16) e = launch_aggregate_bf16(a, gcn, pl.vec, grid, pl.wpb, stream, pl.lpr, pl.ch, pl.lds, pl.team);
+            else e = launch_aggregate_f32(a, gcn, pl.vec, grid, pl.wpb, stream, pl.lpr, pl.ch, pl.lds, pl.team);
             if (e != hipSuccess) return hip_fail(e, "aggregate kernel launch");
         }
-        const int32_t n_split = static_cast<int32_t>(p->split_rows.size() + (fine ? p->fine_split_rows.size() : 0));
+        const int32_t n_split = static_cast<int32_t>(p->split_rows.size() + (pl.fine ? p->fine_split_rows.size() : 0));
         if (n_split > 0) {
             const dim3 fgrid(static_cast<unsigned>((n_split + kWavesPerBlock - 1) / kWavesPerBlock));
             if (bf16)
@@ -391,6 +417,25 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
             if (e != hipSuccess) return hip_fail(e, "fix-up kernel launch");
         }
     }
+    return MGG_OK;
+}
+
+// what plan_aggregate decides, for mgg_aggregate_plan
+mgg_status_t describe_plan(const mgg_partition *p, mgg_agg_t mode, mgg_dtype_t x_dtype, int32_t dim, int64_t ld_x, int32_t base_align, size_t scratch_bytes,
+                           mgg_aggregate_plan_t *o)
+{
+    const bool bf16 = x_dtype == MGG_BF16;
+    const int64_t rows = static_cast<int64_t>(std::min<size_t>(scratch_bytes / (static_cast<size_t>(scratch_ld_for(dim)) * sizeof(float)), INT64_MAX));
+    Plan pl;
+    const mgg_status_t s = plan_aggregate(p, mode, bf16, dim, ld_x, static_cast<uint64_t>(base_align), rows, &pl);
+    if (s != MGG_OK) return s;
+    o->lanes_per_row = pl.lpr; o->vectors_per_lane = pl.ch;
+    o->slab_bytes = static_cast<int32_t>(static_cast<size_t>(pl.slab_vecs) * pl.vec * (bf16 ? 2 : 4));
+    o->n_slabs = pl.n_slabs; o->n_chunks = static_cast<int32_t>(pl.n_chunks);
+    o->team = pl.team ? pl.wpb : 1; o->wpb = pl.wpb;
+    o->items_per_wave = pl.items_per_wave; o->short_per_wave = pl.short_per_wave;
+    o->fine = pl.fine; o->lds_halo = pl.lds && pl.ch == 1 && pl.wpb <= kStageWpb;
+    o->n_workgroups = static_cast<int64_t>(pl.chunk_x) * pl.n_slabs * pl.n_chunks;
     return MGG_OK;
 }
 

@@ -173,6 +173,18 @@ mgg_status_t mgg_aggregate_static(const mgg_partition_t *p, mgg_agg_t mode, floa
                             MGG_F32, scratch, cap);
 }
 
+mgg_status_t mgg_aggregate_plan(const mgg_partition_t *p, mgg_agg_t mode, mgg_dtype_t x_dtype, int32_t dim, int64_t ld_x, int32_t base_align,
+                                size_t scratch_bytes, mgg_aggregate_plan_t *out)
+{
+    if (!p || !out) return fail(MGG_ERR_INVALID_ARG, "NULL argument");
+    if (mode != MGG_AGG_GCN_SYM && mode != MGG_AGG_GIN_SUM) return fail(MGG_ERR_INVALID_ARG, "unknown aggregation mode");
+    if (!dtype_ok(x_dtype)) return fail(MGG_ERR_INVALID_ARG, "unknown dtype");
+    if (dim < 1 || ld_x < dim) return fail(MGG_ERR_INVALID_ARG, "dim %d, ld_x %lld", dim, (long long)ld_x);
+    if (base_align < 1 || (base_align & (base_align - 1))) return fail(MGG_ERR_INVALID_ARG, "base_align %d is no power of two", base_align);
+    *out = mgg_aggregate_plan_t{};
+    return describe_plan(p, mode, x_dtype, dim, ld_x, base_align, scratch_bytes, out);
+}
+
 size_t mgg_aggregate_scratch_bytes(const mgg_partition_t *p, int32_t dim)
 {
     if (!p || dim < 1) return 0;

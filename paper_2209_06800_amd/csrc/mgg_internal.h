@@ -146,6 +146,9 @@ inline int64_t scratch_ld_for(int32_t dim) { return (static_cast<int64_t>(dim) +
 // (the least an aggregation can do with, and what it has a use for)
 inline size_t scratch_bytes_wanted(const mgg_partition *p, int32_t dim) { return static_cast<size_t>(p->n_split_items + p->n_fine_sums) * static_cast<size_t>(scratch_ld_for(dim)) * sizeof(float); }
 inline size_t scratch_bytes_for(const mgg_partition *p, int32_t dim) { return static_cast<size_t>(p->n_split_items) * static_cast<size_t>(scratch_ld_for(dim)) * sizeof(float); }
+// what launch_aggregate would launch (host arithmetic, host-only partitions too)
+mgg_status_t describe_plan(const mgg_partition *p, mgg_agg_t mode, mgg_dtype_t x_dtype, int32_t dim, int64_t ld_x, int32_t base_align, size_t scratch_bytes,
+                           mgg_aggregate_plan_t *o);
 // the library's fixed scratch array on the current device (aggregate.hip); NULL + error set on failure
 float *static_scratch(size_t *bytes);
 mgg_status_t launch_update(int64_t n_rows, mgg_dtype_t a_dtype, const void *a, int64_t ld_a, int32_t d_in,

@@ -127,3 +127,51 @@ def test_the_fine_schedule_is_for_large_shares_with_the_default_cuts():
         assert build(fine_min_neighbours=1, **kw).n_fine_items == 0, kw
     info = build(fine_min_neighbours=-1)
     assert (info.n_fine_items, info.n_fine_split_rows, info.n_fine_split_items) == (0, 0, 0)
+
+
+# ---- what a launch is: mgg_aggregate_plan ------------------------------------------------------------------------
+def _lists(lens, n_table, seed=0):
+    """A directed graph of max(len(lens), n_table) nodes whose first rows have these lengths."""
+    rng = np.random.default_rng(seed)
+    lens = np.concatenate([lens, np.zeros(max(0, n_table - len(lens)), dtype=np.int64)]).astype(np.int64)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    row = np.repeat(np.arange(lens.size), lens)
+    col = rng.integers(0, lens.size - 1, ptr[-1])
+    return ptr, (col + (col >= row)).astype(np.int32)
+
+
+def test_plan_says_which_schedule_runs():
+    """The fine schedule runs from the scratch on that holds its partial sums, the coarse one below; a partition built
+    without it has one schedule whatever the scratch."""
+    ptr, col = _graph(1500, 330, 7, hubs=20)
+    part = binding.mgg_build_partition(ptr, col, host_only=True, hot_phases=-1, fine_min_neighbours=1)
+    one = binding.mgg_build_partition(ptr, col, host_only=True, hot_phases=-1, fine_min_neighbours=-1)
+    for dim in (1, 64, 100, 602):
+        need = binding.mgg_aggregate_scratch_bytes(part, dim)
+        full = need + int(part.info.n_fine_split_items) * (-(-dim // 8) * 8) * 4
+        assert binding.mgg_aggregate_plan(part, "gcn", dim).fine == 1
+        assert [binding.mgg_aggregate_plan(part, "gcn", dim, scratch_bytes=b).fine for b in (need, full - 1, full)] == [0, 0, 1]
+        assert binding.mgg_aggregate_plan(one, "gcn", dim).fine == 0 and need == binding.mgg_aggregate_scratch_bytes(one, dim)
+
+
+def test_plan_checks_its_arguments():
+    part = binding.mgg_build_partition(*_graph(40, 20, 1), host_only=True)
+    for kw in (dict(dim=0), dict(dim=8, ld=4), dict(dim=8, base_align=3), dict(dim=8, base_align=0)):
+        with pytest.raises(binding.MggError) as err:
+            binding.mgg_aggregate_plan(part, "gcn", **kw)
+        assert err.value.status == binding.ERR_INVALID_ARG, kw
+    lib = binding.lib()
+    assert lib.mgg_aggregate_plan(None, 0, 0, 8, 8, 16, 0, None) == binding.ERR_INVALID_ARG
+    assert lib.mgg_aggregate_plan(part.handle, 0, 0, 8, 8, 16, 0, None) == binding.ERR_INVALID_ARG
+    with pytest.raises(binding.MggError):
+        binding.mgg_aggregate_plan(part, "gcn", 2 ** 31 - 8)                    # beyond 65535 slabs of 4 KB
+
+
+@pytest.mark.parametrize("dim,ld,bf16,align,lanes,per_lane", [(1, 1, False, 256, 4, 1), (3, 3, False, 4, 4, 1), (3, 4, False, 16, 4, 1), (16, 16, False, 256, 4, 1),
+                                                              (20, 20, False, 256, 8, 1), (75, 75, False, 4, 32, 1), (64, 64, False, 256, 16, 1),
+                                                              (5, 5, True, 2, 8, 1), (128, 128, True, 256, 16, 1), (260, 260, False, 256, 32, 1)])
+def test_plan_lanes_of_a_row(dim, ld, bf16, align, lanes, per_lane):
+    part = binding.mgg_build_partition(*_graph(40, 20, 1), host_only=True)
+    plan = binding.mgg_aggregate_plan(part, "gcn", dim, ld=ld, bf16=bf16, base_align=align)
+    assert (plan.lanes_per_row, plan.vectors_per_lane) == (lanes, per_lane)
+    assert plan.n_slabs == -(-dim * (2 if bf16 else 4) // plan.slab_bytes)
