@@ -271,7 +271,7 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
             // L2 and 512-byte slabs do not (the 233 k x 2.4 KB table of the configs: 18.7 ms against 20.5 with
             // 512 and 20.4 with 128).  On tables far beyond the caches (2 M rows of 1 KB: 4.70 ms against 4.92
             // without slabs) the gain is small but still there; narrower rows lose to the extra passes.
-            const int64_t table_rows = p->n_own + static_cast<int64_t>(p->halo_gid.size());
+            const int64_t table_rows = p->n_local_rows + static_cast<int64_t>(p->halo_gid.size());
             const int64_t class_rows = (p->xcd_min_deg > 0 ? table_rows / kXcd : table_rows) + 1;
             // Where 256-byte slabs of a class fit one L2 the gathers hit, and what is left to wait for is the id stream: read
             // once per slab, from HBM if it does not stay in the Infinity Cache (bare gathers out of L2: 28.8 TB/s with ids
