@@ -62,7 +62,9 @@ typedef struct {
     int32_t host_only;   /* nonzero: build on the host only, never touch the GPU (for
                             checks of the integer structures); device calls on such a
                             partition fail with MGG_ERR_INVALID_ARG */
-    int32_t wpb;         /* wavefronts (= work items) per workgroup of the aggregation kernel,
+    int32_t wpb;         /* wavefronts (= work items) per workgroup of the aggregation kernel;
+                            given, every launch keeps to it, while the default leaves launches too
+                            small to fill the chip to teams of wavefronts that share an item;
                             1..16; 0 = default 2 */
     int32_t xcd_min_deg; /* rows with at least this many neighbours have their neighbour lists
                             regrouped by source class (see hot_rows), one piece of work per
@@ -390,7 +392,8 @@ mgg_status_t mgg_split_edge_balanced(int64_t num_nodes, const int64_t *row_ptr, 
  * 160 KB of LDS per CU unless the caller has set one.
  *
  * mgg_tune_aggregate drives a tuner on the GPU: for every proposal it builds the partition with
- * base_opts (NULL = defaults) plus the proposed ps / dist / wpb, times `iters` aggregations on
+ * base_opts (NULL = defaults) plus the proposed ps / dist / wpb (given, so that small launches run without
+ * the teams of the default, which is worth timing beside the result), times `iters` aggregations on
  * `stream` with HIP events (synchronises), and reports the mean milliseconds.  Pointers as in
  * mgg_build_partition and mgg_aggregate; `out` is overwritten by every trial.
  * ------------------------------------------------------------------------------------- */

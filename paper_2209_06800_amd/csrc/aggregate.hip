@@ -315,10 +315,10 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
     // wavefronts of these kernels, and a team is worth its barrier and its additions while its members have a batch
     // of loads each and find a place at once: 8 or 4 to an item up to 4096 wavefronts in all (6480 rows, 11.0 us with
     // and without; 370 rows of 115, 8.7 us at 2700 wavefronts and 10.2 at 5400), 2 up to 8192 (4389 rows, 12.0 ->
-    // 10.6 us at 6800).
+    // 10.6 us at 6800).  A caller who says how many wavefronts a workgroup or how many items a wavefront takes gets just that.
     bool team = false;
     int wpb = p->wpb;
-    if (ch == 1 && !lds && p->opt_items_per_wave == 0)
+    if (ch == 1 && !lds && p->opt_items_per_wave == 0 && !p->wpb_given)
         for (int t = kMaxTeam; t >= 2 && !team; t /= 2)
             if (p->n_work_items * n_slabs * t <= (t == 2 ? 8192 : 4096) && p->longest_item >= t * 8 * (64 / lpr)) { team = true; wpb = t; }
     const int64_t n_groups = team ? pl.n_items : (pl.n_items + wpb - 1) / wpb;

@@ -85,6 +85,7 @@ struct mgg_partition {
     bool bags = false;                // built by mgg_build_bags: owned rows are bags, no self term, plain sums
     int32_t num_parts = 1, part_id = 0;
     int32_t ps = 64, dist = 8, short_max = 16, xcd_min_deg = -1, wpb = 4;
+    bool wpb_given = false;           // by the caller: every launch keeps to it
     int32_t hot_rows = 0, hot_phases = 0, n_phases = 0, min_piece = 0, hot_min_count = 0;
     int32_t class_mode = 0;           // 0: no source classes, 1: by hash, 2: by popularity
     std::vector<uint8_t> src_class;   // class of every table row (local rows, then halo slots); empty: no classes

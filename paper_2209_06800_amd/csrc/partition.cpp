@@ -210,6 +210,7 @@ struct Knobs {
     int32_t ps = 64, dist = 8, short_max = 16, host_only = 0, xcd_min_deg = kDefaultXcdMinDeg, wpb = kDefaultWpb;
     int32_t hot_rows = 0, hot_phases = kDefaultHotPhases, min_piece = kDefaultMinPiece, hot_min_count = kDefaultHotMinCount;
     int32_t reserve_dim = 0;
+    bool wpb_given = false;
     int64_t fine_min = kFineMinNeighbours;       // neighbours from which a share has a fine schedule
 };
 
@@ -232,7 +233,7 @@ static mgg_status_t parse_opts(const mgg_build_opts_t *opts, Knobs *k)
         // (a caller who chooses how rows are cut gets just that)
         if (opts->fine_min_neighbours) k->fine_min = opts->fine_min_neighbours;
         if (opts->xcd_min_deg || opts->min_piece) k->fine_min = -1;
-        if (opts->wpb) wpb = opts->wpb;
+        if (opts->wpb) { wpb = opts->wpb; k->wpb_given = true; }
         k->reserve_dim = opts->reserve_dim;
     }
     if (ps < 1 || ps > 64) return fail(MGG_ERR_INVALID_ARG, "ps %d outside [1, 64]", ps);
@@ -302,7 +303,7 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
     const int32_t ps = k.ps, dist = k.dist, short_max = k.short_max, xcd_min_deg = k.xcd_min_deg, wpb = k.wpb;
     const int32_t hot_rows = k.hot_rows, min_piece = k.min_piece, hot_min_count = k.hot_min_count;
     int32_t hot_phases = k.hot_phases;
-    p->ps = ps; p->dist = dist; p->short_max = short_max; p->xcd_min_deg = xcd_min_deg; p->wpb = wpb;
+    p->ps = ps; p->dist = dist; p->short_max = short_max; p->xcd_min_deg = xcd_min_deg; p->wpb = wpb; p->wpb_given = k.wpb_given;
     p->hot_rows = hot_rows; p->hot_phases = hot_phases; p->min_piece = min_piece; p->hot_min_count = hot_min_count;
 
     // ---- source classes -------------------------------------------------------------

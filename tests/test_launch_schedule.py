@@ -190,3 +190,17 @@ def test_slabs_go_by_the_rows_of_the_tables(bags, table, slab_bytes):
         want = 256 if rows // 8 * 512 > 8 << 20 and rows // 8 * 256 <= 8 << 20 else 512
         assert want == slab_bytes or rows < table
         assert binding.mgg_aggregate_plan(part, "gin", 256).slab_bytes == want, (lo, hi)
+
+
+@pytest.mark.parametrize("wpb", [1, 2, 4, 8, 16])
+def test_a_given_number_of_wavefronts_is_kept(wpb):
+    """wpb is a knob and an axis of the parameter search: a launch that a team would take by itself has the workgroups that
+    were asked for, and several wpb are several launches."""
+    ptr, col = _graph(1500, 330, 7, hubs=20)
+    free = binding.mgg_aggregate_plan(binding.mgg_build_partition(ptr, col, host_only=True), "gcn", 64)
+    assert free.team > 1 and free.wpb == free.team
+    part = binding.mgg_build_partition(ptr, col, host_only=True, wpb=wpb)
+    plan = binding.mgg_aggregate_plan(part, "gcn", 64)
+    assert (plan.team, plan.wpb) == (1, wpb)
+    part.set_option("items_per_wave", 2)
+    assert binding.mgg_aggregate_plan(part, "gcn", 64).wpb == wpb
