@@ -301,16 +301,20 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
     while (lpr < slab_vecs && lpr < 64) lpr <<= 1;
     const int ch = (slab_vecs + 63) / 64;
 
-    // the fine schedule where its partial sums have room
-    pl.fine = p->n_fine_sums > 0 && scratch_rows >= p->n_split_items + p->n_fine_sums;
+    // 16-byte loads from memory into LDS want aligned addresses, unlike those into registers, and are given 32-bit row offsets
+    const int64_t most_rows = std::max<int64_t>(p->n_local_rows, static_cast<int64_t>(p->halo_gid.size()));
+    const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned && ch == 1 && p->wpb <= kStageWpb &&
+                     static_cast<uint64_t>(most_rows) * static_cast<uint64_t>(ld_x) * esz < (1ull << 32);
+    // The fine schedule where its partial sums have room; not with halo rows through LDS, which are staged 8 KB at a time
+    // however few a piece has (17.8 M neighbours at 64 columns 0.721 ms with it, 0.609 without; 28 M at 128 in bf16 1.43 and
+    // 1.16).
+    pl.fine = !lds && p->n_fine_sums > 0 && scratch_rows >= p->n_split_items + p->n_fine_sums;
     pl.n_items = static_cast<int32_t>(pl.fine ? p->fine_items.size() : p->items.size());
     const int32_t n_short = static_cast<int32_t>(p->short_rows.size());
     // Work per wavefront: M items (or groups of short rows) one after the other, pipelined.  More per
     // wavefront amortises its start-up latencies; fewer leaves more workgroups for the hardware to
     // balance.  Automatic: 2 where the launch still has about 8192 workgroups (measured on MI355X: 0.3-2.5 %
     // faster than 1 and than 8 on every workload tried), else 1.
-    // (16-byte loads from memory into LDS want aligned addresses, unlike those into registers)
-    const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned;
     // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel).  The chip holds some 5000
     // wavefronts of these kernels, and a team is worth its barrier and its additions while its members have a batch
     // of loads each and find a place at once: 8 or 4 to an item up to 4096 wavefronts in all (6480 rows, 11.0 us with
@@ -434,7 +438,7 @@ mgg_status_t describe_plan(const mgg_partition *p, mgg_agg_t mode, mgg_dtype_t x
     o->n_slabs = pl.n_slabs; o->n_chunks = static_cast<int32_t>(pl.n_chunks);
     o->team = pl.team ? pl.wpb : 1; o->wpb = pl.wpb;
     o->items_per_wave = pl.items_per_wave; o->short_per_wave = pl.short_per_wave;
-    o->fine = pl.fine; o->lds_halo = pl.lds && pl.ch == 1 && pl.wpb <= kStageWpb;
+    o->fine = pl.fine; o->lds_halo = pl.lds;
     o->n_workgroups = static_cast<int64_t>(pl.chunk_x) * pl.n_slabs * pl.n_chunks;
     return MGG_OK;
 }

@@ -803,17 +803,17 @@ template <int N> __device__ __forceinline__ void wait_vmcnt()
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// requests (up to) kStageSlots load steps of a remote partition, starting at step t0, into `stage`;
-// always issues exactly kStageSlots instructions so that outstanding loads can be counted
+// requests (up to) kStageSlots load steps of a remote partition, starting at step t0, into `stage`; lane i holds the
+// byte offset of the table row of neighbour i (the host takes this path for tables below 4 GB).
+// Always issues exactly kStageSlots instructions so that outstanding loads can be counted
 template <class K>
-__device__ __forceinline__ void stage_halo_batch(uint4 (*stage)[kWave], const char *table, uint32_t id, uint64_t ldb, int len, int t0,
-                                                 const Lanes<K> &ln)
+__device__ __forceinline__ void stage_halo_batch(uint4 (*stage)[kWave], const char *table, uint32_t row_off, int len, int t0, const Lanes<K> &ln)
 {
 #pragma unroll
     for (int u = 0; u < kStageSlots; ++u) {
         const int j = (t0 + u) * K::NPW + ln.sub;
-        const uint32_t row = static_cast<uint32_t>(__shfl(static_cast<int>(id), j < len ? j : 0)) & 0x7fffffffu;   // neighbour 0 exists whenever a batch is staged
-        const char *src = table + (static_cast<uint64_t>(row) * ldb + ln.col_off[0]);
+        const uint32_t off = static_cast<uint32_t>(__shfl(static_cast<int>(row_off), j < len ? j : 0));   // neighbour 0 exists whenever a batch is staged
+        const char *src = table + (off + ln.col_off[0]);
         __builtin_amdgcn_global_load_lds((gptr_t)(const void *)src, (lptr_t)(void *)&stage[u][0], 16, 0, 0);
     }
 }
@@ -837,6 +837,7 @@ __device__ __forceinline__ void consume_stage(Acc<K> &acc, uint4 (*stage)[kWave]
 }
 
 // The items of aggregate_kernel with their halo rows through LDS (option lds_halo); local partitions through registers.
+// The same pipeline over items, in pairs of a local and a remote partition.
 template <class K, bool GCN>
 __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu(K::MIN_WAVES))) void aggregate_lds_kernel(const AggArgs a)
 {
@@ -859,35 +860,41 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
     typename K::raw xs[K::CH];
     ItemQueue q;
     q.init(a, ln.block, wave, wpb, lane);
-    int d_cur = q.load(0);
+    int d_cur = q.load(0), d_nxt = q.load(1);
+    bool ids_ready = false;
+    uint32_t id_l = 0, id_r = 0;
+    float w_l = 0.f, w_r = 0.f;
     for (int k = 0; k < q.M; ++k) {
-        const int d_nxt = q.load(k + 1);
-        const ItemFields it = item_fields(a, d_cur);
-        d_cur = d_nxt;
-        if (it.row < 0) continue;
-        const int n_l = it.n_l, n_r = it.n - it.n_l;
+        const int d_nn = q.load(k + 2);
+        const ItemFields it = item_fields(a, d_cur), nx = item_fields(a, d_nxt);
+        d_cur = d_nxt; d_nxt = d_nn;
+        if (it.row < 0) { ids_ready = false; continue; }
+        const int n_l = it.n_l, n_r = it.n - it.n_l, n_pair = max(n_l, n_r);
+        if (!ids_ready) {
+            if (n_l > 0) load_run<GCN>(a, it.beg, min(ps, n_l), lane, id_l, w_l);
+            if (n_r > 0) load_run<GCN>(a, it.rbeg, min(ps, n_r), lane, id_r, w_r);
+        }
         if (it.slot < 0 && !a.no_self && a.phase != 2) load_self_row<K>(a, it.row, ln, xs);
         acc.clear();
-        const int lbeg = it.beg, rbeg = it.rbeg;
-        uint32_t id_l = 0, id_r = 0;
-        float w_l = 0.f, w_r = 0.f;
-        if (n_l > 0) load_run<GCN>(a, lbeg, min(ps, n_l), lane, id_l, w_l);
-        if (n_r > 0) load_run<GCN>(a, rbeg, min(ps, n_r), lane, id_r, w_r);
-        for (int pos = 0; pos < max(n_l, n_r); pos += ps) {
+        for (int pos = 0; pos < n_pair; pos += ps) {
+            // ids of the next pair -- of this item, or the first one of the next
+            const bool last = pos + ps >= n_pair;
+            const int at = last ? 0 : pos + ps, nl = (last ? (nx.n > 0 ? nx.n_l : 0) : n_l) - at, nr = (last ? (nx.n > 0 ? nx.n - nx.n_l : 0) : n_r) - at;
             uint32_t nid_l = 0, nid_r = 0;
             float nw_l = 0.f, nw_r = 0.f;
-            if (pos + ps < n_l) load_run<GCN>(a, lbeg + pos + ps, min(ps, n_l - pos - ps), lane, nid_l, nw_l);
-            if (pos + ps < n_r) load_run<GCN>(a, rbeg + pos + ps, min(ps, n_r - pos - ps), lane, nid_r, nw_r);
+            if (nl > 0) load_run<GCN>(a, (last ? nx.beg : it.beg) + at, min(ps, nl), lane, nid_l, nw_l);
+            if (nr > 0) load_run<GCN>(a, (last ? nx.rbeg : it.rbeg) + at, min(ps, nr), lane, nid_r, nw_r);
             const int len_l = min(ps, n_l - pos), len_r = min(ps, n_r - pos);
             // remote rows travel into LDS one batch ahead of their accumulation; the local partition
             // of the pair is gathered through registers while the first batch is in flight
             const int steps_r = len_r > 0 ? (len_r + K::NPW - 1) / K::NPW : 0;
-            if (steps_r > 0) stage_halo_batch<K>(stage[0], xh, id_r, ldb, len_r, 0, ln);
+            const uint32_t off_r = (id_r & 0x7fffffffu) * static_cast<uint32_t>(ldb);
+            if (steps_r > 0) stage_halo_batch<K>(stage[0], xh, off_r, len_r, 0, ln);
             if (len_l > 0) gather_run<K, GCN>(acc, id_l, w_l, len_l, xl, xh, ldb, ln);
             int buf = 0;
             for (int t0 = 0; t0 < steps_r; t0 += kStageSlots, buf ^= 1) {
                 if (t0 + kStageSlots < steps_r) {
-                    stage_halo_batch<K>(stage[buf ^ 1], xh, id_r, ldb, len_r, t0 + kStageSlots, ln);
+                    stage_halo_batch<K>(stage[buf ^ 1], xh, off_r, len_r, t0 + kStageSlots, ln);
                     wait_vmcnt<kStageSlots>();          // everything but the batch just requested has landed
                 } else {
                     wait_vmcnt<0>();
@@ -897,6 +904,7 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
             }
             id_l = nid_l; w_l = nw_l; id_r = nid_r; w_r = nw_r;
         }
+        ids_ready = n_pair > 0 && nx.n > 0;
         finish_item<K>(a, GCN, acc, xs, it.row, it.slot, ln);
     }
 }
@@ -912,7 +920,7 @@ hipError_t launch_cfg(const AggArgs &a, bool gcn, dim3 grid, int wpb, hipStream_
         }
     }
     if constexpr (K::CH == 1 && sizeof(typename K::raw) == 16) {
-        if (lds_halo && wpb <= kStageWpb) {
+        if (lds_halo) {
             const size_t lds = static_cast<size_t>(wpb) * 2 * kStageSlots * kWave * sizeof(uint4);     // 16 KB per wavefront
             if (gcn) hipLaunchKernelGGL((aggregate_lds_kernel<K, true>), grid, dim3(kWave * wpb), lds, stream, a);
             else hipLaunchKernelGGL((aggregate_lds_kernel<K, false>), grid, dim3(kWave * wpb), lds, stream, a);

@@ -153,3 +153,53 @@ def test_slabs_in_chunks():
     got = binding.mgg_aggregate(part, "gcn", x)
     part.set_option("col_slab_bytes", 256)
     assert torch.equal(got, binding.mgg_aggregate(part, "gcn", x))
+
+
+def _sums(ptr, col, own, x, mode, eps):
+    """Aggregate rows 0 .. own - 1 in float64, and the sums of the magnitudes."""
+    import scipy.sparse as sp
+    n = ptr.size - 1
+    adj = sp.csr_matrix((np.ones(col.size), col, ptr), shape=(n, n))[:own]
+    if mode == "gcn":
+        dinv = 1.0 / np.sqrt(np.diff(ptr) + 1.0)
+        adj, self_w = sp.diags(dinv[:own]) @ adj @ sp.diags(dinv), dinv[:own, None] ** 2
+    else:
+        self_w = 1.0 + eps
+    return adj @ x + self_w * x[:own], adj @ np.abs(x) + np.abs(self_w) * np.abs(x[:own])
+
+
+@pytest.mark.parametrize("lds", [0, 1])
+@pytest.mark.parametrize("wpb,per_wave,ps,dist,xcd_min_deg", [(1, 1, 0, 0, 0), (1, 3, 16, 2, 40), (2, 2, 7, 3, 0), (4, 1, 0, 0, 40), (4, 5, 0, 1, 0), (8, 2, 0, 0, 20), (16, 3, 5, 4, 0),
+                                                              (16, 1, 0, 0, 40)])
+@pytest.mark.parametrize("dim,bf16", [(12, False), (64, False), (100, False), (128, True)])
+def test_items_of_every_queue(dim, bf16, wpb, per_wave, ps, dist, xcd_min_deg, lds):
+    """One wavefront per item, several items one after the other, at every kind of workgroup: queues that end inside a
+    wavefront's items, rows without local or without remote neighbours, empty rows between them; halo rows through
+    registers and through LDS; both lists in one launch and in two."""
+    rng = np.random.default_rng(wpb * 100 + per_wave + dim)
+    n, own = 900, 500
+    lens = rng.integers(0, 90, n)
+    lens[::7] = 0
+    lens[rng.permutation(own)[:12]] = rng.integers(200, 700, 12)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    row = np.repeat(np.arange(n), lens)
+    col = rng.integers(0, n, ptr[-1])
+    col = np.where(row % 5 == 1, col % own, np.where(row % 5 == 2, own + col % (n - own), col))     # local only, remote only
+    col = np.where(col == row, (col + 1) % own, col).astype(np.int32)
+    x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
+    if bf16:
+        x = x.bfloat16()
+    xd = x.double().cpu().numpy()
+    part = binding.mgg_build_partition(ptr, col, 2, 0, np.array([0, own, n], dtype=np.int64), wpb=wpb, ps=ps, dist=dist, xcd_min_deg=xcd_min_deg, short_max=-1 if wpb == 1 else 0)
+    part.set_option("items_per_wave", per_wave)
+    part.set_option("lds_halo", lds)
+    plan = binding.mgg_aggregate_plan(part, "gcn", dim, bf16=bf16)
+    assert (plan.team, plan.wpb, plan.items_per_wave, plan.lds_halo) == (1, wpb, per_wave, int(lds and wpb <= 8))
+    halo = torch.from_numpy(part.export()["halo_gid"].astype(np.int64)).cuda()
+    for mode in ("gin", "gcn"):
+        want, scale = _sums(ptr, col, own, xd, mode, 0.25)
+        for two in (0, 1):
+            part.set_option("split_phases", two)
+            got = binding.mgg_aggregate(part, mode, x[:own].contiguous(), x[halo].contiguous(), eps=0.25).double().cpu().numpy()
+            # one rounding per term on the way, four for factors, self term and row factor, one where two launches meet
+            assert (np.abs(got - want) <= (lens[:own, None] + 6) * U * scale).all(), (mode, two)

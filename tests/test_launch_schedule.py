@@ -204,3 +204,28 @@ def test_a_given_number_of_wavefronts_is_kept(wpb):
     assert (plan.team, plan.wpb) == (1, wpb)
     part.set_option("items_per_wave", 2)
     assert binding.mgg_aggregate_plan(part, "gcn", 64).wpb == wpb
+
+
+def test_plan_of_halo_rows_through_lds():
+    """Staged rows are requested 8 KB at a time: pieces stay as large as the coarse schedule leaves them.  Tables it cannot
+    stage (rows off 16 bytes, 4 GB and more, no halo, workgroups beyond 8 wavefronts, several chunks a lane) take registers."""
+    ptr, col = _graph(1500, 330, 7, hubs=20)
+    kw = dict(host_only=True, hot_phases=-1, fine_min_neighbours=1)
+    part = binding.mgg_build_partition(ptr, col, 2, 0, **kw)
+    assert binding.mgg_aggregate_plan(part, "gcn", 64).fine == 1
+    part.set_option("lds_halo", 1)
+    plan = binding.mgg_aggregate_plan(part, "gcn", 64)
+    assert (plan.lds_halo, plan.fine, plan.team) == (1, 0, 1)
+    rows = max(int(part.info.n_local_rows), int(part.info.num_halo))
+    wide = -(-2 ** 32 // (4 * rows)) // 4 * 4 + 4
+    for dim, more in ((64, dict(base_align=8)), (63, dict(ld=63)), (64, dict(ld=wide))):
+        plan = binding.mgg_aggregate_plan(part, "gcn", dim, **more)
+        assert (plan.lds_halo, plan.fine) == (0, 1), more
+    assert binding.mgg_aggregate_plan(part, "gcn", 64, ld=wide - 8).lds_halo == 1
+    part.set_option("col_slab_bytes", 1)
+    assert [binding.mgg_aggregate_plan(part, "gcn", d).lds_halo for d in (256, 260)] == [1, 0]
+    alone = binding.mgg_build_partition(ptr, col, **kw)
+    many = binding.mgg_build_partition(ptr, col, 2, 0, wpb=16, **kw)
+    for p in (alone, many):
+        p.set_option("lds_halo", 1)
+        assert binding.mgg_aggregate_plan(p, "gcn", 64).lds_halo == 0
