@@ -334,7 +334,7 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
         // flat elsewhere)
         pl.short_per_wave = pick(p->opt_short_per_wave, (short_groups + wpb - 1) / wpb, 1);
     }
-    pl.n_item_blocks = team ? pl.n_items : static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * pl.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * pl.items_per_wave) * kXcd);
+    pl.n_item_blocks = team ? team_blocks(pl.n_items) : static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * pl.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * pl.items_per_wave) * kXcd);
     const int64_t short_waves = (short_groups + pl.short_per_wave - 1) / pl.short_per_wave;
     pl.grid_x = pl.n_item_blocks + static_cast<int>((short_waves + wpb - 1) / wpb);
     if (n_slabs > 1) pl.grid_x = (pl.grid_x + kXcd - 1) / kXcd * kXcd;   // keeps workgroup x on XCD x mod 8 in every slab

@@ -735,7 +735,10 @@ __global__ __launch_bounds__(kWave * kMaxWpb) __attribute__((amdgpu_waves_per_eu
 // Launches with too few items to fill the chip: all wavefronts of a workgroup take one item together, a share of its
 // neighbours each, and the first one adds up what the others leave in LDS, in a fixed order.  What such a launch costs is
 // the chain of loads behind its longest item (466 rows of up to 255 neighbours, 210 fp32 columns: 11.4 -> 4.8 us; 1,592
-// rows, 192 columns: 16.7 -> 9.6 us with the fix-up; 2,125 rows, 139 bf16 columns: 12.1 -> 10.4).
+// rows, 192 columns: 16.7 -> 9.6 us with the fix-up; 2,125 rows, 139 bf16 columns: 12.1 -> 10.4).  The items of an XCD's queue
+// stay on it (team_item): with item b on workgroup b half of the gathers of a regrouped row came out of another XCD's class (60 rows
+// of 20,000 over 200 k rows of 64 columns 66.9 -> 51.6 us, of 128 columns 129.6 -> 108.7; 120 of 3,000 over 60 k rows of 256 columns
+// 56.9 -> 46.2).
 template <class K, bool GCN>
 __global__ __launch_bounds__(kWave * kMaxTeam) void aggregate_team_kernel(const AggArgs a)
 {
@@ -752,8 +755,10 @@ __global__ __launch_bounds__(kWave * kMaxTeam) void aggregate_team_kernel(const 
         short_rows<K, GCN>(a, wave, team, lane, ln, xl, xh, ldb);
         return;
     }
-    const ItemFields it = item_fields(a, reinterpret_cast<const int32_t *>(a.items)[static_cast<int64_t>(ln.block) * 8 + (lane & 7)]);
-    if (it.row < 0) return;                                  // padding: the whole workgroup leaves
+    const int item = team_item(ln.block);
+    if (item >= a.n_items) return;                           // a queue that ends early, padding: the whole workgroup leaves
+    const ItemFields it = item_fields(a, reinterpret_cast<const int32_t *>(a.items)[static_cast<int64_t>(item) * 8 + (lane & 7)]);
+    if (it.row < 0) return;
     const int ps = a.ps;
     const int share = (it.n + team * K::NPW - 1) / (team * K::NPW) * K::NPW;
     const int end = min(it.n, (wave + 1) * share);

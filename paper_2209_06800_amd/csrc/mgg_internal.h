@@ -45,6 +45,12 @@ struct SplitRow {
 constexpr int kXcd = 8;             // accelerator complex dies of an MI355X, each with its own L2
 constexpr int kDefaultWpb = 2;      // work items (wavefronts) per workgroup of the aggregation kernel
 constexpr int kDefaultXcdMinDeg = 256;
+
+// Item of workgroup b where a workgroup takes one item: items lie in groups of kDefaultWpb per XCD queue (the only group
+// size there are teams for), and workgroup b runs on XCD b mod kXcd, so that queue x stays on XCD x.
+constexpr int team_item(int b) { return ((b / kXcd / kDefaultWpb) * kXcd + b % kXcd) * kDefaultWpb + b / kXcd % kDefaultWpb; }
+static_assert(team_item(0) == 0 && team_item(1) == 2 && team_item(kXcd) == 1 && team_item(kXcd + 7) == 15 && team_item(2 * kXcd) == 16, "items 0, 1, 16, 17 are queue 0");
+constexpr int team_blocks(int n_items) { return (n_items + kXcd * kDefaultWpb - 1) / (kXcd * kDefaultWpb) * (kXcd * kDefaultWpb); }
 constexpr int kFineXcdMinDeg = 128;         // rows regrouped in the fine schedule too
 constexpr int64_t kFineMinNeighbours = 8 << 20;   // shares of fewer neighbours have none
 constexpr int kDefaultHotPhases = 0;        // automatic choice between hash classes and popularity phases

@@ -203,3 +203,25 @@ def test_items_of_every_queue(dim, bf16, wpb, per_wave, ps, dist, xcd_min_deg, l
             got = binding.mgg_aggregate(part, mode, x[:own].contiguous(), x[halo].contiguous(), eps=0.25).double().cpu().numpy()
             # one rounding per term on the way, four for factors, self term and row factor, one where two launches meet
             assert (np.abs(got - want) <= (lens[:own, None] + 6) * U * scale).all(), (mode, two)
+
+
+@pytest.mark.parametrize("classes", [False, True])
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 15, 16, 17, 31, 33, 100])
+def test_teams_take_every_item_of_every_queue(rows, classes):
+    """One workgroup per item, queue by queue: lists that end inside a group of a queue, padded lists of regrouped rows, slabs."""
+    rng = np.random.default_rng(rows)
+    n = 2000
+    lens = np.zeros(n, dtype=np.int64)
+    lens[rng.permutation(n)[:rows]] = rng.integers(300, 900, rows)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    row = np.repeat(np.arange(n), lens)
+    col = rng.integers(0, n - 1, ptr[-1])
+    col = (col + (col >= row)).astype(np.int32)
+    part = binding.mgg_build_partition(ptr, col, xcd_min_deg=0 if classes else -1, hot_phases=-1)
+    for dim in (64, 300):
+        x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
+        assert binding.mgg_aggregate_plan(part, "gcn", dim).team > 1
+        want, scale = _sums(ptr, col, n, x.double().cpu().numpy(), "gcn", 0)
+        out = torch.full((n, dim), float("nan"), device="cuda")
+        got = binding.mgg_aggregate(part, "gcn", x, out=out).double().cpu().numpy()
+        assert (np.abs(got - want) <= (lens[:, None] + 6) * U * scale).all()
