@@ -315,18 +315,26 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
     // wavefront amortises its start-up latencies; fewer leaves more workgroups for the hardware to
     // balance.  Automatic: 2 where the launch still has about 8192 workgroups (measured on MI355X: 0.3-2.5 %
     // faster than 1 and than 8 on every workload tried), else 1.
-    // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel).  The chip holds some 5000
-    // wavefronts of these kernels, and a team is worth its barrier and its additions while its members have a batch
-    // of loads each and find a place at once: 8 or 4 to an item up to 4096 wavefronts in all (6480 rows, 11.0 us with
-    // and without; 370 rows of 115, 8.7 us at 2700 wavefronts and 10.2 at 5400), 2 up to 8192 (4389 rows, 12.0 ->
-    // 10.6 us at 6800).  A caller who says how many wavefronts a workgroup or how many items a wavefront takes gets just that.
+    // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel), 8 or 4 to an item up to 4096
+    // wavefronts in all, 2 up to 8192, where the chain of loads behind the longest item is what the launch waits for: each
+    // member of its team has a batch of 8 loads at least, and not less than the launch's loads come to on each of the 5120
+    // wavefronts that are resident (1.5 times that for teams of 4, 3 times for 8; an item or a group of short rows counts as a
+    // batch more).  Without that second half, launches that other rows keep busy or whose items are all short were up to 28 %
+    // slower with a team than without (3,100 rows of 22 neighbours at 128 columns; 300 rows of 2,000 beside 100,000 short ones at
+    // 128 columns: 96 us, 85 without).  Over 632 launches, four team sizes each, the rule is 1.4 % off the best on average, no team
+    // 6.6 %, the rule without the second half 3.8 %.  A caller who says how many wavefronts a workgroup or how many items a
+    // wavefront takes gets just that.
     bool team = false;
     int wpb = p->wpb;
-    if (ch == 1 && !lds && p->opt_items_per_wave == 0 && !p->wpb_given)
+    const int npw = 64 / lpr;
+    const int64_t short_groups = (n_short + npw - 1) / npw;
+    if (ch == 1 && !lds && p->opt_items_per_wave == 0 && !p->wpb_given) {
+        const int64_t nnz = static_cast<int64_t>(p->local_col.size()) + static_cast<int64_t>(p->remote_col.size());
+        const int64_t item_waves = p->n_work_items * n_slabs, loads = (nnz / npw + 8 * (short_groups + p->n_work_items)) * n_slabs;
         for (int t = kMaxTeam; t >= 2 && !team; t /= 2)
-            if (p->n_work_items * n_slabs * t <= (t == 2 ? 8192 : 4096) && p->longest_item >= t * 8 * (64 / lpr)) { team = true; wpb = t; }
+            if (item_waves * t <= (t == 2 ? 8192 : 4096) && p->longest_item / (t * npw) >= std::max<int64_t>(8, (t == 2 ? 2 : t == 4 ? 3 : 6) * loads / (2 * 5120))) { team = true; wpb = t; }
+    }
     const int64_t n_groups = team ? pl.n_items : (pl.n_items + wpb - 1) / wpb;
-    const int64_t short_groups = (n_short + 64 / lpr - 1) / (64 / lpr);
     {
         auto pick = [&](int32_t opt, int64_t units, int64_t most) { return static_cast<int32_t>(opt > 0 ? opt : std::min<int64_t>(most, std::max<int64_t>(1, units * n_slabs / 8192))); };
         pl.items_per_wave = team ? 1 : pick(p->opt_items_per_wave, n_groups, 2);

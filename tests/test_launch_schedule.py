@@ -229,3 +229,17 @@ def test_plan_of_halo_rows_through_lds():
     for p in (alone, many):
         p.set_option("lds_halo", 1)
         assert binding.mgg_aggregate_plan(p, "gcn", 64).lds_halo == 0
+
+
+@pytest.mark.parametrize("lens,short,dim,bf16,team", [
+    ((150, 255, 64), 0, 128, False, 8), ((150, 255, 64), 10000, 128, False, 4), ((150, 255, 64), 100000, 128, False, 1),    # short rows keep the chip busy
+    ((1500, 2500, 300), 2000, 128, False, 2), ((1500, 2500, 300), 100000, 128, False, 1),
+    ((17, 31, 2000), 0, 256, True, 1), ((60, 75, 3000), 0, 64, False, 1),                                                # every item is short
+    ((60, 120, 300), 0, 64, False, 2), ((60, 120, 5000), 0, 64, False, 1), ((400, 511, 900), 0, 64, False, 2)])
+def test_teams_are_for_launches_that_wait_for_their_longest_item(lens, short, dim, bf16, team):
+    """The rule counts all the loads of a launch, those of its short rows too, against the chain behind the longest item."""
+    rng = np.random.default_rng(1)
+    lo, hi, rows = lens
+    ptr, col = _lists(np.concatenate([rng.integers(lo, hi + 1, rows), rng.integers(1, 14, short)]), 4000)
+    part = binding.mgg_build_partition(ptr, col, host_only=True, xcd_min_deg=-1)
+    assert binding.mgg_aggregate_plan(part, "gcn", dim, bf16=bf16).team == team
