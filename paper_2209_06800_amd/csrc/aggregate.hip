@@ -277,12 +277,16 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
             // once per slab, from HBM if it does not stay in the Infinity Cache (bare gathers out of L2: 28.8 TB/s with ids
             // from there, 22.4 from HBM).  Chunks of the work then go through all slabs one after the other, their ids some
             // 36 MB (120 k rows of 1 KB, 46 M neighbours: 2.70 ms with 512-byte slabs, 2.57 so, 2.83 with 256-byte slabs in
-            // one chunk; of 2 KB 5.36 -> 5.21).  Rows off line boundaries pay a line more per slab: 512 (1200-byte rows: 4.14
-            // against 4.17 ms).
+            // one chunk; of 2 KB 5.36 -> 5.21; from 16 k rows on also where 512-byte slabs fit: 60 k rows of 1 KB, 25 M neighbours,
+            // 1.75 with 512, 1.56 so, 30 k 1.07 and 1.02).  Rows off line boundaries pay a line more per slab: 512 (1200-byte rows:
+            // 4.14 against 4.17 ms).  So do small classes whose ids and factors stay in the Infinity Cache from slab to slab in any
+            // case (8 k rows, 17.4 M neighbours: 0.578 ms with 512, 0.619 so; 12 k, 17.7 M: 0.637, 0.667; but 16 k, 21 M: 0.886,
+            // 0.848, and 8 k, 40 M, 319 MB: 1.67, 1.57; sums, 4 bytes a neighbour: 12 k, 55 M 2.11, 1.96).
             const int64_t id_bytes = (static_cast<int64_t>(p->local_col.size()) + static_cast<int64_t>(p->remote_col.size())) * (mode == MGG_AGG_GCN_SYM ? 8 : 4);
             const bool on_lines = ld_x * static_cast<int64_t>(esz) % 128 == 0 && bases % 128 == 0;
             if (static_cast<int64_t>(dim) * static_cast<int64_t>(esz) >= 1024) {
-                if (class_rows * 256 <= (4 << 20) && id_bytes >= (static_cast<int64_t>(128) << 20) && on_lines) {
+                const bool ids_stay = mode == MGG_AGG_GCN_SYM && class_rows * 512 <= (800 << 10) && id_bytes <= (static_cast<int64_t>(256) << 20);
+                if (class_rows * 256 <= (4 << 20) && id_bytes >= (static_cast<int64_t>(128) << 20) && on_lines && !ids_stay) {
                     slab_bytes = 256;
                     n_chunks = (id_bytes + (36 << 20) - 1) / (36 << 20);
                 } else if (class_rows * 512 > (8 << 20) && class_rows * 256 <= (8 << 20)) slab_bytes = 256;

@@ -243,3 +243,20 @@ def test_teams_are_for_launches_that_wait_for_their_longest_item(lens, short, di
     ptr, col = _lists(np.concatenate([rng.integers(lo, hi + 1, rows), rng.integers(1, 14, short)]), 4000)
     part = binding.mgg_build_partition(ptr, col, host_only=True, xcd_min_deg=-1)
     assert binding.mgg_aggregate_plan(part, "gcn", dim, bf16=bf16).team == team
+
+
+def test_chunked_slabs_by_table_and_ids():
+    """256-byte slabs, chunk by chunk, where a class of them fits one L2 and the ids are more than 128 MB; not on rows off line
+    boundaries, nor where the table is small and the ids stay in the Infinity Cache in any case."""
+    nnz = 17 << 20
+    for rows, gcn_slab in ((12000, 512), (16000, 256)):
+        lens = np.full(rows, nnz // rows + 1)
+        ptr, col = _lists(lens, rows)
+        part = binding.mgg_build_partition(ptr, col, host_only=True)
+        plan = lambda mode, dim, **kw: binding.mgg_aggregate_plan(part, mode, dim, **kw)
+        gcn = plan("gcn", 256)
+        assert (gcn.slab_bytes, gcn.n_slabs) == (gcn_slab, 1024 // gcn_slab) and (gcn.n_chunks > 1) == (gcn_slab == 256)
+        assert gcn.n_chunks == (1 if gcn_slab == 512 else -(-int(ptr[-1]) * 8 // (36 << 20)))
+        for other in (plan("gin", 256), plan("gcn", 256, ld=257), plan("gcn", 256, base_align=64), plan("gcn", 300)):      # half the ids; off lines
+            assert (other.slab_bytes, other.n_chunks) == (512, 1)
+        assert plan("gcn", 128).n_slabs == 1
