@@ -112,6 +112,7 @@ struct mgg_partition {
     int64_t n_fine_sums = 0;
     int64_t n_work_items = 0;         // items without the padding of the XCD queues
     int32_t longest_item = 0;         // neighbours of the longest one
+    int64_t n_classed = 0;            // neighbours in rows that are cut by source class
     // run-time switches of this partition's aggregations: the process-wide defaults at build time, then mgg_partition_set_option
     int32_t opt_lds_halo = 0, opt_col_slab_bytes = 0, opt_split_phases = 0, opt_items_per_wave = 0, opt_short_per_wave = 0;
     int32_t reserved_dim = 0;         // widest aggregation the partition's own scratch buffer was sized for

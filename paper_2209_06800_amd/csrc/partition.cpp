@@ -418,6 +418,7 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
         if (use_classes && n_hot > 0 && dl + dr >= xcd_min_deg) {
             cut_by_class(l0, l1, r0, r1);
             first_piece = 0;
+            p->n_classed += dl + dr;
         } else {
             lcut[n_hot] = l0; lcut[n_hot + 1] = l1; rcut[n_hot] = r0; rcut[n_hot + 1] = r1;
         }

@@ -177,17 +177,21 @@ def test_plan_lanes_of_a_row(dim, ld, bf16, align, lanes, per_lane):
     assert plan.n_slabs == -(-dim * (2 if bf16 else 4) // plan.slab_bytes)
 
 
-@pytest.mark.parametrize("bags,table,slab_bytes", [(200000, 4000, 512), (1000, 200000, 256), (1000, 4000, 512), (200000, 200000, 256)])
-def test_slabs_go_by_the_rows_of_the_tables(bags, table, slab_bytes):
-    """What has to stay in L2 is the table, whose rows a bag partition does not own: 256-byte slabs where an eighth of the
-    200,000 rows fits twice the L2 at 256 bytes and not at 512 (25,000 rows), however many bags there are."""
+@pytest.mark.parametrize("bags,per,table,slab_bytes", [(200000, 1, 8000, 512), (200000, 1, 8400, 256), (1000, 30, 200000, 256), (1000, 1, 4000, 512), (1000, 1, 1 << 20, 256),
+                                                       (150000, 1, 1100000, 512), (100, 2000, 60000, 512), (100, 2000, 140000, 256), (100, 2000, 300000, 512)])
+def test_slabs_go_by_the_rows_of_the_tables(bags, per, table, slab_bytes):
+    """What has to stay in L2 is the tables, not the bags that a bag partition owns: the whole of them for short bags, which
+    have no source classes, an eighth for long ones."""
     rng = np.random.default_rng(3)
-    ptr = np.arange(bags + 1, dtype=np.int64)
-    idx = rng.integers(0, table, bags).astype(np.int32)
-    for lo, hi in ((0, table), (0, table // 2)):                                # all rows local; half of them in the halo table
-        part = binding.mgg_build_bags(ptr, idx, table, lo, hi, host_only=True)
+    ptr = np.arange(bags + 1, dtype=np.int64) * per
+    idx = rng.integers(0, table, bags * per).astype(np.int32)
+    for lo, hi in ((0, table), (0, table // 2)):                                # all rows local; half of them served from the halo table
+        part = binding.mgg_build_bags(ptr, idx, table, lo, hi, host_only=True, hot_phases=-1)
         rows = int(part.info.n_local_rows + part.info.num_halo)
-        want = 256 if rows // 8 * 512 > 8 << 20 and rows // 8 * 256 <= 8 << 20 else 512
+        if per <= 32:
+            want = 256 if rows * 512 > 4 << 20 and rows * 256 <= 256 << 20 else 512
+        else:
+            want = 256 if (rows // 8 + 1) * 512 > 8 << 20 and (rows // 8 + 1) * 256 <= 8 << 20 else 512
         assert want == slab_bytes or rows < table
         assert binding.mgg_aggregate_plan(part, "gin", 256).slab_bytes == want, (lo, hi)
 
