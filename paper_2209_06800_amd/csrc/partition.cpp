@@ -2,6 +2,7 @@
 // integer structures, upload to HBM.  All integer work; the only floating-point values made
 // here are the per-node factors 1/sqrt(deg+1) of the GCN normalisation.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -45,11 +46,12 @@ static mgg_status_t upload(const T *h, size_t n, T **d)
 template <typename T>
 static mgg_status_t upload(const std::vector<T> &h, T **d) { return upload(h.data(), h.size(), d); }
 
-// body(begin, end) over [0, n) on up to 8 threads; on this one alone when `work` is little or no thread can be had
+// body(begin, end) over [0, n) on up to 8 threads, each with 2^17 of `work` (neighbours: some 200 us) at least, so that
+// starting them stays small beside it; on this one alone where no thread can be had
 template <typename F>
 static void parallel_for(size_t n, size_t work, const F &body)
 {
-    const size_t n_threads = work < (1 << 17) ? 1 : std::max<size_t>(1, std::min<size_t>({8, n, std::thread::hardware_concurrency()}));
+    const size_t n_threads = work >> 17 < 2 ? 1 : std::max<size_t>(1, std::min<size_t>({8, n, work >> 17, std::thread::hardware_concurrency()}));
     std::vector<std::thread> threads;
     size_t done = 0;
     try {
@@ -117,13 +119,11 @@ static DeviceLayout lay_out_device(const mgg_partition *p)
         at += nl + nr;
     }
     // the lists themselves are independent of each other: several threads where there is enough to copy
-    parallel_for(items.size(), nnz, [&](size_t b, size_t e) {
-        for (size_t i = b; i < e; ++i) put(items[i].beg, p->items[i].lbeg, p->items[i].lend, p->items[i].rbeg, p->items[i].rend);
-    });
-    parallel_for(sd.size(), nnz, [&](size_t b, size_t e) {
-        for (size_t i = b; i < e; ++i) {
-            const int32_t v = sd[i].x;
-            put(sd[i].y, p->local_row_ptr[v], p->local_row_ptr[v + 1], p->remote_row_ptr[v], p->remote_row_ptr[v + 1]);
+    parallel_for(items.size() + sd.size(), nnz, [&](size_t b, size_t e) {
+        for (size_t i = b; i < std::min(e, items.size()); ++i) put(items[i].beg, p->items[i].lbeg, p->items[i].lend, p->items[i].rbeg, p->items[i].rend);
+        for (size_t i = std::max(b, items.size()); i < e; ++i) {
+            const int4 &d = sd[i - items.size()];
+            put(d.y, p->local_row_ptr[d.x], p->local_row_ptr[d.x + 1], p->remote_row_ptr[d.x], p->remote_row_ptr[d.x + 1]);
         }
     });
     l.split_rows = p->split_rows;
@@ -529,10 +529,18 @@ mgg_status_t mgg_build_partition(int64_t num_nodes, const int64_t *row_ptr, cons
         if (row_ptr[v + 1] < row_ptr[v]) return fail(MGG_ERR_BAD_GRAPH, "row_ptr decreases at row %lld", (long long)v);
     const int64_t nnz = row_ptr[num_nodes];
     if (nnz > 0 && !col_idx) return fail(MGG_ERR_INVALID_ARG, "col_idx is NULL");
-    for (int64_t e = 0; e < nnz; ++e)
-        if (col_idx[e] < 0 || col_idx[e] >= num_nodes)
-            return fail(MGG_ERR_BAD_GRAPH, "column %d at position %lld outside [0, %lld)", col_idx[e],
-                        (long long)e, (long long)num_nodes);
+    std::atomic<int64_t> first_bad{nnz};
+    parallel_for(static_cast<size_t>(nnz), static_cast<size_t>(nnz), [&](size_t b, size_t e) {
+        for (size_t i = b; i < e; ++i)
+            if (col_idx[i] < 0 || col_idx[i] >= num_nodes) {
+                int64_t seen = first_bad;
+                while (static_cast<int64_t>(i) < seen && !first_bad.compare_exchange_weak(seen, static_cast<int64_t>(i))) {}
+                return;
+            }
+    });
+    if (first_bad < nnz)
+        return fail(MGG_ERR_BAD_GRAPH, "column %d at position %lld outside [0, %lld)", col_idx[first_bad],
+                    (long long)first_bad, (long long)num_nodes);
 
     // ---- node range --------------------------------------------------------------------
     std::vector<int64_t> bnd(num_parts + 1);
@@ -560,17 +568,27 @@ mgg_status_t mgg_build_partition(int64_t num_nodes, const int64_t *row_ptr, cons
         std::vector<uint8_t> is_halo(static_cast<size_t>(num_nodes), 0);
         p->local_row_ptr.assign(n_own + 1, 0);
         p->remote_row_ptr.assign(n_own + 1, 0);
-        for (int64_t v = 0; v < n_own; ++v) {
-            const int64_t g = lb + v;
-            int32_t nl = 0, nr = 0;
-            for (int64_t e = row_ptr[g]; e < row_ptr[g + 1]; ++e) {
-                const int64_t u = col_idx[e];
-                if (u == g) continue;                       // self term comes from the mode
-                if (u >= lb && u < ub) ++nl;
-                else { ++nr; is_halo[u] = 1; }
+        const size_t own_work = static_cast<size_t>(row_ptr[ub] - row_ptr[lb]);
+        parallel_for(static_cast<size_t>(n_own), own_work, [&](size_t b, size_t e) {
+            for (size_t v = b; v < e; ++v) {
+                const int64_t g = lb + static_cast<int64_t>(v);
+                int32_t nl = 0, nr = 0;
+                for (int64_t i = row_ptr[g]; i < row_ptr[g + 1]; ++i) {
+                    const int64_t u = col_idx[i];
+                    if (u == g) continue;                       // self term comes from the mode
+                    if (u >= lb && u < ub) ++nl;
+                    else {                                      // (written once: hubs are everybody's neighbours)
+                        ++nr;
+                        if (!__atomic_load_n(&is_halo[u], __ATOMIC_RELAXED)) __atomic_store_n(&is_halo[u], uint8_t{1}, __ATOMIC_RELAXED);
+                    }
+                }
+                p->local_row_ptr[v + 1] = nl;
+                p->remote_row_ptr[v + 1] = nr;
             }
-            p->local_row_ptr[v + 1] = p->local_row_ptr[v] + nl;
-            p->remote_row_ptr[v + 1] = p->remote_row_ptr[v] + nr;
+        });
+        for (int64_t v = 0; v < n_own; ++v) {
+            p->local_row_ptr[v + 1] += p->local_row_ptr[v];
+            p->remote_row_ptr[v + 1] += p->remote_row_ptr[v];
         }
         // ---- halo list in ascending global id and the id -> slot map ---------------------
         std::vector<int32_t> slot_of(static_cast<size_t>(num_nodes), -1);
@@ -586,16 +604,18 @@ mgg_status_t mgg_build_partition(int64_t num_nodes, const int64_t *row_ptr, cons
         // ---- pass 2: fill the two column arrays -----------------------------------------
         p->local_col.resize(p->local_row_ptr[n_own]);
         p->remote_col.resize(p->remote_row_ptr[n_own]);
-        for (int64_t v = 0; v < n_own; ++v) {
-            const int64_t g = lb + v;
-            int32_t wl = p->local_row_ptr[v], wr = p->remote_row_ptr[v];
-            for (int64_t e = row_ptr[g]; e < row_ptr[g + 1]; ++e) {
-                const int64_t u = col_idx[e];
-                if (u == g) continue;
-                if (u >= lb && u < ub) p->local_col[wl++] = static_cast<int32_t>(u - lb);
-                else p->remote_col[wr++] = slot_of[u];
+        parallel_for(static_cast<size_t>(n_own), own_work, [&](size_t b, size_t e) {
+            for (size_t v = b; v < e; ++v) {
+                const int64_t g = lb + static_cast<int64_t>(v);
+                int32_t wl = p->local_row_ptr[v], wr = p->remote_row_ptr[v];
+                for (int64_t i = row_ptr[g]; i < row_ptr[g + 1]; ++i) {
+                    const int64_t u = col_idx[i];
+                    if (u == g) continue;
+                    if (u >= lb && u < ub) p->local_col[wl++] = static_cast<int32_t>(u - lb);
+                    else p->remote_col[wr++] = slot_of[u];
+                }
             }
-        }
+        });
         slot_of.clear(); slot_of.shrink_to_fit();
 
         // ---- whole-graph degrees and 1/sqrt(deg+1) ---------------------------------------
@@ -605,12 +625,10 @@ mgg_status_t mgg_build_partition(int64_t num_nodes, const int64_t *row_ptr, cons
             return d;
         };
         p->deg_own.resize(n_own); p->dinv_own.resize(n_own);
-        parallel_for(static_cast<size_t>(n_own), static_cast<size_t>(nnz), [&](size_t b, size_t e) {
-            for (size_t v = b; v < e; ++v) {
-                p->deg_own[v] = degree_of(lb + static_cast<int64_t>(v));
-                p->dinv_own[v] = static_cast<float>(1.0 / std::sqrt(static_cast<double>(p->deg_own[v]) + 1.0));
-            }
-        });
+        for (int64_t v = 0; v < n_own; ++v) {                // (what the two lists hold: self-loops are in neither)
+            p->deg_own[v] = p->local_row_ptr[v + 1] - p->local_row_ptr[v] + p->remote_row_ptr[v + 1] - p->remote_row_ptr[v];
+            p->dinv_own[v] = static_cast<float>(1.0 / std::sqrt(static_cast<double>(p->deg_own[v]) + 1.0));
+        }
         p->deg_halo.resize(num_halo); p->dinv_halo.resize(num_halo);
         parallel_for(static_cast<size_t>(num_halo), static_cast<size_t>(nnz), [&](size_t b, size_t e) {
             for (size_t h = b; h < e; ++h) {

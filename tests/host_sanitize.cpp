@@ -204,7 +204,7 @@ int main()
     }
     // ---- the default cuts with the fine schedule, laid out by several threads -------------------
     for (int trial = 0; trial < 3; ++trial) {
-        const Graph g = random_graph(rng, 1500);
+        const Graph g = random_graph(rng, 2600);
         const int32_t parts = 1 + trial;
         std::vector<int64_t> bounds(parts + 1);
         for (int32_t q = 0; q <= parts; ++q) bounds[q] = g.n * q / parts;

@@ -68,8 +68,8 @@ def _check_cover(part, e, l, items, which):
 
 @pytest.mark.parametrize("parts,part_id,wpb,seed,bags", [(1, 0, 0, 1, False), (2, 0, 1, 2, False), (3, 1, 4, 3, False), (2, 1, 16, 4, False), (1, 0, 2, 5, True)])
 def test_launch_arrays_hold_every_neighbour_once(parts, part_id, wpb, seed, bags):
-    n = 1500
-    ptr, col = _graph(n, 330, seed, hubs=20)
+    n = 2400
+    ptr, col = _graph(n, 330, seed, hubs=30)
     kw = dict(host_only=True, wpb=wpb, hot_phases=-1, fine_min_neighbours=1)
     if bags:
         part = binding.mgg_build_bags(ptr, col, n, 200, 900, **kw)
@@ -77,7 +77,7 @@ def test_launch_arrays_hold_every_neighbour_once(parts, part_id, wpb, seed, bags
         part = binding.mgg_build_partition(ptr, col, parts, part_id, **kw)
     info, e, l = part.info, part.export(), part.export_launch()
     assert info.n_fine_items > 0 and info.n_fine_split_items > 0 and info.n_short_rows > 0
-    assert int(info.nnz_local + info.nnz_remote) >= 1 << 17 or parts > 1       # laid out by several threads, too
+    assert int(info.nnz_local + info.nnz_remote) >= 1 << 18 or parts > 1       # laid out by several threads, too
     assert info.n_fine_split_items <= 2 * info.n_split_items
     _, _ = _check_cover(part, e, l, l["launch_items"], "coarse")
     it, _ = _check_cover(part, e, l, l["launch_fine_items"], "fine")
@@ -264,3 +264,28 @@ def test_chunked_slabs_by_table_and_ids():
         for other in (plan("gin", 256), plan("gcn", 256, ld=257), plan("gcn", 256, base_align=64), plan("gcn", 300)):      # half the ids; off lines
             assert (other.slab_bytes, other.n_chunks) == (512, 1)
         assert plan("gcn", 128).n_slabs == 1
+
+
+@pytest.mark.parametrize("parts,part_id", [(1, 0), (3, 1)])
+def test_large_partition_bit_exact_against_oracle(parts, part_id):
+    """Counted, filled and laid out by several threads: hubs, empty rows, duplicates and self-loops."""
+    import oracle
+    rng = np.random.default_rng(5)
+    n = 6000
+    lens = rng.integers(0, 200, n)
+    lens[rng.permutation(n)[:60]] = rng.integers(2000, 9000, 60)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = (rng.random(ptr[-1]) ** 2 * n).astype(np.int32)
+    assert ptr[-1] >= 6 << 17
+    bounds = np.linspace(0, n, parts + 1).astype(np.int64)
+    want = oracle.build_partition(ptr, col, parts, part_id, bounds)
+    got = binding.mgg_build_partition(ptr, col, parts, part_id, bounds, host_only=True).export()
+    for key in ("local_row_ptr", "local_col", "remote_row_ptr", "remote_col", "halo_gid", "halo_peer_ptr", "deg_own", "deg_halo"):
+        assert np.array_equal(got[key].astype(np.int64), want[key].astype(np.int64)), key
+    for bad in ([123456], [900000 - 1, 7, 654321], [int(ptr[-1]) - 1]):         # the first one is named, whichever thread meets it
+        wrong = col.copy()
+        bad = [b % int(ptr[-1]) for b in bad]
+        wrong[bad] = [n + i for i in range(len(bad))]
+        with pytest.raises(binding.MggError, match=f"column {wrong[min(bad)]} at position {min(bad)} ") as err:
+            binding.mgg_build_partition(ptr, wrong, parts, part_id, bounds, host_only=True)
+        assert err.value.status == binding.ERR_BAD_GRAPH
