@@ -177,8 +177,9 @@ mgg_status_t mgg_partition_info(const mgg_partition_t *p, mgg_partition_info_t *
  * columns wide.  Rows with many neighbours are cut into several wavefront work items (section
  * 4.1 Step-3: neighbour partitions; section 5.1: a wavefront takes a few of them), whose partial
  * sums pass through this buffer: mgg_aggregate_scratch_bytes(p, dim) bytes, nothing when no row
- * is cut (up to three times that where there is room: a schedule with more and smaller pieces, taken for large
- * shares).  Host, synchronous (it may wait for the device and allocate); never shrinks.  The
+ * is cut.  For a share with a fine schedule it allocates room for that one's, too (up to three times
+ * the bytes), and does with the coarse schedule's where that cannot be had.  Host, synchronous (it may
+ * wait for the device and allocate); never shrinks.  The
  * device calls below allocate nothing: mgg_aggregate / mgg_aggregate_to / mgg_bag_sum /
  * mgg_time_aggregate on a width that was not reserved fail with MGG_ERR_INVALID_ARG.
  * mgg_layer_forward does not use this buffer (its workspace holds the partial sums).
@@ -234,9 +235,10 @@ mgg_status_t mgg_aggregate_plan(const mgg_partition_t *p, mgg_agg_t mode, mgg_dt
 
 /* mgg_aggregate for callers that cannot allocate and hold no reserved partition: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and result as
- * mgg_aggregate (up to the order of the sums where that has room for a schedule with more pieces); the partial sums of cut rows go to a fixed 64 MiB array inside the library's device
- * code (one copy per GPU, held until the process ends) instead of the partition's buffer, so the call
- * allocates nothing whatever was or was not reserved.  A partition whose partial sums at this width
+ * mgg_aggregate, bit for bit unless the partition has a fine schedule whose partial sums only one of
+ * the two has room for; the partial sums of cut rows go to a fixed 64 MiB array inside the library's
+ * device code (one copy per GPU, held until the process ends) instead of the partition's buffer, so the
+ * call allocates nothing whatever was or was not reserved.  A partition whose partial sums at this width
  * (mgg_aggregate_scratch_bytes) exceed 64 MiB is refused with MGG_ERR_UNSUPPORTED.  The first call on
  * a device looks up the array's address (not capturable); every call on a GPU shares that GPU's array,
  * so calls that may overlap on one GPU -- two streams, two threads, two partitions -- race: order them
@@ -338,15 +340,21 @@ typedef struct {
 
 /* Bytes of DEVICE workspace mgg_layer_forward needs (aggregation result, the partial sums of rows
  * cut into several work items and, for two linears, the hidden activations; with UPDATE_FIRST the
- * transformed local and halo tables).
- * Returns 0 on bad arguments. */
+ * transformed local and halo tables).  _bytes: what it has a use for; _least_bytes: what it can do
+ * with, the same but for shares with a fine schedule (n_fine_split_items of mgg_partition_info), whose
+ * partial sums are up to three times as many as those of the coarse one.  Return 0 on bad arguments. */
 size_t mgg_layer_workspace_bytes(const mgg_partition_t *p, const mgg_layer_desc_t *layer);
+size_t mgg_layer_workspace_least_bytes(const mgg_partition_t *p, const mgg_layer_desc_t *layer);
 
 /* ---------------------------------------------------------------------------------------
  * mgg_layer_forward -- section 1 "GNN" equation: h' = Update(Aggregate(...)), all on
  * `stream`, no host synchronisation between the kernels.
  * x_local / x_halo / ld_x as in mgg_aggregate with dim = layer->dims[0].  workspace is a
- * DEVICE buffer of at least mgg_layer_workspace_bytes() bytes, 256-byte aligned.
+ * DEVICE buffer of at least mgg_layer_workspace_least_bytes() bytes, 256-byte aligned.  One too small
+ * for the fine schedule (below mgg_layer_workspace_bytes()) runs the coarse one, which adds up the
+ * neighbours of a row in another order: the last bits of the result depend on it, as they do for
+ * mgg_aggregate on what mgg_partition_reserve could allocate.  A partition built with
+ * fine_min_neighbours < 0 has one schedule and the same bits whatever the buffer.
  * out [n_own x dims[n_linear]] DEVICE, out_dtype F32 or BF16.  With BF16 weights the hidden
  * activations of a 2-linear MLP are kept in bf16.
  * UPDATE_FIRST: T = X w[0] is computed for the local AND the halo table (fp32, no bias, no

@@ -27,7 +27,8 @@ _STATUS_NAME = ["OK", "INVALID_ARG", "BAD_GRAPH", "UNSUPPORTED", "ALLOC", "HIP"]
 
 EXPORTED_SYMBOLS = [
     "mgg_build_partition", "mgg_partition_info", "mgg_partition_export", "mgg_partition_destroy",
-    "mgg_partition_reserve", "mgg_aggregate_plan", "mgg_aggregate_scratch_bytes", "mgg_aggregate", "mgg_aggregate_static", "mgg_aggregate_to", "mgg_build_bags", "mgg_bag_sum", "mgg_update", "mgg_update_mlp", "mgg_layer_workspace_bytes", "mgg_layer_forward",
+    "mgg_partition_reserve", "mgg_aggregate_plan", "mgg_aggregate_scratch_bytes", "mgg_aggregate", "mgg_aggregate_static", "mgg_aggregate_to", "mgg_build_bags", "mgg_bag_sum", "mgg_update", "mgg_update_mlp", "mgg_layer_workspace_bytes",
+    "mgg_layer_workspace_least_bytes", "mgg_layer_forward",
     "mgg_split_edge_balanced", "mgg_set_option", "mgg_get_option", "mgg_partition_set_option", "mgg_partition_get_option", "mgg_time_aggregate", "mgg_probe_gather",
     "mgg_model_evaluate", "mgg_tuner_create", "mgg_tuner_set_constraint", "mgg_tuner_next", "mgg_tuner_report", "mgg_tuner_result",
     "mgg_tuner_table", "mgg_tuner_destroy", "mgg_tune_aggregate",
@@ -139,6 +140,8 @@ def lib():
                                      C.c_void_p, C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_int64, C.c_int,
                                      C.c_void_p, C.c_int64, C.c_void_p]
         L.mgg_layer_workspace_bytes.argtypes = [C.c_void_p, C.POINTER(LayerDesc)]
+        L.mgg_layer_workspace_least_bytes.restype = C.c_size_t
+        L.mgg_layer_workspace_least_bytes.argtypes = L.mgg_layer_workspace_bytes.argtypes
         L.mgg_layer_forward.argtypes = [C.c_void_p, C.POINTER(LayerDesc), C.c_int, C.c_void_p, C.c_void_p,
                                         C.c_int64, C.c_void_p, C.c_size_t, C.c_int, C.c_void_p, C.c_int64,
                                         C.c_void_p]
@@ -524,6 +527,13 @@ def mgg_layer_workspace_bytes(part: Partition, mode, weights, acts, eps: float =
                               order: str = "agg_first") -> int:
     d = _layer_desc(mode, eps, weights, biases, acts, order)
     return int(lib().mgg_layer_workspace_bytes(part.handle, C.byref(d)))
+
+
+def mgg_layer_workspace_least_bytes(part: Partition, mode, weights, acts, eps: float = 0.0, biases=None,
+                                    order: str = "agg_first") -> int:
+    """The least workspace mgg_layer_forward takes (less than _bytes for shares with a fine schedule)."""
+    d = _layer_desc(mode, eps, weights, biases, acts, order)
+    return int(lib().mgg_layer_workspace_least_bytes(part.handle, C.byref(d)))
 
 
 def mgg_layer_forward(part: Partition, mode: str, x_local, x_halo, weights, acts, *, eps: float = 0.0,

@@ -97,7 +97,8 @@ struct LayerPlan {
     size_t scratch_bytes = 0;                   // partial sums of rows cut into several work items (last in the workspace)
     size_t least_scratch_bytes = 0;             // those of the schedule that has fewer
     mgg_dtype_t hid_dtype = MGG_F32;
-    size_t total() const { return agg_bytes + hid_bytes + t_local_bytes + t_halo_bytes + scratch_bytes; }
+    size_t total() const { return scratch_offset() + scratch_bytes; }
+    size_t least() const { return scratch_offset() + least_scratch_bytes; }
     size_t scratch_offset() const { return agg_bytes + hid_bytes + t_local_bytes + t_halo_bytes; }
 };
 
@@ -242,18 +243,22 @@ mgg_status_t mgg_update(int64_t n_rows, mgg_dtype_t a_dtype, const void *a, int6
                          static_cast<hipStream_t>(stream));
 }
 
-size_t mgg_layer_workspace_bytes(const mgg_partition_t *p, const mgg_layer_desc_t *layer)
+// the largest need over the dtypes the call may be given (UPDATE_FIRST under AUTO depends on them)
+static size_t layer_workspace(const mgg_partition *p, const mgg_layer_desc_t *layer, size_t (LayerPlan::*bytes)() const)
 {
-    // the largest need over the dtypes the call may be given (UPDATE_FIRST under AUTO depends on them)
     size_t need = 0;
     for (mgg_dtype_t xd : {MGG_F32, MGG_BF16})
         for (mgg_dtype_t od : {MGG_F32, MGG_BF16}) {
             LayerPlan pl;
             if (!plan_layer(p, layer, xd, od, &pl)) return 0;
-            need = std::max(need, pl.total());
+            need = std::max(need, (pl.*bytes)());
         }
     return need + 256;
 }
+
+size_t mgg_layer_workspace_bytes(const mgg_partition_t *p, const mgg_layer_desc_t *layer) { return layer_workspace(p, layer, &LayerPlan::total); }
+
+size_t mgg_layer_workspace_least_bytes(const mgg_partition_t *p, const mgg_layer_desc_t *layer) { return layer_workspace(p, layer, &LayerPlan::least); }
 
 mgg_status_t mgg_layer_forward(const mgg_partition_t *p, const mgg_layer_desc_t *layer, mgg_dtype_t x_dtype,
                                const void *x_local, const void *x_halo, int64_t ld_x, void *workspace,

@@ -132,6 +132,7 @@ def test_fine_schedule():
     w = torch.eye(dim, device="cuda")
     full = binding.mgg_layer_workspace_bytes(part, "gcn", [w], ["none"])
     least = binding.mgg_layer_workspace_bytes(coarse, "gcn", [w], ["none"])
+    assert least == binding.mgg_layer_workspace_least_bytes(part, "gcn", [w], ["none"])
     assert least < full <= least + 2 * need
     outs = [binding.mgg_layer_forward(part, "gcn", xl, xh, [w], ["none"], workspace=torch.empty(b, dtype=torch.uint8, device="cuda")) for b in (full, least)]
     assert torch.equal(outs[0], got) and torch.equal(outs[1], static)

@@ -289,3 +289,22 @@ def test_large_partition_bit_exact_against_oracle(parts, part_id):
         with pytest.raises(binding.MggError, match=f"column {wrong[min(bad)]} at position {min(bad)} ") as err:
             binding.mgg_build_partition(ptr, wrong, parts, part_id, bounds, host_only=True)
         assert err.value.status == binding.ERR_BAD_GRAPH
+
+
+@pytest.mark.parametrize("dims", [(100, 40), (64, 64), (40, 24, 24), (130, 7)])
+@pytest.mark.parametrize("order", ["agg_first", "update_first", "auto"])
+def test_the_least_workspace_is_the_coarse_schedules(dims, order):
+    """A share with a fine schedule asks for a workspace that holds its partial sums; the least is what the same share
+    without one asks for, and what one of the fine schedule adds is the partial sums it has more."""
+    import torch
+    ptr, col = _graph(1500, 330, 7, hubs=20)
+    kw = dict(host_only=True, hot_phases=-1)
+    fine = binding.mgg_build_partition(ptr, col, 2, 0, fine_min_neighbours=1, **kw)
+    one = binding.mgg_build_partition(ptr, col, 2, 0, fine_min_neighbours=-1, **kw)
+    layer = (["gcn"], [torch.zeros(a, b) for a, b in zip(dims, dims[1:])], ["none"] * (len(dims) - 1))
+    ask = lambda f, p: f(p, layer[0][0], layer[1], layer[2], order=order)
+    least = ask(binding.mgg_layer_workspace_least_bytes, fine)
+    assert least == ask(binding.mgg_layer_workspace_bytes, one) == ask(binding.mgg_layer_workspace_least_bytes, one)
+    more = ask(binding.mgg_layer_workspace_bytes, fine) - least
+    extra = [int(fine.info.n_fine_split_items) * (-(-d // 8) * 8) * 4 for d in dims[:2]]
+    assert any(abs(more - x) < 256 for x in extra)
