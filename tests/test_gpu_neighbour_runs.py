@@ -1,7 +1,7 @@
 """Runs of neighbours at every length: what does not fill a load step, a batch of steps or a run of 64, rows whose run
 crosses from the local to the halo table, wavefronts whose short rows differ in length, at every number of lanes a table
-row can take; items taken by a team of wavefronts, as a launch this small does by itself, and one after the other by one
-(items_per_wave given).  Reference: the sum in float64, row by row.
+row can take; items taken by a team of wavefronts, as a launch this small does by itself where a row takes 8 lanes or
+more, and one after the other by one (items_per_wave given).  Reference: the sum in float64, row by row.
 """
 import numpy as np
 import pytest
@@ -75,67 +75,84 @@ def test_a_row_that_is_not_gathered_does_not_count(dim, bf16, per_wave):
             assert bool(torch.isinf(got[v]).all()) if touched else bool(torch.isfinite(got[v]).all()), (mode, v)
 
 
+@pytest.mark.parametrize("rows,team", [(40, 8), (600, 4), (1500, 2)])
 @pytest.mark.parametrize("dim,bf16", [(16, False), (30, False), (64, False), (100, False), (200, False), (128, True), (300, True)])
-def test_teams_of_every_size(dim, bf16):
-    """Launches that take teams of 8, 4 and 2 wavefronts, with rows cut at 1024 neighbours beside whole ones, against
-    one wavefront per item: equal up to the order of the sums."""
+def test_teams_of_every_size(dim, bf16, rows, team):
+    """Launches that take teams of 8, 4 and 2 wavefronts, with rows cut at 512 neighbours of each list beside whole ones,
+    against float64 and against one wavefront per item: equal up to the order of the sums."""
     rng = np.random.default_rng(dim)
-    for rows in (40, 300, 900, 2500):
-        n = 3000
-        lens = np.zeros(n, dtype=np.int64)
-        lens[:rows] = rng.integers(17, 600, rows)
-        lens[rng.integers(0, rows, 3)] = 2500
-        ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
-        row = np.repeat(np.arange(n), lens)
-        col = rng.integers(0, n - 1, ptr[-1])
-        col = (col + (col >= row)).astype(np.int32)
-        x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
-        if bf16:
-            x = x.bfloat16()
-        part = binding.mgg_build_partition(ptr, col, xcd_min_deg=-1)
-        for mode in ("gin", "gcn"):
-            out = []
-            for per_wave in (0, 2):
-                part.set_option("items_per_wave", per_wave)
-                out.append(binding.mgg_aggregate(part, mode, x, eps=0.5).double())
-            scale = binding.mgg_aggregate(part, mode, x.abs(), eps=0.5).double()
-            bound = 2 * (torch.from_numpy(lens).cuda()[:, None] + 5) * U * scale
-            assert ((out[0] - out[1]).abs() <= bound).all(), (rows, mode)
+    n, own = 3000, 2600
+    lens = np.zeros(n, dtype=np.int64)
+    lens[:rows] = rng.integers(17, 600, rows)
+    lens[rng.permutation(rows)[:3]] = 4500                             # 3900 local and 600 remote neighbours, or about that
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    row = np.repeat(np.arange(n), lens)
+    col = rng.integers(0, n - 1, ptr[-1])
+    col = (col + (col >= row)).astype(np.int32)
+    x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
+    if bf16:
+        x = x.bfloat16()
+    part = binding.mgg_build_partition(ptr, col, 2, 0, np.array([0, own, n], dtype=np.int64), xcd_min_deg=-1)
+    assert part.info.n_split_rows >= 3 and part.info.n_split_items > 20
+    assert binding.mgg_aggregate_plan(part, "gcn", dim, bf16=bf16).team == team
+    halo = torch.from_numpy(part.export()["halo_gid"].astype(np.int64)).cuda()
+    xl, xh, xd = x[:own].contiguous(), x[halo].contiguous(), x.double().cpu().numpy()
+    for mode in ("gin", "gcn"):
+        want, scale = _sums(ptr, col, own, xd, mode, 0.5)
+        bound = (lens[:own, None] + 6) * U * scale
+        for per_wave in (0, 2):
+            part.set_option("items_per_wave", per_wave)
+            assert (binding.mgg_aggregate_plan(part, mode, dim, bf16=bf16).team > 1) == (per_wave == 0)
+            got = binding.mgg_aggregate(part, mode, xl, xh, eps=0.5).double().cpu().numpy()
+            assert (np.abs(got - want) <= bound).all(), (mode, per_wave)
 
 
-def test_fine_schedule():
+@pytest.mark.parametrize("dim,bf16", [(80, False), (128, True)])
+def test_fine_schedule(dim, bf16):
     """A share large enough for the schedule that regroups rows of 128 neighbours on: in the partition's own buffer and in
     a layer's workspace there is room for its partial sums, in the fixed array of the static call there is not, and a
-    workspace that holds those of the other schedule is still enough."""
+    workspace that holds those of the other schedule is still enough.  Both against float64; a partition without the
+    second schedule gives the same bits in all of them."""
     rng = np.random.default_rng(8)
-    n, own, dim = 60000, 34000, 80
+    n, own = 60000, 34000
     lens = np.concatenate([rng.integers(100, 256, own // 2), rng.integers(256, 440, own // 2), np.zeros(n - own, dtype=np.int64)])
     ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     row = np.repeat(np.arange(n), lens)
     col = rng.integers(0, n - 1, ptr[-1])
     col = (col + (col >= row)).astype(np.int32)
     bounds = np.array([0, own, n], dtype=np.int64)
-    part = binding.mgg_build_partition(ptr, col, 2, 0, bounds)
-    coarse = binding.mgg_build_partition(ptr, col, 2, 0, bounds, xcd_min_deg=256)
+    part = binding.mgg_build_partition(ptr, col, 2, 0, bounds, fine_min_neighbours=0)
+    one = binding.mgg_build_partition(ptr, col, 2, 0, bounds, fine_min_neighbours=-1)
     need = binding.mgg_aggregate_scratch_bytes(part, dim)
-    assert ptr[-1] > 8 << 20 and need == binding.mgg_aggregate_scratch_bytes(coarse, dim) and need <= 64 << 20
+    assert ptr[-1] > 8 << 20 and need == binding.mgg_aggregate_scratch_bytes(one, dim) and part.info.n_fine_split_items > 0
+    static_fits = need <= 64 << 20
+    assert static_fits == (dim == 80)
+    assert [binding.mgg_aggregate_plan(part, "gcn", dim, bf16=bf16, scratch_bytes=b).fine for b in (None, 64 << 20)] == [1, 0]
     x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
+    if bf16:
+        x = x.bfloat16()
     halo = torch.from_numpy(part.export()["halo_gid"].astype(np.int64)).cuda()
-    xl, xh = x[:own].contiguous(), x[halo].contiguous()
-    for mode in ("gin", "gcn"):
-        scale = binding.mgg_aggregate(coarse, mode, xl.abs(), xh.abs()).double()
-        bound = 2 * (torch.from_numpy(lens[:own]).cuda()[:, None] + 5) * U * scale
-        want = binding.mgg_aggregate(coarse, mode, xl, xh)
-        got, static = binding.mgg_aggregate(part, mode, xl, xh), binding.mgg_aggregate_static(part, mode, xl, xh)
-        assert not torch.equal(got, static), mode                    # another order of the sums: the two schedules
-        assert ((got.double() - want.double()).abs() <= bound).all() and ((static.double() - want.double()).abs() <= bound).all(), mode
-    w = torch.eye(dim, device="cuda")
+    xl, xh, xd = x[:own].contiguous(), x[halo].contiguous(), x.double().cpu().numpy()
+    w = torch.eye(dim, device="cuda", dtype=x.dtype)
     full = binding.mgg_layer_workspace_bytes(part, "gcn", [w], ["none"])
-    least = binding.mgg_layer_workspace_bytes(coarse, "gcn", [w], ["none"])
-    assert least == binding.mgg_layer_workspace_least_bytes(part, "gcn", [w], ["none"])
-    assert least < full <= least + 2 * need
-    outs = [binding.mgg_layer_forward(part, "gcn", xl, xh, [w], ["none"], workspace=torch.empty(b, dtype=torch.uint8, device="cuda")) for b in (full, least)]
-    assert torch.equal(outs[0], got) and torch.equal(outs[1], static)
+    least = binding.mgg_layer_workspace_least_bytes(part, "gcn", [w], ["none"])
+    assert least == binding.mgg_layer_workspace_bytes(one, "gcn", [w], ["none"]) and least < full <= least + 2 * need
+    layer = lambda p, room: binding.mgg_layer_forward(p, mode, xl, xh, [w], ["none"], workspace=torch.empty(room, dtype=torch.uint8, device="cuda"))
+    for mode in ("gin", "gcn"):
+        want, scale = _sums(ptr, col, own, xd, mode, 0)
+        bound = (lens[:own, None] + 6) * U * scale
+        got, coarse = binding.mgg_aggregate(part, mode, xl, xh), binding.mgg_aggregate(one, mode, xl, xh)
+        for g in (got, coarse):
+            assert (np.abs(g.double().cpu().numpy() - want) <= bound).all(), mode
+        assert not torch.equal(got, coarse), mode                    # another order of the sums: the two schedules
+        if static_fits:
+            assert torch.equal(coarse, binding.mgg_aggregate_static(one, mode, xl, xh))
+            static = binding.mgg_aggregate_static(part, mode, xl, xh)
+            assert (np.abs(static.double().cpu().numpy() - want) <= bound).all() and not torch.equal(got, static), mode
+            assert torch.equal(layer(part, full), got) and torch.equal(layer(part, least), static), mode
+        assert torch.equal(layer(one, full), layer(one, least)), mode
+    with pytest.raises(binding.MggError):
+        layer(part, least - 512)
 
 
 def test_slabs_in_chunks():
@@ -151,8 +168,11 @@ def test_slabs_in_chunks():
     assert ptr[-1] * 8 >= 128 << 20
     x = torch.from_numpy(rng.standard_normal((n, dim)).astype(np.float32)).cuda()
     part = binding.mgg_build_partition(ptr, col)
+    plan = binding.mgg_aggregate_plan(part, "gcn", dim)
+    assert (plan.slab_bytes, plan.n_slabs, plan.n_chunks) == (256, 4, 4)
     got = binding.mgg_aggregate(part, "gcn", x)
     part.set_option("col_slab_bytes", 256)
+    assert binding.mgg_aggregate_plan(part, "gcn", dim).n_chunks == 1
     assert torch.equal(got, binding.mgg_aggregate(part, "gcn", x))
 
 

@@ -202,8 +202,8 @@ def test_rows_at_any_element_boundary(dim, bf16, slab):
 
 
 def test_tables_beyond_4gb_take_64_bit_row_offsets():
-    """Row offsets inside a table are 32-bit unless a table reaches beyond 4 GB; rows spaced 2.1 MB apart
-    put a 2048-row table there (work items, short rows and the self term all use the wide path)."""
+    """Rows spaced 2.1 MB apart put a 2048-row table beyond 4 GB: row addresses are 64-bit sums in work items, short rows
+    and the self term, also of row strides that do not fit 32 bits of bytes times rows."""
     row_ptr, col, rng = small_rmat(seed=41)
     n = row_ptr.size - 1
     x = rng.standard_normal((n, 64)).astype(np.float32)
