@@ -256,8 +256,9 @@ class Partition:
     def reserve(self, dim: int):
         """mgg_partition_reserve: size the partition's scratch buffer for aggregations up to `dim` wide."""
         if dim > self._reserved:
-            _check(lib().mgg_partition_reserve(self.handle, int(dim)))
-            self._reserved = int(dim)
+            status = lib().mgg_partition_reserve(self.handle, int(dim))
+            self._reserved = int(dim) if status == OK else 0        # refused: the buffer there was has been given up
+            _check(status)
 
     def set_option(self, key: str, value: int):
         """A run-time switch of this partition's aggregations (mgg_partition_set_option)."""

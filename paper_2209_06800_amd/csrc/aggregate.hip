@@ -186,7 +186,7 @@ mgg_status_t probe_gather(int64_t table_bytes, int32_t row_bytes, int64_t n_gath
     hipError_t e = hipMalloc(reinterpret_cast<void **>(&table), static_cast<size_t>(rows) * row_bytes);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&idx), h.size() * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&sink), sizeof(float));
-    if (e != hipSuccess) st = fail(MGG_ERR_ALLOC, "probe buffers: %s", hipGetErrorString(e));
+    if (e != hipSuccess) st = alloc_fail(e, static_cast<size_t>(rows) * row_bytes + h.size() * sizeof(int32_t), " of probe buffers");
     if (st == MGG_OK) {
         e = hipMemset(table, 0, static_cast<size_t>(rows) * row_bytes);
         if (e == hipSuccess) e = hipMemcpy(idx, h.data(), h.size() * sizeof(int32_t), hipMemcpyHostToDevice);

@@ -215,7 +215,7 @@ mgg_status_t mgg_partition_reserve(mgg_partition_t *p, int32_t dim)
         bytes = scratch_bytes_for(p, dim);
         e = hipMalloc(reinterpret_cast<void **>(&p->d.scratch), bytes);
     }
-    if (e != hipSuccess) { p->reserved_dim = 0; return fail(MGG_ERR_ALLOC, "hipMalloc(%zu bytes of scratch): %s", bytes, hipGetErrorString(e)); }
+    if (e != hipSuccess) { p->reserved_dim = 0; return alloc_fail(e, bytes, " of scratch"); }
     p->d.scratch_ld = need_ld;
     p->d.scratch_rows = rows;
     return MGG_OK;

@@ -124,6 +124,7 @@ namespace mgg {
 
 mgg_status_t fail(mgg_status_t code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 mgg_status_t hip_fail(hipError_t e, const char *what);
+mgg_status_t alloc_fail(hipError_t e, size_t bytes, const char *what);
 
 #define MGG_HIP_TRY(expr)                                    \
     do {                                                     \

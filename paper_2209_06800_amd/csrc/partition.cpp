@@ -25,9 +25,18 @@ mgg_status_t fail(mgg_status_t code, const char *fmt, ...)
     return code;
 }
 
+// An error that a status reports is not left behind as HIP's last one, which the next launch, here or in the caller's
+// program, would find and take for its own.
 mgg_status_t hip_fail(hipError_t e, const char *what)
 {
+    (void)hipGetLastError();
     return fail(MGG_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
+}
+
+mgg_status_t alloc_fail(hipError_t e, size_t bytes, const char *what)
+{
+    (void)hipGetLastError();
+    return fail(MGG_ERR_ALLOC, "hipMalloc(%zu bytes%s): %s", bytes, what, hipGetErrorString(e));
 }
 
 const char *last_error() { return g_err; }
@@ -39,7 +48,7 @@ static mgg_status_t upload(const T *h, size_t n, T **d)
     // one element at least, so that kernels never receive a null table pointer
     size_t bytes = std::max<size_t>(n, 1) * sizeof(T);
     hipError_t e = hipMalloc(reinterpret_cast<void **>(d), bytes);
-    if (e != hipSuccess) return fail(MGG_ERR_ALLOC, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
+    if (e != hipSuccess) return alloc_fail(e, bytes, "");
     if (n > 0) MGG_HIP_TRY(hipMemcpy(*d, h, n * sizeof(T), hipMemcpyHostToDevice));
     return MGG_OK;
 }

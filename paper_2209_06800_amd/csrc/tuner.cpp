@@ -225,7 +225,6 @@ mgg_status_t mgg_tune_aggregate(int64_t num_nodes, const int64_t *row_ptr, const
             // The work items or their partial sums do not fit in memory: the resource constraint
             // of the model.  Such a trial counts as slower than any that fits, and the less so the
             // larger its work items, so the upward sweeps keep moving towards feasible ground.
-            (void)hipGetLastError();
             latency = 1e30 / (static_cast<double>(k.ps) * k.dist * k.wpb);
         } else if (s != MGG_OK) {
             return s;

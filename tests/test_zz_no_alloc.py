@@ -81,3 +81,26 @@ def test_static_scratch_refuses_what_does_not_fit():
     binding.mgg_aggregate_static(part, "gcn", xl[:, : dim // 2], xh[:, : dim // 2], out=out[:, : dim // 2])
     torch.cuda.synchronize()
     part.destroy()
+
+
+def test_a_refused_reservation_leaves_no_error_behind():
+    """A width whose partial sums do not fit the card is refused with a status; the next call, of the library or of the
+    program around it, finds no error that is not its own, and the partition can be reserved again."""
+    rng = np.random.default_rng(0)
+    n = 4000
+    lens = np.zeros(n, dtype=np.int64)
+    lens[:200] = 2000
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = rng.integers(0, n, ptr[-1]).astype(np.int32)
+    part, other = binding.mgg_build_partition(ptr, col), binding.mgg_build_partition(ptr, col)
+    x = torch.randn(n, 64, device="cuda")
+    want = binding.mgg_aggregate(other, "gcn", x)
+    assert torch.equal(binding.mgg_aggregate(part, "gcn", x), want)
+    assert binding.mgg_aggregate_scratch_bytes(part, 1 << 30) > 1 << 42          # 4 TB
+    for _ in range(2):
+        with pytest.raises(binding.MggError) as err:
+            part.reserve(1 << 30)
+        assert err.value.status == binding.ERR_ALLOC
+        assert torch.equal(binding.mgg_aggregate(other, "gcn", x), want)
+        assert torch.equal(torch.relu(x), x.clamp_min(0))
+    assert torch.equal(binding.mgg_aggregate(part, "gcn", x), want)
