@@ -131,8 +131,8 @@ typedef struct {
     int32_t *grp_local_row, *grp_local_start, *grp_local_end;      /* [n_groups_local]       */
     int32_t *grp_remote_row, *grp_remote_start, *grp_remote_end;   /* [n_groups_remote]      */
     int32_t *short_rows;      /* [n_short_rows] owned-row indices of the short bin           */
-    int32_t *sched_local_col; /* [nnz_local]  local_col in the order the kernel walks it: the  */
-    int32_t *sched_remote_col;/* [nnz_remote] same rows, regrouped rows sorted by source class  */
+    int32_t *sched_local_col; /* [nnz_local]  local_col with each row in the order it is walked:  */
+    int32_t *sched_remote_col;/* [nnz_remote] rows that a schedule regroups sorted by source class */
     int32_t *item_row;        /* [n_items] owned row of each work item; -1 = padding item      */
     int32_t *item_lbeg, *item_lend;   /* [n_items] range in sched_local_col                  */
     int32_t *item_rbeg, *item_rend;   /* [n_items] range in sched_remote_col                 */
@@ -436,14 +436,15 @@ mgg_status_t mgg_tune_aggregate(int64_t num_nodes, const int64_t *row_ptr, const
  * built afterwards start from -- existing partitions keep what they have -- and the one switch of the
  * Update kernels, which have no handle to carry it.  Keys:
  *   "lds_halo"    0/1  stage halo rows through LDS ahead of accumulation, where table rows are
- *                      16-byte aligned (default 0)
+ *                      16-byte aligned, tables below 4 GB, wpb at most 8 and a row slab at most 64
+ *                      vectors; such launches run the coarse schedule (default 0)
  *   "split_phases" 0/1 aggregate the local lists and the remote lists in two launches, the
  *                      second adding to the first (no interleaving; default 0)
  *   "col_slab_bytes"   0 = automatic (default), 1 = off, or a power of two in [64, 4096]:
  *                      bytes of an embedding row handled per pass over the work items
  *   "items_per_wave"   0 = automatic (default), or 1..64: work items a wavefront takes one after
  *                      the other, the next one's ids and descriptor requested while it gathers
- *   "short_per_wave"   the same for the groups of short rows a wavefront takes
+ *   "short_per_wave"   the same for the groups of short rows a wavefront takes (automatic: 1)
  *   "update_stream" 0/1 (process-wide only) the Update kernels for bf16 weights that were added for streaming
  *                      efficiency (whole-line kernels, the one-kernel MLP) are used where they apply
  *                      (default 1; 0 = the plain register-resident and slab kernels everywhere);

@@ -322,10 +322,6 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
     pl.fine = !lds && p->n_fine_sums > 0 && scratch_rows >= p->n_split_items + p->n_fine_sums;
     pl.n_items = static_cast<int32_t>(pl.fine ? p->fine_items.size() : p->items.size());
     const int32_t n_short = static_cast<int32_t>(p->short_rows.size());
-    // Work per wavefront: M items (or groups of short rows) one after the other, pipelined.  More per
-    // wavefront amortises its start-up latencies; fewer leaves more workgroups for the hardware to
-    // balance.  Automatic: 2 where the launch still has about 8192 workgroups (measured on MI355X: 0.3-2.5 %
-    // faster than 1 and than 8 on every workload tried), else 1.
     // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel), 8 or 4 to an item up to 4096
     // wavefronts in all, 2 up to 8192, where the chain of loads behind the longest item is what the launch waits for: each
     // member of its team has a batch of 8 loads at least, and not less than the launch's loads come to on each of the 5120
@@ -346,13 +342,14 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
             if (item_waves * t <= (t == 2 ? 8192 : 4096) && p->longest_item / (t * npw) >= std::max<int64_t>(8, (t == 2 ? 2 : t == 4 ? 3 : 6) * loads / (2 * 5120))) { team = true; wpb = t; }
     }
     const int64_t n_groups = team ? pl.n_items : (pl.n_items + wpb - 1) / wpb;
-    {
-        auto pick = [&](int32_t opt, int64_t units, int64_t most) { return static_cast<int32_t>(opt > 0 ? opt : std::min<int64_t>(most, std::max<int64_t>(1, units * n_slabs / 8192))); };
-        pl.items_per_wave = team ? 1 : pick(p->opt_items_per_wave, n_groups, 2);
-        // (groups of short rows: one, since the ids of a group are all requested ahead in it; 26-lookup bags 147.6 -> 144.5 us,
-        // flat elsewhere)
-        pl.short_per_wave = pick(p->opt_short_per_wave, (short_groups + wpb - 1) / wpb, 1);
-    }
+    // Work per wavefront: M items one after the other, pipelined.  More per wavefront amortises its start-up latencies; fewer
+    // leaves more workgroups for the hardware to balance.  Automatic: 2 where the launch still has about 8192 workgroups
+    // (0.3-2.5 % faster than 1 and than 8 on every workload tried), else 1.  Groups of short rows: one, since the ids of a group
+    // are all requested ahead in it (26-lookup bags 147.6 -> 144.5 us, flat elsewhere).
+    if (team) pl.items_per_wave = 1;
+    else if (p->opt_items_per_wave > 0) pl.items_per_wave = p->opt_items_per_wave;
+    else pl.items_per_wave = static_cast<int32_t>(std::min<int64_t>(2, std::max<int64_t>(1, n_groups * n_slabs / 8192)));
+    pl.short_per_wave = std::max<int32_t>(1, p->opt_short_per_wave);
     pl.n_item_blocks = team ? team_blocks(pl.n_items) : static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * pl.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * pl.items_per_wave) * kXcd);
     const int64_t short_waves = (short_groups + pl.short_per_wave - 1) / pl.short_per_wave;
     pl.grid_x = pl.n_item_blocks + static_cast<int>((short_waves + wpb - 1) / wpb);

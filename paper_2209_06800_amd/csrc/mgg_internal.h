@@ -13,9 +13,8 @@
 
 namespace mgg {
 
-// One wavefront work item: a run of neighbour partitions of one owned row, from the local
-// list and from the remote list (section 5.1: a warp handles pairs of local / remote
-// partitions).  slot < 0: the item covers the whole row and writes the final value;
+// One wavefront work item: a run of neighbour partitions of one owned row, from the local list and from the remote list
+// (section 5.1: a warp handles pairs of local / remote partitions; the kernel walks the local ones first).  slot < 0: the item covers the whole row and writes the final value;
 // slot >= 0: it writes a raw partial sum into scratch row `slot`.  row < 0: padding, nothing to do.
 struct WorkItem {
     int32_t row;
@@ -97,7 +96,7 @@ struct mgg_partition {
     std::vector<uint8_t> src_class;   // class of every table row (local rows, then halo slots); empty: no classes
     int device = -1;  // HIP device the arrays live on; -1 = host only
     std::vector<int32_t> local_row_ptr, local_col, remote_row_ptr, remote_col;
-    std::vector<int32_t> sched_local_col, sched_remote_col;   // device order of the columns (empty: same as above)
+    std::vector<int32_t> sched_local_col, sched_remote_col;   // rows in the order they are walked, regrouped ones by source class (empty: same as above)
     std::vector<int32_t> halo_gid, deg_own, deg_halo;
     std::vector<int64_t> halo_peer_ptr;
     std::vector<float> dinv_own, dinv_halo;
