@@ -438,7 +438,7 @@ mgg_status_t mgg_tune_aggregate(int64_t num_nodes, const int64_t *row_ptr, const
  *   "lds_halo"    0/1  stage halo rows through LDS ahead of accumulation, where table rows are
  *                      16-byte aligned, tables below 4 GB, wpb at most 8 and a row slab at most 64
  *                      vectors; such launches run the coarse schedule (default 0)
- *   "split_phases" 0/1 aggregate the local lists and the remote lists in two launches, the
+ *   "split_phases" 0/1 aggregate the local lists and the remote lists in two launches of the coarse schedule, the
  *                      second adding to the first (no interleaving; default 0)
  *   "col_slab_bytes"   0 = automatic (default), 1 = off, or a power of two in [64, 4096]:
  *                      bytes of an embedding row handled per pass over the work items

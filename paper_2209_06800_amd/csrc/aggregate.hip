@@ -216,6 +216,9 @@ mgg_status_t probe_gather(int64_t table_bytes, int32_t row_bytes, int64_t n_gath
 
 namespace {
 
+// the ablation of interleaving: the local lists first, the remote lists in a second launch that adds to the result
+bool two_launches(const mgg_partition *p) { return p->opt_split_phases != 0 && !p->halo_gid.empty(); }
+
 // What one aggregation launches, decided by plan_aggregate: arithmetic on the host alone.
 struct Plan {
     int vec, nvec;               // elements of a vector, vectors of a row
@@ -318,8 +321,8 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
                      static_cast<uint64_t>(most_rows) * static_cast<uint64_t>(ld_x) * esz < (1ull << 32);
     // The fine schedule where its partial sums have room; not with halo rows through LDS, which are staged 8 KB at a time
     // however few a piece has (17.8 M neighbours at 64 columns 0.721 ms with it, 0.609 without; 28 M at 128 in bf16 1.43 and
-    // 1.16).
-    pl.fine = !lds && p->n_fine_sums > 0 && scratch_rows >= p->n_split_items + p->n_fine_sums;
+    // 1.16), nor in two launches, which walk every piece twice and add up its partial sums twice (0.449 and 0.406; 1.01 and 0.88).
+    pl.fine = !lds && !two_launches(p) && p->n_fine_sums > 0 && scratch_rows >= p->n_split_items + p->n_fine_sums;
     pl.n_items = static_cast<int32_t>(pl.fine ? p->fine_items.size() : p->items.size());
     const int32_t n_short = static_cast<int32_t>(p->short_rows.size());
     // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel), 8 or 4 to an item up to 4096
@@ -413,9 +416,8 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
     a.out_dim = out_dim;
     a.relu = act == MGG_ACT_RELU;
     a.out_bf16 = out_dtype == MGG_BF16;
-    // one launch for both neighbour lists (the default), or -- as the ablation of interleaving --
-    // the local lists first and the remote lists in a second launch that adds to the result
-    const bool two_phases = p->opt_split_phases != 0 && !p->halo_gid.empty() && out_dtype != MGG_BF16;   // phase 2 reads `out` back
+    // one launch for both neighbour lists, or two
+    const bool two_phases = two_launches(p) && out_dtype != MGG_BF16;   // phase 2 reads `out` back
     for (int phase = two_phases ? 1 : 0; phase <= (two_phases ? 2 : 0); ++phase) {
         a.phase = phase;
         if (pl.grid_x > 0) {

@@ -210,7 +210,7 @@ def test_a_given_number_of_wavefronts_is_kept(wpb):
     assert binding.mgg_aggregate_plan(part, "gcn", 64).wpb == wpb
 
 
-def test_plan_of_halo_rows_through_lds():
+def test_plan_of_halo_rows_through_lds_and_of_two_launches():
     """Staged rows are requested 8 KB at a time: pieces stay as large as the coarse schedule leaves them.  Tables it cannot
     stage (rows off 16 bytes, 4 GB and more, no halo, workgroups beyond 8 wavefronts, several chunks a lane) take registers."""
     ptr, col = _graph(1500, 330, 7, hubs=20)
@@ -228,7 +228,12 @@ def test_plan_of_halo_rows_through_lds():
     assert binding.mgg_aggregate_plan(part, "gcn", 64, ld=wide - 8).lds_halo == 1
     part.set_option("col_slab_bytes", 1)
     assert [binding.mgg_aggregate_plan(part, "gcn", d).lds_halo for d in (256, 260)] == [1, 0]
+    two = binding.mgg_build_partition(ptr, col, 2, 0, **kw)
+    two.set_option("split_phases", 1)                               # every piece is walked and added up twice
+    assert binding.mgg_aggregate_plan(two, "gcn", 64).fine == 0
     alone = binding.mgg_build_partition(ptr, col, **kw)
+    alone.set_option("split_phases", 1)                             # no halo: one launch
+    assert binding.mgg_aggregate_plan(alone, "gcn", 64).fine == 1
     many = binding.mgg_build_partition(ptr, col, 2, 0, wpb=16, **kw)
     for p in (alone, many):
         p.set_option("lds_halo", 1)
