@@ -347,12 +347,17 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
     const int64_t n_groups = team ? pl.n_items : (pl.n_items + wpb - 1) / wpb;
     // Work per wavefront: M items one after the other, pipelined.  More per wavefront amortises its start-up latencies; fewer
     // leaves more workgroups for the hardware to balance.  Automatic: 2 where the launch still has about 8192 workgroups
-    // (0.3-2.5 % faster than 1 and than 8 on every workload tried), else 1.  Groups of short rows: one, since the ids of a group
-    // are all requested ahead in it (26-lookup bags 147.6 -> 144.5 us, flat elsewhere).
+    // (0.3-2.5 % faster than 1 and than 8 on every workload tried), else 1.  Groups of short rows: the same for rows of a graph
+    // whose ids fit their 16 lanes or more, all requested with the group before (260 k-node R-MAT, half, 75 columns 140.3 -> 137.2
+    // us; 28 M neighbours at 75 columns 1.034 -> 1.024 ms, at 128 1.497 -> 1.488); one where a row takes fewer lanes (16 columns 46.2
+    // -> 49.8 us with 2) and in bags, whose longer lists are requested ahead in the group itself (26 lookups of 64 columns 241 ->
+    // 245 us with 2).
     if (team) pl.items_per_wave = 1;
     else if (p->opt_items_per_wave > 0) pl.items_per_wave = p->opt_items_per_wave;
     else pl.items_per_wave = static_cast<int32_t>(std::min<int64_t>(2, std::max<int64_t>(1, n_groups * n_slabs / 8192)));
-    pl.short_per_wave = std::max<int32_t>(1, p->opt_short_per_wave);
+    if (p->opt_short_per_wave > 0) pl.short_per_wave = p->opt_short_per_wave;
+    else if (p->bags || lpr < 16) pl.short_per_wave = 1;
+    else pl.short_per_wave = static_cast<int32_t>(std::min<int64_t>(2, std::max<int64_t>(1, (short_groups + wpb - 1) / wpb * n_slabs / 8192)));
     pl.n_item_blocks = team ? team_blocks(pl.n_items) : static_cast<int32_t>((n_groups + static_cast<int64_t>(kXcd) * pl.items_per_wave - 1) / (static_cast<int64_t>(kXcd) * pl.items_per_wave) * kXcd);
     const int64_t short_waves = (short_groups + pl.short_per_wave - 1) / pl.short_per_wave;
     pl.grid_x = pl.n_item_blocks + static_cast<int>((short_waves + wpb - 1) / wpb);

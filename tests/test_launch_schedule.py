@@ -313,3 +313,18 @@ def test_the_least_workspace_is_the_coarse_schedules(dims, order):
     more = ask(binding.mgg_layer_workspace_bytes, fine) - least
     extra = [int(fine.info.n_fine_split_items) * (-(-d // 8) * 8) * 4 for d in dims[:2]]
     assert any(abs(more - x) < 256 for x in extra)
+
+
+def test_groups_of_short_rows_per_wavefront():
+    """Two where the launch keeps 8192 workgroups, rows of a graph take 16 lanes or more and their ids therefore come with the
+    group before; one for fewer lanes, for bags and below that."""
+    rng = np.random.default_rng(2)
+    for rows, want in ((120000, 1), (140000, 2)):                              # 4 rows a wavefront, 2 wavefronts a workgroup
+        ptr, col = _lists(rng.integers(1, 5, rows), rows)
+        part = binding.mgg_build_partition(ptr, col, host_only=True)
+        plan = lambda dim, **kw: binding.mgg_aggregate_plan(part, "gcn", dim, **kw).short_per_wave
+        assert (plan(64), plan(128), plan(16), plan(32), plan(128, bf16=True)) == (want, 2, 1, 1, want)
+        bags = binding.mgg_build_bags(ptr, col, rows, 0, rows, host_only=True)
+        assert binding.mgg_aggregate_plan(bags, "gin", 128).short_per_wave == 1
+        part.set_option("short_per_wave", 5)
+        assert plan(16) == 5
