@@ -398,9 +398,10 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
     };
     std::vector<std::pair<WorkItem, int>> row_items;         // item, class (n_hot = cold)
     // The fine schedule costs a partial sum per class and row and keeps the gathers of these rows in one XCD's L2.  From 128
-    // neighbours on (16 per class) it pays on large shares (233 k rows, 602 columns: 18.27 -> 17.63 ms; 120 k rows, 256
-    // columns: 2.93 -> 2.70; 17.8 M neighbours at 64 columns: 356 -> 346 us; 28 M at 128 in bf16: 736 -> 722; from 64 on
-    // nothing more; 3.2 M at 75 columns: 137.4 -> 138.5).  With popularity classes it changes nothing.
+    // neighbours on (16 per class) it pays on large shares (233 k rows, 602 columns: 18.39 -> 17.88 ms; 120 k rows, 256
+    // columns: 2.66 -> 2.57; 28 M neighbours at 128 in bf16: 749 -> 730 us; 17.8 M at 64 columns nothing, 346 and 347; from 64
+    // neighbours on nothing more; 3.2 M at 75 columns, with the threshold moved: 137.4 -> 138.5).  With popularity classes it
+    // changes nothing.
     const int64_t nnz = static_cast<int64_t>(p->local_col.size()) + static_cast<int64_t>(p->remote_col.size());
     bool fine = k.fine_min > 0 && nnz >= k.fine_min && p->class_mode == 1 && n_phase == 1 && xcd_min_deg == kDefaultXcdMinDeg && run >= kDefaultXcdMinDeg;
     std::vector<std::vector<WorkItem>> fine_bucket(fine ? bucket.size() : 0);
