@@ -91,8 +91,9 @@ typedef struct {
     int32_t reserve_dim;   /* > 0: the build ends with mgg_partition_reserve(p, reserve_dim) */
     int32_t fine_min_neighbours;   /* shares with at least this many neighbours and classes by hash have a second,
                               fine schedule beside the one that xcd_min_deg describes: rows of 128 neighbours on
-                              are regrouped, too, for up to twice as many partial sums on top.  It runs where the
-                              scratch at hand holds them (mgg_aggregate_plan says which one does).  0 = default
+                              are regrouped, too, for up to twice as many partial sums on top.  It runs for rows
+                              wide enough to pay for them (never up to 32 columns) where the scratch at hand
+                              holds them (mgg_aggregate_plan says which one does).  0 = default
                               2^23, negative = never: one schedule, the same bits whatever the scratch.  Not with
                               an xcd_min_deg or min_piece of the caller's. */
 } mgg_build_opts_t;

@@ -319,10 +319,19 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
     const int64_t most_rows = std::max<int64_t>(p->n_local_rows, static_cast<int64_t>(p->halo_gid.size()));
     const bool lds = p->opt_lds_halo != 0 && !p->halo_gid.empty() && rows_aligned && ch == 1 && p->wpb <= kStageWpb &&
                      static_cast<uint64_t>(most_rows) * static_cast<uint64_t>(ld_x) * esz < (1ull << 32);
-    // The fine schedule where its partial sums have room; not with halo rows through LDS, which are staged 8 KB at a time
-    // however few a piece has (17.8 M neighbours at 64 columns 0.721 ms with it, 0.609 without; 28 M at 128 in bf16 1.43 and
-    // 1.16), nor in two launches, which walk every piece twice and add up its partial sums twice (0.449 and 0.406; 1.01 and 0.88).
-    pl.fine = !lds && !two_launches(p) && p->n_fine_sums > 0 && scratch_rows >= p->n_split_items + p->n_fine_sums;
+    // The fine schedule where its partial sums have room and rows are wide enough to pay for them: what a gather from L2 saves
+    // goes by the row's bytes, an item and its partial sum of 4 bytes a column cost the same whatever those are.  Time with it
+    // over time without, nine shares of 10 to 44 M neighbours: fp32 of up to 32 columns 1.01 to 1.28, 48 and 64 columns 0.90 to
+    // 1.01, 100 to 256 columns 0.87 to 0.99; bf16 of up to 64 columns 1.03 to 1.32, 216 and 256 columns 0.93 to 1.01; 16 lanes of
+    // bf16 (128 columns, or 256-byte slabs) 0.95 to 0.98 on tables of 400 k rows and more with 20 M neighbours and more, 0.99 to
+    // 1.13 on smaller ones.
+    const int64_t all_rows = p->n_local_rows + static_cast<int64_t>(p->halo_gid.size());
+    const int64_t nnz = static_cast<int64_t>(p->local_col.size()) + static_cast<int64_t>(p->remote_col.size());
+    const bool pays = lpr >= (bf16 ? 32 : 16) || (lpr == 16 && all_rows >= (3 << 17) && nnz >= 20000000);
+    // Not with halo rows through LDS, which are staged 8 KB at a time however few a piece has (17.8 M neighbours at 64 columns
+    // 0.721 ms with it, 0.609 without; 28 M at 128 in bf16 1.43 and 1.16), nor in two launches, which walk every piece twice and
+    // add up its partial sums twice (0.449 and 0.406; 1.01 and 0.88).
+    pl.fine = pays && !lds && !two_launches(p) && p->n_fine_sums > 0 && scratch_rows >= p->n_split_items + p->n_fine_sums;
     pl.n_items = static_cast<int32_t>(pl.fine ? p->fine_items.size() : p->items.size());
     const int32_t n_short = static_cast<int32_t>(p->short_rows.size());
     // Few items: a team of wavefronts takes each of them together (aggregate_team_kernel), 8 or 4 to an item up to 4096
@@ -339,7 +348,6 @@ mgg_status_t plan_aggregate(const mgg_partition *p, mgg_agg_t mode, bool bf16, i
     const int npw = 64 / lpr;
     const int64_t short_groups = (n_short + npw - 1) / npw;
     if (ch == 1 && !lds && p->opt_items_per_wave == 0 && !p->wpb_given) {
-        const int64_t nnz = static_cast<int64_t>(p->local_col.size()) + static_cast<int64_t>(p->remote_col.size());
         const int64_t item_waves = p->n_work_items * n_slabs, loads = (nnz / npw + 8 * (short_groups + p->n_work_items)) * n_slabs;
         for (int t = kMaxTeam; t >= 2 && !team; t /= 2)
             if (item_waves * t <= (t == 2 ? 8192 : 4096) && p->longest_item / (t * npw) >= std::max<int64_t>(8, (t == 2 ? 2 : t == 4 ? 3 : 6) * loads / (2 * 5120))) { team = true; wpb = t; }

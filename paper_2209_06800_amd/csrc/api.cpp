@@ -207,9 +207,9 @@ mgg_status_t mgg_partition_reserve(mgg_partition_t *p, int32_t dim)
     MGG_HIP_TRY(hipDeviceSynchronize());
     if (p->d.scratch) { (void)hipFree(p->d.scratch); p->d.scratch = nullptr; p->d.scratch_ld = 0; p->d.scratch_rows = 0; }
     size_t bytes = scratch_bytes_wanted(p, dim);
-    int64_t rows = p->n_split_items + p->n_fine_sums;
+    int64_t rows = scratch_rows_wanted(p, dim);
     hipError_t e = hipMalloc(reinterpret_cast<void **>(&p->d.scratch), bytes);
-    if (e != hipSuccess && p->n_fine_sums > 0) {        // the schedule with fewer partial sums will do
+    if (e != hipSuccess && rows > p->n_split_items) {        // the schedule with fewer partial sums will do
         (void)hipGetLastError();
         rows = p->n_split_items;
         bytes = scratch_bytes_for(p, dim);

@@ -52,6 +52,7 @@ static_assert(team_item(0) == 0 && team_item(1) == 2 && team_item(kXcd) == 1 && 
 constexpr int team_blocks(int n_items) { return (n_items + kXcd * kDefaultWpb - 1) / (kXcd * kDefaultWpb) * (kXcd * kDefaultWpb); }
 constexpr int kFineXcdMinDeg = 128;         // rows regrouped in the fine schedule too
 constexpr int64_t kFineMinNeighbours = 8 << 20;   // shares of fewer neighbours have none
+constexpr int kFineMinDim = 32;             // up to this width it is never taken (plan_aggregate)
 constexpr int kDefaultHotPhases = 0;        // automatic choice between hash classes and popularity phases
 constexpr int kAutoHotPhases = 4;           // phases when the automatic choice takes popularity classes
 constexpr int kMaxHotPhases = 31;           // class index phase * 8 + XCD has to stay below kColdClass
@@ -152,7 +153,8 @@ mgg_status_t launch_aggregate(const mgg_partition *p, mgg_agg_t mode, float eps,
 // own buffer (mgg_partition_reserve).  The launch allocates nothing: too small a buffer is an error.
 inline int64_t scratch_ld_for(int32_t dim) { return (static_cast<int64_t>(dim) + 7) / 8 * 8; }   // rows of partial sums start on 32-byte boundaries
 // (the least an aggregation can do with, and what it has a use for)
-inline size_t scratch_bytes_wanted(const mgg_partition *p, int32_t dim) { return static_cast<size_t>(p->n_split_items + p->n_fine_sums) * static_cast<size_t>(scratch_ld_for(dim)) * sizeof(float); }
+inline int64_t scratch_rows_wanted(const mgg_partition *p, int32_t dim) { return p->n_split_items + (dim > kFineMinDim ? p->n_fine_sums : 0); }
+inline size_t scratch_bytes_wanted(const mgg_partition *p, int32_t dim) { return static_cast<size_t>(scratch_rows_wanted(p, dim)) * static_cast<size_t>(scratch_ld_for(dim)) * sizeof(float); }
 inline size_t scratch_bytes_for(const mgg_partition *p, int32_t dim) { return static_cast<size_t>(p->n_split_items) * static_cast<size_t>(scratch_ld_for(dim)) * sizeof(float); }
 // what launch_aggregate would launch (host arithmetic, host-only partitions too)
 mgg_status_t describe_plan(const mgg_partition *p, mgg_agg_t mode, mgg_dtype_t x_dtype, int32_t dim, int64_t ld_x, int32_t base_align, size_t scratch_bytes,

@@ -107,7 +107,7 @@ def test_teams_of_every_size(dim, bf16, rows, team):
             assert (np.abs(got - want) <= bound).all(), (mode, per_wave)
 
 
-@pytest.mark.parametrize("dim,bf16", [(80, False), (128, True)])
+@pytest.mark.parametrize("dim,bf16", [(80, False), (256, True)])
 def test_fine_schedule(dim, bf16):
     """A share large enough for the schedule that regroups rows of 128 neighbours on: in the partition's own buffer and in
     a layer's workspace there is room for its partial sums, in the fixed array of the static call there is not, and a

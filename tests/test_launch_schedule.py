@@ -142,16 +142,25 @@ def _lists(lens, n_table, seed=0):
 
 def test_plan_says_which_schedule_runs():
     """The fine schedule runs from the scratch on that holds its partial sums, the coarse one below; a partition built
-    without it has one schedule whatever the scratch."""
+    without it has one schedule whatever the scratch.  Narrow rows do not pay for it and ask for no room."""
     ptr, col = _graph(1500, 330, 7, hubs=20)
     part = binding.mgg_build_partition(ptr, col, host_only=True, hot_phases=-1, fine_min_neighbours=1)
     one = binding.mgg_build_partition(ptr, col, host_only=True, hot_phases=-1, fine_min_neighbours=-1)
-    for dim in (1, 64, 100, 602):
+    for dim in (36, 64, 100, 602):
         need = binding.mgg_aggregate_scratch_bytes(part, dim)
         full = need + int(part.info.n_fine_split_items) * (-(-dim // 8) * 8) * 4
         assert binding.mgg_aggregate_plan(part, "gcn", dim).fine == 1
         assert [binding.mgg_aggregate_plan(part, "gcn", dim, scratch_bytes=b).fine for b in (need, full - 1, full)] == [0, 0, 1]
         assert binding.mgg_aggregate_plan(one, "gcn", dim).fine == 0 and need == binding.mgg_aggregate_scratch_bytes(one, dim)
+    for dim, bf16, fine in ((1, False, 0), (16, False, 0), (32, False, 0), (33, False, 1), (7, True, 0), (64, True, 0), (128, True, 0), (129, True, 1), (256, True, 1)):
+        assert binding.mgg_aggregate_plan(part, "gcn", dim, bf16=bf16).fine == fine, (dim, bf16)
+    # 16 lanes of bf16: on large tables with many neighbours
+    for table, more, want in ((380000, 0, 0), (400000, 0, 1), (400000, -2000, 0)):
+        lens = np.concatenate([np.full(25000, 200), np.full(29500 + more, 512)])
+        ptr, col = _lists(lens, table)
+        big = binding.mgg_build_partition(ptr, col, host_only=True, hot_phases=-1)
+        assert big.info.n_fine_items > 0 and (ptr[-1] >= 20000000) == (more == 0)
+        assert [binding.mgg_aggregate_plan(big, "gcn", d, bf16=True).fine for d in (64, 128, 256)] == [0, want, 1]
 
 
 def test_plan_checks_its_arguments():
@@ -311,7 +320,7 @@ def test_the_least_workspace_is_the_coarse_schedules(dims, order):
     least = ask(binding.mgg_layer_workspace_least_bytes, fine)
     assert least == ask(binding.mgg_layer_workspace_bytes, one) == ask(binding.mgg_layer_workspace_least_bytes, one)
     more = ask(binding.mgg_layer_workspace_bytes, fine) - least
-    extra = [int(fine.info.n_fine_split_items) * (-(-d // 8) * 8) * 4 for d in dims[:2]]
+    extra = [int(fine.info.n_fine_split_items) * (-(-d // 8) * 8) * 4 if -(-d // 8) * 8 > 32 else 0 for d in dims[:2]]
     assert any(abs(more - x) < 256 for x in extra)
 
 
