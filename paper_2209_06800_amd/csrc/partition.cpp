@@ -384,18 +384,6 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
     std::vector<std::vector<WorkItem>> bucket(static_cast<size_t>(std::max(n_hot, 1)));   // hot items by class
     std::vector<WorkItem> cold;                              // cold pieces and whole rows
     std::vector<std::vector<int32_t>> by_len(short_max >= 0 ? short_max + 1 : 0);
-    std::vector<int32_t> n_in(static_cast<size_t>(n_hot) + 1), lcut(static_cast<size_t>(n_hot) + 2), rcut(static_cast<size_t>(n_hot) + 2), pos(static_cast<size_t>(n_hot) + 1), tmp;
-    std::vector<uint8_t> final_class(static_cast<size_t>(n_hot) + 1);
-    // stable counting sort of col[b, e) by final class of the table row `base + col`; cut[c] = start of class c
-    auto regroup = [&](std::vector<int32_t> &col, int32_t b, int32_t e, int64_t base, std::vector<int32_t> &cut) {
-        std::fill(pos.begin(), pos.end(), 0);
-        for (int32_t i = b; i < e; ++i) ++pos[final_class[std::min<int>(p->src_class[base + col[i]], n_hot)]];
-        cut[0] = b;
-        for (int c = 0; c <= n_hot; ++c) cut[c + 1] = cut[c] + pos[c];
-        tmp.assign(col.begin() + b, col.begin() + e);
-        for (int c = 0; c <= n_hot; ++c) pos[c] = cut[c];
-        for (int32_t u : tmp) col[pos[final_class[std::min<int>(p->src_class[base + u], n_hot)]]++] = u;
-    };
     std::vector<std::pair<WorkItem, int>> row_items;         // item, class (n_hot = cold)
     // The fine schedule costs a partial sum per class and row and keeps the gathers of these rows in one XCD's L2.  From 128
     // neighbours on (16 per class) it pays on large shares (233 k rows, 602 columns: 18.39 -> 17.88 ms; 120 k rows, 256
@@ -406,15 +394,56 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
     bool fine = k.fine_min > 0 && nnz >= k.fine_min && p->class_mode == 1 && n_phase == 1 && xcd_min_deg == kDefaultXcdMinDeg && run >= kDefaultXcdMinDeg;
     std::vector<std::vector<WorkItem>> fine_bucket(fine ? bucket.size() : 0);
     std::vector<WorkItem> fine_cold;
-    // the pieces of a row by class: cuts of its two regrouped lists
-    auto cut_by_class = [&](int32_t l0, int32_t l1, int32_t r0, int32_t r1) {
-        std::fill(n_in.begin(), n_in.end(), 0);
-        for (int32_t i = l0; i < l1; ++i) ++n_in[std::min<int>(p->src_class[p->local_col[i]], n_hot)];
-        for (int32_t i = r0; i < r1; ++i) ++n_in[std::min<int>(p->src_class[n_loc + p->remote_col[i]], n_hot)];
-        for (int c = 0; c < n_hot; ++c) final_class[c] = static_cast<uint8_t>(n_in[c] >= min_piece ? c : n_hot);
-        final_class[n_hot] = static_cast<uint8_t>(n_hot);
-        regroup(p->sched_local_col, l0, l1, 0, lcut);
-        regroup(p->sched_remote_col, r0, r1, n_loc, rcut);
+    // The pieces of a row by class: its two lists sorted by final class (stable), class c of the local one in
+    // [cuts[c], cuts[c + 1]), of the remote one in [cuts[n_cut + c], cuts[n_cut + c + 1]).  `in`: room for the counts.
+    const int n_cut = n_hot + 2;
+    auto cut_by_class = [&](int64_t v, int32_t *cuts, int32_t *in) {
+        const int32_t l0 = p->local_row_ptr[v], l1 = p->local_row_ptr[v + 1], r0 = p->remote_row_ptr[v], r1 = p->remote_row_ptr[v + 1];
+        int32_t *l_in = in, *r_in = in + n_hot + 1;
+        std::fill(in, in + 2 * (n_hot + 1), 0);
+        for (int32_t i = l0; i < l1; ++i) ++l_in[std::min<int>(p->src_class[p->local_col[i]], n_hot)];
+        for (int32_t i = r0; i < r1; ++i) ++r_in[std::min<int>(p->src_class[n_loc + p->remote_col[i]], n_hot)];
+        uint64_t alone[(kColdClass + 64) / 64] = {};                // classes that are a piece of their own
+        for (int c = 0; c < n_hot; ++c) {
+            if (l_in[c] + r_in[c] >= min_piece) { alone[c / 64] |= uint64_t{1} << (c % 64); continue; }
+            l_in[n_hot] += l_in[c]; r_in[n_hot] += r_in[c];
+            l_in[c] = r_in[c] = 0;
+        }
+        auto sort_list = [&](const std::vector<int32_t> &from, std::vector<int32_t> &to, int32_t b, int32_t e, int64_t base, int32_t *cut, int32_t *pos) {
+            cut[0] = b;
+            for (int c = 0; c <= n_hot; ++c) { cut[c + 1] = cut[c] + pos[c]; pos[c] = cut[c]; }
+            for (int32_t i = b; i < e; ++i) {
+                const int c = std::min<int>(p->src_class[base + from[i]], n_hot);
+                to[pos[c < n_hot && (alone[c / 64] >> (c % 64) & 1) ? c : n_hot]++] = from[i];
+            }
+        };
+        sort_list(p->local_col, p->sched_local_col, l0, l1, 0, cuts, l_in);
+        sort_list(p->remote_col, p->sched_remote_col, r0, r1, n_loc, cuts + n_cut, r_in);
+    };
+    // Which rows that is done for, and block by block of the rows, on several threads, the doing of it.
+    auto degree = [&](int64_t v) { return static_cast<int64_t>(p->local_row_ptr[v + 1]) - p->local_row_ptr[v] + p->remote_row_ptr[v + 1] - p->remote_row_ptr[v]; };
+    auto is_cut = [&](int64_t d) { return use_classes && n_hot > 0 && !(short_max >= 0 && d <= short_max) && d >= (fine ? std::min<int64_t>(kFineXcdMinDeg, xcd_min_deg) : xcd_min_deg); };
+    const size_t block_rows = std::max<size_t>(1, (size_t{1} << 22) / (2 * static_cast<size_t>(n_cut)));      // cuts of 16 MB at most
+    std::vector<int64_t> cut_rows;
+    std::vector<int32_t> cuts, whole(2 * static_cast<size_t>(n_cut));
+    size_t next_cut = 0;
+    auto cut_block = [&](int64_t from) {
+        cut_rows.clear();
+        size_t work = 0;
+        for (int64_t v = from; v < n_own && cut_rows.size() < block_rows; ++v)
+            if (const int64_t d = degree(v); is_cut(d)) { cut_rows.push_back(v); work += static_cast<size_t>(d); }
+        cuts.resize(cut_rows.size() * 2 * n_cut);
+        std::atomic<bool> no_memory{false};
+        parallel_for(cut_rows.size(), work, [&](size_t b, size_t e) {
+            try {
+                std::vector<int32_t> in(2 * (static_cast<size_t>(n_hot) + 1));
+                for (size_t i = b; i < e; ++i) cut_by_class(cut_rows[i], &cuts[i * 2 * n_cut], in.data());
+            } catch (const std::bad_alloc &) {
+                no_memory = true;
+            }
+        });
+        if (no_memory) throw std::bad_alloc();
+        next_cut = 0;
     };
     for (int64_t v = 0; v < n_own; ++v) {
         const int32_t l0 = p->local_row_ptr[v], l1 = p->local_row_ptr[v + 1];
@@ -425,12 +454,18 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
         if (short_max >= 0 && dl + dr <= short_max) { by_len[dl + dr].push_back(static_cast<int32_t>(v)); continue; }
         // the pieces of this row: one per surviving class if it is regrouped, otherwise the whole row
         int first_piece = n_hot, n_piece_end = n_hot + 1;     // default: only the cold piece = the whole row
+        const int32_t *row_cuts = nullptr;
+        if (is_cut(dl + dr)) {
+            if (next_cut == cut_rows.size()) cut_block(v);
+            row_cuts = &cuts[next_cut++ * 2 * n_cut];
+        }
+        const int32_t *lcut = whole.data(), *rcut = whole.data() + n_cut;
         if (use_classes && n_hot > 0 && dl + dr >= xcd_min_deg) {
-            cut_by_class(l0, l1, r0, r1);
+            lcut = row_cuts; rcut = row_cuts + n_cut;
             first_piece = 0;
             p->n_classed += dl + dr;
         } else {
-            lcut[n_hot] = l0; lcut[n_hot + 1] = l1; rcut[n_hot] = r0; rcut[n_hot + 1] = r1;
+            whole[n_hot] = l0; whole[n_hot + 1] = l1; whole[n_cut + n_hot] = r0; whole[n_cut + n_hot + 1] = r1;
         }
         row_items.clear();
         for (int c = first_piece; c < n_piece_end; ++c) {
@@ -460,7 +495,7 @@ static void build_schedule(mgg_partition *p, const Knobs &k)
         }
         if (!fine) continue;
         if (dl + dr >= kFineXcdMinDeg && dl + dr < xcd_min_deg) {
-            cut_by_class(l0, l1, r0, r1);
+            lcut = row_cuts; rcut = row_cuts + n_cut;
             const size_t first = p->fine_split_rows.size();
             int32_t pieces = 0;
             for (int c = 0; c <= n_hot; ++c) pieces += lcut[c + 1] - lcut[c] + rcut[c + 1] - rcut[c] > 0;
