@@ -75,21 +75,6 @@ static void parallel_for(size_t n, size_t work, const F &body)
     for (std::thread &t : threads) t.join();
 }
 
-// position of the first of n indices outside [0, end), n if there is none
-static int64_t first_outside(const int32_t *idx, int64_t n, int64_t end)
-{
-    std::atomic<int64_t> first{n};
-    parallel_for(static_cast<size_t>(n), static_cast<size_t>(n), [&](size_t b, size_t e) {
-        for (size_t i = b; i < e; ++i)
-            if (idx[i] < 0 || idx[i] >= end) {
-                int64_t seen = first;
-                while (static_cast<int64_t>(i) < seen && !first.compare_exchange_weak(seen, static_cast<int64_t>(i))) {}
-                return;
-            }
-    });
-    return first;
-}
-
 static void free_device(mgg_partition *p)
 {
     if (p->device < 0) return;
@@ -589,10 +574,18 @@ mgg_status_t mgg_build_partition(int64_t num_nodes, const int64_t *row_ptr, cons
         if (row_ptr[v + 1] < row_ptr[v]) return fail(MGG_ERR_BAD_GRAPH, "row_ptr decreases at row %lld", (long long)v);
     const int64_t nnz = row_ptr[num_nodes];
     if (nnz > 0 && !col_idx) return fail(MGG_ERR_INVALID_ARG, "col_idx is NULL");
-    const int64_t bad = first_outside(col_idx, nnz, num_nodes);
-    if (bad < nnz)
-        return fail(MGG_ERR_BAD_GRAPH, "column %d at position %lld outside [0, %lld)", col_idx[bad], (long long)bad,
-                    (long long)num_nodes);
+    std::atomic<int64_t> first_bad{nnz};
+    parallel_for(static_cast<size_t>(nnz), static_cast<size_t>(nnz), [&](size_t b, size_t e) {
+        for (size_t i = b; i < e; ++i)
+            if (col_idx[i] < 0 || col_idx[i] >= num_nodes) {
+                int64_t seen = first_bad;
+                while (static_cast<int64_t>(i) < seen && !first_bad.compare_exchange_weak(seen, static_cast<int64_t>(i))) {}
+                return;
+            }
+    });
+    if (first_bad < nnz)
+        return fail(MGG_ERR_BAD_GRAPH, "column %d at position %lld outside [0, %lld)", col_idx[first_bad],
+                    (long long)first_bad, (long long)num_nodes);
 
     // ---- node range --------------------------------------------------------------------
     std::vector<int64_t> bnd(num_parts + 1);
@@ -727,9 +720,9 @@ mgg_status_t mgg_build_bags(int64_t num_bags, const int64_t *bag_ptr, const int3
     const int64_t nnz = bag_ptr[num_bags];
     if (nnz >= INT32_MAX) return fail(MGG_ERR_UNSUPPORTED, "2^31-1 or more lookups");
     if (nnz > 0 && !bag_idx) return fail(MGG_ERR_INVALID_ARG, "bag_idx is NULL");
-    const int64_t bad = first_outside(bag_idx, nnz, table_rows);
-    if (bad < nnz)
-        return fail(MGG_ERR_BAD_GRAPH, "table row %d at position %lld outside [0, %lld)", bag_idx[bad], (long long)bad, (long long)table_rows);
+    for (int64_t e = 0; e < nnz; ++e)
+        if (bag_idx[e] < 0 || bag_idx[e] >= table_rows)
+            return fail(MGG_ERR_BAD_GRAPH, "table row %d at position %lld outside [0, %lld)", bag_idx[e], (long long)e, (long long)table_rows);
 
     mgg_partition *p = new (std::nothrow) mgg_partition;
     if (!p) return fail(MGG_ERR_ALLOC, "out of host memory");
@@ -738,30 +731,24 @@ mgg_status_t mgg_build_bags(int64_t num_bags, const int64_t *bag_ptr, const int3
         p->bags = true;
         p->num_nodes = table_rows; p->lb = local_lo; p->ub = local_hi; p->n_own = num_bags; p->n_local_rows = local_hi - local_lo;
         p->num_parts = 1; p->part_id = 0;
+        // rows of the table outside the local slice that are looked up, in ascending order, and their slots
+        std::vector<uint8_t> used(static_cast<size_t>(table_rows), 0);
+        for (int64_t e = 0; e < nnz; ++e)
+            if (bag_idx[e] < local_lo || bag_idx[e] >= local_hi) used[bag_idx[e]] = 1;
+        std::vector<int32_t> slot_of(static_cast<size_t>(table_rows), -1);
+        for (int64_t u = 0; u < table_rows; ++u)
+            if (used[u]) { slot_of[u] = static_cast<int32_t>(p->halo_gid.size()); p->halo_gid.push_back(static_cast<int32_t>(u)); }
+        p->halo_peer_ptr = {0, static_cast<int64_t>(p->halo_gid.size())};
         p->local_row_ptr.assign(num_bags + 1, 0);
         p->remote_row_ptr.assign(num_bags + 1, 0);
-        if (local_lo == 0 && local_hi == table_rows) {      // the whole table is local: the lookups as they stand
-            p->local_col.assign(bag_idx, bag_idx + nnz);
-            for (int64_t b = 0; b < num_bags; ++b) p->local_row_ptr[b + 1] = static_cast<int32_t>(bag_ptr[b + 1]);
-            p->halo_peer_ptr = {0, 0};
-        } else {
-            // rows of the table outside the local slice that are looked up, in ascending order, and their slots
-            std::vector<uint8_t> used(static_cast<size_t>(table_rows), 0);
-            for (int64_t e = 0; e < nnz; ++e)
-                if (bag_idx[e] < local_lo || bag_idx[e] >= local_hi) used[bag_idx[e]] = 1;
-            std::vector<int32_t> slot_of(static_cast<size_t>(table_rows), -1);
-            for (int64_t u = 0; u < table_rows; ++u)
-                if (used[u]) { slot_of[u] = static_cast<int32_t>(p->halo_gid.size()); p->halo_gid.push_back(static_cast<int32_t>(u)); }
-            p->halo_peer_ptr = {0, static_cast<int64_t>(p->halo_gid.size())};
-            for (int64_t b = 0; b < num_bags; ++b) {
-                for (int64_t e = bag_ptr[b]; e < bag_ptr[b + 1]; ++e) {
-                    const int32_t u = bag_idx[e];
-                    if (u >= local_lo && u < local_hi) p->local_col.push_back(static_cast<int32_t>(u - local_lo));
-                    else p->remote_col.push_back(slot_of[u]);
-                }
-                p->local_row_ptr[b + 1] = static_cast<int32_t>(p->local_col.size());
-                p->remote_row_ptr[b + 1] = static_cast<int32_t>(p->remote_col.size());
+        for (int64_t b = 0; b < num_bags; ++b) {
+            for (int64_t e = bag_ptr[b]; e < bag_ptr[b + 1]; ++e) {
+                const int32_t u = bag_idx[e];
+                if (u >= local_lo && u < local_hi) p->local_col.push_back(static_cast<int32_t>(u - local_lo));
+                else p->remote_col.push_back(slot_of[u]);
             }
+            p->local_row_ptr[b + 1] = static_cast<int32_t>(p->local_col.size());
+            p->remote_row_ptr[b + 1] = static_cast<int32_t>(p->remote_col.size());
         }
         p->deg_own.resize(num_bags);
         for (int64_t b = 0; b < num_bags; ++b) p->deg_own[b] = static_cast<int32_t>(bag_ptr[b + 1] - bag_ptr[b]);

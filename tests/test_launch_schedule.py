@@ -337,31 +337,3 @@ def test_groups_of_short_rows_per_wavefront():
         assert binding.mgg_aggregate_plan(bags, "gin", 128).short_per_wave == 1
         part.set_option("short_per_wave", 5)
         assert plan(16) == 5
-
-
-@pytest.mark.parametrize("lo,hi", [(0, 900), (0, 899), (1, 900)])
-def test_lookups_of_a_whole_local_table_stand_as_given(lo, hi):
-    """A table that is local as a whole is taken without a look at its rows; one row less and the general path finds the
-    remote ones.  Empty bags in front, between and behind."""
-    rng = np.random.default_rng(21)
-    sizes = rng.integers(0, 30, 400)
-    sizes[[0, 7, 399]] = 0
-    ptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
-    idx = rng.integers(0, 900, ptr[-1]).astype(np.int32)
-    idx[:2] = [0, 899]
-    part = binding.mgg_build_bags(ptr, idx, 900, lo, hi, host_only=True)
-    got, here = part.export(), (idx >= lo) & (idx < hi)
-    assert np.array_equal(got["halo_gid"], np.unique(idx[~here]))
-    assert np.array_equal(got["local_col"], idx[here] - lo)
-    bag = np.repeat(np.arange(400), sizes)
-    for name, mine in (("local_row_ptr", here), ("remote_row_ptr", ~here)):
-        assert np.array_equal(got[name], np.concatenate([[0], np.cumsum(np.bincount(bag[mine], minlength=400))]))
-    part.destroy()
-
-
-def test_the_first_bad_lookup_is_the_one_named():
-    idx = np.zeros(600000, np.int32)                  # more than one thread's share
-    idx[[200001, 400000, 599999]] = [70, -1, 50]
-    ptr = np.array([0, 600000], np.int64)
-    with pytest.raises(binding.MggError, match="table row 70 at position 200001 outside"):
-        binding.mgg_build_bags(ptr, idx, 50, 0, 50, host_only=True)
